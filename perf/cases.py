@@ -112,7 +112,10 @@ def draw(rng):
         frames = _log(rng, 8, min(2048, 131072 // frame))
         Sq = max(64, min(4096, chunk * _log(rng, max(4, frames // 2), 2 * frames) - rng.choice((0, 0, 1))))
         Bn = rng.choice((1, 1, 2)) if Hkv * frame * frames * D <= 1 << 27 else 1
-        return _case("train", Hq, Hkv, D, Sq, frame * frames, B=Bn, q_chunk=chunk, kv_block=frame, mask=mask)
+        c = _case("train", Hq, Hkv, D, Sq, frame * frames, B=Bn, q_chunk=chunk, kv_block=frame, mask=mask)
+        while work(c)["flops"] > _MOST_FLOPS:
+            c["Sq"] //= 2
+        return c
     if kind == "f32":
         Hq, Hkv = rng.choice(((2, 2), (4, 2), (8, 8)))
         blocks = rng.choice((1, 4))
