@@ -128,7 +128,8 @@ def draw(rng):
         most = _MOST_FLOPS / (18.0 * Hq * Sq * D + 16.0 * E * Hkv * D)
         return _case("layer", Hq, Hkv, D, Sq, blocks * _size(rng, 1024, int(min(most, 65536)) // blocks),
                      blocks=blocks, E=E)
-    return _case("project", 0, Hkv, D, 0, _size(rng, 2048, 131072), E=E)
+    most = _MOST_FLOPS / (12.0 * E * Hkv * D)
+    return _case("project", 0, Hkv, D, 0, _size(rng, 2048, int(min(most, 131072))), E=E)
 
 
 # ---- one case -------------------------------------------------------------------------------
