@@ -173,11 +173,17 @@ size_t bwd_ws_fixed(const Dims& d) {   // delta [B,Hq,Sq] + padded statistics [B
   return align_up((size_t)d.B * d.Hq * d.Sq * sizeof(float)) +
          align_up((stats_floats(d) + (has_stats_ovl(d) ? (size_t)d.B * d.Hq * 64 : 0)) * sizeof(float));
 }
-size_t bwd_ws_part(const Dims& d, int n_split) {   // the dQ kernel's partial sums [n_split, B,Hq,Sq,D] when it splits
-  return n_split > 1 ? align_up((size_t)n_split * d.B * d.Hq * d.Sq * d.D * sizeof(float)) : 0;
+// The dQ kernel's partial sums [n, B,Hq,Sq,D] when it splits.  A masked bf16 call always has one
+// slice at least: the words of MaskRows go into the last slice, which the kernels that read them
+// leave alone (they use half the splits), and which the others fill only after the words' last reader.
+int bwd_slices(const Dims& d, lvx_dtype dtype, bool masked) {
+  const int n = bwd_split(d, dtype, masked);
+  return n > 1 || (masked && dtype == LVX_BF16) ? n : 0;
 }
-size_t bwd_ws(const Dims& d, int n_split, bool fused) {   // ... + the fused kernel's dQ tiles and locks
-  return bwd_ws_fixed(d) + bwd_ws_part(d, n_split) + (fused ? align_up(bwd_fused_ws_bytes(d)) : 0);
+size_t bwd_slice_bytes(const Dims& d) { return (size_t)d.B * d.Hq * d.Sq * d.D * sizeof(float); }
+size_t bwd_ws_part(const Dims& d, int n_slices) { return n_slices > 0 ? align_up(n_slices * bwd_slice_bytes(d)) : 0; }
+size_t bwd_ws(const Dims& d, int n_slices, bool fused) {   // ... + the fused kernel's dQ tiles and locks
+  return bwd_ws_fixed(d) + bwd_ws_part(d, n_slices) + (fused ? align_up(bwd_fused_ws_bytes(d)) : 0);
 }
 
 }  // namespace
@@ -218,7 +224,7 @@ size_t lvx_xattn_workspace_bytes(const lvx_problem* p, lvx_dtype dtype, int whic
   if (which == LVX_WS_FWD)
     return fwd_ws(d, larger(larger(masked_parts, fwd_split(d, dtype, true)), fwd_split(d, dtype, false) + tail_part));
   if (which == LVX_WS_BWD)
-    return bwd_ws(d, larger(bwd_split(d, dtype, true), bwd_split(d, dtype, false)),
+    return bwd_ws(d, larger(bwd_slices(d, dtype, true), bwd_slices(d, dtype, false)),
                   dtype == LVX_BF16 && bwd_fused_bf16_supported(d, false));
   if (which == LVX_WS_FWD_MERGE)
   {
@@ -391,7 +397,8 @@ lvx_status lvx_xattn_bwd_stages(const lvx_problem* p, lvx_dtype dtype, const voi
   const bool can_fuse = dtype == LVX_BF16 && bwd_fused_bf16_supported(a.d, mask != nullptr);
   const bool want_fuse = (stages & LVX_BWD_FUSED) || (FUSED_BY_DEFAULT && !(stages & LVX_BWD_SPLIT));
   const bool fused = can_fuse && want_fuse && (stages & (LVX_BWD_DKDV | LVX_BWD_DQ)) == (LVX_BWD_DKDV | LVX_BWD_DQ);
-  const size_t need = bwd_ws(a.d, a.n_split_dq, can_fuse);
+  const int n_slices = bwd_slices(a.d, dtype, mask != nullptr);
+  const size_t need = bwd_ws(a.d, n_slices, can_fuse);
   if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < need) return LVX_ERR_WORKSPACE;
   a.q = q; a.k = k; a.v = v; a.o = o; a.d_o = d_o; a.lse = lse;
   a.delta = (float*)workspace;
@@ -400,7 +407,10 @@ lvx_status lvx_xattn_bwd_stages(const lvx_problem* p, lvx_dtype dtype, const voi
   a.stats_ovl = has_stats_ovl(a.d) ? a.stats + stats_floats(a.d) : nullptr;
   a.dq_accum = dq_accum; a.dk = dk; a.dv = dv;
   a.dq_part = a.n_split_dq > 1 ? (float*)((char*)workspace + bwd_ws_fixed(a.d)) : nullptr;
-  a.dq_tiles = fused ? (float*)((char*)workspace + bwd_ws_fixed(a.d) + bwd_ws_part(a.d, a.n_split_dq)) : nullptr;
+  a.rows = MaskRows{nullptr, 0, 0, 0};
+  a.rows_ws = mask != nullptr && n_slices > 0 ? (char*)workspace + bwd_ws_fixed(a.d) + (n_slices - 1) * bwd_slice_bytes(a.d) : nullptr;
+  a.rows_ws_bytes = bwd_slice_bytes(a.d);
+  a.dq_tiles = fused ? (float*)((char*)workspace + bwd_ws_fixed(a.d) + bwd_ws_part(a.d, n_slices)) : nullptr;
   a.dq_locks = nullptr; a.dq_err = nullptr; a.dq_stagger = 0;
   hipStream_t s = (hipStream_t)hip_stream;
   hipError_t e = hipSuccess;
@@ -418,10 +428,10 @@ lvx_status lvx_xattn_bwd_error_word(const lvx_problem* p, lvx_dtype dtype, const
   if (!word) return LVX_ERR_NULL;
   if ((st = check_mask(p, mask)) != LVX_OK) return st;
   const Dims d = make_dims(p);
-  const int n_split = bwd_split(d, dtype, mask != nullptr);
+  const int n_slices = bwd_slices(d, dtype, mask != nullptr);
   const bool fused = dtype == LVX_BF16 && bwd_fused_bf16_supported(d, mask != nullptr);
-  if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < bwd_ws(d, n_split, fused)) return LVX_ERR_WORKSPACE;
-  *word = fused ? (const int*)((char*)workspace + bwd_ws_fixed(d) + bwd_ws_part(d, n_split) + bwd_fused_ws_bytes(d) - 256)
+  if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < bwd_ws(d, n_slices, fused)) return LVX_ERR_WORKSPACE;
+  *word = fused ? (const int*)((char*)workspace + bwd_ws_fixed(d) + bwd_ws_part(d, n_slices) + bwd_fused_ws_bytes(d) - 256)
                 : nullptr;
   return LVX_OK;
 }

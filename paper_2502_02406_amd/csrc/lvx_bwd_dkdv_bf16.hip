@@ -70,6 +70,9 @@ template <int D, int KVB> struct DkvSmem {
   static constexpr int BITS_BYTES = 2048;           // visibility bits of up to 16320 steps (media mask only)
   static constexpr int WIN_BYTES = 2048;            // window of the mask bitmap (media mask only)
   static constexpr int TOTAL = RING + BITS_BYTES + WIN_BYTES;
+  static constexpr int TOTAL_WORDS = 160 * 1024;    // ... with everything that is left for the words (WORDS variant)
+  static constexpr int WORDS_CAP = (TOTAL_WORDS - RING) / 4;
+  static_assert(TOTAL <= TOTAL_WORDS, "the layout fits a compute unit");
   static_assert(RUN >= 64, "a run must hold at least one full copy");
 };
 template <int D> constexpr int dkdv_step_list_cap() {
@@ -85,6 +88,17 @@ template <int D> constexpr int dkdv_step_list_cap() {
 // visible to all of a workgroup's keys or to none, so the mask only selects WHICH steps a
 // workgroup performs: the dense kernel runs over a list of them and nothing inside a step
 // changes.
+// WORDS (with STEPS): any other media mask.  A step may be visible to some of a workgroup's keys and
+// a key to some of a step's rows; which ones is one word per (step, key block) from MaskRows, of
+// which a lane reads its key's with one LDS read per step, a step ahead.  Every probability then
+// meets its bit of the word -- a bit-field extract and an AND, 64 vector instructions on top of the
+// about 200 of a step -- and the loop stays one basic block: branches that tell full steps from cut
+// ones cost the general kernel below more than masking everything costs here (it also owns only
+// 128 keys per workgroup, half the reuse of every operand).  Key tiles are dealt to the XCDs in
+// turn, since the early ones of a causal mask have the most steps.  2048 rows x 28 heads in chunks
+// of 64 against 32 frames of 729 keys, causal, D = 128: 2.73 -> 0.75 ms, of which 0.68 is the longest
+// workgroup (448 steps); 4096 rows x 8 heads in chunks of 2, each seeing one of 2048 frames of 64
+// keys, D = 64: 0.54 -> 0.17 ms (reads and writes 268 MB each).
 // Measurement builds only (python -m paper_2502_02406_amd.build --define LVX_DKDV_PROBE=1): every
 // workgroup with steps to run adds the clocks of its three phases (set-up until the first tiles and
 // K, V are in place; the loop; the epilogue until its stores have been acknowledged), a count and
@@ -96,11 +110,12 @@ __device__ unsigned long long dkdv_probe[8];
 #define DKDV_STAMP(x)
 #endif
 
-template <int D, bool GENERAL, bool STEPS = false>
+template <int D, bool GENERAL, bool STEPS = false, bool WORDS = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 bwd_dkdv_bf16_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   static_assert(!(GENERAL && STEPS), "the step list is a variant of the dense kernel");
+  static_assert(STEPS || !WORDS, "the words belong to the step list");
   constexpr int KVB = kvb_of(GENERAL);
   constexpr int XE = 16 * KVB;     // all elements of a step are converted during the contraction
                                    // (measured: no gain from moving some of them to the scoring)
@@ -112,7 +127,7 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   const int G = d.Hq / d.Hkv;
   const int n_kt = (d.Skv + KN - 1) / KN;
   HeadWork hw;
-  if (!xcd_decode(blockIdx.x, d.B * d.Hkv, n_kt, &hw)) return;
+  if (!xcd_decode(blockIdx.x, d.B * d.Hkv, n_kt, &hw, STEPS)) return;
   DKDV_STAMP(stamp0);
   const int b = hw.head / d.Hkv, hk = hw.head % d.Hkv;
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, kl = lane & 31;
@@ -143,9 +158,43 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   }
   // STEPS: the row tiles that see this workgroup's keys (the same for every head), compacted
   // into a list by one wave; its length goes into the last word of the area.
-  constexpr int LIST_CAP = dkdv_step_list_cap<D>();
+  // WORDS: the list holds the steps that any of the workgroup's keys is seen by, and behind it
+  // stands, for every step t and every key block f0 + f that the workgroup's keys lie in, the word
+  // of the step's 32 rows (MaskRows; for a short last step, of rows Sq-32 .. Sq-1).
+  constexpr int LIST_CAP = WORDS ? SM::WORDS_CAP - 1 : dkdv_step_list_cap<D>();
   int* const tl = (int*)(smem + SM::RING);
-  if (STEPS) {
+  const int f0 = WORDS ? j_wg0 / a.mask.kv_block : 0, nf = WORDS ? j_wg1 / a.mask.kv_block - f0 + 1 : 1;
+  const unsigned* const wtab = (const unsigned*)tl + spH;
+  int wlane[KVB] = {};                             // byte offset of this lane's key block's word in a step's row of words
+  unsigned wcur[KVB] = {};                         // the word of the step being converted, shifted to this lane's rows
+  if (WORDS) {
+#pragma unroll
+    for (int kb = 0; kb < KVB; ++kb) wlane[kb] = (min(j_wave0 + 32 * kb + kl, d.Skv - 1) / a.mask.kv_block - f0) * 4;
+    const unsigned* const rw = a.rows.words + b * a.rows.stride_b;
+    for (int c = tid; c < spH * nf; c += 256) {
+      const int t = c / nf, f = f0 + c % nf;
+      auto word = [&](int tt) -> unsigned { return rw[((long)(tt >> 3) * a.rows.w1 + f) * 8 + (tt & 7)]; };
+      unsigned x = word(t);
+      if (t == spH - 1 && d.Sq % KM != 0) x = (word(t - 1) >> (d.Sq % KM)) | (x << (KM - d.Sq % KM));
+      ((unsigned*)wtab)[c] = x;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      int count = 0;
+      for (int base = 0; base < spH; base += 64) {     // (wave-uniform trip count)
+        const int t = base + lane;
+        unsigned any = 0;
+        for (int f = 0; f < nf; ++f) any |= wtab[min(t, spH - 1) * nf + f];
+        const bool on = t < spH && any != 0;
+        const unsigned long long m = __ballot(on);
+        if (on) tl[count + __popcll(m & ((1ull << lane) - 1ull))] = t;
+        count += (int)__popcll(m);
+      }
+      if (lane == 0) tl[LIST_CAP] = count;
+    }
+    __syncthreads();
+    per_head = __builtin_amdgcn_readfirstlane(tl[LIST_CAP]);
+  } else if (STEPS) {
     const uint8_t* const col = a.mask.allow + b * a.mask.stride_b + j_wg0 / a.mask.kv_block;
     if (wave == 0) {
       int count = 0;
@@ -510,6 +559,13 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   // can start an element under one matrix instruction and finish it under the next: a
   // transcendental result read by the very next instruction costs an idle issue slot.
   struct Carry { float pr, ds, ex; };
+  auto load_words = [&](int row_tile) __attribute__((always_inline)) {      // the words of a step (rows 32 row_tile ...)
+    if constexpr (WORDS) {
+      const char* const row = (const char*)(wtab + __builtin_amdgcn_readfirstlane(row_tile) * nf);
+#pragma unroll
+      for (int kb = 0; kb < KVB; ++kb) wcur[kb] = *(const unsigned*)(row + wlane[kb]) >> (4 * g);
+    }
+  };
   auto conv_start = [&](int x, const f32x16 (&s)[KVB]) __attribute__((always_inline)) -> float {
     const int q4 = x / (4 * KVB), kb = (x / 4) % KVB, e = x % 4, v = 4 * q4 + e;
     return __builtin_amdgcn_exp2f(s[kb][v]);
@@ -517,7 +573,10 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   auto conv_finish = [&](int x, Carry& cy, const f32x16 (&p)[KVB],
                          u32x4 (&pwo)[KVB][2], u32x4 (&swo)[KVB][2]) __attribute__((always_inline)) {
     const int q4 = x / (4 * KVB), kb = (x / 4) % KVB, e = x % 4, v = 4 * q4 + e;
-    const float pr = cy.ex;
+    float pr = cy.ex;
+    // (WORDS: a probability is kept or becomes zero by one bit of the word; whatever the scores of
+    // a pair that is not visible gave, nothing of them is left in P, and dS = 0 dP)
+    if (WORDS) pr = __uint_as_float(__float_as_uint(pr) & (unsigned)__builtin_amdgcn_sbfe((int)wcur[kb], 8 * q4 + e, 1));
     const float ds = pr * p[kb][v];
     if (e % 2 == 0) { cy.pr = pr; cy.ds = ds; return; }
     pwo[kb][q4 >> 1][2 * (q4 & 1) + e / 2] = pack2_bf16(cy.pr, pr);
@@ -595,13 +654,14 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   // barrier of the iteration, every wave is done with step i, whose stage takes step i + 4, and
   // step i + 2 -- issued two iterations ago -- has landed; then step i + 2 is scored.
   DKDV_STAMP(stamp_a);
-  int e[NSTG + 1];                                 // step ids of steps i .. i + 4 (static indexing only)
+  int e[NSTG + 1];                                 // step ids of steps i .. i + 4 (static indexing only; WORDS: row tiles)
+  auto step_id = [&]() __attribute__((always_inline)) -> int { return WORDS ? cursor.i0 / KM : cursor.s; };
 #pragma unroll
   for (int q = 0; q <= NSTG; ++q) e[q] = n_all;
 #pragma unroll
   for (int q = 0; q < NSTG; ++q) {
     if (q < n) {
-      e[q] = cursor.s;
+      e[q] = step_id();
       issue_tile(cursor, smem + q * SM::STAGE);
       advance(cursor);
     }
@@ -619,7 +679,9 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   if (n > 0) {
     score(smem, vw, s, p, nothing, first_y(smem, vw), no_tail);
     mask_scores(e[0], s);
+    load_words(e[0]);
     convert(s, p, pf0, sf0);
+    if (n > 1) load_words(e[1]);
     if (n > 1) { score(smem + SM::STAGE, vw, s, p, nothing, first_y(smem + SM::STAGE, vw), no_tail); mask_scores(e[1], s); }
   }
   auto mid = [&](auto all_in_flight, bool issue, char* st_copy) __attribute__((always_inline)) {
@@ -631,7 +693,7 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
     else wait_vmcnt<0>();
     wg_barrier();
     if (issue) {
-      e[4] = cursor.s;
+      e[4] = step_id();
       issue_tile(cursor, st_copy);
       advance(cursor);
     }
@@ -646,7 +708,7 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   auto full_iter = [&](char* st_copy, const char* __restrict__ t0, const char* __restrict__ t1,
                        const char* __restrict__ t2, const char* __restrict__ vw_, const u32x4 (&pfi)[KVB][2],
                        const u32x4 (&sfi)[KVB][2], u32x4 (&pfo)[KVB][2], u32x4 (&sfo)[KVB][2]) __attribute__((always_inline)) {
-    auto next_x = [&]() __attribute__((always_inline)) { fx = first_x(t1); };
+    auto next_x = [&]() __attribute__((always_inline)) { fx = first_x(t1); load_words(e[2]); };
     if constexpr (GENERAL) {
       contract_convert(t0, pfi, sfi, s, p, pfo, sfo, fx, nothing);
       mid(std::false_type{}, true, st_copy);
@@ -660,7 +722,7 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
         }
         if (m == NM_X - 3) fy = first_y(t2, vw_);
       });
-      e[4] = cursor.s;
+      e[4] = step_id();
       const Tile tl = tile_of(cursor, st_copy);
       advance(cursor);
       constexpr int NU = 2 * KVB * KS, EVERY = NU / NDMA;
@@ -682,7 +744,7 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   for (; i < n; ++i) {                             // the last (at most five) iterations
     contract(stage(i), pf0, sf0);
     mid(std::false_type{}, i + 4 < n, stage(i));
-    if (i + 1 < n) convert(s, p, pf0, sf0);
+    if (i + 1 < n) { load_words(e[1]); convert(s, p, pf0, sf0); }
     if (i + 2 < n) { score(stage(i + 2), vw, s, p, nothing, first_y(stage(i + 2), vw), no_tail); mask_scores(e[2], s); }
     e[0] = e[1]; e[1] = e[2]; e[2] = e[3]; e[3] = e[4];
   }
@@ -757,29 +819,48 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
 #endif
 }
 
-template <int D, bool GENERAL, bool STEPS = false>
+template <int D, bool GENERAL, bool STEPS = false, bool WORDS = false>
 hipError_t launch(const BwdArgs& a, hipStream_t s) {
   const long grid = xcd_grid(a.d.B * a.d.Hkv, (a.d.Skv + DkvSmem<D, kvb_of(GENERAL)>::KN - 1) / DkvSmem<D, kvb_of(GENERAL)>::KN);
   static SmemOnce once;
   using SM = DkvSmem<D, kvb_of(GENERAL)>;
-  hipError_t e = ensure_dynamic_lds((const void*)bwd_dkdv_bf16_kernel<D, GENERAL, STEPS>, SM::TOTAL, &once);
+  constexpr int lds = WORDS ? SM::TOTAL_WORDS : SM::TOTAL;
+  hipError_t e = ensure_dynamic_lds((const void*)bwd_dkdv_bf16_kernel<D, GENERAL, STEPS, WORDS>, lds, &once);
   if (e != hipSuccess) return e;
-  bwd_dkdv_bf16_kernel<D, GENERAL, STEPS><<<(unsigned)grid, 256, SM::TOTAL, s>>>(a);
+  bwd_dkdv_bf16_kernel<D, GENERAL, STEPS, WORDS><<<(unsigned)grid, 256, lds, s>>>(a);
   return hipGetLastError();
+}
+
+bool dkdv_rows_ok(const Dims& d) { return d.Sq % KM == 0 || d.Sq >= KM; }   // (a ragged Sq needs 32 rows to overlap)
+bool dkdv_steps(const Dims& d, const MaskDev& m) {
+  return m.allow != nullptr && dkdv_rows_ok(d) && m.q_chunk % KM == 0 && m.kv_block % DkvSmem<128, 2>::KN == 0 &&
+         (d.Sq + KM - 1) / KM <= dkdv_step_list_cap<128>();
 }
 
 }  // namespace
 
+// A mask that cuts through the steps or through a workgroup's keys, while its list and words fit
+// beside the ring: one word for every step and for every key block that 256 keys can lie in.
+bool bwd_dkdv_bf16_takes_rows(const Dims& d, const MaskDev& m) {
+  if (m.allow == nullptr || !dkdv_rows_ok(d) || dkdv_steps(d, m)) return false;
+  constexpr int KN = DkvSmem<128, 2>::KN;
+  const int w = (d.Skv - 1) / m.kv_block + 1, spH = (d.Sq + KM - 1) / KM;
+  long nf = m.kv_block % KN == 0 ? 1 : KN % m.kv_block == 0 ? KN / m.kv_block : (KN - 2) / m.kv_block + 2;
+  if (nf > w) nf = w;
+  const int cap = d.D == 64 ? DkvSmem<64, 2>::WORDS_CAP : d.D == 96 ? DkvSmem<96, 2>::WORDS_CAP : DkvSmem<128, 2>::WORDS_CAP;
+  return (1 + nf) * spH + 1 <= cap;
+}
+
 hipError_t launch_bwd_dkdv_bf16(const BwdArgs& a, hipStream_t s) {
   const Dims& d = a.d;
   // a mask that only selects whole steps for whole workgroups runs on the dense kernel
-  const bool rows_ok = d.Sq % KM == 0 || d.Sq >= KM;           // (a ragged Sq needs 32 rows to overlap)
-  const bool steps = a.mask.allow != nullptr && rows_ok && a.mask.q_chunk % KM == 0 &&
-                     a.mask.kv_block % DkvSmem<128, 2>::KN == 0 && (d.Sq + KM - 1) / KM <= dkdv_step_list_cap<128>();
+  const bool rows_ok = dkdv_rows_ok(d), steps = dkdv_steps(d, a.mask);
   static_assert(DkvSmem<64, 2>::KN == DkvSmem<128, 2>::KN && dkdv_step_list_cap<64>() == dkdv_step_list_cap<128>() &&
                 DkvSmem<96, 2>::KN == DkvSmem<128, 2>::KN && dkdv_step_list_cap<96>() == dkdv_step_list_cap<128>(),
                 "the test above is the same for both head dims");
   if (steps) return d.D == 64 ? launch<64, false, true>(a, s) : d.D == 96 ? launch<96, false, true>(a, s) : launch<128, false, true>(a, s);
+  if (a.rows.words != nullptr)
+    return d.D == 64 ? launch<64, false, true, true>(a, s) : d.D == 96 ? launch<96, false, true, true>(a, s) : launch<128, false, true, true>(a, s);
   const bool general = a.mask.allow != nullptr || !rows_ok;
   if (d.D == 64) return general ? launch<64, true>(a, s) : launch<64, false>(a, s);
   if (d.D == 96) return general ? launch<96, true>(a, s) : launch<96, false>(a, s);

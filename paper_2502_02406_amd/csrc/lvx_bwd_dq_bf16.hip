@@ -834,8 +834,13 @@ hipError_t launch_bwd_bf16(const BwdArgs& a, unsigned stages, hipStream_t s) {
     rest.dq_tiles = nullptr;
     return launch_bwd_bf16(rest, stages, s);
   }
-  if (stages & 2) e = launch_bwd_dkdv_bf16(a, s);
-  if (e == hipSuccess && (stages & 4)) e = launch_bwd_dq_bf16(a, s);
+  BwdArgs m = a;
+  if (a.mask.allow != nullptr && (stages & 2) && bwd_dkdv_bf16_takes_rows(a.d, a.mask)) {
+    m.rows = mask_rows_of(a.d, a.mask);
+    if (a.rows_ws != nullptr && mask_rows_bytes(a.d, m.rows) <= a.rows_ws_bytes) e = launch_mask_rows(a.d, a.mask, &m.rows, a.rows_ws, s);
+  }
+  if (e == hipSuccess && (stages & 2)) e = launch_bwd_dkdv_bf16(m, s);
+  if (e == hipSuccess && (stages & 4)) e = launch_bwd_dq_bf16(m, s);
   return e;
 }
 

@@ -15,6 +15,17 @@ struct MaskDev {
   long stride_b, stride_q;
 };
 
+// The bitmap regrouped by launch_mask_rows: word ((b, qt, f), rb) holds, for the 32 query rows
+// 256 qt + 32 rb + (0 .. 31) of a head, which of them see key block f (bit r = row r; rows past the
+// last one see nothing).  The eight words of a key block and a tile of 256 rows stand together,
+// and every tile has one padding block more that nobody sees, so that the words of two neighbouring
+// key blocks are one run of 64 bytes for every block there is.
+struct MaskRows {
+  const unsigned* words;  // nullptr: not made for this call
+  int w1, n_qt;           // key blocks (with the padding one), tiles of 256 rows
+  long stride_b;          // words from one batch to the next (0: one bitmap for all)
+};
+
 // Shape, strides (in elements) and scale shared by every kernel.
 struct Dims {
   int B, Hq, Hkv, Sq, Skv, D;
@@ -46,6 +57,9 @@ struct FwdArgs {
 struct BwdArgs {
   Dims d;
   MaskDev mask;
+  MaskRows rows;        // set by launch_bwd_bf16 where a kernel reads it
+  void* rows_ws;        // workspace for its words (rows_ws_bytes), or nullptr
+  size_t rows_ws_bytes;
   const void *q, *k, *v, *o, *d_o;
   const float* lse;     // final statistic, [B,Hq,Sq]
   float* delta;         // workspace, [B,Hq,Sq]: rowsum(dO * O)
@@ -170,6 +184,10 @@ bool fwd_bf16_two_pass_fits(const Dims& d, const MaskDev& m);   // a masked forw
 bool fwd_bf16_one_pass_fits(const Dims& d, const MaskDev& m);   // ... or as one launch of the dense kernel over tile lists
 hipError_t launch_fwd_general_bf16(const FwdArgs& a, hipStream_t s);   // masked or ragged problems
 int bwd_bf16_pick_split(const Dims& d, int n_cu, bool masked);
+MaskRows mask_rows_of(const Dims& d, const MaskDev& m);                 // the geometry (no words yet)
+size_t mask_rows_bytes(const Dims& d, const MaskRows& r);
+hipError_t launch_mask_rows(const Dims& d, const MaskDev& m, MaskRows* r, void* words, hipStream_t s);
+bool bwd_dkdv_bf16_takes_rows(const Dims& d, const MaskDev& m);         // the dK/dV kernel masks by MaskRows
 // memory-bound helpers
 hipError_t launch_merge(const MergeArgs& a, int part_is_f32, int out_is_f32, hipStream_t s);
 hipError_t launch_delta(const Dims& d, const void* o, const void* d_o, int is_f32, const float* lse,

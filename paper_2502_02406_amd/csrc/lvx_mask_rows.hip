@@ -1,0 +1,63 @@
+// Media mask, regrouped once per call for the kernels that mask by data instead of by control flow
+// (lvx_internal.h, MaskRows): for every block of 32 query rows and every key block, one word whose
+// bit r says whether row r of the block sees the key block.  The kernels then answer "which
+// rows see these keys" with one word, whatever the chunk length, instead of probing the bitmap a
+// chunk at a time in every workgroup of every head.
+//
+// Bound by the latency of its probes: a thread makes one word from its 1 .. 32 chunks, eight
+// probes on their way at a time, a wave's lanes on 64 neighbouring key blocks of one chunk row.
+// 2048 chunks of two rows x 2048 key blocks (4 MiB of bitmap, 1 MiB of words): 8.4 us; 32 chunks x
+// 32 key blocks: 4.5 us, a launch and a round trip.
+#include "lvx_internal.h"
+
+namespace lvx {
+
+namespace {
+
+constexpr int FB = 64;                 // key blocks per workgroup
+
+__global__ void __launch_bounds__(512) mask_rows_kernel(MaskDev m, MaskRows r, int Sq, unsigned* out) {
+  const int f = blockIdx.x * FB + (threadIdx.x & (FB - 1)), rb = threadIdx.x / FB, qt = blockIdx.y;
+  if (f >= r.w1) return;
+  const int i0 = qt * 256 + rb * 32, rows = min(32, Sq - i0);
+  unsigned bits = 0;
+  if (f < r.w1 - 1 && rows > 0) {      // (the last key block is a padding one that nobody sees)
+    const uint8_t* const base = m.allow + blockIdx.z * m.stride_b + f;
+    const int ca = i0 / m.q_chunk, cb = (i0 + rows - 1) / m.q_chunk;
+    for (int c = ca; c <= cb; c += 8) {
+      uint8_t v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = base[(long)min(c + u, cb) * m.stride_q];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const long lo = (long)(c + u) * m.q_chunk - i0;                // the chunk's rows, relative to the block
+        const int a = (int)max(lo, 0L), z = (int)min(lo + m.q_chunk, (long)rows);
+        if (c + u <= cb && v[u] != 0 && z > a) bits |= (z - a == 32 ? ~0u : ((1u << (z - a)) - 1u) << a);
+      }
+    }
+  }
+  out[blockIdx.z * r.stride_b + ((long)qt * r.w1 + f) * 8 + rb] = bits;
+}
+
+}  // namespace
+
+MaskRows mask_rows_of(const Dims& d, const MaskDev& m) {
+  MaskRows r;
+  r.words = nullptr;
+  r.w1 = (d.Skv - 1) / m.kv_block + 2;
+  r.n_qt = (d.Sq + 255) / 256;
+  r.stride_b = m.stride_b != 0 ? (long)r.n_qt * r.w1 * 8 : 0;          // (one bitmap for all batches: one set of words)
+  return r;
+}
+size_t mask_rows_bytes(const Dims& d, const MaskRows& r) {
+  return (size_t)(r.stride_b != 0 ? d.B : 1) * r.n_qt * r.w1 * 8 * sizeof(unsigned);
+}
+
+hipError_t launch_mask_rows(const Dims& d, const MaskDev& m, MaskRows* r, void* words, hipStream_t s) {
+  r->words = (const unsigned*)words;
+  const dim3 grid((r->w1 + FB - 1) / FB, r->n_qt, r->stride_b != 0 ? d.B : 1);
+  mask_rows_kernel<<<grid, 512, 0, s>>>(m, *r, d.Sq, (unsigned*)words);
+  return hipGetLastError();
+}
+
+}  // namespace lvx

@@ -305,13 +305,18 @@ __host__ __device__ inline long xcd_grid(int n_heads, int items_per_head) {
   const long n_vh = (long)n_heads * S;                    // multiple of 8
   return n_vh * per_vh;
 }
-__device__ __forceinline__ bool xcd_decode(long pid, int n_heads, int items_per_head, HeadWork* w) {
+// interleave: the parts of a head take its items in turn instead of a run each, for items whose
+// work falls or rises along the head (key tiles under a causal mask): with runs, one XCD would get
+// the long items of a head and another the short ones.
+__device__ __forceinline__ bool xcd_decode(long pid, int n_heads, int items_per_head, HeadWork* w,
+                                           bool interleave = false) {
   const int S = xcd_parts(n_heads);
   const int per_vh = (items_per_head + S - 1) / S;
   const int xcd = (int)(pid % 8);
   const long slot = pid / 8;
   const long vh = (slot / per_vh) * 8 + xcd;
-  const int item = (int)(vh % S) * per_vh + (int)(slot % per_vh);
+  const int item = interleave ? (int)(slot % per_vh) * S + (int)(vh % S)
+                              : (int)(vh % S) * per_vh + (int)(slot % per_vh);
   w->head = (int)(vh / S);
   w->item = item;
   return item < items_per_head;

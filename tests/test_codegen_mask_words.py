@@ -1,0 +1,12 @@
+"""Generated-code checks of the kernels that mask by words (see test_codegen.py for the rules)."""
+import pytest
+
+from test_codegen import _asm, _blocks, _kernel
+
+
+@pytest.mark.parametrize("D,loop_mfma", [(64, 64), (96, 96), (128, 128)])
+def test_dkdv_words_loop_is_one_block(D, loop_mfma):
+    body = _kernel(_asm("lvx_bwd_dkdv_bf16.hip"), f"bwd_dkdv_bf16_kernelILi{D}ELb0ELb1ELb1E")
+    loops = [b for b in _blocks(body) if b.count("v_mfma_f32_32x32x16_bf16") == loop_mfma]
+    assert len(loops) == 1, "steady-state loop not found as one basic block"
+    assert "v_accvgpr" not in loops[0] and "scratch_" not in loops[0]

@@ -1,0 +1,35 @@
+"""Media masks that cut through tiles, against the fp64 oracle: the kernels that keep or drop
+probabilities by one word per (32 query rows, key block) at the sizes where the words can go wrong --
+chunks of one row, of an odd length, longer than a workgroup's rows; key blocks that straddle the
+workgroups' keys, that several share, that one fills; a last step of rows that overlaps the one
+before (Sq % 32), a last key block of a few keys, rows and keys that pair with nothing, a bitmap per
+batch entry, several heads per K/V head.  Tolerances: those of test_gpu_parity (bf16)."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import run_case, small
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("name,kw,p_on", [
+    ("mw_chunks_of_one", dict(D=64, Hq=2, Hkv=1, Sq=96, Skv=1024, q_chunk=1, kv_block=64), 0.3),
+    ("mw_odd_chunks_729", dict(Hq=7, Hkv=1, Sq=333, Skv=2187 + 10, q_chunk=37, kv_block=729), 0.5),
+    ("mw_recent_pairs", dict(D=64, Hq=2, Hkv=2, Sq=512, Skv=16384, q_chunk=2, kv_block=64), "recent"),
+    ("mw_batch_ragged", dict(B=2, Hq=4, Hkv=2, Sq=65, Skv=1333, q_chunk=16, kv_block=100), 0.4),
+    ("mw_causal_729", dict(Hq=4, Hkv=1, Sq=640, Skv=7290, q_chunk=64, kv_block=729), "causal"),
+    ("mw_long_chunks_d96", dict(D=96, Hq=4, Hkv=2, Sq=700, Skv=1500, q_chunk=300, kv_block=450), 0.6),
+    ("mw_sparse", dict(Hq=2, Sq=288, Skv=6000, q_chunk=9, kv_block=75), 0.03),
+    ("mw_short_blocks", dict(Hq=2, Sq=70, Skv=700, q_chunk=33, kv_block=40), 0.5),
+])
+def test_masks_by_words(name, kw, p_on):
+    w = small(name, **kw)
+    nq, nk = -(-w.Sq // w.q_chunk), -(-w.Skv // w.kv_block)
+    if p_on == "recent":
+        allow = np.arange(nk)[None, :] == np.minimum(np.arange(nq)[:, None], nk - 1)
+    elif p_on == "causal":
+        allow = np.arange(nk)[None, :] <= np.arange(nq)[:, None]
+    else:
+        rng = np.random.Generator(np.random.Philox(99 + len(name)))
+        allow = rng.random((w.B, nq, nk) if w.B > 1 else (nq, nk)) < p_on
+    run_case(w, do_bwd=True, allow=allow)
