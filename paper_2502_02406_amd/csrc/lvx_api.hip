@@ -85,33 +85,6 @@ int bwd_split(const Dims& d, lvx_dtype dtype, bool masked) {
   return dtype == LVX_BF16 ? bwd_bf16_pick_split(d, device_cu_count(), masked) : 1;
 }
 
-// bf16, no mask, a key count that is no multiple of the 64-key tile (and at least two tiles): the
-// dense kernel takes the whole tiles, the general kernel the keys that are left, as one more
-// partial result of the combine.
-constexpr int FWD_TILE = 64;
-bool fwd_has_tail(const Dims& d, lvx_dtype dtype, bool masked) {
-  return dtype == LVX_BF16 && !masked && d.Skv % FWD_TILE != 0 && d.Skv >= 2 * FWD_TILE;
-}
-// launches of the bf16 forward that leave partial results in slices [0, n_split (+ 1)) of
-// o_part / lse_part: every split of the whole tiles, then the tail
-hipError_t launch_fwd_bf16_parts(FwdArgs a, hipStream_t s) {
-  const int tail = a.d.Skv % FWD_TILE;
-  FwdArgs head = a;
-  head.partial = 1;
-  head.part0 = 0;
-  head.d.Skv = a.d.Skv - tail;
-  hipError_t e = launch_fwd_bf16(head, s);
-  if (e != hipSuccess) return e;
-  FwdArgs rest = a;
-  rest.partial = 1;
-  rest.part0 = a.n_split;
-  rest.n_split = 1;
-  rest.k = (const uint16_t*)a.k + (long)head.d.Skv * a.d.kv_ss;
-  rest.v = (const uint16_t*)a.v + (long)head.d.Skv * a.d.kv_ss;
-  rest.d.Skv = tail;
-  return launch_fwd_bf16(rest, s);
-}
-
 // bf16 under a media mask that fits (fwd_bf16_two_pass_fits): the dense kernel over the key tiles
 // that every row of a workgroup sees, then the general kernel on the other visible tiles; each
 // launch leaves n_split partial results (slices [0, n_split) and [n_split, 2 n_split)).
@@ -120,7 +93,7 @@ int fwd_two_pass_split(int n_split, int reserve) {   // each launch's split coun
   return n_split < cap ? n_split : cap;
 }
 bool fwd_two_pass(const Dims& d, lvx_dtype dtype, const MaskDev& m) {
-  return dtype == LVX_BF16 && fwd_bf16_two_pass_fits(d, m);
+  return dtype == LVX_BF16 && fwd_bf16_two_pass_fits(d, m) && !fwd_bf16_takes_rows(d, m);
 }
 hipError_t launch_fwd_bf16_two_pass(FwdArgs a, hipStream_t s) {
   a.partial = 1;
@@ -133,21 +106,23 @@ hipError_t launch_fwd_bf16_two_pass(FwdArgs a, hipStream_t s) {
   return launch_fwd_bf16(a, s);
 }
 
-// How lvx_xattn_fwd runs a problem: the KV splits of each launch, whether a ragged tail or a media
-// mask makes it two launches, and the partial results the combine then reads.
-struct FwdPlan { int n_split; bool tail, two; int n_parts; };
-FwdPlan fwd_plan(const Dims& d, lvx_dtype dtype, const MaskDev& m) {
-  const bool masked = m.allow != nullptr;
+// How a forward call runs: the KV splits of each launch, whether a media mask makes it two launches,
+// the partial results the combine then reads, and the bytes of MaskRows' words the kernel reads.
+// `reserve` parts of the combine are taken already (lvx_xattn_fwd_merge: the running state).
+struct FwdPlan { int n_split; bool two; int n_parts; size_t rows_bytes; };
+FwdPlan fwd_plan(const Dims& d, lvx_dtype dtype, const MaskDev& m, int reserve) {
+  const bool masked = m.allow != nullptr, bf16 = dtype == LVX_BF16;
   FwdPlan f;
   f.n_split = fwd_split(d, dtype, masked);
-  f.tail = fwd_has_tail(d, dtype, masked);
+  if (f.n_split > LVX_MAX_PARTS - reserve) f.n_split = LVX_MAX_PARTS - reserve;
   f.two = masked && fwd_two_pass(d, dtype, m);
-  if (f.tail && f.n_split > LVX_MAX_PARTS - 1) f.n_split = LVX_MAX_PARTS - 1;
-  if (f.two) f.n_split = fwd_two_pass_split(f.n_split, 0);
+  if (f.two) f.n_split = fwd_two_pass_split(f.n_split, reserve);
+  const bool rows = masked && bf16 && fwd_bf16_takes_rows(d, m);
+  f.rows_bytes = rows ? align_up(mask_rows_bytes(d, mask_rows_of(d, m))) : 0;
   // (one launch over tile lists: its workgroups start longest first, which evens the load out
   // with half the splits the other masked forms want)
-  if (masked && dtype == LVX_BF16 && fwd_bf16_one_pass_fits(d, m) && f.n_split > 1) f.n_split /= 2;
-  f.n_parts = f.two ? 2 * f.n_split : f.n_split + (f.tail ? 1 : 0);
+  if (masked && bf16 && (rows || fwd_bf16_one_pass_fits(d, m)) && f.n_split > 1) f.n_split /= 2;
+  f.n_parts = f.two ? 2 * f.n_split : f.n_split;
   return f;
 }
 
@@ -158,10 +133,6 @@ size_t fwd_ws(const Dims& d, int n_split) {
 }
 // lvx_xattn_fwd_merge: the splits' partial results (bf16 kernels that split the key range), or one
 // float32 partial result (float32 kernels, which have no fused epilogue)
-int fwd_merge_split(const Dims& d, lvx_dtype dtype, bool masked) {
-  const int n = fwd_split(d, dtype, masked);
-  return n < LVX_MAX_PARTS ? n : LVX_MAX_PARTS - 1;     // the running state is one more part of the combine
-}
 size_t fwd_merge_ws(const Dims& d, lvx_dtype dtype, int n_split) {
   return fwd_ws(d, dtype == LVX_F32 ? 2 : n_split);      // (fwd_ws(d, 2) holds more than one partial result)
 }
@@ -192,7 +163,8 @@ namespace lvx {
 size_t fwd_workspace_need(const lvx_problem* p, lvx_dtype dtype, const lvx_mask* mask) {
   if (check_problem(p, dtype) != LVX_OK || check_mask(p, mask) != LVX_OK) return 0;
   const Dims d = make_dims(p);
-  return fwd_ws(d, fwd_plan(d, dtype, make_mask(mask)).n_parts);
+  const FwdPlan f = fwd_plan(d, dtype, make_mask(mask), 0);
+  return fwd_ws(d, f.n_parts) + f.rows_bytes;
 }
 }  // namespace lvx
 
@@ -216,22 +188,21 @@ const char* lvx_strerror(lvx_status s) {
 size_t lvx_xattn_workspace_bytes(const lvx_problem* p, lvx_dtype dtype, int which) {
   if (check_problem(p, dtype) != LVX_OK) return 0;
   const Dims d = make_dims(p);
-  // (the size does not depend on whether the call will carry a mask: the larger of the two split counts)
+  // (the size does not depend on whether the call will carry a mask, nor on which: the larger of the
+  // split counts -- a masked bf16 call may run as two launches that leave their splits' partial results
+  // side by side -- and the most words that MaskRows can take)
   const auto larger = [](int x, int y) { return x > y ? x : y; };
-  const int tail_part = fwd_has_tail(d, dtype, false) ? 1 : 0;        // (one more partial result: the tail's)
-  // (a masked bf16 call may run as two launches that leave their splits' partial results side by side)
-  const int masked_parts = dtype == LVX_BF16 ? 2 * fwd_two_pass_split(fwd_split(d, dtype, true), 0) : fwd_split(d, dtype, true);
-  if (which == LVX_WS_FWD)
-    return fwd_ws(d, larger(larger(masked_parts, fwd_split(d, dtype, true)), fwd_split(d, dtype, false) + tail_part));
+  const size_t rows_most = dtype == LVX_BF16 ? align_up(fwd_bf16_rows_bytes_most(d)) : 0;
+  const auto parts = [&](int reserve) {
+    const int masked = dtype == LVX_BF16 ? 2 * fwd_two_pass_split(fwd_split(d, dtype, true), reserve) : 1;
+    const auto cap = [&](int n) { return n < LVX_MAX_PARTS - reserve ? n : LVX_MAX_PARTS - reserve; };
+    return larger(larger(masked, cap(fwd_split(d, dtype, true))), cap(fwd_split(d, dtype, false)));
+  };
+  if (which == LVX_WS_FWD) return fwd_ws(d, parts(0)) + rows_most;
   if (which == LVX_WS_BWD)
     return bwd_ws(d, larger(bwd_slices(d, dtype, true), bwd_slices(d, dtype, false)),
                   dtype == LVX_BF16 && bwd_fused_bf16_supported(d, false));
-  if (which == LVX_WS_FWD_MERGE)
-  {
-    const int masked_merge = dtype == LVX_BF16 ? 2 * fwd_two_pass_split(fwd_merge_split(d, dtype, true), 1) : 1;
-    return fwd_merge_ws(d, dtype, larger(larger(masked_merge, fwd_merge_split(d, dtype, true)),
-                                         fwd_merge_split(d, dtype, false) + tail_part));
-  }
+  if (which == LVX_WS_FWD_MERGE) return fwd_merge_ws(d, dtype, parts(1)) + rows_most;
   return 0;
 }
 
@@ -250,22 +221,22 @@ lvx_status lvx_xattn_fwd(const lvx_problem* p, lvx_dtype dtype, const void* q, c
   a.q = q; a.k = k; a.v = v; a.o = o; a.o_is_f32 = o_dtype == LVX_F32; a.lse = lse;
   a.merge_into = 0;
   a.partial = 0; a.part0 = 0; a.pass = 0;
-  const FwdPlan plan = fwd_plan(a.d, dtype, a.mask);
+  const FwdPlan plan = fwd_plan(a.d, dtype, a.mask, 0);
   a.n_split = plan.n_split;
-  const bool tail = plan.tail, two = plan.two;
   const int n_parts = plan.n_parts;
   a.o_part = nullptr; a.lse_part = nullptr;
-  const size_t need = fwd_ws(a.d, n_parts);
+  const size_t need = fwd_ws(a.d, n_parts) + plan.rows_bytes;
   if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < need) return LVX_ERR_WORKSPACE;
+  a.rows = MaskRows{};
+  a.rows_ws = plan.rows_bytes > 0 ? (char*)workspace + fwd_ws(a.d, n_parts) : nullptr;
   hipStream_t s = (hipStream_t)hip_stream;
   const size_t rows = (size_t)a.d.B * a.d.Hq * a.d.Sq;
   if (n_parts > 1) {
     a.o_part = (float*)workspace;
     a.lse_part = (float*)((char*)workspace + align_up(rows * a.d.D * sizeof(float) * n_parts));
   }
-  hipError_t e = two    ? launch_fwd_bf16_two_pass(a, s)
-                 : tail ? launch_fwd_bf16_parts(a, s)
-                        : dtype == LVX_BF16 ? launch_fwd_bf16(a, s) : launch_fwd_f32(a, s);
+  hipError_t e = plan.two ? launch_fwd_bf16_two_pass(a, s)
+                          : dtype == LVX_BF16 ? launch_fwd_bf16(a, s) : launch_fwd_f32(a, s);
   if (e != hipSuccess) return LVX_ERR_HIP;
   if (n_parts > 1) {
     MergeArgs m;
@@ -298,31 +269,28 @@ lvx_status lvx_xattn_fwd_merge(const lvx_problem* p, lvx_dtype dtype, const void
   a.mask = make_mask(mask);
   a.q = q; a.k = k; a.v = v; a.o_is_f32 = 1;
   a.partial = 0; a.part0 = 0; a.pass = 0;
-  a.n_split = fwd_merge_split(a.d, dtype, mask != nullptr);
-  const bool tail = fwd_has_tail(a.d, dtype, mask != nullptr);
-  const bool two = mask != nullptr && fwd_two_pass(a.d, dtype, a.mask);
-  if (tail && a.n_split > LVX_MAX_PARTS - 2) a.n_split = LVX_MAX_PARTS - 2;    // (the running state and the tail are parts too)
-  if (two) a.n_split = fwd_two_pass_split(a.n_split, 1);
-  if (mask != nullptr && dtype == LVX_BF16 && fwd_bf16_one_pass_fits(a.d, a.mask) && a.n_split > 1) a.n_split /= 2;
-  const int n_launch_parts = two ? 2 * a.n_split : a.n_split + (tail ? 1 : 0);
+  const FwdPlan plan = fwd_plan(a.d, dtype, a.mask, 1);          // (the running state is one more part of the combine)
+  a.n_split = plan.n_split;
   a.o_part = nullptr; a.lse_part = nullptr;
-  const size_t need = fwd_merge_ws(a.d, dtype, n_launch_parts);
+  const size_t need = fwd_merge_ws(a.d, dtype, plan.n_parts) + plan.rows_bytes;
   if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < need) return LVX_ERR_WORKSPACE;
+  a.rows = MaskRows{};
+  a.rows_ws = plan.rows_bytes > 0 ? (char*)workspace + fwd_merge_ws(a.d, dtype, plan.n_parts) : nullptr;
   hipStream_t s = (hipStream_t)hip_stream;
   const size_t rows = (size_t)a.d.B * a.d.Hq * a.d.Sq;
-  if (dtype == LVX_BF16 && a.n_split == 1 && !tail && !two) {   // Rescale in the kernel's epilogue
+  if (dtype == LVX_BF16 && plan.n_parts == 1) {   // Rescale in the kernel's epilogue
     a.o = o_acc; a.lse = lse_acc; a.merge_into = 1;
     return launch_fwd_bf16(a, s) == hipSuccess ? LVX_OK : LVX_ERR_HIP;
   }
   // partial result(s) in the workspace, then one combine over the running state and them
   a.merge_into = 0;
-  const int n_parts = dtype == LVX_BF16 ? n_launch_parts : 1;
+  const int n_parts = plan.n_parts;
   float* const o_part = (float*)workspace;
   float* const l_part = (float*)((char*)workspace + align_up(rows * a.d.D * sizeof(float) * n_parts));
   hipError_t e;
   if (dtype == LVX_BF16) {
     a.o = nullptr; a.lse = nullptr; a.o_part = o_part; a.lse_part = l_part;
-    e = two ? launch_fwd_bf16_two_pass(a, s) : tail ? launch_fwd_bf16_parts(a, s) : launch_fwd_bf16(a, s);
+    e = plan.two ? launch_fwd_bf16_two_pass(a, s) : launch_fwd_bf16(a, s);
   } else {
     a.o = o_part; a.lse = l_part; a.n_split = 1;
     e = launch_fwd_f32(a, s);
@@ -407,7 +375,7 @@ lvx_status lvx_xattn_bwd_stages(const lvx_problem* p, lvx_dtype dtype, const voi
   a.stats_ovl = has_stats_ovl(a.d) ? a.stats + stats_floats(a.d) : nullptr;
   a.dq_accum = dq_accum; a.dk = dk; a.dv = dv;
   a.dq_part = a.n_split_dq > 1 ? (float*)((char*)workspace + bwd_ws_fixed(a.d)) : nullptr;
-  a.rows = MaskRows{nullptr, 0, 0, 0};
+  a.rows = MaskRows{};
   a.rows_ws = mask != nullptr && n_slices > 0 ? (char*)workspace + bwd_ws_fixed(a.d) + (n_slices - 1) * bwd_slice_bytes(a.d) : nullptr;
   a.rows_ws_bytes = bwd_slice_bytes(a.d);
   a.dq_tiles = fused ? (float*)((char*)workspace + bwd_ws_fixed(a.d) + bwd_ws_part(a.d, n_slices)) : nullptr;

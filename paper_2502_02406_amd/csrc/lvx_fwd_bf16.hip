@@ -45,8 +45,13 @@ constexpr float LAZY_SUM = 64.0f;      // a lane's 16 probabilities of a half ma
 #endif
 constexpr int XE = LVX_FWD_XE;                  // elements of a half converted during the contraction (of 32)
 
-// Dense attention with Skv a multiple of 64 only: no mask code and no ragged tile, so that nothing
-// stands between the phases of the pipeline (masked and ragged problems: lvx_fwd_general_bf16.hip).
+// Dense attention, no mask code, so that nothing stands between the phases of the pipeline (other
+// masks: lvx_fwd_general_bf16.hip).  A key count that is no multiple of 64 needs none either: the last
+// tile takes the keys Skv-64 .. Skv-1, and those of them that the tile before has seen get the score
+// -infinity; the last tile is always handled in the unpipelined end of the loop.
+// (A launch of the general kernel for the keys left over, and a combine with its partial result, took
+// 46 + 55 of 2500 us for 5514 rows x 32 heads against 32020 keys, and 8 of 43 us for one row against
+// 6404 keys.)
 // LIST = 1: the same kernel over a list of key tiles -- those that EVERY row of the workgroup sees
 // under a media mask (FwdArgs::pass == 1).  Nothing is masked inside such a tile; only the tile
 // numbers come from the list, which the KV splits share evenly.  The other visible tiles are left
@@ -58,6 +63,18 @@ constexpr int XE = LVX_FWD_XE;                  // elements of a half converted 
 // every probability is exp2(-inf) = 0 -- so that the whole mask costs two selects per half tile
 // and one launch does it all.  (A workgroup moves at the pace of its busiest wave anyway: a wave
 // that skipped the tile would wait at the barrier.)
+// LIST = 3: any other mask of at least 64 keys per key block.  The list holds the tiles that any row
+// of the workgroup sees (from one bit per key block, MaskRows::any); with every tile's copies
+// travel the words of the two key blocks it can lie in, and a half's reference becomes +infinity
+// lane by lane, by one select with such a word as the lane mask.  A half that a key block's end
+// cuts for some row of the wave takes the branch that raises the reference: its scores get
+// -infinity where the words say so and it is converted again from the registers they are still in,
+// so the steady loop has no other branch than before.  A row's first visible half, whose reference
+// comes from keys it does not see, goes the same way when its sum shows that it is far too high.
+// Bound by the same issue slots as the dense loop, plus about 45 instructions a tile.  2048 rows x 28
+// heads in chunks of 64 against 32 frames of 729 keys, causal, D = 128: 0.82 -> 0.45 ms (780 TFLOP/s of
+// visible pairs); 4096 rows x 8 heads in chunks of 2, each seeing one of 2048 frames of 64 keys,
+// D = 64: 0.78 -> 0.13 ms for 268 MB of K and V.
 template <int D, int LIST = 0>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 fwd_bf16_kernel(FwdArgs a) {
@@ -77,7 +94,7 @@ fwd_bf16_kernel(FwdArgs a) {
   const int n_qt = (rows_kv + QM - 1) / QM;
   const int per_split = PACK ? n_qt : G * n_qt;
   int b, hk, split, hq0, qt;
-  if constexpr (LIST == 2) {
+  if constexpr (LIST >= 2) {
     // Under a mask the query tiles of a head differ in how many key tiles they see (under a causal
     // one, the later the tile the more).  Workgroups start in the order of their numbers: the later
     // query tiles go first, so that the short ones fill the gaps the long ones leave at the end;
@@ -137,7 +154,42 @@ fwd_bf16_kernel(FwdArgs a) {
   int* const tlist = (int*)(smem + SM::RING + SM::BITS_BYTES);
   constexpr int LIST_CAP = SM::WIN_BYTES / 4 - 1;
   constexpr int VIS_SHIFT = 24;                     // LIST = 2: a list entry is tile | row-block bits << 24
-  if (LIST) {
+  if constexpr (LIST == 3) {
+    // one bit per key block -> one bit per tile -> the list; both planes in the bits area
+    unsigned long long* const any = (unsigned long long*)(smem + SM::RING);
+    unsigned long long* const plane = any + 256;
+    const unsigned long long* const src = a.rows.any + b * a.rows.any_stride_b + (long)qt * a.rows.any_words;
+    for (int w = tid; w < a.rows.any_words; w += 256) any[w] = src[w];
+    __syncthreads();
+    for (int base = 0; base < n_tiles; base += 256) {          // workgroup-uniform trip count
+      const int t = base + tid;
+      bool on = false;
+      if (t < n_tiles) {
+        const int fa = t * TN / a.mask.kv_block, fb = min(t * TN + TN, d.Skv) - 1, fz = fb / a.mask.kv_block;
+        on = ((any[fa / 64] >> (fa % 64)) | (any[fz / 64] >> (fz % 64))) & 1ull;
+      }
+      const unsigned long long m = __ballot(on);
+      if ((tid & 63) == 0 && t < n_tiles) plane[t / 64] = m;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      const int n_words = (n_tiles + 63) / 64;                 // at most 64: a word per lane
+      const unsigned long long mine = lane < n_words ? plane[lane] : 0ull;
+      int count = 0;
+      for (int k = 0; k < n_words; ++k) {
+        const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)mine, k);
+        const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(mine >> 32), k);
+        const unsigned long long m = ((unsigned long long)hi << 32) | lo;
+        if ((m >> lane) & 1ull) tlist[count + __popcll(m & ((1ull << lane) - 1ull))] = k * 64 + lane;
+        count += (int)__popcll(m);
+      }
+      if (lane == 0) tlist[LIST_CAP] = count;
+    }
+    __syncthreads();
+    const int nn = __builtin_amdgcn_readfirstlane(tlist[LIST_CAP]);
+    t_begin = (int)((long)split * nn / a.n_split);
+    t_end = (int)((long)(split + 1) * nn / a.n_split);
+  } else if (LIST) {
     const int i_wg0 = qt * QM, i_wg1 = min(d.Sq, i_wg0 + QM) - 1;
     const int c0 = i_wg0 / a.mask.q_chunk, h = i_wg1 / a.mask.q_chunk - c0 + 1;     // chunks of this workgroup's rows
     const int w = (d.Skv - 1) / a.mask.kv_block + 1;
@@ -221,6 +273,24 @@ fwd_bf16_kernel(FwdArgs a) {
     else
       return (1 << QB) - 1;
   };
+  // first key of a tile (LIST = 0, 3: the last tile is moved back to end with the last key), and
+  // how many of its keys the tile before has seen
+  constexpr bool RAGGED = LIST == 0 || LIST == 3;
+  auto tile_j0 = [&](int t) __attribute__((always_inline)) -> int { return RAGGED ? min(t * TN, d.Skv - TN) : t * TN; };
+  // LIST = 3: what a wave needs to know of a tile.  a, b: which rows of its two row blocks see the
+  // key block the tile starts in, and the one after it; edge: the tile's first key of that one (>= 64:
+  // none); low: keys that the tile before has seen
+  struct TileVis { unsigned a[QB], b[QB]; int edge, low; };
+  auto frame_of = [&](int j0) __attribute__((always_inline)) -> int {     // j0 / kv_block: exact for j0 < 2^18
+    return (int)(__umulhi((unsigned)j0, a.frame_magic) >> 4);
+  };
+  auto half_word = [&](const TileVis& v, int hb, int qb) __attribute__((always_inline)) -> unsigned {   // rows that see something
+    return (v.edge > 32 * hb ? v.a[qb] : 0u) | (v.edge < 32 * hb + 32 ? v.b[qb] : 0u);
+  };
+  auto half_cut = [&](const TileVis& v, int hb) __attribute__((always_inline)) -> bool {  // ... but some of them not everything
+    const unsigned x = (v.a[0] ^ v.b[0]) | (v.a[1] ^ v.b[1]);
+    return (v.edge > 32 * hb && v.edge < 32 * hb + 32 && x != 0u) || v.low > 32 * hb;
+  };
   const int nt = max(t_end - t_begin, 0);          // number of tiles this workgroup performs
   auto next_tile = [&](int t) __attribute__((always_inline)) -> int { return min(t, t_end); };
   int cursor = t_begin;                            // next tile to issue
@@ -244,17 +314,38 @@ fwd_bf16_kernel(FwdArgs a) {
   // matrix instructions of a phase: issued back to back, each waits for the one before it to be
   // accepted by the memory pipeline, and the wave would stand still for hundreds of cycles.
   const unsigned smem_u = lds_base(smem);
-  auto issue_part = [&](int t, char* st, int k) __attribute__((always_inline)) {   // full tiles only
-    const long tile = (long)t * TN * row_bytes + (long)wave * row_bytes;           // this wave's first row: tile row w
+  const unsigned words_u = smem_u + SM::TOTAL;     // LIST = 3: 256 bytes of words per ring stage, past everything else
+  const char* const rw0 = LIST == 3 ? (const char*)(a.rows.words + b * a.rows.stride_b + (long)qt * a.rows.w1 * 8) : nullptr;
+  auto issue_part = [&](int t, char* st, int k, int slot) __attribute__((always_inline)) {   // slot: the ring stage's number
+    const int j0 = tile_j0(t);
+    if (LIST == 3 && k == 2 * NCR) {               // the words of the tile's key block and of the next one: 64 bytes
+      dma4u(rw0 + (long)frame_of(j0) * 32, (unsigned)min(lane, 15) * 4, words_u + slot * 256);
+      return;
+    }
+    const long tile = (long)j0 * row_bytes + (long)wave * row_bytes;               // this wave's first row: tile row w
     const unsigned kdst = smem_u + (unsigned)(st - smem) + wave * SM::GS;
     if (k % 2 == 0) dma16u(k0 + tile, cp_off[k / 2], kdst + run_start(k / 2) * 16);
     else dma16u(v0 + tile, cp_off[k / 2], kdst + SM::TILE + run_start(k / 2) * 16);
   };
-  auto issue_tile = [&](int t, char* st) __attribute__((always_inline)) {
+  constexpr int NDMA = 2 * NCR + (LIST == 3 ? 1 : 0);    // copies per wave and tile
+  auto issue_tile = [&](int t, char* st, int slot) __attribute__((always_inline)) {
 #pragma unroll
-    for (int k = 0; k < 2 * NCR; ++k) issue_part(t, st, k);
+    for (int k = 0; k < NDMA; ++k) issue_part(t, st, k, slot);
   };
-  constexpr int NDMA = 2 * NCR;                    // copies per wave and tile
+  auto tile_vis = [&](int t, int slot) __attribute__((always_inline)) -> TileVis {     // of a tile that has landed in that stage
+    TileVis v;
+    const char* const w = smem + SM::TOTAL + slot * 256 + wave * QB * 4;
+    const u32x2 wa = *(const u32x2*)w, wb = *(const u32x2*)(w + 32);
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      v.a[qb] = (unsigned)__builtin_amdgcn_readfirstlane((int)wa[qb]);
+      v.b[qb] = (unsigned)__builtin_amdgcn_readfirstlane((int)wb[qb]);
+    }
+    const int j0 = tile_j0(t);
+    v.edge = (frame_of(j0) + 1) * a.mask.kv_block - j0;
+    v.low = t * TN - j0;
+    return v;
+  };
 
   // ---- softmax state of this lane's two query rows (both half-waves keep identical copies)
   f32x16 oacc[QB][DB];                 // O^T, relative to the reference
@@ -263,7 +354,15 @@ fwd_bf16_kernel(FwdArgs a) {
   // the reference that conversions subtract: r itself, or (LIST = 2) +infinity for a row block
   // that does not see the tile whose scores are being converted
   float rq_own[QB];
-  float (&rq)[QB] = *(LIST == 2 ? &rq_own : &r);
+  float (&rq)[QB] = *(LIST >= 2 ? &rq_own : &r);
+  auto set_rq_lanes = [&](const TileVis& v, int hb) __attribute__((always_inline)) {      // LIST = 3
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      const unsigned w = half_word(v, hb, qb);
+      const unsigned long long m = ((unsigned long long)w << 32) | w;       // (both half-waves hold the same rows)
+      asm("v_cndmask_b32 %0, %1, %2, %3" : "=v"(rq[qb]) : "v"(INFINITY), "v"(r[qb]), "s"(m));
+    }
+  };
   auto set_rq = [&](int vb) __attribute__((always_inline)) {
     if constexpr (LIST == 2) {
 #pragma unroll
@@ -364,18 +463,67 @@ fwd_bf16_kernel(FwdArgs a) {
   // -- and the accepted sums shrink by alpha = 2^(old - new), and the half is converted again
   // from its scores, which are still in their registers.  Rows that keep their reference get
   // identical values again.
-  auto commit = [&](const f32x16 (&s)[QB], u32x4 (&pw)[QB][2], int vb) __attribute__((always_inline)) {
+  // scores of keys below `low` of a tile -> -infinity (half hb)
+  auto mask_low = [&](f32x16 (&s)[QB], int hb, int low) __attribute__((always_inline)) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const bool out = 32 * hb + 8 * (v / 4) + 4 * g + (v % 4) < low;
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) s[qb][v] = out ? -INFINITY : s[qb][v];
+    }
+  };
+  // LIST = 3: scores of a half that the lane's row does not see -> -infinity
+  auto mask_words = [&](f32x16 (&s)[QB], int hb, const TileVis& v) __attribute__((always_inline)) {
+    auto below = [](int n) __attribute__((always_inline)) -> unsigned { return n <= 0 ? 0u : n >= 32 ? ~0u : (1u << n) - 1u; };
+    const unsigned first = below(v.edge - 32 * hb), seen = ~below(v.low - 32 * hb);
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      const unsigned va = 0u - ((v.a[qb] >> ql) & 1u), vb = 0u - ((v.b[qb] >> ql) & 1u);
+      const unsigned keys = (((va & first) | (vb & ~first)) & seen) >> (4 * g);
+#pragma unroll
+      for (int x = 0; x < 16; ++x) s[qb][x] = (keys >> (8 * (x / 4) + (x % 4))) & 1u ? s[qb][x] : -INFINITY;
+    }
+  };
+  constexpr float TOO_HIGH = 0x1p-60f;             // a row whose sum so far is smaller than this has a reference far above its scores
+  // (vb: LIST = 2, row blocks that see the tile; vis, hb: LIST = 3, the half's words)
+  auto commit = [&](f32x16 (&s)[QB], u32x4 (&pw)[QB][2], int vb, const TileVis& vis, int hb) __attribute__((always_inline)) {
     bool need = false;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) need |= !(l_half[qb] <= LAZY_SUM);
+    if constexpr (LIST == 3) {
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {
+        const unsigned w = half_word(vis, hb, qb);
+        need |= l_run[qb] + l_half[qb] < TOO_HIGH && ((w >> ql) & 1u);
+      }
+      if (__builtin_expect(half_cut(vis, hb), 0)) {
+        asm volatile("" ::: "memory");
+        mask_words(s, hb, vis);
+        convert(s, pw);
+        need = false;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+          need |= !(l_half[qb] <= LAZY_SUM) ||
+                  (l_run[qb] + l_half[qb] < TOO_HIGH && ((half_word(vis, hb, qb) >> ql) & 1u));
+      }
+    }
     if (__builtin_expect(__any(need), 0)) {
       asm volatile("" ::: "memory");               // keep this a real, rarely taken branch
       drain_oacc();
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
         if (LIST == 2 && !((vb >> qb) & 1)) continue;          // (scores the rows do not see raise nothing)
-        const float r_new = fmaxf(r[qb], row_max(s[qb]));
-        const float alpha = __builtin_amdgcn_exp2f(r[qb] - r_new);
+        float r_new = fmaxf(r[qb], row_max(s[qb]));
+        float alpha = __builtin_amdgcn_exp2f(r[qb] - r_new);
+        if constexpr (LIST == 3) {
+          // (scores the row does not see raise nothing; a row that has added up nothing yet takes its
+          // first visible half's maximum, be it lower than what it started from)
+          const bool seen = (half_word(vis, hb, qb) >> ql) & 1u;
+          const bool fresh = xhalf_sum(l_run[qb]) == 0.f;
+          const float m = row_max(s[qb]);
+          r_new = !seen || m == -INFINITY ? r[qb] : fresh ? m : fmaxf(r[qb], m);
+          alpha = fresh ? 0.f : __builtin_amdgcn_exp2f(r[qb] - r_new);
+        }
         r[qb] = r_new;
         l_run[qb] *= alpha;
 #pragma unroll
@@ -394,6 +542,7 @@ fwd_bf16_kernel(FwdArgs a) {
           asm volatile("s_nop 7" : "+a"(oacc[qb][0]), "+a"(oacc[qb][1]));
       }
       set_rq(vb);
+      if constexpr (LIST == 3) set_rq_lanes(vis, hb);
       convert(s, pw);
     }
 #pragma unroll
@@ -458,41 +607,61 @@ fwd_bf16_kernel(FwdArgs a) {
   // 2T and 2T+1): contract 2T | convert 2T+1 | score 2T+2, then contract 2T+1 | convert 2T+2, the
   // one barrier of the tile -- every wave is done with tile T, whose stage takes tile T + 4, and
   // tile T + 2, issued two tiles ago, has landed -- and score 2T+3.
+  int e[NSTG + 1] = {};                            // tiles T .. T + 4 of the sequence (static indexing only)
 #pragma unroll
   for (int q = 0; q < NSTG; ++q) {
     if (q < nt) {
-      issue_tile(tile_at(cursor), smem + q * SM::STAGE);
+      const int t = tile_at(cursor);
+      e[q] = t;
+      issue_tile(t, smem + q * SM::STAGE, q);
       cursor = next_tile(cursor + 1);
     }
   }
   wait_vmcnt<0>();
   __syncthreads();
   auto stage = [&](int q) __attribute__((always_inline)) -> char* { return smem + (q % NSTG) * SM::STAGE; };
-  auto mid = [&](auto all_in_flight, bool issue, char* st_copy) __attribute__((always_inline)) {
+  auto mid = [&](auto all_in_flight, bool issue, char* st_copy, int slot) __attribute__((always_inline)) {
     // all_in_flight: tiles T + 2 and T + 3 were both issued, so leaving one tile's copies
     // outstanding still guarantees that tile T + 2 has landed
     if constexpr (decltype(all_in_flight)::value) wait_vmcnt<NDMA>();
     else wait_vmcnt<0>();
     wg_barrier();
     if (issue) {
-      issue_tile(tile_at(cursor), st_copy);
+      e[4] = tile_at(cursor);
+      issue_tile(e[4], st_copy, slot);
       cursor = next_tile(cursor + 1);
+    }
+  };
+  auto shift_e = [&]() __attribute__((always_inline)) { e[0] = e[1]; e[1] = e[2]; e[2] = e[3]; e[3] = e[4]; };
+  const int t_ragged = LIST == 0 && d.Skv % TN != 0 ? n_tiles - 1 : -1, low0 = (n_tiles * TN - d.Skv);   // (LIST = 0)
+  auto mask_ragged = [&](f32x16 (&s)[QB], int t, int hb) __attribute__((always_inline)) {
+    if (LIST == 0 && t == t_ragged) {
+      asm volatile("" ::: "memory");
+      mask_low(s, hb, low0);
     }
   };
 
   f32x16 s0[QB], s1[QB];                           // scores of even / odd halves
   u32x4 p0[QB][2] = {}, p1[QB][2] = {};            // packed P^T operands of even / odd halves
   Carry cy;
+  TileVis vt = {};                                 // LIST = 3: of tile T
   if (nt > 0) {
+    if constexpr (LIST == 3) vt = tile_vis(e[0], 0);
     score(smem, 0, s0, nothing, first_k(smem, 0), no_tail);
     settle_scores(s0);
+    mask_ragged(s0, t_begin, 0);
+    if constexpr (LIST == 3) {
+      if (half_cut(vt, 0)) mask_words(s0, 0, vt);
+    }
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) r[qb] = row_max(s0[qb]);     // no probability of the first half exceeds 1
-    // (LIST = 2: rows that do not see the first tile start from a reference that means nothing
-    // yet; any finite one will do, their first visible tile raises it if it has to)
+    for (int qb = 0; qb < QB; ++qb) r[qb] = fmaxf(row_max(s0[qb]), -1e30f);     // no probability of the first half exceeds 1
+    // (LIST >= 2: rows that do not see the first tile start from a reference that means nothing
+    // yet; any finite one will do, their first visible tile moves it if it has to)
     set_rq(vis_at(0));
+    if constexpr (LIST == 3) set_rq_lanes(vt, 0);
     convert(s0, p0);
-    commit(s0, p0, vis_at(0));
+    commit(s0, p0, vis_at(0), vt, 0);
+    if constexpr (LIST == 3) set_rq_lanes(vt, 1);
     score(smem, 1, s1, nothing, first_k(smem, 1), no_tail);
   }
   int T = 0;
@@ -504,40 +673,58 @@ fwd_bf16_kernel(FwdArgs a) {
     char* const sa = stage(T);
     char* const sb = stage(T + 1);
     const int vb_t = vis_at(T), vb_n = vis_at(T + 1);          // (the conversions under way are tile T's)
+    TileVis vn = {};
+    if constexpr (LIST == 3) vn = tile_vis(e[1], (T + 1) % NSTG);
     contract_convert(sa, 0, p0, s1, p1, cy, fvt, [&]() __attribute__((always_inline)) { fk = first_k(sb, 0); });
     asm volatile("" : "+v"(fk));                   // (waited for here, where the compiler still knows what is in flight)
     score_convert(sb, 0, s0, s1, p1, cy, fk, [&]() __attribute__((always_inline)) { fvt = first_vt(sa, 1); }, nothing);
     asm volatile("" : "+v"(fvt));
-    commit(s1, p1, vb_t);
+    commit(s1, p1, vb_t, vt, 1);
     set_rq(vb_n);                                  // from here on: scores of tile T + 1
+    if constexpr (LIST == 3) set_rq_lanes(vn, 0);
     contract_convert(sa, 1, p1, s0, p0, cy, fvt, [&]() __attribute__((always_inline)) { fk = first_k(sb, 1); });
     asm volatile("" : "+v"(fk));
-    mid(std::true_type{}, false, sa);
+    mid(std::true_type{}, false, sa, 0);
     // the copies of tile T + 4 go out during the phase (LIST: its number was fetched a tile ago)
     const int t_new = LIST ? tile_of(__builtin_amdgcn_readfirstlane(id_next)) : cursor;
+    e[4] = t_new;
     cursor = next_tile(cursor + 1);
     if (LIST) id_next = tlist[cursor < t_end ? cursor : t_begin];
     constexpr int EVERY = QB * KS / NDMA;
     static_assert(EVERY >= 1, "more copies than matrix instructions in the score phase");
     score_convert(sb, 1, s1, s0, p0, cy, fk, [&]() __attribute__((always_inline)) { fvt = first_vt(sb, 0); },
                   [&](int m) __attribute__((always_inline)) {
-                    if (m % EVERY == EVERY - 1 && m / EVERY < NDMA) issue_part(t_new, sa, m / EVERY);
+                    if (m % EVERY == EVERY - 1 && m / EVERY < NDMA) issue_part(t_new, sa, m / EVERY, T % NSTG);
                   });
     asm volatile("" : "+v"(fvt));
-    commit(s0, p0, vb_n);
+    commit(s0, p0, vb_n, vn, 0);
+    if constexpr (LIST == 3) { vt = vn; set_rq_lanes(vt, 1); }
+    shift_e();
   }
   for (; T < nt; ++T) {                            // the last (at most four) tiles, phase after phase
     const bool more = T + 1 < nt;
     const int vb_t = vis_at(T), vb_n = more ? vis_at(T + 1) : 0;
+    TileVis vn = {};
+    if constexpr (LIST == 3) { if (more) vn = tile_vis(e[1], (T + 1) % NSTG); }
     contract(stage(T), 0, p0);
     settle_scores(s1);                             // (outside the pipelined loop the wait comes first, as a real dependence)
+    mask_ragged(s1, t_begin + T, 1);
     convert(s1, p1);
-    commit(s1, p1, vb_t);                          // (a raise comes before anything relative to the new reference is added)
+    commit(s1, p1, vb_t, vt, 1);                   // (a raise comes before anything relative to the new reference is added)
     if (more) { score(stage(T + 1), 0, s0, nothing, first_k(stage(T + 1), 0), no_tail); }
     contract(stage(T), 1, p1);
-    if (more) { settle_scores(s0); set_rq(vb_n); convert(s0, p0); commit(s0, p0, vb_n); }
-    mid(std::false_type{}, T + 4 < nt, stage(T));
+    if (more) {
+      settle_scores(s0);
+      mask_ragged(s0, t_begin + T + 1, 0);
+      set_rq(vb_n);
+      if constexpr (LIST == 3) set_rq_lanes(vn, 0);
+      convert(s0, p0);
+      commit(s0, p0, vb_n, vn, 0);
+      if constexpr (LIST == 3) { vt = vn; set_rq_lanes(vt, 1); }
+    }
+    mid(std::false_type{}, T + 4 < nt, stage(T), T % NSTG);
     if (more) { score(stage(T + 1), 1, s1, nothing, first_k(stage(T + 1), 1), no_tail); }
+    shift_e();
   }
 
   // ---- epilogue: O = acc / l, L = r ln 2 + ln l (the reference is in units of log2).  The last
@@ -616,9 +803,11 @@ fwd_bf16_kernel(FwdArgs a) {
 template <int D, int LIST = 0>
 hipError_t launch(const FwdArgs& a, long grid, hipStream_t s) {
   static SmemOnce once;
-  const hipError_t e = ensure_dynamic_lds((const void*)fwd_bf16_kernel<D, LIST>, KvSmem<D>::TOTAL, &once);
+  constexpr int lds = KvSmem<D>::TOTAL + (LIST == 3 ? NSTG * 256 : 0);
+  static_assert(lds <= 160 * 1024, "the layout fits a compute unit");
+  const hipError_t e = ensure_dynamic_lds((const void*)fwd_bf16_kernel<D, LIST>, lds, &once);
   if (e != hipSuccess) return e;
-  fwd_bf16_kernel<D, LIST><<<(unsigned)grid, 256, KvSmem<D>::TOTAL, s>>>(a);
+  fwd_bf16_kernel<D, LIST><<<(unsigned)grid, 256, lds, s>>>(a);
   return hipGetLastError();
 }
 
@@ -629,7 +818,7 @@ int fwd_bf16_pick_split(const Dims& d, int n_cu, bool masked) {
   // visible work differs from one query tile to the next (the splits of a tile share its visible
   // key tiles evenly), so four times as many workgroups are made to even the load out.
   // (the dense kernel tiles the rows of a whole group of query heads, the general one each head's)
-  const bool dense = !masked && (d.Skv % TN == 0 || d.Skv >= 2 * TN);   // (a ragged key count: whole tiles on the dense kernel)
+  const bool dense = !masked && d.Skv >= TN;
   const long base = dense ? (long)d.B * d.Hkv * (((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM)
                           : (long)d.B * d.Hq * ((d.Sq + QM - 1) / QM);
   const int n_tiles = (d.Skv + TN - 1) / TN;
@@ -666,8 +855,32 @@ bool fwd_bf16_two_pass_fits(const Dims& d, const MaskDev& m) {
   return list_fits(d, m) && m.q_chunk >= 8 && !fwd_bf16_one_pass_fits(d, m);
 }
 
+// ... or of any key blocks of 64 keys and more: a tile then lies in two of them at most
+bool fwd_bf16_takes_rows(const Dims& d, const MaskDev& m) {
+  return m.allow != nullptr && d.Skv >= TN && (d.Skv + TN - 1) / TN <= KvSmem<128>::WIN_BYTES / 4 - 1 && m.kv_block >= TN &&
+         !fwd_bf16_one_pass_fits(d, m);
+}
+size_t fwd_bf16_rows_bytes_most(const Dims& d) {
+  if (d.Skv < TN || (d.Skv + TN - 1) / TN > KvSmem<128>::WIN_BYTES / 4 - 1) return 0;
+  MaskDev m = {};
+  m.kv_block = TN;                                 // (the smallest key block it takes, a bitmap per batch)
+  m.stride_b = 1;
+  return mask_rows_bytes(d, mask_rows_of(d, m));
+}
+
 hipError_t launch_fwd_bf16(const FwdArgs& a, hipStream_t s) {
   const Dims& d = a.d;
+  if (a.pass == 0 && a.rows_ws != nullptr && fwd_bf16_takes_rows(d, a.mask)) {
+    FwdArgs w = a;
+    w.rows = mask_rows_of(d, a.mask);
+    // (rounded up: exact for j0 < 2^18 and key blocks of any length, as j0 times the rounding, less
+    // than 2^18 kv_block / kv_block of a unit in 2^36, never carries into the quotient)
+    w.frame_magic = (unsigned)(((1ull << 36) + (unsigned)a.mask.kv_block - 1) / (unsigned)a.mask.kv_block);
+    const hipError_t e = launch_mask_rows(d, a.mask, &w.rows, a.rows_ws, s);
+    if (e != hipSuccess) return e;
+    const long grid = (long)d.B * d.Hq * a.n_split * ((d.Sq + QM - 1) / QM);
+    return d.D == 64 ? launch<64, 3>(w, grid, s) : d.D == 96 ? launch<96, 3>(w, grid, s) : launch<128, 3>(w, grid, s);
+  }
   if (a.pass == 1) {                               // the dense kernel over the tiles every row of a workgroup sees
     const long grid = xcd_grid(d.B * d.Hkv, a.n_split * (d.Hq / d.Hkv) * ((d.Sq + QM - 1) / QM));
     return d.D == 64 ? launch<64, 1>(a, grid, s) : d.D == 96 ? launch<96, 1>(a, grid, s) : launch<128, 1>(a, grid, s);
@@ -681,7 +894,7 @@ hipError_t launch_fwd_bf16(const FwdArgs& a, hipStream_t s) {
   // problems too run the general kernel, whose eight waves of 32 rows put two waves on every SIMD.
   return launch_fwd_general_bf16(a, s);
 #endif
-  if (a.mask.allow != nullptr || d.Skv % TN != 0) return launch_fwd_general_bf16(a, s);
+  if (a.mask.allow != nullptr || d.Skv < TN) return launch_fwd_general_bf16(a, s);
   const int n_qt = (int)(((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM);
   const long grid = xcd_grid(d.B * d.Hkv, a.n_split * n_qt);
   return d.D == 64 ? launch<64>(a, grid, s) : d.D == 96 ? launch<96>(a, grid, s) : launch<128>(a, grid, s);

@@ -24,6 +24,10 @@ struct MaskRows {
   const unsigned* words;  // nullptr: not made for this call
   int w1, n_qt;           // key blocks (with the padding one), tiles of 256 rows
   long stride_b;          // words from one batch to the next (0: one bitmap for all)
+  // any[(b n_qt + qt) any_words + f / 64], bit f % 64: some row of tile qt sees key block f
+  const unsigned long long* any;
+  long any_stride_b;
+  int any_words;
 };
 
 // Shape, strides (in elements) and scale shared by every kernel.
@@ -47,6 +51,9 @@ struct FwdArgs {
   int partial;          // 1: write partial results even with n_split == 1 (this launch is one of several
                         // whose results are combined)
   int part0;            // index of the partial slice that split 0 of this launch writes
+  MaskRows rows;        // set by the launch where the kernel masks by it
+  void* rows_ws;        // workspace for its words, or nullptr
+  unsigned frame_magic; // 2^36 / kv_block, rounded up (set with rows)
   int pass;             // media mask, bf16: 0 = one launch over every visible tile; 1 = this launch takes the key
                         // tiles that EVERY row of a workgroup sees (dense kernel over a list of them), 2 = this
                         // launch takes the other visible tiles (general kernel)
@@ -182,6 +189,8 @@ inline int pick_split_balanced(long base, int n_cu, long cap, double t_full, dou
 int fwd_bf16_pick_split(const Dims& d, int n_cu, bool masked);
 bool fwd_bf16_two_pass_fits(const Dims& d, const MaskDev& m);   // a masked forward may run as passes 1 and 2
 bool fwd_bf16_one_pass_fits(const Dims& d, const MaskDev& m);   // ... or as one launch of the dense kernel over tile lists
+bool fwd_bf16_takes_rows(const Dims& d, const MaskDev& m);      // ... or as one launch of it that masks by MaskRows
+size_t fwd_bf16_rows_bytes_most(const Dims& d);                 // the most those words can take for any mask on this problem
 hipError_t launch_fwd_general_bf16(const FwdArgs& a, hipStream_t s);   // masked or ragged problems
 int bwd_bf16_pick_split(const Dims& d, int n_cu, bool masked);
 MaskRows mask_rows_of(const Dims& d, const MaskDev& m);                 // the geometry (no words yet)

@@ -16,9 +16,10 @@ namespace {
 
 constexpr int FB = 64;                 // key blocks per workgroup
 
-__global__ void __launch_bounds__(512) mask_rows_kernel(MaskDev m, MaskRows r, int Sq, unsigned* out) {
-  const int f = blockIdx.x * FB + (threadIdx.x & (FB - 1)), rb = threadIdx.x / FB, qt = blockIdx.y;
-  if (f >= r.w1) return;
+__global__ void __launch_bounds__(512) mask_rows_kernel(MaskDev m, MaskRows r, int Sq, unsigned* out,
+                                                        unsigned long long* any) {
+  __shared__ unsigned tile[8][FB];
+  const int lane = threadIdx.x & (FB - 1), f = blockIdx.x * FB + lane, rb = threadIdx.x / FB, qt = blockIdx.y;
   const int i0 = qt * 256 + rb * 32, rows = min(32, Sq - i0);
   unsigned bits = 0;
   if (f < r.w1 - 1 && rows > 0) {      // (the last key block is a padding one that nobody sees)
@@ -36,7 +37,15 @@ __global__ void __launch_bounds__(512) mask_rows_kernel(MaskDev m, MaskRows r, i
       }
     }
   }
-  out[blockIdx.z * r.stride_b + ((long)qt * r.w1 + f) * 8 + rb] = bits;
+  if (f < r.w1) out[blockIdx.z * r.stride_b + ((long)qt * r.w1 + f) * 8 + rb] = bits;
+  tile[rb][lane] = bits;
+  __syncthreads();
+  if (rb == 0) {                       // one bit per key block: some row of the tile sees it
+#pragma unroll
+    for (int k = 1; k < 8; ++k) bits |= tile[k][lane];
+    const unsigned long long on = __ballot(bits != 0);
+    if (lane == 0) any[((long)blockIdx.z * r.n_qt + qt) * gridDim.x + blockIdx.x] = on;
+  }
 }
 
 }  // namespace
@@ -44,19 +53,23 @@ __global__ void __launch_bounds__(512) mask_rows_kernel(MaskDev m, MaskRows r, i
 MaskRows mask_rows_of(const Dims& d, const MaskDev& m) {
   MaskRows r;
   r.words = nullptr;
+  r.any = nullptr;
   r.w1 = (d.Skv - 1) / m.kv_block + 2;
   r.n_qt = (d.Sq + 255) / 256;
   r.stride_b = m.stride_b != 0 ? (long)r.n_qt * r.w1 * 8 : 0;          // (one bitmap for all batches: one set of words)
   return r;
 }
 size_t mask_rows_bytes(const Dims& d, const MaskRows& r) {
-  return (size_t)(r.stride_b != 0 ? d.B : 1) * r.n_qt * r.w1 * 8 * sizeof(unsigned);
+  return (size_t)(r.stride_b != 0 ? d.B : 1) * r.n_qt * ((size_t)r.w1 * 32 + (size_t)(r.w1 + FB - 1) / FB * 8);
 }
 
 hipError_t launch_mask_rows(const Dims& d, const MaskDev& m, MaskRows* r, void* words, hipStream_t s) {
-  r->words = (const unsigned*)words;
   const dim3 grid((r->w1 + FB - 1) / FB, r->n_qt, r->stride_b != 0 ? d.B : 1);
-  mask_rows_kernel<<<grid, 512, 0, s>>>(m, *r, d.Sq, (unsigned*)words);
+  r->words = (const unsigned*)words;
+  r->any = (const unsigned long long*)((const char*)words + (size_t)grid.z * r->n_qt * r->w1 * 32);
+  r->any_stride_b = r->stride_b != 0 ? (long)r->n_qt * grid.x : 0;
+  r->any_words = (int)grid.x;
+  mask_rows_kernel<<<grid, 512, 0, s>>>(m, *r, d.Sq, (unsigned*)words, (unsigned long long*)r->any);
   return hipGetLastError();
 }
 

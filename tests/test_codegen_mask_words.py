@@ -10,3 +10,14 @@ def test_dkdv_words_loop_is_one_block(D, loop_mfma):
     loops = [b for b in _blocks(body) if b.count("v_mfma_f32_32x32x16_bf16") == loop_mfma]
     assert len(loops) == 1, "steady-state loop not found as one basic block"
     assert "v_accvgpr" not in loops[0] and "scratch_" not in loops[0]
+
+
+@pytest.mark.parametrize("D", [64, 96, 128])
+def test_forward_words_moves_no_accumulator(D):
+    body = _kernel(_asm("lvx_fwd_bf16.hip"), f"fwd_bf16_kernelILi{D}ELi3EE")
+    n = 0
+    for blk in _blocks(body):
+        if "v_mfma_f32_32x32x16_bf16" in blk:
+            n += 1
+            assert "v_accvgpr" not in blk and "scratch_" not in blk
+    assert n > 0

@@ -33,3 +33,26 @@ def test_masks_by_words(name, kw, p_on):
         rng = np.random.Generator(np.random.Philox(99 + len(name)))
         allow = rng.random((w.B, nq, nk) if w.B > 1 else (nq, nk)) < p_on
     run_case(w, do_bwd=True, allow=allow)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_rows_whose_keys_score_far_below_the_first_tile(D):
+    # Rows of chunk c see key block c only; the keys of block 0 are 40 times larger along one direction
+    # that all queries share, so they score up to hundreds of units above everybody else's: a
+    # reference taken from them leaves a row that does not see them no probability at all.
+    import torch
+    import oracle
+    from paper_2502_02406_amd import workloads as W
+    from paper_2502_02406_amd.blockloop import BlockLoop, MediaMask
+    from test_gpu_parity import TOL, check_fwd
+    w = small(f"mw_far_below_d{D}", D=D, Hq=2, Sq=128, Skv=1024, q_chunk=16, kv_block=128)
+    x = W.make_inputs(w)
+    x["q"][..., 0] = 4.0
+    x["k"][:, :, :128, 0] = 800.0
+    allow = torch.from_numpy((np.arange(8)[None, :] == np.arange(8)[:, None]).astype(np.uint8))
+    loop = BlockLoop(tuple(x["q"].shape), tuple(x["k"].shape), torch.bfloat16, 1,
+                     MediaMask(allow.cuda(), w.q_chunk, w.kv_block))
+    O, L = loop.forward(*(x[n].cuda() for n in ("q", "k", "v")))
+    torch.cuda.synchronize()
+    Oref, Lref = oracle.fwd(*(W.as_f32_numpy(x[n]) for n in ("q", "k", "v")), mask=oracle.Mask(allow.numpy(), w.q_chunk, w.kv_block))
+    check_fwd(O, L, Oref, Lref, TOL["bf16"], w.name)
