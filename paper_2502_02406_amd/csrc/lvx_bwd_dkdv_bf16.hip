@@ -859,7 +859,7 @@ hipError_t launch_bwd_dkdv_bf16(const BwdArgs& a, hipStream_t s) {
                 DkvSmem<96, 2>::KN == DkvSmem<128, 2>::KN && dkdv_step_list_cap<96>() == dkdv_step_list_cap<128>(),
                 "the test above is the same for both head dims");
   if (steps) return d.D == 64 ? launch<64, false, true>(a, s) : d.D == 96 ? launch<96, false, true>(a, s) : launch<128, false, true>(a, s);
-  if (a.rows.words != nullptr)
+  if (a.rows.words != nullptr && bwd_dkdv_bf16_takes_rows(d, a.mask))
     return d.D == 64 ? launch<64, false, true, true>(a, s) : d.D == 96 ? launch<96, false, true, true>(a, s) : launch<128, false, true, true>(a, s);
   const bool general = a.mask.allow != nullptr || !rows_ok;
   if (d.D == 64) return general ? launch<64, true>(a, s) : launch<64, false>(a, s);

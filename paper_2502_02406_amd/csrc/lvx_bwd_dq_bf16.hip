@@ -44,8 +44,11 @@ __device__ unsigned long long dq_probe[8];
 #define DQ_STAMP(x)
 #endif
 
-// GENERAL = false: dense attention and Skv a multiple of 64 (no mask code, no ragged tile, so that
-// the steady-state loop is one basic block); GENERAL = true: everything else.
+// GENERAL = false: dense attention (no mask code, so that the steady-state loop is one basic block; a
+// key count that is no multiple of 64 moves the last tile back to end with the last key, and the keys it
+// shares with the tile before get the exponent -infinity in the unpipelined end of the loop: a launch of
+// the general kernel for those keys took 34 us on top of 711 for 512 rows x 28 heads against 91125 keys);
+// GENERAL = true: everything else.
 // LIST (with GENERAL = false): the dense kernel over a list of key tiles -- those that EVERY row
 // of the workgroup sees under a media mask (BwdArgs::dq_pass == 1).  Inside such a tile nothing is
 // masked, so the loop is the dense one; only the tile numbers come from the list.  The other
@@ -55,6 +58,13 @@ __device__ unsigned long long dq_probe[8];
 // that ANY row of the workgroup sees, each with one bit per 32-row block of the workgroup; the
 // dS operands of a row block that does not see a tile are replaced by zeros as they are packed
 // (whatever its scores gave, nothing of it reaches a matrix instruction).  One launch does it all.
+// LIST = 3: any other mask of at least 64 keys per key block, by the words that travel with the tiles
+// (lvx_kv_ring.h).  Where some row of a wave does not see all of a half, its packed dS -- complete
+// between two phases, in ordinary registers that no matrix instruction writes -- meets the lane's key
+// bits, a mask of two elements at a time, in a branch of about 80 instructions per half; halves
+// that every row sees skip it.  2048 rows in chunks of 64 x 28 heads against 32 frames of 729 keys,
+// causal, D = 128: 1.34 -> 0.50 ms (1060 TFLOP/s of visible pairs; the general kernel below before); 4096
+// rows x 8 heads in chunks of 2, each seeing one of 2048 frames of 64 keys, D = 64: 1.09 -> 0.16 ms.
 template <int D, bool GENERAL, int LIST = 0>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 bwd_dq_bf16_kernel(BwdArgs a) {
@@ -74,7 +84,7 @@ bwd_dq_bf16_kernel(BwdArgs a) {
   const int n_qt = (rows_lim + QM - 1) / QM;
   const int per_split = PACK ? n_qt : G * n_qt;
   int b, hk, split, hq, qt;
-  if constexpr (LIST == 2) {
+  if constexpr (LIST >= 2) {
     // (as in the forward: the later query tiles, which under a causal mask see the most key tiles,
     // start first; the head varies fastest)
     const int n_hq = d.B * d.Hq;
@@ -211,7 +221,13 @@ bwd_dq_bf16_kernel(BwdArgs a) {
   int* const tlist = (int*)(smem + SM::RING + SM::BITS_BYTES);
   constexpr int LIST_CAP = SM::WIN_BYTES / 4 - 1;
   constexpr int VIS_SHIFT = 24;                    // LIST = 2: a list entry is tile | row-block bits << 24
-  if (LIST) {
+  if constexpr (LIST == 3) {
+    const int nn = list_row_tiles(a.rows, b, qt, a.mask.kv_block, d.Skv, n_tiles, (unsigned long long*)bits, tlist,
+                                  tlist + LIST_CAP, tid);
+    t_begin = (int)((long)split * nn / a.n_split_dq);
+    t_end = (int)((long)(split + 1) * nn / a.n_split_dq);
+    nt = t_end - t_begin;
+  } else if (LIST) {
     const int c0 = i_wg0 / a.mask.q_chunk, h = i_wg1 / a.mask.q_chunk - c0 + 1;     // chunks of this workgroup's rows
     const int w = (d.Skv - 1) / a.mask.kv_block + 1;
     // full[f]: 1 if all h chunks see key block f (LIST = 2: bit k = the k-th 32-row block of the
@@ -338,17 +354,26 @@ bwd_dq_bf16_kernel(BwdArgs a) {
   // matrix instructions of a phase: issued back to back, each waits for the one before it to be
   // accepted by the memory pipeline, and the wave would stand still for hundreds of cycles.
   const unsigned smem_u = lds_base(smem);
-  auto issue_part = [&](int t, char* st, int k) __attribute__((always_inline)) {   // full tiles only
-    const long tile = (long)t * TN * row_bytes + (long)wave * row_bytes;           // this wave's first row: tile row w
+  constexpr bool MOVED = !GENERAL && (LIST == 0 || LIST == 3);   // the last tile ends with the last key
+  const unsigned words_u = smem_u + SM::TOTAL;     // LIST = 3: 256 bytes of words per ring stage, past everything else
+  const char* const rw0 = LIST == 3 ? (const char*)(a.rows.words + b * a.rows.stride_b + (long)qt * a.rows.w1 * 8) : nullptr;
+  auto issue_part = [&](int t, char* st, int k, int slot) __attribute__((always_inline)) {   // full tiles only; slot: the ring stage's number
+    const int j0 = MOVED ? moved_tile_j0(t, d.Skv) : t * TN;
+    if (LIST == 3 && k == 2 * NCR) {               // the words of the tile's key block and of the next one: 64 bytes
+      dma4u(rw0 + (long)frame_of(j0, a.frame_magic) * 32, (unsigned)min(lane, 15) * 4, words_u + slot * 256);
+      return;
+    }
+    const long tile = (long)j0 * row_bytes + (long)wave * row_bytes;               // this wave's first row: tile row w
     const unsigned kdst = smem_u + (unsigned)(st - smem) + wave * SM::GS;
     if (k % 2 == 0) dma16u(k0 + tile, cp_off[k / 2], kdst + run_start(k / 2) * 16);
     else dma16u(v0 + tile, cp_off[k / 2], kdst + SM::TILE + run_start(k / 2) * 16);
   };
-  auto issue_tile = [&](int t, char* st) __attribute__((always_inline)) {
+  constexpr int NDMA = 2 * NCR + (LIST == 3 ? 1 : 0);    // copies per wave and tile
+  auto issue_tile = [&](int t, char* st, int slot) __attribute__((always_inline)) {
     const int rows = min(TN, d.Skv - t * TN);
     if (!GENERAL || rows == TN) {
 #pragma unroll
-      for (int k = 0; k < 2 * NCR; ++k) issue_part(t, st, k);
+      for (int k = 0; k < NDMA; ++k) issue_part(t, st, k, slot);
       return;
     }
     const long tile = (long)t * TN * row_bytes;    // ragged last tile: clamp the rows
@@ -363,7 +388,6 @@ bwd_dq_bf16_kernel(BwdArgs a) {
       dma16s(v0 + tile, off, vdst + run_start(c) * 16);
     }
   };
-  constexpr int NDMA = 2 * NCR;                    // copies per wave and tile
 
   f32x16 dq[QB][DB];
 #pragma unroll
@@ -427,6 +451,34 @@ bwd_dq_bf16_kernel(BwdArgs a) {
   // matrix instructions into the next phase; everywhere else this wait comes first.
   auto settle_scores = [&](f32x16 (&s)[QB]) __attribute__((always_inline)) {
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" : "+v"(s[0]), "+v"(s[1]));
+  };
+  // LIST = 3: the lane's dS operands of half hb lose the keys that its rows do not see
+  auto mask_words = [&](u32x4 (&dsw)[QB][2], int hb, const TileVis& v) __attribute__((always_inline)) {
+    if (__builtin_expect(half_full(v, hb), 1)) return;
+    asm volatile("" ::: "memory");                 // keep this a real branch
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      const int keys = (int)lane_keys(v, hb, qb, ql, g);
+#pragma unroll
+      for (int x = 0; x < 16; x += 2) {            // registers x, x + 1: one packed word
+        const int bit = 8 * (x / 4) + x % 4;
+        const unsigned lo = (unsigned)__builtin_amdgcn_sbfe(keys, bit, 1), hi = (unsigned)__builtin_amdgcn_sbfe(keys, bit + 1, 1);
+        dsw[qb][x / 8][(x % 8) / 2] &= (lo & 0xffffu) | (hi & 0xffff0000u);
+      }
+    }
+  };
+  // dense, ragged key count: the exponents of keys that the tile before the last has seen -> -inf
+  const int t_ragged = !GENERAL && LIST == 0 && d.Skv % TN != 0 ? n_tiles - 1 : -1, low0 = n_tiles * TN - d.Skv;
+  auto mask_ragged = [&](f32x16 (&s)[QB], int t, int hb) __attribute__((always_inline)) {
+    if (!GENERAL && LIST == 0 && t == t_ragged) {
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const bool out = 32 * hb + 8 * (v / 4) + 4 * g + (v % 4) < low0;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) s[qb][v] = out ? -INFINITY : s[qb][v];
+      }
+    }
   };
   // key tail and masked elements of a half's scores -> -inf (wave-uniform decision, rarely taken)
   auto mask_scores = [&](int t, int hb, f32x16 (&s)[QB]) __attribute__((always_inline)) {
@@ -545,8 +597,8 @@ bwd_dq_bf16_kernel(BwdArgs a) {
 #pragma unroll
   for (int q = 0; q < NSTG; ++q) {
     if (q < nt) {
-      e[q] = cursor;
-      issue_tile(tile_at(cursor), smem + q * SM::STAGE);
+      e[q] = LIST == 3 ? tile_at(cursor) : cursor;
+      issue_tile(LIST == 3 ? e[q] : tile_at(cursor), smem + q * SM::STAGE, q);
       cursor = next_tile(cursor + 1);
     }
   }
@@ -554,7 +606,21 @@ bwd_dq_bf16_kernel(BwdArgs a) {
   __syncthreads();
   DQ_STAMP(stamp1);
   auto stage = [&](int q) __attribute__((always_inline)) -> char* { return smem + (q % NSTG) * SM::STAGE; };
-  auto mid = [&](auto all_in_flight, bool issue, char* st_copy) __attribute__((always_inline)) {
+  // LIST = 3: a landed tile's visibility.  Rows past the last one count as seeing everything (their
+  // statistics make every probability zero), so that they keep no half from being full.
+  unsigned past[QB];
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    const int n = d.Sq - (i_wave0 + 32 * qb);      // rows of the block that exist
+    past[qb] = n >= 32 ? 0u : n <= 0 ? ~0u : ~0u << n;
+  }
+  auto tile_vis = [&](int t, int slot) __attribute__((always_inline)) -> TileVis {
+    TileVis v = read_tile_vis(smem + SM::TOTAL + slot * 256, wave, t, d.Skv, a.mask.kv_block, a.frame_magic);
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) { v.a[qb] |= past[qb]; v.b[qb] |= past[qb]; }
+    return v;
+  };
+  auto mid = [&](auto all_in_flight, bool issue, char* st_copy, int slot) __attribute__((always_inline)) {
     // (The general variant may spill registers inside the loop; its spill stores are counted with
     // the copies but complete out of order with them, so it always waits for everything.)
     // all_in_flight: tiles T + 2 and T + 3 were both issued, so leaving one tile's copies
@@ -563,8 +629,8 @@ bwd_dq_bf16_kernel(BwdArgs a) {
     else wait_vmcnt<0>();
     wg_barrier();
     if (issue) {
-      e[4] = cursor;
-      issue_tile(tile_at(cursor), st_copy);
+      e[4] = LIST == 3 ? tile_at(cursor) : cursor;
+      issue_tile(LIST == 3 ? e[4] : tile_at(cursor), st_copy, slot);
       cursor = next_tile(cursor + 1);
     }
   };
@@ -572,13 +638,17 @@ bwd_dq_bf16_kernel(BwdArgs a) {
   f32x16 s0[QB], p0[QB], s1[QB], p1[QB];           // scores of even / odd halves
   u32x4 ds0[QB][2] = {}, ds1[QB][2] = {};          // packed dS operands of even / odd halves
   Carry cy;
+  TileVis vt = {};                                 // LIST = 3: of tile T
   if (nt > 0) {
     vcur = vis_at(0);
+    if constexpr (LIST == 3) vt = tile_vis(e[0], 0);
     score(smem, 0, s0, p0, nothing, first_kv(smem, 0), no_tail);
     mask_scores(e[0], 0, s0);
     settle_scores(s0);
     settle_scores(p0);
+    mask_ragged(s0, t_begin, 0);
     convert(s0, p0, ds0);
+    if constexpr (LIST == 3) mask_words(ds0, 0, vt);
     score(smem, 1, s1, p1, nothing, first_kv(smem, 1), no_tail);
     mask_scores(e[0], 1, s1);
   }
@@ -590,16 +660,22 @@ bwd_dq_bf16_kernel(BwdArgs a) {
     char* const sa = stage(T);
     char* const sb = stage(T + 1);
     const int vnext = vis_at(T + 1);               // (the conversions under way are tile T's)
+    TileVis vn = {};
+    if constexpr (LIST == 3) vn = tile_vis(e[1], (T + 1) % NSTG);
     contract_convert(sa, 0, ds0, s1, p1, ds1, cy, fkt, [&]() __attribute__((always_inline)) { fkv = first_kv(sb, 0); });
     score_convert(sb, 0, s0, p0, s1, p1, ds1, cy, fkv, [&]() __attribute__((always_inline)) { fkt = first_kt(sa, 1); }, nothing);
     mask_scores(e[1], 0, s0);
+    if constexpr (LIST == 3) {
+      asm volatile("" : "+v"(fkt));                // (waited for here, where the compiler still knows what is in flight)
+      mask_words(ds1, 1, vt);
+    }
     vcur = vnext;                                  // from here on: scores of tile T + 1
     contract_convert(sa, 1, ds1, s0, p0, ds0, cy, fkt, [&]() __attribute__((always_inline)) { fkv = first_kv(sb, 1); });
     if constexpr (GENERAL) {
-      mid(std::false_type{}, true, sa);
+      mid(std::false_type{}, true, sa, 0);
       score_convert(sb, 1, s1, p1, s0, p0, ds0, cy, fkv, [&]() __attribute__((always_inline)) { fkt = first_kt(sb, 0); }, nothing);
     } else {
-      mid(std::true_type{}, false, sa);
+      mid(std::true_type{}, false, sa, 0);
       // the copies of tile T + 4 go out during the phase (LIST: its number was fetched a tile ago,
       // and the operands waited for here were fetched after it)
       const int t_new = LIST ? tile_of(__builtin_amdgcn_readfirstlane(id_next)) : cursor;
@@ -610,23 +686,38 @@ bwd_dq_bf16_kernel(BwdArgs a) {
       static_assert(EVERY >= 1, "more copies than matrix instructions in the score phase");
       score_convert(sb, 1, s1, p1, s0, p0, ds0, cy, fkv, [&]() __attribute__((always_inline)) { fkt = first_kt(sb, 0); },
                     [&](int m) __attribute__((always_inline)) {
-                      if (m % EVERY == EVERY - 1 && m / EVERY < NDMA) issue_part(t_new, sa, m / EVERY);
+                      if (m % EVERY == EVERY - 1 && m / EVERY < NDMA) issue_part(t_new, sa, m / EVERY, T % NSTG);
                     });
     }
     mask_scores(e[1], 1, s1);
+    if constexpr (LIST == 3) {
+      asm volatile("" : "+v"(fkt));
+      mask_words(ds0, 0, vn);
+      vt = vn;
+    }
     e[0] = e[1]; e[1] = e[2]; e[2] = e[3]; e[3] = e[4];
   }
   for (; T < nt; ++T) {                            // the last (at most four) tiles
     const bool more = T + 1 < nt;
+    TileVis vn = {};
+    if constexpr (LIST == 3) { if (more) vn = tile_vis(e[1], (T + 1) % NSTG); }
     contract(stage(T), 0, ds0);
     settle_scores(s1);                             // (outside the pipelined loop the wait comes first, as a real dependence)
     settle_scores(p1);
+    mask_ragged(s1, t_begin + T, 1);
     convert(s1, p1, ds1);
+    if constexpr (LIST == 3) mask_words(ds1, 1, vt);
     if (more) vcur = vis_at(T + 1);
     if (more) { score(stage(T + 1), 0, s0, p0, nothing, first_kv(stage(T + 1), 0), no_tail); mask_scores(e[1], 0, s0); }
     contract(stage(T), 1, ds1);
-    if (more) { settle_scores(s0); settle_scores(p0); convert(s0, p0, ds0); }
-    mid(std::false_type{}, T + 4 < nt, stage(T));
+    if (more) {
+      settle_scores(s0);
+      settle_scores(p0);
+      mask_ragged(s0, t_begin + T + 1, 0);
+      convert(s0, p0, ds0);
+      if constexpr (LIST == 3) { mask_words(ds0, 0, vn); vt = vn; }
+    }
+    mid(std::false_type{}, T + 4 < nt, stage(T), T % NSTG);
     if (more) { score(stage(T + 1), 1, s1, p1, nothing, first_kv(stage(T + 1), 1), no_tail); mask_scores(e[1], 1, s1); }
     e[0] = e[1]; e[1] = e[2]; e[2] = e[3]; e[3] = e[4];
   }
@@ -714,9 +805,11 @@ bwd_dq_bf16_kernel(BwdArgs a) {
 template <int D, bool GENERAL, int LIST = 0>
 hipError_t launch(const BwdArgs& a, long grid, hipStream_t s) {
   static SmemOnce once;
-  hipError_t e = ensure_dynamic_lds((const void*)bwd_dq_bf16_kernel<D, GENERAL, LIST>, DqSmem<D>::TOTAL, &once);
+  constexpr int lds = DqSmem<D>::TOTAL + (LIST == 3 ? NSTG * 256 : 0);
+  static_assert(lds <= 160 * 1024, "the layout fits a compute unit");
+  hipError_t e = ensure_dynamic_lds((const void*)bwd_dq_bf16_kernel<D, GENERAL, LIST>, lds, &once);
   if (e != hipSuccess) return e;
-  bwd_dq_bf16_kernel<D, GENERAL, LIST><<<(unsigned)grid, 256, DqSmem<D>::TOTAL, s>>>(a);
+  bwd_dq_bf16_kernel<D, GENERAL, LIST><<<(unsigned)grid, 256, lds, s>>>(a);
   return hipGetLastError();
 }
 
@@ -726,7 +819,7 @@ int bwd_bf16_pick_split(const Dims& d, int n_cu, bool masked) {
   // one workgroup per CU; split the KV axis until the grid covers the chip (four times as many
   // workgroups with a media mask, whose visible work differs from one query tile to the next)
   // (the dense kernel tiles the rows of a whole group of query heads, the general one each head's)
-  const bool dense = !masked && (d.Skv % TN == 0 || d.Skv >= 2 * TN);
+  const bool dense = !masked && d.Skv >= TN;
   const long base = dense ? (long)d.B * d.Hkv * (((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM)
                           : (long)d.B * d.Hq * ((d.Sq + QM - 1) / QM);
   const int n_tiles = (d.Skv + TN - 1) / TN;
@@ -751,12 +844,13 @@ namespace {
 hipError_t launch_one(const BwdArgs& a, bool general, hipStream_t s) {
   const Dims& d = a.d;
   const int G = d.Hq / d.Hkv;
-  const bool list = a.dq_pass == 1 || a.dq_pass == 3;   // the dense kernel over a list of tiles: rows tiled per head
+  const bool list = a.dq_pass == 1 || a.dq_pass >= 3;   // the dense kernel over a list of tiles: rows tiled per head
   const long per_split = general || list ? (long)G * ((d.Sq + QM - 1) / QM) : ((long)G * d.Sq + QM - 1) / QM;
-  const long grid = a.dq_pass == 3 ? (long)d.B * d.Hq * a.n_split_dq * ((d.Sq + QM - 1) / QM)
+  const long grid = a.dq_pass >= 3 ? (long)d.B * d.Hq * a.n_split_dq * ((d.Sq + QM - 1) / QM)
                                    : xcd_grid(d.B * d.Hkv, (int)(a.n_split_dq * per_split));
   hipError_t e;
-  if (a.dq_pass == 3) e = d.D == 64 ? launch<64, false, 2>(a, grid, s) : d.D == 96 ? launch<96, false, 2>(a, grid, s) : launch<128, false, 2>(a, grid, s);
+  if (a.dq_pass == 4) e = d.D == 64 ? launch<64, false, 3>(a, grid, s) : d.D == 96 ? launch<96, false, 3>(a, grid, s) : launch<128, false, 3>(a, grid, s);
+  else if (a.dq_pass == 3) e = d.D == 64 ? launch<64, false, 2>(a, grid, s) : d.D == 96 ? launch<96, false, 2>(a, grid, s) : launch<128, false, 2>(a, grid, s);
   else if (list) e = d.D == 64 ? launch<64, false, 1>(a, grid, s) : d.D == 96 ? launch<96, false, 1>(a, grid, s) : launch<128, false, 1>(a, grid, s);
   else if (d.D == 64) e = general ? launch<64, true>(a, grid, s) : launch<64, false>(a, grid, s);
   else if (d.D == 96) e = general ? launch<96, true>(a, grid, s) : launch<96, false>(a, grid, s);
@@ -787,6 +881,14 @@ hipError_t launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s) {
       if (p3.n_split_dq > 1) p3.n_split_dq /= 2;    // (its workgroups start longest first: half the splits even the load out)
       return launch_one(p3, false, s);
     }
+    // ... or of any other mask with key blocks of 64 keys and more, by the words that travel with the tiles
+    if (a.rows.words != nullptr && bwd_dq_bf16_takes_rows(d, a.mask)) {
+      BwdArgs p4 = a;
+      p4.dq_pass = 4;
+      p4.frame_magic = frame_magic_of(a.mask.kv_block);
+      if (p4.n_split_dq > 1) p4.n_split_dq /= 2;
+      return launch_one(p4, false, s);
+    }
     const bool two = d.Skv % TN == 0 && plan_fits(h_max, w, n_tiles, DqSmem<128>::BITS_BYTES, DqSmem<128>::WIN_BYTES) &&
                      n_tiles <= DqSmem<128>::WIN_BYTES / 4 - 1 && ((w + 1) & ~1) + (n_tiles + 63) / 64 * 2 <= DqSmem<128>::BITS_BYTES / 4;
     if (!two) return launch_one(a, true, s);
@@ -796,24 +898,11 @@ hipError_t launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s) {
     const hipError_t e = launch_one(p1, false, s);
     return e != hipSuccess ? e : launch_one(p2, true, s);
   }
-  const int tail = d.Skv % TN;
-  if (tail == 0) return launch_one(a, false, s);
-  if (d.Skv < 2 * TN) return launch_one(a, true, s);
-  // A key count that is no multiple of the tile: the dense kernel takes the whole tiles, the
-  // general one the few keys that are left; dQ is a sum over keys, and both add into dq_accum
-  // one after the other on the stream.
-  BwdArgs head = a;
-  head.d.Skv = d.Skv - tail;
-  hipError_t e = launch_one(head, false, s);
-  if (e != hipSuccess) return e;
-  BwdArgs rest = a;
-  rest.k = (const uint16_t*)a.k + (long)head.d.Skv * d.kv_ss;
-  rest.v = (const uint16_t*)a.v + (long)head.d.Skv * d.kv_ss;
-  rest.d.Skv = tail;
-  rest.n_split_dq = 1;
-  rest.dq_part = nullptr;
-  return launch_one(rest, true, s);
+  return launch_one(a, d.Skv < TN, s);
 }
+
+// the masks that the forward takes by words too: see launch_bwd_dq_bf16 for the order of choice
+bool bwd_dq_bf16_takes_rows(const Dims& d, const MaskDev& m) { return fwd_bf16_takes_rows(d, m); }
 
 hipError_t launch_bwd_bf16(const BwdArgs& a, unsigned stages, hipStream_t s) {
   hipError_t e = hipSuccess;
@@ -835,7 +924,8 @@ hipError_t launch_bwd_bf16(const BwdArgs& a, unsigned stages, hipStream_t s) {
     return launch_bwd_bf16(rest, stages, s);
   }
   BwdArgs m = a;
-  if (a.mask.allow != nullptr && (stages & 2) && bwd_dkdv_bf16_takes_rows(a.d, a.mask)) {
+  if (a.mask.allow != nullptr && (((stages & 2) && bwd_dkdv_bf16_takes_rows(a.d, a.mask)) ||
+                                  ((stages & 4) && bwd_dq_bf16_takes_rows(a.d, a.mask)))) {
     m.rows = mask_rows_of(a.d, a.mask);
     if (a.rows_ws != nullptr && mask_rows_bytes(a.d, m.rows) <= a.rows_ws_bytes) e = launch_mask_rows(a.d, a.mask, &m.rows, a.rows_ws, s);
   }

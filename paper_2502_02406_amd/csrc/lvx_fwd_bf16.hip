@@ -155,38 +155,8 @@ fwd_bf16_kernel(FwdArgs a) {
   constexpr int LIST_CAP = SM::WIN_BYTES / 4 - 1;
   constexpr int VIS_SHIFT = 24;                     // LIST = 2: a list entry is tile | row-block bits << 24
   if constexpr (LIST == 3) {
-    // one bit per key block -> one bit per tile -> the list; both planes in the bits area
-    unsigned long long* const any = (unsigned long long*)(smem + SM::RING);
-    unsigned long long* const plane = any + 256;
-    const unsigned long long* const src = a.rows.any + b * a.rows.any_stride_b + (long)qt * a.rows.any_words;
-    for (int w = tid; w < a.rows.any_words; w += 256) any[w] = src[w];
-    __syncthreads();
-    for (int base = 0; base < n_tiles; base += 256) {          // workgroup-uniform trip count
-      const int t = base + tid;
-      bool on = false;
-      if (t < n_tiles) {
-        const int fa = t * TN / a.mask.kv_block, fb = min(t * TN + TN, d.Skv) - 1, fz = fb / a.mask.kv_block;
-        on = ((any[fa / 64] >> (fa % 64)) | (any[fz / 64] >> (fz % 64))) & 1ull;
-      }
-      const unsigned long long m = __ballot(on);
-      if ((tid & 63) == 0 && t < n_tiles) plane[t / 64] = m;
-    }
-    __syncthreads();
-    if (wave == 0) {
-      const int n_words = (n_tiles + 63) / 64;                 // at most 64: a word per lane
-      const unsigned long long mine = lane < n_words ? plane[lane] : 0ull;
-      int count = 0;
-      for (int k = 0; k < n_words; ++k) {
-        const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)mine, k);
-        const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(mine >> 32), k);
-        const unsigned long long m = ((unsigned long long)hi << 32) | lo;
-        if ((m >> lane) & 1ull) tlist[count + __popcll(m & ((1ull << lane) - 1ull))] = k * 64 + lane;
-        count += (int)__popcll(m);
-      }
-      if (lane == 0) tlist[LIST_CAP] = count;
-    }
-    __syncthreads();
-    const int nn = __builtin_amdgcn_readfirstlane(tlist[LIST_CAP]);
+    const int nn = list_row_tiles(a.rows, b, qt, a.mask.kv_block, d.Skv, n_tiles, (unsigned long long*)(smem + SM::RING),
+                                  tlist, tlist + LIST_CAP, tid);
     t_begin = (int)((long)split * nn / a.n_split);
     t_end = (int)((long)(split + 1) * nn / a.n_split);
   } else if (LIST) {
@@ -276,21 +246,7 @@ fwd_bf16_kernel(FwdArgs a) {
   // first key of a tile (LIST = 0, 3: the last tile is moved back to end with the last key), and
   // how many of its keys the tile before has seen
   constexpr bool RAGGED = LIST == 0 || LIST == 3;
-  auto tile_j0 = [&](int t) __attribute__((always_inline)) -> int { return RAGGED ? min(t * TN, d.Skv - TN) : t * TN; };
-  // LIST = 3: what a wave needs to know of a tile.  a, b: which rows of its two row blocks see the
-  // key block the tile starts in, and the one after it; edge: the tile's first key of that one (>= 64:
-  // none); low: keys that the tile before has seen
-  struct TileVis { unsigned a[QB], b[QB]; int edge, low; };
-  auto frame_of = [&](int j0) __attribute__((always_inline)) -> int {     // j0 / kv_block: exact for j0 < 2^18
-    return (int)(__umulhi((unsigned)j0, a.frame_magic) >> 4);
-  };
-  auto half_word = [&](const TileVis& v, int hb, int qb) __attribute__((always_inline)) -> unsigned {   // rows that see something
-    return (v.edge > 32 * hb ? v.a[qb] : 0u) | (v.edge < 32 * hb + 32 ? v.b[qb] : 0u);
-  };
-  auto half_cut = [&](const TileVis& v, int hb) __attribute__((always_inline)) -> bool {  // ... but some of them not everything
-    const unsigned x = (v.a[0] ^ v.b[0]) | (v.a[1] ^ v.b[1]);
-    return (v.edge > 32 * hb && v.edge < 32 * hb + 32 && x != 0u) || v.low > 32 * hb;
-  };
+  auto tile_j0 = [&](int t) __attribute__((always_inline)) -> int { return RAGGED ? moved_tile_j0(t, d.Skv) : t * TN; };
   const int nt = max(t_end - t_begin, 0);          // number of tiles this workgroup performs
   auto next_tile = [&](int t) __attribute__((always_inline)) -> int { return min(t, t_end); };
   int cursor = t_begin;                            // next tile to issue
@@ -319,7 +275,7 @@ fwd_bf16_kernel(FwdArgs a) {
   auto issue_part = [&](int t, char* st, int k, int slot) __attribute__((always_inline)) {   // slot: the ring stage's number
     const int j0 = tile_j0(t);
     if (LIST == 3 && k == 2 * NCR) {               // the words of the tile's key block and of the next one: 64 bytes
-      dma4u(rw0 + (long)frame_of(j0) * 32, (unsigned)min(lane, 15) * 4, words_u + slot * 256);
+      dma4u(rw0 + (long)frame_of(j0, a.frame_magic) * 32, (unsigned)min(lane, 15) * 4, words_u + slot * 256);
       return;
     }
     const long tile = (long)j0 * row_bytes + (long)wave * row_bytes;               // this wave's first row: tile row w
@@ -333,18 +289,7 @@ fwd_bf16_kernel(FwdArgs a) {
     for (int k = 0; k < NDMA; ++k) issue_part(t, st, k, slot);
   };
   auto tile_vis = [&](int t, int slot) __attribute__((always_inline)) -> TileVis {     // of a tile that has landed in that stage
-    TileVis v;
-    const char* const w = smem + SM::TOTAL + slot * 256 + wave * QB * 4;
-    const u32x2 wa = *(const u32x2*)w, wb = *(const u32x2*)(w + 32);
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      v.a[qb] = (unsigned)__builtin_amdgcn_readfirstlane((int)wa[qb]);
-      v.b[qb] = (unsigned)__builtin_amdgcn_readfirstlane((int)wb[qb]);
-    }
-    const int j0 = tile_j0(t);
-    v.edge = (frame_of(j0) + 1) * a.mask.kv_block - j0;
-    v.low = t * TN - j0;
-    return v;
+    return read_tile_vis(smem + SM::TOTAL + slot * 256, wave, t, d.Skv, a.mask.kv_block, a.frame_magic);
   };
 
   // ---- softmax state of this lane's two query rows (both half-waves keep identical copies)
@@ -474,12 +419,9 @@ fwd_bf16_kernel(FwdArgs a) {
   };
   // LIST = 3: scores of a half that the lane's row does not see -> -infinity
   auto mask_words = [&](f32x16 (&s)[QB], int hb, const TileVis& v) __attribute__((always_inline)) {
-    auto below = [](int n) __attribute__((always_inline)) -> unsigned { return n <= 0 ? 0u : n >= 32 ? ~0u : (1u << n) - 1u; };
-    const unsigned first = below(v.edge - 32 * hb), seen = ~below(v.low - 32 * hb);
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-      const unsigned va = 0u - ((v.a[qb] >> ql) & 1u), vb = 0u - ((v.b[qb] >> ql) & 1u);
-      const unsigned keys = (((va & first) | (vb & ~first)) & seen) >> (4 * g);
+      const unsigned keys = lane_keys(v, hb, qb, ql, g);
 #pragma unroll
       for (int x = 0; x < 16; ++x) s[qb][x] = (keys >> (8 * (x / 4) + (x % 4))) & 1u ? s[qb][x] : -INFINITY;
     }
@@ -873,9 +815,7 @@ hipError_t launch_fwd_bf16(const FwdArgs& a, hipStream_t s) {
   if (a.pass == 0 && a.rows_ws != nullptr && fwd_bf16_takes_rows(d, a.mask)) {
     FwdArgs w = a;
     w.rows = mask_rows_of(d, a.mask);
-    // (rounded up: exact for j0 < 2^18 and key blocks of any length, as j0 times the rounding, less
-    // than 2^18 kv_block / kv_block of a unit in 2^36, never carries into the quotient)
-    w.frame_magic = (unsigned)(((1ull << 36) + (unsigned)a.mask.kv_block - 1) / (unsigned)a.mask.kv_block);
+    w.frame_magic = frame_magic_of(a.mask.kv_block);
     const hipError_t e = launch_mask_rows(d, a.mask, &w.rows, a.rows_ws, s);
     if (e != hipSuccess) return e;
     const long grid = (long)d.B * d.Hq * a.n_split * ((d.Sq + QM - 1) / QM);

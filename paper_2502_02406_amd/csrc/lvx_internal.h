@@ -67,6 +67,7 @@ struct BwdArgs {
   MaskRows rows;        // set by launch_bwd_bf16 where a kernel reads it
   void* rows_ws;        // workspace for its words (rows_ws_bytes), or nullptr
   size_t rows_ws_bytes;
+  unsigned frame_magic; // 2^36 / kv_block, rounded up (set where the dQ kernel masks by rows)
   const void *q, *k, *v, *o, *d_o;
   const float* lse;     // final statistic, [B,Hq,Sq]
   float* delta;         // workspace, [B,Hq,Sq]: rowsum(dO * O)
@@ -83,7 +84,9 @@ struct BwdArgs {
   int n_split_dq;       // KV splits of the dQ kernel
   int dq_pass;          // media mask, dQ kernel: 0 = one launch over every visible tile; 1 = this launch takes the
                         // key tiles that EVERY row of a workgroup sees (dense kernel over a list of them),
-                        // 2 = this launch takes the other visible tiles (general kernel)
+                        // 2 = this launch takes the other visible tiles (general kernel); 3, 4 = one launch of
+                        // the dense kernel over the tiles any row sees (row blocks that see a tile or do not;
+                        // masked by rows)
   float* dq_part;       // workspace, [n_split_dq, B,Hq,Sq,D] float32: the splits' sums (n_split_dq > 1),
                         // added to dq_accum by a reduction that follows the kernel
   // fused kernel (all five products in one pass): workspace of bwd_fused_ws_bytes, zeroed by the launch
@@ -196,6 +199,7 @@ int bwd_bf16_pick_split(const Dims& d, int n_cu, bool masked);
 MaskRows mask_rows_of(const Dims& d, const MaskDev& m);                 // the geometry (no words yet)
 size_t mask_rows_bytes(const Dims& d, const MaskRows& r);
 hipError_t launch_mask_rows(const Dims& d, const MaskDev& m, MaskRows* r, void* words, hipStream_t s);
+bool bwd_dq_bf16_takes_rows(const Dims& d, const MaskDev& m);           // the dQ kernel masks by MaskRows
 bool bwd_dkdv_bf16_takes_rows(const Dims& d, const MaskDev& m);         // the dK/dV kernel masks by MaskRows
 // memory-bound helpers
 hipError_t launch_merge(const MergeArgs& a, int part_is_f32, int out_is_f32, hipStream_t s);

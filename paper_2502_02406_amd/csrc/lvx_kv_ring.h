@@ -2,6 +2,7 @@
 // workgroup of four wavefronts, one per SIMD, each owning 64 query rows (two 32-row blocks), and a
 // ring of K/V tiles of 64 keys in LDS.  The mask planner at the end serves the dQ kernel.
 #pragma once
+#include "lvx_internal.h"
 #include "lvx_mfma.h"
 
 namespace lvx {
@@ -68,6 +69,100 @@ __device__ __forceinline__ void mfma_next(f32x16& c, bf16x8 a, bf16x8 b_acc) {  
 }
 __device__ __forceinline__ void mfma_acc(f32x16& c_acc, bf16x8 a, bf16x8 b) {       // c += a b, c in acc regs
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c_acc) : "v"(a), "v"(b));
+}
+
+// ---- tile lists with words (LIST = 3 of the query-stationary kernels): a media mask whose key blocks
+// have at least 64 keys, regrouped by launch_mask_rows (MaskRows).  A tile of 64 keys then lies in two
+// key blocks at most; their words -- which of the workgroup's 256 rows see them -- are one run of 64
+// bytes in memory, and travel to LDS with the tile's copies.
+
+// The last tile ends with the last key (Skv >= 64), so that no copy and no matrix product meets a row
+// that is not there: first key of tile t, of which t * TN minus that many were in the tile before.
+__device__ __forceinline__ int moved_tile_j0(int t, int Skv) { return min(t * TN, Skv - TN); }
+// j0 / kv_block for 0 <= j0 < 2^18 and any kv_block >= 64, with magic = 2^36 / kv_block rounded up: the
+// rounding adds less than j0 / 2^36 < 2^-18 to the quotient, which stays below the next whole number
+// (a quotient with kv_block <= j0 is a multiple of more than 2^-18, one with kv_block > j0 is below 1 - 2^-18
+// or has kv_block < 2^18).
+__host__ inline unsigned frame_magic_of(int kv_block) {
+  return (unsigned)(((1ull << 36) + (unsigned)kv_block - 1) / (unsigned)kv_block);
+}
+__device__ __forceinline__ int frame_of(int j0, unsigned magic) { return (int)(__umulhi((unsigned)j0, magic) >> 4); }
+
+// What a wave needs to know of a tile.  a, b: which rows of its row blocks see the key block that the
+// tile starts in, and the one after it; edge: the tile's first key of that one (64 and more: none);
+// low: keys that the tile before has seen.
+struct TileVis { unsigned a[QB], b[QB]; int edge, low; };
+__device__ __forceinline__ TileVis read_tile_vis(const char* words, int wave, int t, int Skv, int kv_block, unsigned magic) {
+  TileVis v;
+  const u32x2 wa = *(const u32x2*)(words + wave * QB * 4), wb = *(const u32x2*)(words + wave * QB * 4 + 32);
+  static_assert(QB == 2, "two words are read");
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    v.a[qb] = (unsigned)__builtin_amdgcn_readfirstlane((int)wa[qb]);
+    v.b[qb] = (unsigned)__builtin_amdgcn_readfirstlane((int)wb[qb]);
+  }
+  const int j0 = moved_tile_j0(t, Skv);
+  v.edge = (frame_of(j0, magic) + 1) * kv_block - j0;
+  v.low = t * TN - j0;
+  return v;
+}
+// rows that see something of half hb
+__device__ __forceinline__ unsigned half_word(const TileVis& v, int hb, int qb) {
+  return (v.edge > 32 * hb ? v.a[qb] : 0u) | (v.edge < 32 * hb + 32 ? v.b[qb] : 0u);
+}
+// some row sees a part of half hb only
+__device__ __forceinline__ bool half_cut(const TileVis& v, int hb) {
+  return (v.edge > 32 * hb && v.edge < 32 * hb + 32 && ((v.a[0] ^ v.b[0]) | (v.a[1] ^ v.b[1])) != 0u) || v.low > 32 * hb;
+}
+// every row sees all of half hb
+__device__ __forceinline__ bool half_full(const TileVis& v, int hb) {
+  const unsigned a = v.a[0] & v.a[1], b = v.b[0] & v.b[1];
+  return ((v.edge > 32 * hb ? a : ~0u) & (v.edge < 32 * hb + 32 ? b : ~0u)) == ~0u && v.low <= 32 * hb;
+}
+// keys of half hb that the lane's row of block qb sees, in the order of a score register file: bit
+// 8 (v / 4) + v % 4 belongs to register v
+__device__ __forceinline__ unsigned lane_keys(const TileVis& v, int hb, int qb, int ql, int g) {
+  auto below = [](int n) __attribute__((always_inline)) -> unsigned { return n <= 0 ? 0u : n >= 32 ? ~0u : (1u << n) - 1u; };
+  const unsigned first = below(v.edge - 32 * hb), seen = ~below(v.low - 32 * hb);
+  const unsigned va = 0u - ((v.a[qb] >> ql) & 1u), vb = 0u - ((v.b[qb] >> ql) & 1u);
+  return (((va & first) | (vb & ~first)) & seen) >> (4 * g);
+}
+// The tiles that any row of row tile qt sees, in ascending order, into tlist; returns how many (all
+// threads of the workgroup call this).  scratch: 2560 bytes, for at most 4096 tiles and key blocks.
+__device__ inline int list_row_tiles(const MaskRows& rows, int b, int qt, int kv_block, int Skv, int n_tiles,
+                                     unsigned long long* scratch, int* tlist, int* count_out, int tid) {
+  unsigned long long* const any = scratch;         // one bit per key block ...
+  unsigned long long* const plane = scratch + 256; // ... one per tile
+  const int lane = tid & 63;
+  const unsigned long long* const src = rows.any + b * rows.any_stride_b + (long)qt * rows.any_words;
+  for (int w = tid; w < rows.any_words; w += 256) any[w] = src[w];
+  __syncthreads();
+  for (int base = 0; base < n_tiles; base += 256) {            // workgroup-uniform trip count
+    const int t = base + tid;
+    bool on = false;
+    if (t < n_tiles) {
+      const int fa = t * TN / kv_block, fz = (min(t * TN + TN, Skv) - 1) / kv_block;
+      on = ((any[fa / 64] >> (fa % 64)) | (any[fz / 64] >> (fz % 64))) & 1ull;
+    }
+    const unsigned long long m = __ballot(on);
+    if (lane == 0 && t < n_tiles) plane[t / 64] = m;
+  }
+  __syncthreads();
+  if (tid < 64) {
+    const int n_words = (n_tiles + 63) / 64;                   // at most 64: a word per lane
+    const unsigned long long mine = lane < n_words ? plane[lane] : 0ull;
+    int count = 0;
+    for (int k = 0; k < n_words; ++k) {
+      const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)mine, k);
+      const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(mine >> 32), k);
+      const unsigned long long m = ((unsigned long long)hi << 32) | lo;
+      if ((m >> lane) & 1ull) tlist[count + __popcll(m & ((1ull << lane) - 1ull))] = k * 64 + lane;
+      count += (int)__popcll(m);
+    }
+    if (lane == 0) *count_out = count;
+  }
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(*count_out);
 }
 
 // Media mask, analysed once per workgroup (all 256 threads call this; it ends with a barrier).

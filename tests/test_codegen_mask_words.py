@@ -13,8 +13,10 @@ def test_dkdv_words_loop_is_one_block(D, loop_mfma):
 
 
 @pytest.mark.parametrize("D", [64, 96, 128])
-def test_forward_words_moves_no_accumulator(D):
-    body = _kernel(_asm("lvx_fwd_bf16.hip"), f"fwd_bf16_kernelILi{D}ELi3EE")
+@pytest.mark.parametrize("src,kernel", [("lvx_fwd_bf16.hip", "fwd_bf16_kernelILi%dELi3EE"),
+                                        ("lvx_bwd_dq_bf16.hip", "bwd_dq_bf16_kernelILi%dELb0ELi3EE")])
+def test_tile_words_move_no_accumulator(src, kernel, D):
+    body = _kernel(_asm(src), kernel % D)
     n = 0
     for blk in _blocks(body):
         if "v_mfma_f32_32x32x16_bf16" in blk:
