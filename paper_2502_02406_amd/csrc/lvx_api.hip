@@ -245,6 +245,7 @@ lvx_status lvx_xattn_fwd(const lvx_problem* p, lvx_dtype dtype, const void* q, c
       m.o_parts[i] = a.o_part + (size_t)i * rows * a.d.D;
       m.lse_parts[i] = a.lse_part + (size_t)i * rows;
     }
+    m.o_slices = a.o_part; m.lse_slices = a.lse_part; m.first = 0;
     m.rows = (long)rows; m.D = a.d.D; m.o_out = o; m.lse_out = lse;
     m.Hq = a.d.Hq; m.Sq = a.d.Sq; m.o_sb = a.d.q_sb; m.o_sh = a.d.q_sh; m.o_ss = a.d.q_ss;
     e = launch_merge(m, 1, a.o_is_f32, s);
@@ -303,6 +304,7 @@ lvx_status lvx_xattn_fwd_merge(const lvx_problem* p, lvx_dtype dtype, const void
     m.o_parts[i + 1] = o_part + (size_t)i * rows * a.d.D;
     m.lse_parts[i + 1] = l_part + (size_t)i * rows;
   }
+  m.o_slices = o_part; m.lse_slices = l_part; m.first = 1;
   m.rows = (long)rows; m.D = a.d.D; m.o_out = o_acc; m.lse_out = lse_acc;
   m.Hq = a.d.Hq; m.Sq = a.d.Sq; m.o_ss = a.d.D; m.o_sh = (long)a.d.Sq * a.d.D; m.o_sb = (long)a.d.Hq * a.d.Sq * a.d.D;
   e = launch_merge(m, 1, 1, s);
@@ -327,6 +329,7 @@ lvx_status lvx_xattn_merge(int32_t B, int32_t Hq, int32_t Sq, int32_t D, int32_t
     m.lse_parts[i] = lse_parts[i];
   }
   m.n_parts = n_parts;
+  m.o_slices = m.lse_slices = nullptr; m.first = 0;
   m.rows = (long)B * Hq * Sq; m.D = D; m.o_out = o_out; m.lse_out = lse_out;
   m.Hq = Hq; m.Sq = Sq; m.o_ss = D; m.o_sh = (long)Sq * D; m.o_sb = (long)Hq * Sq * D;
   hipError_t e = launch_merge(m, part_dtype == LVX_F32, out_dtype == LVX_F32, (hipStream_t)hip_stream);

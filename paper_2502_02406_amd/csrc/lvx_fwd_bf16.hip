@@ -756,6 +756,7 @@ hipError_t launch(const FwdArgs& a, long grid, hipStream_t s) {
 }  // namespace
 
 int fwd_bf16_pick_split(const Dims& d, int n_cu, bool masked) {
+  if (fwd_rows_bf16_takes(d, masked)) return fwd_rows_bf16_pick_split(d, n_cu);
   // one workgroup per CU; split the KV axis until the grid covers the chip.  With a media mask the
   // visible work differs from one query tile to the next (the splits of a tile share its visible
   // key tiles evenly), so four times as many workgroups are made to even the load out.
@@ -834,6 +835,7 @@ hipError_t launch_fwd_bf16(const FwdArgs& a, hipStream_t s) {
   // problems too run the general kernel, whose eight waves of 32 rows put two waves on every SIMD.
   return launch_fwd_general_bf16(a, s);
 #endif
+  if (fwd_rows_bf16_takes(d, a.mask.allow != nullptr)) return launch_fwd_rows_bf16(a, s);
   if (a.mask.allow != nullptr || d.Skv < TN) return launch_fwd_general_bf16(a, s);
   const int n_qt = (int)(((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM);
   const long grid = xcd_grid(d.B * d.Hkv, a.n_split * n_qt);

@@ -100,6 +100,10 @@ struct MergeArgs {
   const void* o_parts[64];
   const float* lse_parts[64];
   int n_parts;
+  // parts first .. n_parts - 1 are slices of one float32 array, `rows * D` and `rows` elements apart, that
+  // start here (nullptr: not so; the pointers above are always set)
+  const float *o_slices, *lse_slices;
+  int first;
   long rows;            // B*Hq*Sq
   int D;
   void* o_out;
@@ -194,6 +198,9 @@ bool fwd_bf16_two_pass_fits(const Dims& d, const MaskDev& m);   // a masked forw
 bool fwd_bf16_one_pass_fits(const Dims& d, const MaskDev& m);   // ... or as one launch of the dense kernel over tile lists
 bool fwd_bf16_takes_rows(const Dims& d, const MaskDev& m);      // ... or as one launch of it that masks by MaskRows
 size_t fwd_bf16_rows_bytes_most(const Dims& d);                 // the most those words can take for any mask on this problem
+bool fwd_rows_bf16_takes(const Dims& d, bool masked);           // few query rows: a stream from memory
+int fwd_rows_bf16_pick_split(const Dims& d, int n_cu);
+hipError_t launch_fwd_rows_bf16(const FwdArgs& a, hipStream_t s);
 hipError_t launch_fwd_general_bf16(const FwdArgs& a, hipStream_t s);   // masked or ragged problems
 int bwd_bf16_pick_split(const Dims& d, int n_cu, bool masked);
 MaskRows mask_rows_of(const Dims& d, const MaskDev& m);                 // the geometry (no words yet)
