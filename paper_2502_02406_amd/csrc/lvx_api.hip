@@ -63,6 +63,7 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 Dims make_dims(const lvx_problem* p) {
   Dims d;
   d.B = p->B; d.Hq = p->Hq; d.Hkv = p->Hkv; d.Sq = p->Sq; d.Skv = p->Skv; d.D = p->D;
+  d.G = p->Hq / p->Hkv;
   d.q_sb = p->q_sb; d.q_sh = p->q_sh; d.q_ss = p->q_ss;
   d.kv_sb = p->kv_sb; d.kv_sh = p->kv_sh; d.kv_ss = p->kv_ss;
   d.scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)p->D);
@@ -279,23 +280,18 @@ lvx_status lvx_xattn_fwd_merge(const lvx_problem* p, lvx_dtype dtype, const void
   a.rows_ws = plan.rows_bytes > 0 ? (char*)workspace + fwd_merge_ws(a.d, dtype, plan.n_parts) : nullptr;
   hipStream_t s = (hipStream_t)hip_stream;
   const size_t rows = (size_t)a.d.B * a.d.Hq * a.d.Sq;
-  if (dtype == LVX_BF16 && plan.n_parts == 1) {   // Rescale in the kernel's epilogue
+  if (plan.n_parts == 1) {   // Rescale in the kernel's epilogue
     a.o = o_acc; a.lse = lse_acc; a.merge_into = 1;
-    return launch_fwd_bf16(a, s) == hipSuccess ? LVX_OK : LVX_ERR_HIP;
+    return (dtype == LVX_BF16 ? launch_fwd_bf16(a, s) : launch_fwd_f32(a, s)) == hipSuccess ? LVX_OK : LVX_ERR_HIP;
   }
-  // partial result(s) in the workspace, then one combine over the running state and them
+  // partial results in the workspace, then one combine over the running state and them (the float32
+  // kernels never split the key range)
   a.merge_into = 0;
   const int n_parts = plan.n_parts;
   float* const o_part = (float*)workspace;
   float* const l_part = (float*)((char*)workspace + align_up(rows * a.d.D * sizeof(float) * n_parts));
-  hipError_t e;
-  if (dtype == LVX_BF16) {
-    a.o = nullptr; a.lse = nullptr; a.o_part = o_part; a.lse_part = l_part;
-    e = plan.two ? launch_fwd_bf16_two_pass(a, s) : launch_fwd_bf16(a, s);
-  } else {
-    a.o = o_part; a.lse = l_part; a.n_split = 1;
-    e = launch_fwd_f32(a, s);
-  }
+  a.o = nullptr; a.lse = nullptr; a.o_part = o_part; a.lse_part = l_part;
+  hipError_t e = plan.two ? launch_fwd_bf16_two_pass(a, s) : launch_fwd_bf16(a, s);
   if (e != hipSuccess) return LVX_ERR_HIP;
   MergeArgs m;
   m.n_parts = n_parts + 1;

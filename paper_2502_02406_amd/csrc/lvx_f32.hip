@@ -1,268 +1,481 @@
-// float32 instantiation of the forward and backward passes: LDS-tiled, plain FMA arithmetic.
-// It exists so that float32 workloads (the tiny exact check) are computed in float32 end to end
-// instead of being rounded to bf16 for the matrix cores; it is not the performance path.
+// float32 forward and backward passes, computed in float32 end to end on the float32 matrix
+// instruction (v_mfma_f32_32x32x2_f32: float32 products and sums, 64 operations per clock and SIMD,
+// twice what the vector ALU's multiply-adds reach and without their operand traffic).
 //
-// Thread layout shared by the three kernels: 256 threads = 16 "owner" rows x 16 lanes.  The 16
-// lanes of a row split the columns of the opposite sequence (score phase) and then the head
-// dimension (accumulation phase).
+// Every wave works on one 32 x 32 block of scores at a time, transposed as in the bf16 kernels: the
+// stationary side (32 query rows; in dK/dV 32 keys) is a lane's column, the streamed side its 16
+// registers.  A contraction may run in any order both operands agree on, and the orders are chosen so
+// that registers are operands as they are:
+//  * over the head dim (S, dP): lane group g takes dims 8 i + 4 g + e in step (i, e), so that a lane's
+//    operands are 16-byte reads of its row;
+//  * over the streamed rows (P V, dS K, ...): register v of a score block holds row
+//    8 (v / 4) + 4 g + v % 4 in lane group g, and IS the B operand of a step whose A operand is that
+//    row's element of the lane's column.
+// Tiles come from memory as whole rows (a lane that fetches its own row makes the memory pipeline walk 64
+// lines per instruction: 8 waves spent 8000 of their 22000 clocks on that) into registers a tile
+// ahead, and through an LDS tile of the wave's own, from which rows and columns are read.  The waves of a
+// workgroup share the stationary side and deal the streamed tiles out among them; their results meet in
+// LDS at the end.  All rows of the query heads that share a K/V head are one list of G Sq rows (as in the
+// bf16 kernels), so short query blocks fill tiles.
+//
+// Bound by the matrix instructions where there is work enough (512 rows x 8 heads x 4096 keys x 128:
+// forward 0.20 ms = 43 TFLOP/s on the half of the chip its 128 workgroups occupy, backward 0.49 ms; the
+// plain multiply-add kernels before took 3.55 ms for the step, now 0.65), by latency on the smallest: 128
+// rows x 2 heads x 256 keys x 64 per launch 31 -> 9.4 us forward, 39 + 23 -> 11.3 us backward.
 #include "lvx_internal.h"
+#include "lvx_mfma.h"
 
 namespace lvx {
 
 namespace {
 
-constexpr int R = 16;    // owner rows per workgroup
-constexpr int T = 32;    // rows of the streamed tile
+constexpr int waves_of(int D) { return D == 64 ? 8 : 4; }     // (wider heads need more than half of a SIMD's registers per wave)
+constexpr int pitch_of(int D) { return D + 4; }               // floats per row of an LDS tile of 32 rows
+constexpr int tile_of(int D) { return 32 * pitch_of(D); }
 
+__device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+// e^x for x <= 0, -infinity included: 2^h (1 + l ln 2) with h + l = x log2(e), h rounded and l what the
+// rounding and the constant's own lost (within 2 ulp like the library's, in half its instructions: a
+// launch whose waves pass through their code once is bound by fetching it)
+__device__ __forceinline__ float exp_neg(float x) {
+  x = fmaxf(x, -200.f);                            // (e^-200 is 0 in float32; keeps infinities out of l)
+  const float h = x * 1.44269504f;
+  const float l = fmaf(x, 1.925963033e-8f, fmaf(x, 1.44269504f, -h));
+  const float e = __builtin_amdgcn_exp2f(h);
+  return fmaf(e, l * 0.693147181f, e);
+}
 __device__ __forceinline__ bool visible(const MaskDev& m, int b, int i, int j) {
-  if (!m.allow) return true;
   return m.allow[b * m.stride_b + (long)(i / m.q_chunk) * m.stride_q + (j / m.kv_block)] != 0;
 }
-
-// Forward: workgroup owns R query rows of one (b, hq); streams K/V tiles of T rows.
-template <int D>
-__global__ void __launch_bounds__(256) fwd_f32_kernel(FwdArgs a) {
-  __shared__ float Qs[R][D];
-  __shared__ float Ks[T][D + 1];
-  __shared__ float Vs[T][D];
-  __shared__ float Ps[R][T];
-  const Dims& d = a.d;
-  const int tid = threadIdx.x, r = tid / 16, c = tid % 16;
-  const int b = blockIdx.z, hq = blockIdx.y, hk = hq / (d.Hq / d.Hkv);
-  const int i = blockIdx.x * R + r;
-  const bool row_ok = i < d.Sq;
-  const float* q = (const float*)a.q + b * d.q_sb + hq * d.q_sh;
-  const float* k = (const float*)a.k + b * d.kv_sb + hk * d.kv_sh;
-  const float* v = (const float*)a.v + b * d.kv_sb + hk * d.kv_sh;
-  for (int e = c; e < D; e += 16) Qs[r][e] = row_ok ? q[(long)i * d.q_ss + e] : 0.f;
-
-  float m = -INFINITY, l = 0.f;
-  float acc[D / 16];
+// row of a score block that register v holds: reg_u(v) + 4 g
+__device__ __forceinline__ constexpr int reg_u(int v) { return 8 * (v / 4) + (v % 4); }
+// A tile of 32 rows on its way from memory to LDS: piece it of a lane is 16 bytes of row
+// row_of_piece(it, lane).
+template <int D> struct Pieces { f32x4 x[D / 8]; };
+template <int D> __device__ __forceinline__ int row_of_piece(int it, int lane) { return (64 * it + lane) / (D / 4); }
+template <int D> __device__ __forceinline__ int col_of_piece(int it, int lane) { return (64 * it + lane) % (D / 4) * 4; }
+// n rows `stride` apart (rows past them re-read the last one)
+template <int D> __device__ __forceinline__ Pieces<D> fetch(const float* first, int n, long stride, int lane) {
+  Pieces<D> p;
 #pragma unroll
-  for (int e = 0; e < D / 16; ++e) acc[e] = 0.f;
-
-  for (int j0 = 0; j0 < d.Skv; j0 += T) {
-    __syncthreads();
-    for (int e = tid; e < T * D; e += 256) {
-      const int jj = e / D, dd = e % D;
-      const bool ok = j0 + jj < d.Skv;
-      Ks[jj][dd] = ok ? k[(long)(j0 + jj) * d.kv_ss + dd] : 0.f;
-      Vs[jj][dd] = ok ? v[(long)(j0 + jj) * d.kv_ss + dd] : 0.f;
+  for (int it = 0; it < D / 8; ++it)
+    p.x[it] = *(const f32x4*)(first + (long)min(row_of_piece<D>(it, lane), n - 1) * stride + col_of_piece<D>(it, lane));
+  return p;
+}
+template <int D> __device__ __forceinline__ void put_tile(float* tile, const Pieces<D>& p, int lane) {
+#pragma unroll
+  for (int it = 0; it < D / 8; ++it) *(f32x4*)(tile + row_of_piece<D>(it, lane) * pitch_of(D) + col_of_piece<D>(it, lane)) = p.x[it];
+}
+// a lane's row of the stationary side, 16 bytes per step group i: dims 8 i + 4 g ...
+template <int D> struct RowOps { f32x4 x[D / 8]; };
+template <int D> __device__ __forceinline__ RowOps<D> row_ops(const float* tile, int l31, int g) {
+  RowOps<D> r;
+#pragma unroll
+  for (int i = 0; i < D / 8; ++i) r.x[i] = *(const f32x4*)(tile + l31 * pitch_of(D) + 8 * i + 4 * g);
+  return r;
+}
+// 32 x 32 block of products over the head dim: rows of the tile in registers, stationary rows in lanes
+template <int D> __device__ __forceinline__ f32x16 products(const float* tile, const RowOps<D>& b, int l31, int g) {
+  f32x16 c = zero16();
+#pragma unroll
+  for (int i = 0; i < D / 8; ++i) {
+    const f32x4 a = *(const f32x4*)(tile + l31 * pitch_of(D) + 8 * i + 4 * g);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c = mfma_f32(a[e], b.x[i][e], c);
+  }
+  return c;
+}
+// ... with the stationary rows in LDS as well
+template <int D> __device__ __forceinline__ f32x16 products(const float* tile, const float* btile, int l31, int g) {
+  f32x16 c = zero16();
+#pragma unroll
+  for (int i = 0; i < D / 8; ++i) {
+    const f32x4 a = *(const f32x4*)(tile + l31 * pitch_of(D) + 8 * i + 4 * g);
+    const f32x4 b = *(const f32x4*)(btile + l31 * pitch_of(D) + 8 * i + 4 * g);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c = mfma_f32(a[e], b[e], c);
+  }
+  return c;
+}
+// acc += (tile's columns, 32 rows) x b
+template <int D> __device__ __forceinline__ void contract(f32x16 (&acc)[D / 32], const float* tile, const float (&b)[16], int l31, int g) {
+#pragma unroll
+  for (int v = 0; v < 16; ++v)
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) acc[db] = mfma_f32(tile[(reg_u(v) + 4 * g) * pitch_of(D) + 32 * db + l31], b[v], acc[db]);
+}
+// the (transposed) result block of a wave -> its part of the combine buffer: row ql, columns of D
+template <int D> __device__ __forceinline__ void put_block(float* buf, const f32x16 (&acc)[D / 32], int ql, int g) {
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const f32x4 y = {acc[db][4 * q4], acc[db][4 * q4 + 1], acc[db][4 * q4 + 2], acc[db][4 * q4 + 3]};
+      *(f32x4*)(buf + ql * pitch_of(D) + 32 * db + 8 * q4 + 4 * g) = y;
     }
-    __syncthreads();
-    float s[T / 16];
+}
+// Where the rows of the group's list lie: row r is row r % Sq of head r / Sq of the group.
+struct Rows {
+  const Dims& d;
+  long base;                                       // first element of the group's first head (batch and head offset)
+  float inv_sq;
+  __device__ __forceinline__ Rows(const Dims& d_, int b, int hk)
+      : d(d_), base(b * d_.q_sb + (long)(hk * d_.G) * d_.q_sh), inv_sq(1.f / (float)d_.Sq) {}
+  struct At { long off; int i; };                  // element offset of the row, its number in its head
+  // (r / Sq in float is off by less than one, the heads of a group being fewer than 2^23)
+  __device__ __forceinline__ At operator()(int r) const {
+    int h = (int)((float)r * inv_sq), i = r - h * d.Sq;
+    if (i < 0) { --h; i += d.Sq; }
+    if (i >= d.Sq) { ++h; i -= d.Sq; }
+    return {base + (long)h * d.q_sh + (long)i * d.q_ss, i};
+  }
+};
+
+// Forward: a workgroup's 32 rows against all keys; its waves take the tiles of 32 keys in turn.
+template <int D, bool MASKED>
+__global__ void __launch_bounds__(64 * waves_of(D)) fwd_f32_kernel(FwdArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  constexpr int NW = waves_of(D), DB = D / 32, P = pitch_of(D), T = tile_of(D);
+  const Dims& d = a.d;
+  const int rows = d.G * d.Sq, b = blockIdx.z, hk = blockIdx.y;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, ql = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r0 = blockIdx.x * 32;
+  float* const lds = (float*)smem;
+  float* const kt = lds + wave * 2 * T;            // this wave's tiles of K and V
+  float* const vt = kt + T;
+  const Rows at(d, b, hk);
+  const float* const k = (const float*)a.k + b * d.kv_sb + hk * d.kv_sh;
+  const float* const v = (const float*)a.v + b * d.kv_sb + hk * d.kv_sh;
+  Pieces<D> kp, vp;
+  auto request = [&](int j0) __attribute__((always_inline)) {
+    kp = fetch<D>(k + (long)j0 * d.kv_ss, d.Skv - j0, d.kv_ss, lane);
+    vp = fetch<D>(v + (long)j0 * d.kv_ss, d.Skv - j0, d.kv_ss, lane);
+  };
+  // Q: wave w brings its share of the tile's pieces, every wave reads all rows' operands
+#pragma unroll
+  for (int x = tid; x < 32 * (D / 4); x += 64 * NW) {
+    const int r = x / (D / 4), c = x % (D / 4) * 4;
+    *(f32x4*)(lds + r * P + c) = *(const f32x4*)((const float*)a.q + at(min(r0 + r, rows - 1)).off + c);
+  }
+  if (32 * wave < d.Skv) request(32 * wave);
+  __syncthreads();
+  const RowOps<D> q = row_ops<D>(lds, ql, g);
+  __syncthreads();
+
+  f32x16 acc[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db) acc[db] = zero16();
+  float m = -INFINITY, l = 0.f;                    // (l: this lane's share)
+  const int i_lane = MASKED ? at(min(r0 + ql, rows - 1)).i : 0;
+  for (int j0 = 32 * wave; j0 < d.Skv; j0 += 32 * NW) {
+    const int n = d.Skv - j0;
+    put_tile<D>(kt, kp, lane);
+    put_tile<D>(vt, vp, lane);
+    if (n > 32 * NW) request(j0 + 32 * NW);
+    f32x16 s = products<D>(kt, q, ql, g);
+    if (MASKED || n < 32) {
+#pragma unroll
+      for (int x = 0; x < 16; ++x) {
+        const int j = reg_u(x) + 4 * g;
+        if (j >= n || (MASKED && !visible(a.mask, b, i_lane, j0 + min(j, n - 1)))) s[x] = -INFINITY;
+      }
+    }
     float tmax = -INFINITY;
 #pragma unroll
-    for (int t = 0; t < T / 16; ++t) {
-      const int jj = c + 16 * t, j = j0 + jj;
-      float x = 0.f;
-      for (int e = 0; e < D; ++e) x = fmaf(Qs[r][e], Ks[jj][e], x);
-      x *= d.scale;
-      if (!row_ok || j >= d.Skv || !visible(a.mask, b, i, j)) x = -INFINITY;
-      s[t] = x;
-      tmax = fmaxf(tmax, x);
+    for (int x = 0; x < 16; ++x) { s[x] *= d.scale; tmax = fmaxf(tmax, s[x]); }
+    const float m_new = fmaxf(m, xhalf_max(tmax));
+    if (m_new != m) {                              // (some lane's row has risen: l and O^T follow)
+      const float alpha = exp_neg(m - m_new);      // m = -inf -> 0
+      m = m_new;
+      l *= alpha;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int x = 0; x < 16; ++x) acc[db][x] *= alpha;
     }
+    const float m_ref = m == -INFINITY ? 0.f : m;
+    float p[16];
 #pragma unroll
-    for (int w = 8; w >= 1; w >>= 1) tmax = fmaxf(tmax, __shfl_xor(tmax, w, 16));
-    const float m_new = fmaxf(m, tmax);
-    float alpha = 1.f, psum = 0.f;
-    if (m_new != -INFINITY) {
-      alpha = expf(m - m_new);                  // m = -inf -> 0
+    for (int x = 0; x < 16; ++x) {
+      p[x] = exp_neg(s[x] - m_ref);
+      l += p[x];
+    }
+    contract<D>(acc, vt, p, ql, g);
+  }
+
+  // ---- the waves' results meet: every wave's O in its K tile, references and sums behind all tiles
+  float* const st_m = lds + NW * 2 * T;            // [wave][32] references, sums; the rows' new L
+  float* const st_l = st_m + NW * 32;
+  float* const l_next = st_l + NW * 32;
+  const float l_row = xhalf_sum(l);
+  if (g == 0) { st_m[wave * 32 + ql] = m; st_l[wave * 32 + ql] = l_row; }
+  put_block<D>(kt, acc, ql, g);
+  __syncthreads();
+  const long row_b = ((long)b * d.Hq + hk * d.G) * d.Sq;       // L rows of the group follow each other
+  constexpr int PASSES = 32 * (D / 4) / (64 * NW);
+  static_assert(PASSES * 64 * NW == 32 * (D / 4), "whole passes");
+#pragma unroll 1
+  for (int pass = 0; pass < PASSES; ++pass) {
+    const int x = pass * 64 * NW + tid, r = x / (D / 4), c = x % (D / 4) * 4, rr = min(r0 + r, rows - 1);
+    float* const o = (float*)a.o + (a.merge_into ? (row_b + rr) * D : at(rr).off) + c;
+    f32x4 old = {0.f, 0.f, 0.f, 0.f};
+    float L0 = -INFINITY;
+    if (a.merge_into) {                            // Rescale with the running (O, L)
+      old = *(const f32x4*)o;
+      L0 = a.lse[row_b + rr];
+    }
+    float M = L0;
 #pragma unroll
-      for (int t = 0; t < T / 16; ++t) {
-        const float p = expf(s[t] - m_new);     // s = -inf -> 0
-        Ps[r][c + 16 * t] = p;
-        psum += p;
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, st_m[w * 32 + r]);
+    const float Mz = M == -INFINITY ? 0.f : M;
+    float z = exp_neg(L0 - Mz);
+    f32x4 y;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = z * old[e];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float f = exp_neg(st_m[w * 32 + r] - Mz);          // (a wave without a key: 0)
+      const f32x4 ow = *(const f32x4*)(lds + w * 2 * T + r * P + c);
+      z += f * st_l[w * 32 + r];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) y[e] += f * ow[e];
+    }
+    const float inv = z > 0.f ? 1.f / z : 0.f, lse = z > 0.f ? M + logf(z) : -INFINITY;
+    if (r0 + r >= rows) continue;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] *= inv;
+    *(f32x4*)o = y;
+    if (c == 0) {
+      if (a.merge_into) l_next[r] = lse;
+      else a.lse[row_b + rr] = lse;
+    }
+  }
+  if (a.merge_into) {                              // L is replaced once every thread has read it
+    __syncthreads();
+    if (tid < 32 && r0 + tid < rows) a.lse[row_b + r0 + tid] = l_next[tid];
+  }
+}
+
+// Backward, dQ: a workgroup's 32 query rows against all keys.
+template <int D, bool MASKED>
+__device__ void bwd_dq_f32(const BwdArgs& a, int tile, int hk, int b, char* smem) {
+  constexpr int NW = waves_of(D), DB = D / 32, P = pitch_of(D), T = tile_of(D);
+  const Dims& d = a.d;
+  const int rows = d.G * d.Sq;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, ql = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r0 = tile * 32, rl = min(r0 + ql, rows - 1);
+  float* const lds = (float*)smem;
+  float* const kt = lds + wave * 2 * T;
+  float* const vt = kt + T;
+  const Rows at(d, b, hk);
+  const long row_b = ((long)b * d.Hq + hk * d.G) * d.Sq;
+  const float* const k = (const float*)a.k + b * d.kv_sb + hk * d.kv_sh;
+  const float* const v = (const float*)a.v + b * d.kv_sb + hk * d.kv_sh;
+  Pieces<D> kp, vp;
+  auto request = [&](int j0) __attribute__((always_inline)) {
+    kp = fetch<D>(k + (long)j0 * d.kv_ss, d.Skv - j0, d.kv_ss, lane);
+    vp = fetch<D>(v + (long)j0 * d.kv_ss, d.Skv - j0, d.kv_ss, lane);
+  };
+  const float L = a.lse[row_b + rl], delta = a.delta[row_b + rl];
+  const float nl = L == -INFINITY ? -INFINITY : -L;            // (a row without keys: every exponent -inf)
+#pragma unroll
+  for (int x = tid; x < 32 * (D / 4); x += 64 * NW) {
+    const int r = x / (D / 4), c = x % (D / 4) * 4;
+    const long off = at(min(r0 + r, rows - 1)).off + c;
+    *(f32x4*)(lds + r * P + c) = *(const f32x4*)((const float*)a.q + off);
+    *(f32x4*)(lds + T + r * P + c) = *(const f32x4*)((const float*)a.d_o + off);
+  }
+  if (32 * wave < d.Skv) request(32 * wave);
+  __syncthreads();
+  const RowOps<D> q = row_ops<D>(lds, ql, g), go = row_ops<D>(lds + T, ql, g);
+  __syncthreads();
+  const int i_lane = MASKED ? at(rl).i : 0;
+  f32x16 acc[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db) acc[db] = zero16();
+  for (int j0 = 32 * wave; j0 < d.Skv; j0 += 32 * NW) {
+    const int n = d.Skv - j0;
+    put_tile<D>(kt, kp, lane);
+    put_tile<D>(vt, vp, lane);
+    if (n > 32 * NW) request(j0 + 32 * NW);
+    f32x16 s = products<D>(kt, q, ql, g);
+    const f32x16 dp = products<D>(vt, go, ql, g);
+    if (MASKED || n < 32) {
+#pragma unroll
+      for (int x = 0; x < 16; ++x) {
+        const int j = reg_u(x) + 4 * g;
+        if (j >= n || (MASKED && !visible(a.mask, b, i_lane, j0 + min(j, n - 1)))) s[x] = -INFINITY;
       }
+    }
+    float ds[16];
+#pragma unroll
+    for (int x = 0; x < 16; ++x) ds[x] = exp_neg(fmaf(s[x], d.scale, nl)) * (dp[x] - delta);
+    contract<D>(acc, kt, ds, ql, g);
+  }
+  put_block<D>(kt, acc, ql, g);
+  __syncthreads();
+#pragma unroll 1
+  for (int x = tid; x < 32 * (D / 4); x += 64 * NW) {
+    const int r = x / (D / 4), c = x % (D / 4) * 4;
+    if (r0 + r >= rows) continue;
+    float* const o = a.dq_accum + (row_b + r0 + r) * D + c;    // (rows are owned by one workgroup)
+    f32x4 old = *(const f32x4*)o;
+    f32x4 y = *(const f32x4*)(lds + r * P + c);
+#pragma unroll
+    for (int w = 1; w < NW; ++w) y += *(const f32x4*)(lds + w * 2 * T + r * P + c);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) old[e] += y[e] * d.scale;
+    *(f32x4*)o = old;
+  }
+}
+
+// Backward, dK and dV: a workgroup's 32 keys against the query rows of the whole group of heads.
+template <int D, bool MASKED>
+__device__ void bwd_dkdv_f32(const BwdArgs& a, int tile, int hk, int b, char* smem) {
+  constexpr int NW = waves_of(D), DB = D / 32, P = pitch_of(D), T = tile_of(D);
+  const Dims& d = a.d;
+  const int rows = d.G * d.Sq;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, kl = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j0 = tile * 32, jc = min(j0 + kl, d.Skv - 1);
+  float* const lds = (float*)smem;
+  float* const qt = lds + wave * 2 * T;            // this wave's tiles of Q and dO
+  float* const gt = qt + T;
+  float* const v_t = lds + NW * 2 * T;             // V of the workgroup's keys stays in LDS (dK and dV fill the registers)
+  float* const st = v_t + T + wave * 64;           // this wave's rows' -L (-inf: no probability), then delta
+  const long row_b = ((long)b * d.Hq + hk * d.G) * d.Sq, kv_h = b * d.kv_sb + hk * d.kv_sh;
+  const Rows at(d, b, hk);
+  Pieces<D> qp, gp;
+  float sp;
+  auto request = [&](int r0) __attribute__((always_inline)) {
+    if (r0 + 32 <= rows && r0 / d.Sq == (r0 + 31) / d.Sq) {    // whole, and in one head: as a rule
+      const long off = at(r0).off;
+      qp = fetch<D>((const float*)a.q + off, 32, d.q_ss, lane);
+      gp = fetch<D>((const float*)a.d_o + off, 32, d.q_ss, lane);
     } else {
+#pragma unroll 1
+      for (int it = 0; it < D / 8; ++it) {         // (through this wave's LDS tiles, which are free by now: see the callers)
+        const int r = row_of_piece<D>(it, lane), c = col_of_piece<D>(it, lane);
+        const long off = at(min(r0 + r, rows - 1)).off + c;
+        *(f32x4*)(qt + r * P + c) = *(const f32x4*)((const float*)a.q + off);
+        *(f32x4*)(gt + r * P + c) = *(const f32x4*)((const float*)a.d_o + off);
+      }
 #pragma unroll
-      for (int t = 0; t < T / 16; ++t) Ps[r][c + 16 * t] = 0.f;
+      for (int it = 0; it < D / 8; ++it) {
+        const int r = row_of_piece<D>(it, lane), c = col_of_piece<D>(it, lane);
+        qp.x[it] = *(const f32x4*)(qt + r * P + c);
+        gp.x[it] = *(const f32x4*)(gt + r * P + c);
+      }
     }
+    const int rr = min(r0 + kl, rows - 1);
+    const float x = g == 0 ? a.lse[row_b + rr] : a.delta[row_b + rr];
+    sp = g == 0 ? (x == -INFINITY || r0 + kl >= rows ? -INFINITY : -x) : x;
+  };
 #pragma unroll
-    for (int w = 8; w >= 1; w >>= 1) psum += __shfl_xor(psum, w, 16);
-    l = l * alpha + psum;
-    m = m_new;
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < D / 16; ++e) {
-      float x = acc[e] * alpha;
-      for (int jj = 0; jj < T; ++jj) x = fmaf(Ps[r][jj], Vs[jj][c + 16 * e], x);
-      acc[e] = x;
-    }
+  for (int x = tid; x < 32 * (D / 4); x += 64 * NW) {
+    const int r = x / (D / 4), c = x % (D / 4) * 4;
+    const long off = kv_h + (long)min(j0 + r, d.Skv - 1) * d.kv_ss + c;
+    *(f32x4*)(lds + r * P + c) = *(const f32x4*)((const float*)a.k + off);
+    *(f32x4*)(v_t + r * P + c) = *(const f32x4*)((const float*)a.v + off);
   }
-  if (!row_ok) return;
-  const long row = ((long)b * d.Hq + hq) * d.Sq + i;
-  const float inv = l > 0.f ? 1.f / l : 0.f;
-  float* o = (float*)a.o + b * d.q_sb + hq * d.q_sh + (long)i * d.q_ss;
+  __syncthreads();
+  const RowOps<D> k = row_ops<D>(lds, kl, g);
+  __syncthreads();
+  f32x16 dk[DB], dv[DB];
 #pragma unroll
-  for (int e = 0; e < D / 16; ++e) o[c + 16 * e] = acc[e] * inv;
-  if (c == 0) a.lse[row] = l > 0.f ? m + logf(l) : -INFINITY;
+  for (int db = 0; db < DB; ++db) { dk[db] = zero16(); dv[db] = zero16(); }
+  if (32 * wave < rows) request(32 * wave);
+  for (int r0 = 32 * wave; r0 < rows; r0 += 32 * NW) {
+    put_tile<D>(qt, qp, lane);
+    put_tile<D>(gt, gp, lane);
+    st[lane] = sp;
+    const int rn = r0 + 32 * NW;
+    const bool more = rn < rows, plain = rn + 32 <= rows && rn / d.Sq == (rn + 31) / d.Sq;
+    if (more && plain) request(rn);
+    const f32x16 s = products<D>(qt, k, kl, g), dp = products<D>(gt, v_t, kl, g);
+    float p[16], ds[16];
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const f32x4 nl = *(const f32x4*)(st + 8 * q4 + 4 * g), de = *(const f32x4*)(st + 32 + 8 * q4 + 4 * g);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int x = 4 * q4 + e;
+        float t = fmaf(s[x], d.scale, nl[e]);
+        if (MASKED && !visible(a.mask, b, at(min(r0 + reg_u(x) + 4 * g, rows - 1)).i, jc)) t = -INFINITY;
+        p[x] = exp_neg(t);
+        ds[x] = p[x] * (dp[x] - de[e]);
+      }
+    }
+    contract<D>(dv, gt, p, kl, g);
+    contract<D>(dk, qt, ds, kl, g);
+    if (more && !plain) request(rn);               // (row by row, once the tiles have been read)
+  }
+  put_block<D>(qt, dk, kl, g);
+  put_block<D>(gt, dv, kl, g);
+  __syncthreads();
+#pragma unroll 1
+  for (int x = tid; x < 2 * 32 * (D / 4); x += 64 * NW) {
+    const int which = x / (32 * (D / 4)), r = x / (D / 4) % 32, c = x % (D / 4) * 4;
+    if (j0 + r >= d.Skv) continue;
+    f32x4 y = *(const f32x4*)(lds + which * T + r * P + c);
+#pragma unroll
+    for (int w = 1; w < NW; ++w) y += *(const f32x4*)(lds + (2 * w + which) * T + r * P + c);
+    const float f = which == 0 ? d.scale : 1.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] *= f;
+    *(f32x4*)((float*)(which == 0 ? a.dk : a.dv) + kv_h + (long)(j0 + r) * d.kv_ss + c) = y;
+  }
 }
 
-// Backward, dQ part: workgroup owns R query rows; streams K/V tiles; p = exp(s - L).
-template <int D>
-__global__ void __launch_bounds__(256) bwd_dq_f32_kernel(BwdArgs a) {
-  __shared__ float Qs[R][D];
-  __shared__ float Gs[R][D];
-  __shared__ float Ks[T][D + 1];
-  __shared__ float Vs[T][D + 1];
-  __shared__ float Ss[R][T];
-  const Dims& d = a.d;
-  const int tid = threadIdx.x, r = tid / 16, c = tid % 16;
-  const int b = blockIdx.z, hq = blockIdx.y, hk = hq / (d.Hq / d.Hkv);
-  const int i = blockIdx.x * R + r;
-  const bool row_ok = i < d.Sq;
-  const long qoff = b * d.q_sb + hq * d.q_sh + (long)i * d.q_ss;
-  const float* k = (const float*)a.k + b * d.kv_sb + hk * d.kv_sh;
-  const float* v = (const float*)a.v + b * d.kv_sb + hk * d.kv_sh;
-  for (int e = c; e < D; e += 16) {
-    Qs[r][e] = row_ok ? ((const float*)a.q)[qoff + e] : 0.f;
-    Gs[r][e] = row_ok ? ((const float*)a.d_o)[qoff + e] : 0.f;
-  }
-  const long row = ((long)b * d.Hq + hq) * d.Sq + i;
-  const float L = row_ok ? a.lse[row] : -INFINITY;
-  const float delta = row_ok ? a.delta[row] : 0.f;
-  float acc[D / 16];
-#pragma unroll
-  for (int e = 0; e < D / 16; ++e) acc[e] = 0.f;
-
-  for (int j0 = 0; j0 < d.Skv; j0 += T) {
-    __syncthreads();
-    for (int e = tid; e < T * D; e += 256) {
-      const int jj = e / D, dd = e % D;
-      const bool ok = j0 + jj < d.Skv;
-      Ks[jj][dd] = ok ? k[(long)(j0 + jj) * d.kv_ss + dd] : 0.f;
-      Vs[jj][dd] = ok ? v[(long)(j0 + jj) * d.kv_ss + dd] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < T / 16; ++t) {
-      const int jj = c + 16 * t, j = j0 + jj;
-      float x = 0.f, g = 0.f;
-      for (int e = 0; e < D; ++e) {
-        x = fmaf(Qs[r][e], Ks[jj][e], x);
-        g = fmaf(Gs[r][e], Vs[jj][e], g);
-      }
-      float ds = 0.f;
-      if (row_ok && j < d.Skv && L != -INFINITY && visible(a.mask, b, i, j))
-        ds = expf(x * d.scale - L) * (g - delta);
-      Ss[r][jj] = ds;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < D / 16; ++e) {
-      float x = acc[e];
-      for (int jj = 0; jj < T; ++jj) x = fmaf(Ss[r][jj], Ks[jj][c + 16 * e], x);
-      acc[e] = x;
-    }
-  }
-  if (!row_ok) return;
-  float* dq = a.dq_accum + row * D;
-#pragma unroll
-  for (int e = 0; e < D / 16; ++e) dq[c + 16 * e] += acc[e] * d.scale;   // rows are owned exclusively
+// Both parts in one launch (they share nothing and neither fills the card on small problems): the first
+// n_q workgroups of a K/V head form dQ, the others dK and dV.
+template <int D, bool MASKED>
+__global__ void __launch_bounds__(64 * waves_of(D)) bwd_f32_kernel(BwdArgs a, int n_q) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  if ((int)blockIdx.x < n_q) bwd_dq_f32<D, MASKED>(a, blockIdx.x, blockIdx.y, blockIdx.z, smem);
+  else bwd_dkdv_f32<D, MASKED>(a, blockIdx.x - n_q, blockIdx.y, blockIdx.z, smem);
 }
 
-// Backward, dK/dV part: workgroup owns R key rows of one (b, hkv); streams the query rows of
-// every head in the group.
-template <int D>
-__global__ void __launch_bounds__(256) bwd_dkdv_f32_kernel(BwdArgs a) {
-  __shared__ float Ks[R][D];
-  __shared__ float Vs[R][D];
-  __shared__ float Qs[T][D + 1];
-  __shared__ float Gs[T][D + 1];
-  __shared__ float Ps[R][T];
-  __shared__ float Ss[R][T];
-  __shared__ float Ls[T], Ds[T];
-  const Dims& d = a.d;
-  const int tid = threadIdx.x, r = tid / 16, c = tid % 16;
-  const int b = blockIdx.z, hk = blockIdx.y, G = d.Hq / d.Hkv;
-  const int j = blockIdx.x * R + r;
-  const bool row_ok = j < d.Skv;
-  const long koff = b * d.kv_sb + hk * d.kv_sh + (long)j * d.kv_ss;
-  for (int e = c; e < D; e += 16) {
-    Ks[r][e] = row_ok ? ((const float*)a.k)[koff + e] : 0.f;
-    Vs[r][e] = row_ok ? ((const float*)a.v)[koff + e] : 0.f;
-  }
-  float dk[D / 16], dv[D / 16];
-#pragma unroll
-  for (int e = 0; e < D / 16; ++e) { dk[e] = 0.f; dv[e] = 0.f; }
-
-  for (int hq = hk * G; hq < (hk + 1) * G; ++hq) {
-    const float* q = (const float*)a.q + b * d.q_sb + hq * d.q_sh;
-    const float* g = (const float*)a.d_o + b * d.q_sb + hq * d.q_sh;
-    const long row0 = ((long)b * d.Hq + hq) * d.Sq;
-    for (int i0 = 0; i0 < d.Sq; i0 += T) {
-      __syncthreads();
-      for (int e = tid; e < T * D; e += 256) {
-        const int ii = e / D, dd = e % D;
-        const bool ok = i0 + ii < d.Sq;
-        Qs[ii][dd] = ok ? q[(long)(i0 + ii) * d.q_ss + dd] : 0.f;
-        Gs[ii][dd] = ok ? g[(long)(i0 + ii) * d.q_ss + dd] : 0.f;
-      }
-      if (tid < T) {
-        const bool ok = i0 + tid < d.Sq;
-        Ls[tid] = ok ? a.lse[row0 + i0 + tid] : -INFINITY;
-        Ds[tid] = ok ? a.delta[row0 + i0 + tid] : 0.f;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int t = 0; t < T / 16; ++t) {
-        const int ii = c + 16 * t, i = i0 + ii;
-        float x = 0.f, gv = 0.f;
-        for (int e = 0; e < D; ++e) {
-          x = fmaf(Qs[ii][e], Ks[r][e], x);
-          gv = fmaf(Gs[ii][e], Vs[r][e], gv);
-        }
-        float p = 0.f;
-        if (row_ok && i < d.Sq && Ls[ii] != -INFINITY && visible(a.mask, b, i, j))
-          p = expf(x * d.scale - Ls[ii]);
-        Ps[r][ii] = p;
-        Ss[r][ii] = p * (gv - Ds[ii]);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int e = 0; e < D / 16; ++e) {
-        float x = dv[e], y = dk[e];
-        for (int ii = 0; ii < T; ++ii) {
-          x = fmaf(Ps[r][ii], Gs[ii][c + 16 * e], x);
-          y = fmaf(Ss[r][ii], Qs[ii][c + 16 * e], y);
-        }
-        dv[e] = x; dk[e] = y;
-      }
-    }
-  }
-  if (!row_ok) return;
-#pragma unroll
-  for (int e = 0; e < D / 16; ++e) {
-    ((float*)a.dk)[koff + c + 16 * e] = dk[e] * d.scale;
-    ((float*)a.dv)[koff + c + 16 * e] = dv[e];
-  }
+template <int D, bool MASKED> hipError_t launch_fwd(const FwdArgs& a, hipStream_t s) {
+  static SmemOnce once;
+  constexpr int lds = (waves_of(D) * (2 * tile_of(D) + 64) + 32) * 4;
+  static_assert(lds <= 160 * 1024, "the tiles fit a compute unit");
+  const hipError_t e = ensure_dynamic_lds((const void*)fwd_f32_kernel<D, MASKED>, lds, &once);
+  if (e != hipSuccess) return e;
+  const dim3 grid((a.d.G * a.d.Sq + 31) / 32, a.d.Hkv, a.d.B);
+  fwd_f32_kernel<D, MASKED><<<grid, 64 * waves_of(D), lds, s>>>(a);
+  return hipGetLastError();
+}
+template <int D, bool MASKED> hipError_t launch_bwd(const BwdArgs& a, unsigned stages, hipStream_t s) {
+  static SmemOnce once;
+  constexpr int lds = (waves_of(D) * (2 * tile_of(D) + 64) + tile_of(D)) * 4;
+  static_assert(lds <= 160 * 1024, "the tiles fit a compute unit");
+  const hipError_t e = ensure_dynamic_lds((const void*)bwd_f32_kernel<D, MASKED>, lds, &once);
+  if (e != hipSuccess) return e;
+  const int n_q = stages & 4 ? (a.d.G * a.d.Sq + 31) / 32 : 0, n_k = stages & 2 ? (a.d.Skv + 31) / 32 : 0;
+  bwd_f32_kernel<D, MASKED><<<dim3(n_q + n_k, a.d.Hkv, a.d.B), 64 * waves_of(D), lds, s>>>(a, n_q);
+  return hipGetLastError();
+}
+template <bool MASKED> hipError_t fwd_by_width(const FwdArgs& a, hipStream_t s) {
+  return a.d.D == 64 ? launch_fwd<64, MASKED>(a, s) : a.d.D == 96 ? launch_fwd<96, MASKED>(a, s) : launch_fwd<128, MASKED>(a, s);
+}
+template <bool MASKED> hipError_t bwd_by_width(const BwdArgs& a, unsigned stages, hipStream_t s) {
+  return a.d.D == 64 ? launch_bwd<64, MASKED>(a, stages, s)
+       : a.d.D == 96 ? launch_bwd<96, MASKED>(a, stages, s) : launch_bwd<128, MASKED>(a, stages, s);
 }
 
 }  // namespace
 
 hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t s) {
-  dim3 grid((a.d.Sq + R - 1) / R, a.d.Hq, a.d.B);
-  if (a.d.D == 64) fwd_f32_kernel<64><<<grid, 256, 0, s>>>(a);
-  else if (a.d.D == 96) fwd_f32_kernel<96><<<grid, 256, 0, s>>>(a);
-  else fwd_f32_kernel<128><<<grid, 256, 0, s>>>(a);
-  return hipGetLastError();
+  return a.mask.allow != nullptr ? fwd_by_width<true>(a, s) : fwd_by_width<false>(a, s);
 }
 
 hipError_t launch_bwd_f32(const BwdArgs& a, unsigned stages, hipStream_t s) {
-  dim3 gq((a.d.Sq + R - 1) / R, a.d.Hq, a.d.B);
-  dim3 gk((a.d.Skv + R - 1) / R, a.d.Hkv, a.d.B);
-  if (a.d.D == 64) {
-    if (stages & 4) bwd_dq_f32_kernel<64><<<gq, 256, 0, s>>>(a);
-    if (stages & 2) bwd_dkdv_f32_kernel<64><<<gk, 256, 0, s>>>(a);
-  } else if (a.d.D == 96) {
-    if (stages & 4) bwd_dq_f32_kernel<96><<<gq, 256, 0, s>>>(a);
-    if (stages & 2) bwd_dkdv_f32_kernel<96><<<gk, 256, 0, s>>>(a);
-  } else {
-    if (stages & 4) bwd_dq_f32_kernel<128><<<gq, 256, 0, s>>>(a);
-    if (stages & 2) bwd_dkdv_f32_kernel<128><<<gk, 256, 0, s>>>(a);
-  }
-  return hipGetLastError();
+  return a.mask.allow != nullptr ? bwd_by_width<true>(a, stages, s) : bwd_by_width<false>(a, stages, s);
 }
 
 }  // namespace lvx

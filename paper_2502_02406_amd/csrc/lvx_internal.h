@@ -33,6 +33,7 @@ struct MaskRows {
 // Shape, strides (in elements) and scale shared by every kernel.
 struct Dims {
   int B, Hq, Hkv, Sq, Skv, D;
+  int G;                // query heads per K/V head
   long q_sb, q_sh, q_ss;
   long kv_sb, kv_sh, kv_ss;
   float scale;          // multiplies Q K^T (natural-log domain)
