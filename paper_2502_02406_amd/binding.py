@@ -242,6 +242,32 @@ def lvx_xattn_bwd_error_word(p: lvx_problem, dtype: int, mask: Optional[lvx_mask
     return int(out.value or 0)
 
 
+class Calls:
+    """The visits of one query block on one stream: what every call of a block loop has in common -- the
+    problem, the workspace, the stream and the library's functions -- is marshalled once, the
+    calls take device addresses (of tensors that the caller keeps and has checked)."""
+
+    def __init__(self, p: lvx_problem, dtype: torch.dtype, workspace: torch.Tensor):
+        lib = load()
+        self._f, self._m, self._b = lib.lvx_xattn_fwd, lib.lvx_xattn_fwd_merge, lib.lvx_xattn_bwd_stages
+        self._p, self._dt = C.byref(p), dtype_code(dtype)
+        self._ws, self._n = workspace.data_ptr(), workspace.numel() * workspace.element_size()
+        self._s = _stream()
+
+    def fwd(self, q: int, k: int, v: int, mask: Optional[lvx_mask], o: int, o_dtype: torch.dtype, lse: int) -> None:
+        _check(self._f(self._p, self._dt, q, k, v, C.byref(mask) if mask is not None else None, o, dtype_code(o_dtype),
+                       lse, self._ws, self._n, self._s), "lvx_xattn_fwd")
+
+    def fwd_merge(self, q: int, k: int, v: int, mask: Optional[lvx_mask], o_acc: int, lse_acc: int) -> None:
+        _check(self._m(self._p, self._dt, q, k, v, C.byref(mask) if mask is not None else None, o_acc, lse_acc,
+                       self._ws, self._n, self._s), "lvx_xattn_fwd_merge")
+
+    def bwd(self, q: int, k: int, v: int, o: int, lse: int, d_o: int, mask: Optional[lvx_mask], dq_accum: int,
+            dk: int, dv: int, stages: int) -> None:
+        _check(self._b(self._p, self._dt, q, k, v, o, lse, d_o, C.byref(mask) if mask is not None else None, dq_accum,
+                       dk, dv, self._ws, self._n, self._s, stages), "lvx_xattn_bwd_stages")
+
+
 def lvx_xattn_dq_finalize(p: lvx_problem, dq_accum, dq) -> None:
     code = load().lvx_xattn_dq_finalize(C.byref(p), dq_accum.data_ptr(), dq.data_ptr(),
                                         dtype_code(dq.dtype), _stream())

@@ -50,10 +50,14 @@ class BlockLoop:
         rows = (self.Bsz, self.Hq, self.Sq)
         self.lse = torch.empty(rows, **f32)
         self.o = torch.empty(q_shape, dtype=dtype, device=device)
-        if n_blocks > 1:
-            self.o_acc = torch.empty(q_shape, **f32)       # running O_j of Algorithm 1 (L_j lives in self.lse)
+        # Running O_j of Algorithm 1 (L_j lives in self.lse) and the dQ sums.  Both are float32: a float32
+        # problem's are its results already, with nothing left to round.
         self.dq_accum = torch.empty(q_shape, **f32)
-        self.dq = torch.empty(q_shape, dtype=dtype, device=device)
+        if dtype == torch.float32:
+            self.o_acc, self.dq = self.o, self.dq_accum
+        else:
+            self.o_acc = torch.empty(q_shape, **f32) if n_blocks > 1 else None
+            self.dq = torch.empty(q_shape, dtype=dtype, device=device)
         # one workspace sized for the larger of the two passes
         qd = torch.empty(q_shape, dtype=dtype, device="meta")
         kd = torch.empty((self.Bsz, self.Hkv, self.blk, self.D), dtype=dtype, device="meta")
@@ -75,40 +79,52 @@ class BlockLoop:
         nkb = (self.blk + self.mask.kv_block - 1) // self.mask.kv_block
         return B.make_mask(self.mask.allow, self.mask.q_chunk, self.mask.kv_block, n * per, nkb)
 
+    def _blocks(self, q, k):
+        """The problem of every block (they differ in where their keys start only) and the bytes from one
+        block's keys to the next's."""
+        if not q.is_cuda:
+            raise RuntimeError("BlockLoop needs device tensors")
+        p = B.make_problem(q, k, self.scale)
+        if self.n_blocks > 1:
+            p.Skv = self.blk
+        return p, self.blk * k.stride(2) * k.element_size()
+
     def forward(self, q, k, v) -> Tuple[torch.Tensor, torch.Tensor]:
         """Returns (O in the input dtype, L float32); both are buffers owned by this object."""
         # (the running O of the block loop is written with Q's strides by the first visit and read as
         # a contiguous tensor by the others)
         assert self.n_blocks == 1 or q.is_contiguous(), "the block loop needs a contiguous Q"
+        p, step = self._blocks(q, k)
+        call = B.Calls(p, q.dtype, self.ws)
+        qp, kp, vp, lp = q.data_ptr(), k.data_ptr(), v.data_ptr(), self.lse.data_ptr()
         if self.n_blocks == 1:
-            p = B.make_problem(q, k, self.scale)
-            B.lvx_xattn_fwd(p, q, k, v, self._mask_for(0), self.o, self.lse, self.ws)
+            call.fwd(qp, kp, vp, self._mask_for(0), self.o.data_ptr(), self.o.dtype, lp)
             return self.o, self.lse
-        for n in range(self.n_blocks):
-            kb = k[:, :, n * self.blk:(n + 1) * self.blk]
-            vb = v[:, :, n * self.blk:(n + 1) * self.blk]
-            p = B.make_problem(q, kb, self.scale)
-            if n == 0:      # merging with the identity (0, -inf) is a no-op: write the state directly
-                B.lvx_xattn_fwd(p, q, kb, vb, self._mask_for(n), self.o_acc, self.lse, self.ws)
-            else:           # the FlashAttention call and Rescale of Algorithm 1 in one call
-                B.lvx_xattn_fwd_merge(p, q, kb, vb, self._mask_for(n), self.o_acc, self.lse, self.ws)
-        B.lvx_xattn_merge([self.o_acc], [self.lse], self.o, self.lse)    # round to the output dtype
+        op = self.o_acc.data_ptr()
+        # merging with the identity (0, -inf) is a no-op: the first visit writes the state directly
+        call.fwd(qp, kp, vp, self._mask_for(0), op, torch.float32, lp)
+        for n in range(1, self.n_blocks):       # the FlashAttention call and Rescale of Algorithm 1 in one call
+            call.fwd_merge(qp, kp + n * step, vp + n * step, self._mask_for(n), op, lp)
+        if self.o_acc is not self.o:
+            B.lvx_xattn_merge([self.o_acc], [self.lse], self.o, self.lse)    # round to the output dtype
         return self.o, self.lse
 
     def backward(self, q, k, v, o, lse, d_o, dk, dv) -> torch.Tensor:
         """dk/dv (same shape and strides as k) are overwritten; returns dQ in the input dtype."""
+        assert dk.stride() == k.stride() and dv.stride() == k.stride() and v.stride() == k.stride()
+        assert o.stride() == q.stride() and d_o.stride() == q.stride()
         self.dq_accum.zero_()
+        p, step = self._blocks(q, k)
+        call = B.Calls(p, q.dtype, self.ws)
+        qp, kp, vp, dkp, dvp = q.data_ptr(), k.data_ptr(), v.data_ptr(), dk.data_ptr(), dv.data_ptr()
+        op, lp, gp, ap = o.data_ptr(), lse.data_ptr(), d_o.data_ptr(), self.dq_accum.data_ptr()
         for n in range(self.n_blocks):
-            sl = slice(n * self.blk, (n + 1) * self.blk)
-            kb, vb = k[:, :, sl], v[:, :, sl]
-            p = B.make_problem(q, kb, self.scale)
             # delta = rowsum(dO * O) depends on the query block only: the first visit computes it
             # into the workspace, the others reuse it
             stages = (B.LVX_BWD_ALL if n == 0 else (B.LVX_BWD_DKDV | B.LVX_BWD_DQ)) | self.bwd_flags
-            B.lvx_xattn_bwd(p, q, kb, vb, o, lse, d_o, self._mask_for(n), self.dq_accum,
-                            dk[:, :, sl], dv[:, :, sl], self.ws, stages)
-        p = B.make_problem(q, k, self.scale)
-        B.lvx_xattn_dq_finalize(p, self.dq_accum, self.dq)
+            call.bwd(qp, kp + n * step, vp + n * step, op, lp, gp, self._mask_for(n), ap, dkp + n * step, dvp + n * step, stages)
+        if self.dq is not self.dq_accum:
+            B.lvx_xattn_dq_finalize(p, self.dq_accum, self.dq)
         return self.dq
 
 
@@ -175,6 +191,7 @@ class RecomputeLayer:
             B.lvx_xattn_bwd(p, self.q, self.k, self.v, o, lse, d_o, None, lp.dq_accum, self.dk, self.dv, lp.ws, stages)
             B.lvx_xattn_project_bwd(yb, wkv, [self.dk, self.dv],
                                     dx=self.dy[:, n * self.blk:(n + 1) * self.blk], dw=self.dwkv)
-        B.lvx_xattn_dq_finalize(p, lp.dq_accum, lp.dq)
+        if lp.dq is not lp.dq_accum:
+            B.lvx_xattn_dq_finalize(p, lp.dq_accum, lp.dq)
         B.lvx_xattn_project_bwd(x, wq, [lp.dq], dx=self.dx, dw=self.dwq)
         return self.dx, self.dy, self.dwq, self.dwkv
