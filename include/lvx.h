@@ -220,11 +220,13 @@ lvx_status lvx_xattn_project(const lvx_projection* p, lvx_dtype dtype, const voi
  * float32 sum per element in the order of the definition: correctness-grade, slow).
  * LVX_BF16: pointers and x's row stride must be 16-byte aligned.  No workspace.
  * When dw has fewer tiles of 256 x 256 than the GPU has compute units, the tokens are divided
- * among several workgroups per tile, which add their sums to dw one after the other in a fixed
- * order (so results still repeat bit for bit); whose turn it is stands in a small table inside the
- * library, one per GPU, that every call leaves as it found it.  Two such calls running at the same
- * time on one GPU (different streams) would share that table: do not overlap them.  Waits are
- * bounded; a workgroup whose turn never came writes NaN over its part of dw instead of a sum. */
+ * among several workgroups per tile, whose sums are added to dw in a fixed order (so results still
+ * repeat bit for bit): one after the other, as a small table inside the library says whose turn it
+ * is, or, from four workgroups per tile on, from an array of 64 MiB inside the library that holds
+ * them all.  Both exist once per GPU, and every call leaves the table as it found it.  Two such calls
+ * running at the same time on one GPU (different streams) would share them: do not overlap them.
+ * Waits are bounded; a workgroup whose turn never came writes NaN over its part of dw instead of a
+ * sum. */
 lvx_status lvx_xattn_project_bwd(const lvx_projection* p, lvx_dtype dtype, const void* x, const void* w,
                                  int n_out, const void* const* d_out, void* dx, float* dw,
                                  void* hip_stream);

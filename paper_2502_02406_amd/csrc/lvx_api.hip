@@ -440,6 +440,7 @@ lvx_status lvx_xattn_project(const lvx_projection* p, lvx_dtype dtype, const voi
   a.N = n_out * p->H * p->D;
   a.H = p->H;
   a.D = p->D;
+  a.n_cu = device_cu_count();
   if (dtype == LVX_BF16 && !project_bf16_supported(a)) return LVX_ERR_UNSUPPORTED;
   // (a tile's copies address its rows with 32-bit byte offsets from the tile's first row)
   if (dtype == LVX_BF16 && 256 * p->x_ss * esz > (int64_t)UINT32_MAX) return LVX_ERR_STRIDE;

@@ -121,6 +121,7 @@ struct ProjArgs {
   void* out[2];         // each [B, H, S, D] contiguous, x's dtype
   long M, ldx;
   int S, E, N, H, D;
+  int n_cu;             // compute units of the device (picks the tile height)
 };
 bool project_bf16_supported(const ProjArgs& a);   // shapes the matrix-core kernel takes
 hipError_t launch_project(const ProjArgs& a, int is_f32, hipStream_t s);

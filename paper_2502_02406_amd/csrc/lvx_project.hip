@@ -19,6 +19,10 @@
 // reads together cover all banks.  The one barrier per 64 matrix instructions sits before the
 // last quarter of a tile pair, when its last operands are already in registers: behind it the
 // first operands of the next pair are read and the slot is free for the pair after that.
+// Problems with fewer 256 x 256 tiles than three quarters of the compute units take tiles of 128 tokens
+// (IB = 2: six operands per eight matrix instructions instead of eight per sixteen, but twice the
+// workgroups): 2048 tokens x 4096 features x 4096 columns, 128 tiles of 256 x 256, 87 -> 67 us; 2048
+// tokens x 512 x 1024 19 -> 12.6 us.
 // The epilogue turns the tile around in LDS (rounded to bf16) and writes whole 256-byte rows.
 #include "lvx_internal.h"
 #include "lvx_mfma.h"
@@ -30,17 +34,16 @@ namespace lvx {
 
 namespace {
 
-constexpr int TM = 256, TN = 256;      // tokens x columns per workgroup
+constexpr int TN = 256;                // columns per workgroup
 constexpr int BK = 64;                 // features per tile pair
 constexpr int NSLOT = 2;               // LDS slots
 constexpr int ROWB = BK * 2;           // bytes of a tile row: one 128-byte line
-constexpr int TILE_B = 256 * ROWB;     // one operand's tile
+constexpr int TILE_B = 256 * ROWB;     // one operand's tile (of x: of the room for it)
 constexpr int SLOT_B = 2 * TILE_B;     // x tile, then w tile
 constexpr int RING_B = NSLOT * SLOT_B;
 constexpr int TB_PITCH = 128 * 2 + 16; // epilogue: a wave's 128 tokens x 128 columns of bf16, padded rows
 constexpr int TB_WAVE = 128 * TB_PITCH;
 constexpr int SMEM_B = RING_B > 4 * TB_WAVE ? RING_B : 4 * TB_WAVE;
-constexpr int NPART = 16;              // copies per wave and tile pair: 8 of x, 8 of w (8 rows each)
 
 // Position permutation of a tile row's eight chunks: chunk c of row r sits at position
 // c ^ perm_of(r).  Eight consecutive rows get eight different values, and two rows eight apart
@@ -48,9 +51,14 @@ constexpr int NPART = 16;              // copies per wave and tile pair: 8 of x,
 // bank (rows are 128 bytes apart).
 __device__ __forceinline__ int perm_of(int r) { return (r & 7) ^ ((r >> 3) & 1); }
 
+// IB: blocks of 32 tokens per wave
+template <int IB>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 project_bf16_kernel(ProjArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
+  constexpr int TM = 64 * IB;                        // tokens per workgroup
+  constexpr int XC = 2 * IB;                         // copies of x per wave and tile pair (8 rows each; of w: 8)
+  constexpr int NPART = XC + 8;
   const int n_mt = (int)((a.M + TM - 1) / TM), n_nt = a.N / TN;
   HeadWork hw;                                       // the column tiles of a token tile share an XCD (and its L2)
   if (!xcd_decode(blockIdx.x, n_mt, n_nt, &hw)) return;
@@ -58,19 +66,19 @@ project_bf16_kernel(ProjArgs a) {
   const int n0 = hw.item * TN;
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, l31 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;           // this wave's 128 tokens / 128 columns of the tile
+  const int wm = wave >> 1, wn = wave & 1;           // this wave's 32 IB tokens / 128 columns of the tile
   const int nk = a.E / BK;
 
   // ---- copies: one instruction moves 8 rows x 128 bytes; lane l fills slot l of them, i.e. row
   // l / 8, position l % 8, which holds chunk (l % 8) ^ perm_of(row).  A wave copies rows
-  // 64 wave + 8 j + l / 8 of both tiles, j = 0 .. 7.  Rows past the last token re-read the last
+  // 8 XC wave + 8 j + l / 8 of the x tile, 64 wave + 8 j + l / 8 of the w tile.  Rows past the last token re-read the last
   // one (their results are never stored).
   const unsigned xrow_b = (unsigned)(a.ldx * 2), wrow_b = (unsigned)(a.E * 2);
   const long m_last = a.M - 1 - m0;
-  unsigned xo[8], wo[2];
+  unsigned xo[XC], wo[2];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int r = 64 * wave + 8 * j + (lane >> 3);
+  for (int j = 0; j < XC; ++j) {
+    const int r = 8 * XC * wave + 8 * j + (lane >> 3);
     const unsigned swz = 16u * (unsigned)((lane & 7) ^ perm_of(8 * j + (lane >> 3)));
     xo[j] = (unsigned)(r < m_last ? r : (int)m_last) * xrow_b + swz;
     if (j < 2) wo[j] = (unsigned)(lane >> 3) * wrow_b + swz;      // (the permutation repeats every 16 rows)
@@ -79,10 +87,12 @@ project_bf16_kernel(ProjArgs a) {
   const char* const wg = (const char*)a.w + ((long)n0 + 64 * wave) * wrow_b;
   auto issue_part = [&](int kt, int part) __attribute__((always_inline)) {
     char* const st = smem + (kt % NSLOT) * SLOT_B;
-    const int j = part & 7;
-    char* const dst = st + (part >> 3) * TILE_B + (64 * wave + 8 * j) * ROWB;
-    if (part < 8) dma16s(xg + (long)kt * ROWB, xo[j], dst);
-    else dma16s(wg + (long)(8 * j) * wrow_b + (long)kt * ROWB, wo[j & 1], dst);
+    if (part < XC) {
+      dma16s(xg + (long)kt * ROWB, xo[part], st + (8 * XC * wave + 8 * part) * ROWB);
+    } else {
+      const int j = part - XC;
+      dma16s(wg + (long)(8 * j) * wrow_b + (long)kt * ROWB, wo[j & 1], st + TILE_B + (64 * wave + 8 * j) * ROWB);
+    }
   };
 
   // ---- operands: block i of this wave's tokens / block j of its columns, k-step q = 0 .. 3 of a
@@ -90,7 +100,7 @@ project_bf16_kernel(ProjArgs a) {
   int rd[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) rd[q] = l31 * ROWB + 16 * ((2 * q + g) ^ perm_of(l31));
-  const int xbase = wm * 128 * ROWB, wbase = TILE_B + wn * 128 * ROWB;
+  const int xbase = wm * 32 * IB * ROWB, wbase = TILE_B + wn * 128 * ROWB;
   auto x_op = [&](const char* st, int q, int i) __attribute__((always_inline)) -> bf16x8 {
     return *(const bf16x8*)(st + xbase + 32 * i * ROWB + rd[q]);
   };
@@ -98,20 +108,20 @@ project_bf16_kernel(ProjArgs a) {
     return *(const bf16x8*)(st + wbase + 32 * j * ROWB + rd[q]);
   };
 
-  f32x16 acc[4][4];                                  // [column block j][token block i], transposed blocks
+  f32x16 acc[4][IB];                                 // [column block j][token block i], transposed blocks
 #pragma unroll
   for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { acc[j][i] = zero16(); asm volatile("" : "+a"(acc[j][i])); }
+    for (int i = 0; i < IB; ++i) { acc[j][i] = zero16(); asm volatile("" : "+a"(acc[j][i])); }
 
-  // 16 matrix instructions of one k-step; hook(u) is other work issued after instruction u
-  auto mma16 = [&](const bf16x8 (&xv)[4], const bf16x8 (&wv)[4], auto&& hook) __attribute__((always_inline)) {
+  // the 4 IB matrix instructions of one k-step; hook(u) is other work issued after instruction u
+  auto mma16 = [&](const bf16x8 (&xv)[IB], const bf16x8 (&wv)[4], auto&& hook) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < IB; ++i) {
         kvring::mfma_acc(acc[j][i], wv[j], xv[i]);
-        hook(4 * j + i);
+        hook(IB * j + i);
         __builtin_amdgcn_sched_barrier(0);
       }
   };
@@ -128,22 +138,25 @@ project_bf16_kernel(ProjArgs a) {
   if (nk > 1) wait_vmcnt<NPART>();
   else wait_vmcnt<0>();
   wg_barrier();
-  bf16x8 xa[4], wa[4], xb[4], wb[4];                 // operands of even / odd k-steps
+  bf16x8 xa[IB], wa[4], xb[IB], wb[4];               // operands of even / odd k-steps
 #pragma unroll
-  for (int i = 0; i < 4; ++i) { xa[i] = x_op(smem, 0, i); wa[i] = w_op(smem, 0, i); }
+  for (int i = 0; i < IB; ++i) xa[i] = x_op(smem, 0, i);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) wa[i] = w_op(smem, 0, i);
 
   // fetches the operands of k-step q of the pair in slot st, one per matrix instruction
-  auto fetch = [&](const char* st, int q, int u, bf16x8 (&xv)[4], bf16x8 (&wv)[4]) __attribute__((always_inline)) {
-    if (u < 4) xv[u] = x_op(st, q, u);
-    else if (u < 8) wv[u - 4] = w_op(st, q, u - 4);
+  auto fetch = [&](const char* st, int q, int u, bf16x8 (&xv)[IB], bf16x8 (&wv)[4]) __attribute__((always_inline)) {
+    if (u < IB) xv[u] = x_op(st, q, u);
+    else if (u < IB + 4) wv[u - IB] = w_op(st, q, u - IB);
   };
+  constexpr int EW = 4 * IB / 8;                     // a copy of w every EW matrix instructions of a k-step, one of x every two
   auto pair = [&](int P, auto steady, bool send2, bool send1, bool more) __attribute__((always_inline)) {
     constexpr bool STEADY = decltype(steady)::value;   // send2, send1 and more are all true
     const char* const st = smem + (P % NSLOT) * SLOT_B;
     const char* const sn = smem + ((P + 1) % NSLOT) * SLOT_B;
     mma16(xa, wa, [&](int u) __attribute__((always_inline)) {
       fetch(st, 1, u, xb, wb);
-      if ((STEADY || send2) && u % 2 == 1) issue_part(P + 1, 8 + u / 2);
+      if ((STEADY || send2) && u % EW == EW - 1) issue_part(P + 1, XC + u / EW);
     });
     mma16(xb, wb, [&](int u) __attribute__((always_inline)) { fetch(st, 2, u, xa, wa); });
     mma16(xa, wa, [&](int u) __attribute__((always_inline)) { fetch(st, 3, u, xb, wb); });
@@ -169,10 +182,11 @@ project_bf16_kernel(ProjArgs a) {
   wg_barrier();
 #pragma unroll
   for (int j = 0; j < 4; ++j)
-    asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[j][0]), "+a"(acc[j][1]), "+a"(acc[j][2]), "+a"(acc[j][3]));
+#pragma unroll
+    for (int i = 0; i < IB; i += 2) asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[j][i]), "+a"(acc[j][i + 1]));
   char* const tb = smem + wave * TB_WAVE;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < IB; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -186,16 +200,20 @@ project_bf16_kernel(ProjArgs a) {
   const int HD = a.H * a.D;
   uint16_t* const out = (uint16_t*)a.out[nw / HD];
   const int nn = nw % HD;
+  // A lane's column is the same in every row it writes, and its rows are 4 apart: the divisions that
+  // find head and batch are made once
+  const int row0 = lane >> 4, ch = lane & 15, col = nn + 8 * ch;
+  const long mr = m0 + wm * 32 * IB + row0;
+  long bb = mr / a.S;
+  int sr = (int)(mr - bb * a.S);
+  uint16_t* const out_c = out + (long)(col / a.D) * a.S * a.D + col % a.D;
+  const long batch = (long)a.H * a.S * a.D;
 #pragma unroll 4
-  for (int it = 0; it < 32; ++it) {
-    const int row = 4 * it + (lane >> 4), ch = lane & 15;
-    const long m = m0 + wm * 128 + row;
-    const u32x4 y = *(const u32x4*)(tb + row * TB_PITCH + ch * 16);
-    if (m < a.M) {
-      const int col = nn + 8 * ch;
-      const long b = m / a.S, s = m % a.S;
-      *(u32x4*)(out + ((b * a.H + col / a.D) * a.S + s) * a.D + col % a.D) = y;
-    }
+  for (int it = 0; it < 8 * IB; ++it) {
+    const u32x4 y = *(const u32x4*)(tb + (4 * it + row0) * TB_PITCH + ch * 16);
+    if (mr + 4 * it < a.M) *(u32x4*)(out_c + bb * batch + (long)sr * a.D) = y;
+    sr += 4;
+    while (sr >= a.S) { sr -= a.S; ++bb; }
   }
 }
 
@@ -220,18 +238,25 @@ bool project_bf16_supported(const ProjArgs& a) {
   return a.E % BK == 0 && a.N % TN == 0 && (a.H * a.D) % 128 == 0 && a.D % 8 == 0;
 }
 
+namespace {
+template <int IB> hipError_t launch_tiles(const ProjArgs& a, hipStream_t s) {
+  static SmemOnce once;
+  const hipError_t e = ensure_dynamic_lds((const void*)project_bf16_kernel<IB>, SMEM_B, &once);
+  if (e != hipSuccess) return e;
+  const long grid = xcd_grid((int)((a.M + 64 * IB - 1) / (64 * IB)), a.N / TN);
+  project_bf16_kernel<IB><<<(unsigned)grid, 256, SMEM_B, s>>>(a);
+  return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_project(const ProjArgs& a, int is_f32, hipStream_t s) {
   if (is_f32) {
     const long n = a.M * a.N;
     project_f32_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(a);
     return hipGetLastError();
   }
-  static SmemOnce once;
-  const hipError_t e = ensure_dynamic_lds((const void*)project_bf16_kernel, SMEM_B, &once);
-  if (e != hipSuccess) return e;
-  const long grid = xcd_grid((int)((a.M + TM - 1) / TM), a.N / TN);
-  project_bf16_kernel<<<(unsigned)grid, 256, SMEM_B, s>>>(a);
-  return hipGetLastError();
+  const long tiles = (a.M + 255) / 256 * (a.N / TN);
+  return tiles * 4 <= 3L * a.n_cu ? launch_tiles<2>(a, s) : launch_tiles<4>(a, s);
 }
 
 }  // namespace lvx

@@ -33,7 +33,13 @@
 // sets the word back to zero.  The order is fixed, so results repeat bit for bit; a part only ever
 // waits for a workgroup with a lower number, which was started before it, so the waits end (they
 // are bounded all the same).  Calls that overlap in time on one GPU would share the turn words and
-// must not be made.  (Without that, tiles 128 rows high: a wave owns 64 x 128, the G tile is
+// must not be made.  From DW_SUMS parts on that chain -- a few trips to memory per part, one part after
+// the other -- is longer than moving all the sums: the parts then store their tiles side by side in
+// an array of the library, in register order, and a second launch adds them to dw in the order of their
+// numbers (8 tiles x 32 parts, 131072 tokens x 1024 columns x 512 features: 295 -> 197
+// us, of which the second launch is about 20; 9 parts of 5000 tokens: 57 -> 26 us; with 2 or 3 parts the
+// chain is the shorter one: 32768 tokens x 2048 columns x 4096 features, 2 parts, 487 us either way).
+// (Without that, tiles 128 rows high: a wave owns 64 x 128, the G tile is
 // [token][128 columns] with rows of 256 bytes, same permutation.)
 #include "lvx_internal.h"
 #include "lvx_mfma.h"
@@ -70,6 +76,11 @@ constexpr int SMEM_B = RING_B > 4 * TB_WAVE ? RING_B : 4 * TB_WAVE;
 
 __device__ __forceinline__ int perm_of(int r) { return (r & 7) ^ ((r >> 3) & 1); }
 
+// parts from which their sums go through memory instead of taking turns
+constexpr int DW_SUMS = 4;
+constexpr int MAX_SUM_TILES = 256;     // tiles x parts that the array below holds
+__device__ __align__(256) float dw_sums[(size_t)MAX_SUM_TILES * T * T];
+
 // whose turn it is to add to tile t of dw (0 between launches)
 __device__ int dw_turn[MAX_TURNS * 8];
 typedef int __attribute__((address_space(1))) gint;
@@ -87,16 +98,16 @@ __device__ __forceinline__ void div_tokens(int m, int S, float inv_S, int* b, in
 
 // MODE 0: dx = G W (rows = tokens, columns = features e, contraction over n)
 // MODE 1: dw += G^T X (rows = columns n of the projection, columns = e, contraction over tokens)
-// RB: 32-row blocks of the result per wave (4: tiles of 256 rows; 2: of 128 rows, MODE 1 only)
+// RB: 32-row blocks of the result per wave (4: tiles of 256 rows; 2: of 128 rows)
 // GA (MODE 0): heads are multiples of 64 wide, so that a tile pair's 64 columns of G are one line
 template <int MODE, int RB, bool GA = true>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 project_bwd_bf16_kernel(ProjBwdArgs a) {
-  static_assert(RB == 4 || (RB == 2 && MODE == 1), "tile heights");
+  static_assert(RB == 4 || RB == 2, "tile heights");
   constexpr int TR = 64 * RB;                        // rows of a workgroup's tile
   constexpr int BROWB = TR * 2;                      // MODE 1: bytes of a row of the G tile [k][TR]
   constexpr int RPI = 1024 / BROWB;                  // ... rows that one copy instruction moves (2 or 4)
-  constexpr int NB = MODE == 0 ? 8 : 16 / RPI;       // copies per wave and tile pair: B side,
+  constexpr int NB = MODE == 0 ? 2 * RB : 16 / RPI;  // copies per wave and tile pair: B side,
   constexpr int NPART = 8 + NB;                      // and with the 8 of the A side
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int n_rt = MODE == 0 ? (int)((a.M + TR - 1) / TR) : a.N / TR;   // row tiles of the result
@@ -139,9 +150,9 @@ project_bwd_bf16_kernel(ProjBwdArgs a) {
   for (int par = 0; par < 2; ++par) kr_chunk[par] = 16u * (unsigned)(pos ^ (4 * ((2 * par + lh) & 3)));
 
   // MODE 0: rows of the G tile ([256 tokens][64 n], the forward's x layout): one instruction
-  // moves 8 rows x 128 bytes; a wave copies rows 64 wave + 8 j + l / 8.  Tokens past the last
+  // moves 8 rows x 128 bytes; a wave copies rows 16 RB wave + 8 j + l / 8.  Tokens past the last
   // one re-read it (their results are never stored).
-  unsigned g_row[8];
+  unsigned g_row[2 * RB];
   // MODE 1: the G tile [64 tokens][TR columns]: one instruction moves RPI rows; lane l fills
   // position l % (64 / RPI) of row l / (64 / RPI); a wave copies rows 16 wave + RPI j + that.
   // g_col: the lane's column part of a G address, j even / odd (the columns of the tile lie in
@@ -151,8 +162,8 @@ project_bwd_bf16_kernel(ProjBwdArgs a) {
   const char* g_tile_base = nullptr;                 // MODE 1: the output's gradient
   if (MODE == 0) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int r = 64 * wave + 8 * j + (lane >> 3);
+    for (int j = 0; j < 2 * RB; ++j) {
+      const int r = 16 * RB * wave + 8 * j + (lane >> 3);
       const long m = r0 + r < a.M ? r0 + r : a.M - 1;
       int b, s;
       div_tokens((int)m, a.S, inv_S, &b, &s);
@@ -216,7 +227,7 @@ project_bwd_bf16_kernel(ProjBwdArgs a) {
         }
       }
       dma16u(g_pair_base, g_row[j] + (GA ? 0u : (j & 1) ? g_lane1 : g_lane0),
-             st + (unsigned)(TILE_B + (64 * wave + 8 * j) * RK_ROWB));
+             st + (unsigned)(TILE_B + (16 * RB * wave + 8 * j) * RK_ROWB));
     } else {                                         // B side: G, 64 tokens x TR columns
       const int jb = part - 8;
       const long m_first = (long)PROBE_PAIR(k0 + kt) * BK;
@@ -256,7 +267,7 @@ project_bwd_bf16_kernel(ProjBwdArgs a) {
   int rk[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q)
-    rk[q] = TILE_B + (wm * 128 + l31) * RK_ROWB + 16 * ((2 * q + g) ^ perm_of(l31));
+    rk[q] = TILE_B + (wm * 32 * RB + l31) * RK_ROWB + 16 * ((2 * q + g) ^ perm_of(l31));
   auto a_op = [&](const char* st, int q, int jj) __attribute__((always_inline)) -> bf16x8 {
     return tr_op(st + ka[jj] + 16 * q * KR_ROWB, std::integral_constant<int, KR_ROWB>{});
   };
@@ -365,7 +376,7 @@ project_bwd_bf16_kernel(ProjBwdArgs a) {
     // turn the tile around in LDS (rounded to bf16) and write whole 256-byte row segments
     char* const tb = smem + wave * TB_WAVE;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < RB; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -376,9 +387,9 @@ project_bwd_bf16_kernel(ProjBwdArgs a) {
         }
     uint16_t* const out = (uint16_t*)a.dx + e0 + wn * 128;
 #pragma unroll 4
-    for (int it = 0; it < 32; ++it) {
+    for (int it = 0; it < 8 * RB; ++it) {
       const int row = 4 * it + (lane >> 4), ch = lane & 15;
-      const long m = r0 + wm * 128 + row;
+      const long m = r0 + wm * 32 * RB + row;
       const u32x4 y = *(const u32x4*)(tb + row * TB_PITCH + ch * 16);
       if (m < a.M) *(u32x4*)(out + m * a.ldx + 8 * ch) = y;
     }
@@ -404,6 +415,18 @@ project_bwd_bf16_kernel(ProjBwdArgs a) {
             *(f32x4*)(out + (long)(32 * i) * a.E + 32 * j + 8 * q) = v[j][q];
           }
       }
+    } else if (a.dw_parts >= DW_SUMS) {
+      // this part's sums, 16 bytes per lane and register group, as dw_add_sums_kernel reads them
+      float* const out = dw_sums + (((long)tpart * n_rt + hw.head) * n_ct + hw.item) * (T * T) + wave * (T * T / 4) + lane * 4;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x4 v = {acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]};
+            *(f32x4*)(out + ((j * RB + i) * 4 + q) * 256) = v;
+          }
     } else {
       // A tile whose tokens are divided (dw_parts > 1): the parts take turns, in the order of their
       // numbers; an undivided tile goes the same way without the waiting.  Every wave owns a quarter
@@ -470,6 +493,31 @@ project_bwd_bf16_kernel(ProjBwdArgs a) {
   }
 }
 
+// dw += the parts' sums, in the order of the parts.  One thread per 16 bytes of a tile in register order;
+// bound by reading the sums (64 MB at most).
+__global__ void __launch_bounds__(256) dw_add_sums_kernel(float* dw, int E, int n_rt, int n_ct, int parts) {
+  const int tile = blockIdx.x / (T * T / 1024), x = (blockIdx.x % (T * T / 1024)) * 256 + threadIdx.x;
+  const int lane = x & 63, q = (x >> 6) & 3, i = (x >> 8) & 3, j = (x >> 10) & 3, wave = x >> 12;
+  const int row = (tile / n_ct) * T + (wave >> 1) * 128 + 32 * i + (lane & 31);
+  const int col = (tile % n_ct) * T + (wave & 1) * 128 + 32 * j + 8 * q + 4 * (lane >> 5);
+  const long step = (long)n_rt * n_ct * T * T;
+  const float* src = dw_sums + (long)tile * T * T + x * 4;
+  float* const dst = dw + (long)row * E + col;
+  f32x4 sum = *(const f32x4*)dst;
+  for (int p = 0; p < parts; p += 8) {
+    f32x4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = *(const f32x4*)(src + min(p + u, parts - 1) * step);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const float on = p + u < parts ? 1.f : 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sum[e] = fmaf(on, v[u][e], sum[e]);
+    }
+  }
+  *(f32x4*)dst = sum;
+}
+
 // Any shape and both types: one thread per element of the result, the sum in float32 in the order
 // of the definition.
 template <typename TIn> __device__ __forceinline__ float to_f32(TIn v);
@@ -521,24 +569,29 @@ bool mfma_common(const ProjBwdArgs& a) {
 }  // namespace
 bool project_bwd_bf16_supported(const ProjBwdArgs& a) { return mfma_common(a); }
 
+namespace {
+template <int RB, bool GA> hipError_t launch_dx(const ProjBwdArgs& a, hipStream_t s) {
+  static SmemOnce once;
+  const hipError_t e = ensure_dynamic_lds((const void*)project_bwd_bf16_kernel<0, RB, GA>, SMEM_B, &once);
+  if (e != hipSuccess) return e;
+  const long grid = xcd_grid((int)((a.M + 64 * RB - 1) / (64 * RB)), a.E / T);
+  project_bwd_bf16_kernel<0, RB, GA><<<(unsigned)grid, 256, SMEM_B, s>>>(a);
+  return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_project_bwd(const ProjBwdArgs& a, int is_f32, hipStream_t s) {
   const bool mfma_w = !is_f32 && mfma_common(a), mfma_x = mfma_w;
-  static SmemOnce once_x, once_xu, once_w, once_w2;
+  static SmemOnce once_w, once_w2;
   ProjBwdArgs rest = a;                              // what is left for the plain kernels
   if (mfma_x) rest.dx = nullptr;
   if (mfma_w) rest.dw = nullptr;
   if (mfma_w) {
     if (a.dx && mfma_x) {
-      const long grid = xcd_grid((int)((a.M + T - 1) / T), a.E / T);
-      if (a.D % BK == 0) {
-        const hipError_t e = ensure_dynamic_lds((const void*)project_bwd_bf16_kernel<0, 4, true>, SMEM_B, &once_x);
-        if (e != hipSuccess) return e;
-        project_bwd_bf16_kernel<0, 4, true><<<(unsigned)grid, 256, SMEM_B, s>>>(a);
-      } else {
-        const hipError_t e = ensure_dynamic_lds((const void*)project_bwd_bf16_kernel<0, 4, false>, SMEM_B, &once_xu);
-        if (e != hipSuccess) return e;
-        project_bwd_bf16_kernel<0, 4, false><<<(unsigned)grid, 256, SMEM_B, s>>>(a);
-      }
+      const bool low = (a.M + T - 1) / T * (a.E / T) * 4 <= (long)a.n_cu * 3;      // (as in the forward projection)
+      const hipError_t e = low ? (a.D % BK == 0 ? launch_dx<2, true>(a, s) : launch_dx<2, false>(a, s))
+                               : (a.D % BK == 0 ? launch_dx<4, true>(a, s) : launch_dx<4, false>(a, s));
+      if (e != hipSuccess) return e;
     }
     if (a.dw) {
       // Fewer 256 x 256 tiles than three quarters of the compute units: the token range is cut
@@ -552,6 +605,7 @@ hipError_t launch_project_bwd(const ProjBwdArgs& a, int is_f32, hipStream_t s) {
         long parts = a.n_cu / tiles;
         if (parts > 32) parts = 32;
         if (parts > pairs / 8) parts = pairs / 8;
+        if (parts >= DW_SUMS && parts * tiles > MAX_SUM_TILES) parts = MAX_SUM_TILES / tiles;
         if (parts >= 2) w.dw_parts = (int)parts;
       }
       if (tiles * 4 > (long)a.n_cu * 3 || w.dw_parts > 1) {
@@ -559,6 +613,8 @@ hipError_t launch_project_bwd(const ProjBwdArgs& a, int is_f32, hipStream_t s) {
         if (e != hipSuccess) return e;
         w.dw_tiles_grid = (unsigned)xcd_grid(a.N / T, a.E / T);
         project_bwd_bf16_kernel<1, 4><<<w.dw_tiles_grid * (unsigned)w.dw_parts, 256, SMEM_B, s>>>(w);
+        if (w.dw_parts >= DW_SUMS)
+          dw_add_sums_kernel<<<(unsigned)(tiles * (T * T / 1024)), 256, 0, s>>>(a.dw, a.E, a.N / T, a.E / T, w.dw_parts);
       } else {
         const hipError_t e = ensure_dynamic_lds((const void*)project_bwd_bf16_kernel<1, 2>, SMEM_B, &once_w2);
         if (e != hipSuccess) return e;
