@@ -1,0 +1,36 @@
+"""The projections' choices of tile height and of how dW's token parts meet, each at a small size, on
+sampled tokens and columns against the fp64 oracle (bounds: those of test_gpu_project).  256-token tiles
+need more than 192 of them (50000 tokens with one column tile, the last tile ragged); two and three parts
+per dW tile take turns, four and more go through memory."""
+import numpy as np
+import pytest
+
+from test_gpu_project import check, check_bwd, run, run_bwd
+
+pytestmark = pytest.mark.gpu
+
+
+def _sample(S, N, k=12):
+    rng = np.random.default_rng(S + N)
+    rows = np.stack([np.zeros(k, dtype=np.int64), np.sort(rng.choice(S, k, replace=False))], axis=1)
+    cols = np.sort(rng.choice(N, k, replace=False))
+    rows[0, 1], rows[-1, 1], cols[0], cols[-1] = 0, S - 1, 0, N - 1
+    return rows.astype(np.int32), cols.astype(np.int32)
+
+
+@pytest.mark.parametrize("E,H,D,n_out", [(256, 2, 128, 1), (256, 8, 96, 1)])
+def test_tall_token_tiles(E, H, D, n_out):
+    S = 50001
+    rows, cols = _sample(S, n_out * H * D)
+    x, w, outs = run(1, S, E, H, D, n_out, "bf16", seed=3)
+    check(x, w, outs, H, "bf16", "tall", rows=rows)
+    x, w, gs, dx, dw = run_bwd(1, S, E, H, D, n_out, "bf16", seed=3)
+    check_bwd(x, w, gs, dx, dw, H, "bf16", "tall", cols=cols, rows=rows)
+
+
+@pytest.mark.parametrize("S,E,H,D", [(1090, 1536, 32, 128), (1600, 1280, 16, 256), (2100, 1024, 16, 256), (2111, 256, 4, 64)],
+                         ids=["two_parts", "three_parts", "four_parts", "one_tile"])
+def test_parts_of_dw(S, E, H, D):
+    rows, cols = _sample(S, H * D)
+    x, w, gs, dx, dw = run_bwd(1, S, E, H, D, 1, "bf16", seed=8)
+    check_bwd(x, w, gs, dx, dw, H, "bf16", "parts", cols=cols, rows=rows)
