@@ -9,6 +9,8 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 
 __device__ __forceinline__ float bf16_lo(unsigned u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned u) { return __uint_as_float(u & 0xffff0000u); }
+// the larger, or the NaN (a part without a value must not look like one without keys)
+__device__ __forceinline__ float max_or_nan(float a, float b) { return b > a || b != b ? b : a; }
 __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
   typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
   bf16x2 r;
@@ -98,8 +100,8 @@ __global__ void __launch_bounds__(256) merge_kernel(MergeArgs a) {
     }
     float M = -INFINITY;
 #pragma unroll
-    for (int k = 0; k < LG; ++k) M = fmaxf(M, lk[k]);
-    for (int k = LG; k < n; ++k) M = fmaxf(M, a.lse_parts[k][row[u]]);
+    for (int k = 0; k < LG; ++k) M = max_or_nan(M, lk[k]);
+    for (int k = LG; k < n; ++k) M = max_or_nan(M, a.lse_parts[k][row[u]]);
     if (M == -INFINITY) continue;
     float z = 0.f;
 #pragma unroll
@@ -190,7 +192,7 @@ __global__ void __launch_bounds__(256) merge_row_kernel(MergeRowArgs a) {
   const float L = lane < a.n ? Lp : -INFINITY;
   float M = L;
 #pragma unroll
-  for (int w = 32; w >= 1; w >>= 1) M = fmaxf(M, __shfl_xor(M, w, 64));
+  for (int w = 32; w >= 1; w >>= 1) M = max_or_nan(M, __shfl_xor(M, w, 64));
   float z = M == -INFINITY ? 0.f : expf(L - M);
 #pragma unroll
   for (int w = 32; w >= 1; w >>= 1) z += __shfl_xor(z, w, 64);

@@ -40,7 +40,7 @@ __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
 // rounding and the constant's own lost (within 2 ulp like the library's, in half its instructions: a
 // launch whose waves pass through their code once is bound by fetching it)
 __device__ __forceinline__ float exp_neg(float x) {
-  x = fmaxf(x, -200.f);                            // (e^-200 is 0 in float32; keeps infinities out of l)
+  x = x < -200.f ? -200.f : x;                     // (e^-200 is 0 in float32; keeps infinities out of l, and a NaN a NaN)
   const float h = x * 1.44269504f;
   const float l = fmaf(x, 1.925963033e-8f, fmaf(x, 1.44269504f, -h));
   const float e = __builtin_amdgcn_exp2f(h);

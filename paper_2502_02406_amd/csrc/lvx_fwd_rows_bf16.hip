@@ -231,7 +231,7 @@ __global__ void __launch_bounds__(256) fwd_rows_bf16_kernel(FwdArgs a) {
 #pragma unroll
     for (int w = 0; w < NWV; ++w) {
       const float lw = st_l[w * 64 + r];
-      if (lw > 0.f) {                              // (a wave without a unit has nothing to add)
+      if (lw != 0.f) {                             // (a wave without a unit has nothing to add; a NaN has)
         const float e = __builtin_amdgcn_exp2f((st_m[w * 64 + r] - M) * c2);
         const f32x4 o = *(const f32x4*)(smem + w * SM::WAVE + r * 2 * SM::ROWB + ((c ^ (r & 31 & (2 * CH - 1))) * 16));
         l += e * lw;
@@ -240,7 +240,7 @@ __global__ void __launch_bounds__(256) fwd_rows_bf16_kernel(FwdArgs a) {
       }
     }
     const float inv = l > 0.f ? 1.f / l : 0.f;
-    const float lse = l > 0.f ? M * d.scale + logf(l) : -INFINITY;
+    const float lse = l != 0.f ? M * d.scale + logf(l) : -INFINITY;   // (NaN scores: NaN, which no combine drops)
 #pragma unroll
     for (int k = 0; k < 4; ++k) y[k] *= inv;
     const int hq = hk * G + r / d.Sq, i = r % d.Sq;
@@ -281,8 +281,8 @@ __global__ void __launch_bounds__(256) fwd_rows_bf16_kernel(FwdArgs a) {
       float M = -INFINITY, l = 0.f;
       for (int w = 0; w < NWV; ++w) M = fmaxf(M, st_m[w * 64 + r]);
       for (int w = 0; w < NWV; ++w)
-        if (st_l[w * 64 + r] > 0.f) l += __builtin_amdgcn_exp2f((st_m[w * 64 + r] - M) * c2) * st_l[w * 64 + r];
-      const float lse = l > 0.f ? M * d.scale + logf(l) : -INFINITY;
+        if (st_l[w * 64 + r] != 0.f) l += __builtin_amdgcn_exp2f((st_m[w * 64 + r] - M) * c2) * st_l[w * 64 + r];
+      const float lse = l != 0.f ? M * d.scale + logf(l) : -INFINITY;   // (NaN scores: NaN, which no combine drops)
       const long row = ((long)b * d.Hq + hk * G + r / d.Sq) * d.Sq + r % d.Sq;
       const float L0 = a.lse[row], Mx = fmaxf(L0, lse);
       a.lse[row] = Mx == -INFINITY ? -INFINITY : Mx + logf(expf(L0 - Mx) + expf(lse - Mx));
