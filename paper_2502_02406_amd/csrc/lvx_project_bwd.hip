@@ -115,7 +115,19 @@ project_bwd_bf16_kernel(ProjBwdArgs a) {
   HeadWork hw;
   // (dw: workgroups part * dw_tiles_grid + i, i = 0 .. dw_tiles_grid - 1, are part `part` of the token range)
   const unsigned wg = MODE == 1 ? blockIdx.x % a.dw_tiles_grid : blockIdx.x;
-  const int tpart = MODE == 1 ? (int)(blockIdx.x / a.dw_tiles_grid) : 0;
+  int tpart = MODE == 1 ? (int)(blockIdx.x / a.dw_tiles_grid) : 0;
+  if (MODE == 1 && a.dw_parts >= DW_SUMS) {
+    // Parts that do not wait for each other: every XCD takes a run of the list (part, tile), so that the
+    // tiles of a part, which read the same tokens, meet in its L2.  With a tile's parts on one XCD instead
+    // every tile fetched its panels of G and x for itself: 131072 tokens x 1024 columns x 512 features, 8
+    // tiles x 32 parts, forward + gradients 488 -> 463 us.
+    const int tiles = n_rt * n_ct, total = tiles * a.dw_parts, per = (total + 7) / 8;
+    const int x = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+    if (x >= total) return;                          // (the grid has 8 per workgroups)
+    tpart = x / tiles;
+    hw.head = x % tiles / n_ct;
+    hw.item = x % n_ct;
+  } else
   if (MODE == 1 && n_rt % 2 == 0 && n_ct % 4 == 0) {
     // dw streams a [tokens][TR] panel of G per row tile and a [tokens][256] panel of x per column
     // tile, and each XCD has an L2 of its own: the XCDs (workgroup number mod 8) are laid out 2 x 4
@@ -612,7 +624,9 @@ hipError_t launch_project_bwd(const ProjBwdArgs& a, int is_f32, hipStream_t s) {
         const hipError_t e = ensure_dynamic_lds((const void*)project_bwd_bf16_kernel<1, 4>, SMEM_B, &once_w);
         if (e != hipSuccess) return e;
         w.dw_tiles_grid = (unsigned)xcd_grid(a.N / T, a.E / T);
-        project_bwd_bf16_kernel<1, 4><<<w.dw_tiles_grid * (unsigned)w.dw_parts, 256, SMEM_B, s>>>(w);
+        const unsigned grid = w.dw_parts >= DW_SUMS ? (unsigned)((tiles * w.dw_parts + 7) / 8 * 8)
+                                                    : w.dw_tiles_grid * (unsigned)w.dw_parts;
+        project_bwd_bf16_kernel<1, 4><<<grid, 256, SMEM_B, s>>>(w);
         if (w.dw_parts >= DW_SUMS)
           dw_add_sums_kernel<<<(unsigned)(tiles * (T * T / 1024)), 256, 0, s>>>(a.dw, a.E, a.N / T, a.E / T, w.dw_parts);
       } else {
