@@ -521,11 +521,9 @@ __global__ void __launch_bounds__(256) dw_add_sums_kernel(float* dw, int E, int 
 #pragma unroll
     for (int u = 0; u < 8; ++u) v[u] = *(const f32x4*)(src + min(p + u, parts - 1) * step);
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const float on = p + u < parts ? 1.f : 0.f;
+    for (int u = 0; u < 8; ++u)                      // (a select: the last part read again may hold an infinity)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) sum[e] = fmaf(on, v[u][e], sum[e]);
-    }
+      for (int e = 0; e < 4; ++e) sum[e] = p + u < parts ? sum[e] + v[u][e] : sum[e];
   }
   *(f32x4*)dst = sum;
 }

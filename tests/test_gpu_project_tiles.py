@@ -4,7 +4,9 @@ need more than 192 of them (50000 tokens with one column tile, the last tile rag
 per dW tile take turns, four and more go through memory."""
 import numpy as np
 import pytest
+import torch
 
+from paper_2502_02406_amd import workloads as W
 from test_gpu_project import check, check_bwd, run, run_bwd
 
 pytestmark = pytest.mark.gpu
@@ -34,3 +36,20 @@ def test_parts_of_dw(S, E, H, D):
     rows, cols = _sample(S, H * D)
     x, w, gs, dx, dw = run_bwd(1, S, E, H, D, 1, "bf16", seed=8)
     check_bwd(x, w, gs, dx, dw, H, "bf16", "parts", cols=cols, rows=rows)
+
+
+def test_infinity_in_the_last_part_of_dw():
+    # An infinite gradient of the last token, which the last of five parts sums: the row of dW it reaches is
+    # infinite with x's signs, not NaN, and every other row is finite.
+    from paper_2502_02406_amd import binding as Bn
+    S, E, H, D = 2600, 256, 2, 128
+    inp = W.projection_inputs(1, S, E, H * D, "bf16", seed=4)
+    g = W.projection_grad_inputs(1, S, H, D, 1, "bf16", seed=4)[0]
+    x = inp["x"]
+    x[0, -1] = torch.where(x[0, -1] < 0, -1.0, 1.0).to(x.dtype)
+    g[0, 1, -1, 5] = float("inf")
+    dw = torch.zeros((H * D, E), dtype=torch.float32, device="cuda")
+    Bn.lvx_xattn_project_bwd(x.cuda(), inp["w"].cuda(), [g.cuda()], dw=dw)
+    row = D + 5
+    assert torch.equal(dw[row].cpu(), x[0, -1].float() * float("inf"))
+    assert torch.isfinite(dw[:row]).all() and torch.isfinite(dw[row + 1:]).all()
