@@ -313,7 +313,10 @@ __device__ void bwd_dq_f32(const BwdArgs& a, int tile, int hk, int b, char* smem
     }
     float ds[16];
 #pragma unroll
-    for (int x = 0; x < 16; ++x) ds[x] = exp_neg(fmaf(s[x], d.scale, nl)) * (dp[x] - delta);
+    for (int x = 0; x < 16; ++x) {                 // (a pair that does not count adds 0, whatever its dP)
+      const float t = fmaf(s[x], d.scale, nl);
+      ds[x] = t == -INFINITY ? 0.f : exp_neg(t) * (dp[x] - delta);
+    }
     contract<D>(acc, kt, ds, ql, g);
   }
   put_block<D>(kt, acc, ql, g);

@@ -24,3 +24,20 @@ def test_nan_key(dtype, Sq, Skv, n_blocks):
         o = loop.forward(q, bad, v)[0]
         assert torch.isnan(o[:, 2:]).all(), f"key {j}: a row of the second K/V head has a value"
         assert torch.equal(o[:, :2], clean[:, :2]), f"key {j}: the first K/V head changed"
+
+
+def test_infinite_gradient_of_a_row_without_keys():
+    # float32: pairs that a mask leaves out add 0 to dQ whatever their dO says
+    from paper_2502_02406_amd.blockloop import BlockLoop, MediaMask
+    g = torch.Generator().manual_seed(6)
+    q, do = (torch.randn((1, 2, 40, 64), generator=g).cuda() for _ in range(2))
+    k, v = (torch.randn((1, 1, 100, 64), generator=g).cuda() for _ in range(2))
+    allow = torch.ones((5, 4), dtype=torch.uint8)
+    allow[2] = 0                                   # rows 16 .. 23 see no key
+    loop = BlockLoop(tuple(q.shape), tuple(k.shape), torch.float32, 1, MediaMask(allow.cuda(), 8, 25))
+    o, lse = loop.forward(q, k, v)
+    dk, dv = torch.empty_like(k), torch.empty_like(v)
+    clean = loop.backward(q, k, v, o, lse, do, dk, dv).clone()
+    do[0, 1, 20] = float("inf")
+    assert torch.equal(loop.backward(q, k, v, o, lse, do, dk, dv), clean)
+    assert not clean[0, 1, 16:24].any()
