@@ -61,7 +61,7 @@ project_bf16_kernel(ProjArgs a) {
   constexpr int NPART = XC + 8;
   const int n_mt = (int)((a.M + TM - 1) / TM), n_nt = a.N / TN;
   HeadWork hw;                                       // the column tiles of a token tile share an XCD (and its L2)
-  if (!xcd_decode(blockIdx.x, n_mt, n_nt, &hw)) return;
+  if (!tile_decode(blockIdx.x, n_mt, n_nt, &hw)) return;
   const long m0 = (long)hw.head * TM;
   const int n0 = hw.item * TN;
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, l31 = lane & 31;
@@ -243,7 +243,7 @@ template <int IB> hipError_t launch_tiles(const ProjArgs& a, hipStream_t s) {
   static SmemOnce once;
   const hipError_t e = ensure_dynamic_lds((const void*)project_bf16_kernel<IB>, SMEM_B, &once);
   if (e != hipSuccess) return e;
-  const long grid = xcd_grid((int)((a.M + 64 * IB - 1) / (64 * IB)), a.N / TN);
+  const long grid = tile_grid((int)((a.M + 64 * IB - 1) / (64 * IB)), a.N / TN);
   project_bf16_kernel<IB><<<(unsigned)grid, 256, SMEM_B, s>>>(a);
   return hipGetLastError();
 }

@@ -137,7 +137,7 @@ project_bwd_bf16_kernel(ProjBwdArgs a) {
     hw.head = (xcd / 4) * (n_rt / 2) + slot / pc;
     hw.item = (xcd % 4) * pc + slot % pc;
     if (hw.head >= ((xcd / 4) + 1) * (n_rt / 2)) return;
-  } else if (!xcd_decode(wg, n_rt, n_ct, &hw)) {   // the column tiles of a row tile share an XCD
+  } else if (MODE == 0 ? !tile_decode(wg, n_rt, n_ct, &hw) : !xcd_decode(wg, n_rt, n_ct, &hw)) {   // the column tiles of a row tile share an XCD
     return;
   }
   const long r0 = (long)hw.head * TR;                // first token (MODE 0) / first column n (MODE 1)
@@ -584,7 +584,7 @@ template <int RB, bool GA> hipError_t launch_dx(const ProjBwdArgs& a, hipStream_
   static SmemOnce once;
   const hipError_t e = ensure_dynamic_lds((const void*)project_bwd_bf16_kernel<0, RB, GA>, SMEM_B, &once);
   if (e != hipSuccess) return e;
-  const long grid = xcd_grid((int)((a.M + 64 * RB - 1) / (64 * RB)), a.E / T);
+  const long grid = tile_grid((int)((a.M + 64 * RB - 1) / (64 * RB)), a.E / T);
   project_bwd_bf16_kernel<0, RB, GA><<<(unsigned)grid, 256, SMEM_B, s>>>(a);
   return hipGetLastError();
 }

@@ -53,3 +53,13 @@ def test_infinity_in_the_last_part_of_dw():
     row = D + 5
     assert torch.equal(dw[row].cpu(), x[0, -1].float() * float("inf"))
     assert torch.isfinite(dw[:row]).all() and torch.isfinite(dw[row + 1:]).all()
+
+
+@pytest.mark.parametrize("S,E,H", [(17958, 256, 8), (18100, 512, 4), (300, 256, 2), (1100, 768, 2)])
+def test_odd_numbers_of_token_tiles(S, E, H):
+    # 71 token tiles of 256 (the last one ragged), 141, 3 and 9 of 128: not a multiple of the XCDs, nor the tiles
+    rows, cols = _sample(S, 2 * H * 128)
+    x, w, outs = run(1, S, E, H, 128, 2, "bf16", seed=S)
+    check(x, w, outs, H, "bf16", "odd", rows=rows)
+    x, w, gs, dx, dw = run_bwd(1, S, E, H, 128, 2, "bf16", seed=S)
+    check_bwd(x, w, gs, dx, dw, H, "bf16", "odd", cols=cols, rows=rows)
