@@ -326,8 +326,8 @@ __device__ __forceinline__ bool xcd_decode(long pid, int n_heads, int items_per_
 // instead, so that no XCD has more than one tile beyond another and the column tiles of a row tile still meet in
 // one L2 (but for a row tile that two runs share).  An odd number of row tiles with 4 column tiles left four
 // XCDs idle: projection of 17958 tokens x 512 features x 1024 columns 63 -> 36 us, its dx 86 -> 35; 60001 x
-// 1024 x 1024 263 -> 125 and 237 -> 126 us.  Even parts stay as they are: there row tiles go round the XCDs, and
-// the chip walks through the tokens in one front (dx of 131072 x 1024 x 512: 155 us, in runs 173).
+// 1024 x 1024 263 -> 125 and 237 -> 126 us.  Even parts stay as they are: there runs gain nothing (131072 x 512 x
+// 1024: forward 201 us, in runs 207; dx 168 and 174).
 __host__ __device__ inline bool tile_runs(int n_rt, int n_ct) { return n_ct % xcd_parts(n_rt) != 0; }
 __host__ __device__ inline long tile_grid(int n_rt, int n_ct) {
   return tile_runs(n_rt, n_ct) ? ((long)n_rt * n_ct + 7) / 8 * 8 : xcd_grid(n_rt, n_ct);
