@@ -63,8 +63,9 @@ __device__ unsigned long long dq_probe[8];
 // between two phases, in ordinary registers that no matrix instruction writes -- meets the lane's key
 // bits, a mask of two elements at a time, in a branch of about 80 instructions per half; halves
 // that every row sees skip it.  2048 rows in chunks of 64 x 28 heads against 32 frames of 729 keys,
-// causal, D = 128: 1.34 -> 0.50 ms (1060 TFLOP/s of visible pairs; the general kernel below before); 4096
-// rows x 8 heads in chunks of 2, each seeing one of 2048 frames of 64 keys, D = 64: 1.09 -> 0.16 ms.
+// causal, D = 128: 1.34 -> 0.51 ms (1035 TFLOP/s of visible pairs; the general kernel below before; 13 us of
+// it go to the scores' scale, which is not folded into Q here); 4096 rows x 8 heads in chunks of 2, each
+// seeing one of 2048 frames of 64 keys, D = 64: 1.09 -> 0.165 ms.
 template <int D, bool GENERAL, int LIST = 0>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 bwd_dq_bf16_kernel(BwdArgs a) {
@@ -117,11 +118,14 @@ bwd_dq_bf16_kernel(BwdArgs a) {
   int t_end = min(n_tiles, t_begin + tps);
 
   // ---- stationary operands and statistics of this lane's query rows i_wave0 + 32 qb + ql
-  // The dense variant folds the statistics into the matrix products (FOLD): Q is held as
-  // bf16(Q * scale * log2 e) and the accumulations start from 16 copies of -L log2 e and of -delta
-  // (a lane's registers all belong to one query row), so that S^T comes out as the exponent of P
-  // and dP^T as dP - delta without a vector instruction.
-  constexpr bool FOLD = !GENERAL;
+  // The dense variant folds the statistics into the matrix products: Q is held as
+  // bf16(Q * scale * log2 e) and the accumulations start from 16 copies of -L log2 e (FOLD) and of
+  // -delta (FOLD_D; a lane's registers all belong to one query row), so that S^T comes out as the exponent
+  // of P and dP^T as dP - delta without a vector instruction.
+  // Rounding the scaled Q to bf16 costs precision where scores are large (it moves a score by up to 2^-9
+  // of sum |q k|), so the kernel does it where every key is seen whole, and nowhere else: masks by words
+  // (LIST = 3) and the last tile of a ragged key count take Q as given and scale the float32 score.
+  constexpr bool FOLD = !GENERAL && LIST != 3, FOLD_D = !GENERAL;
   const float c2 = d.scale * LOG2E;
   bf16x8 qf[QB][KS], gf[QB][KS];
   float nl2[QB], nd[QB];               // -L log2(e) (-inf: no probability mass) and -delta
@@ -164,15 +168,50 @@ bwd_dq_bf16_kernel(BwdArgs a) {
     }
     asm volatile("" : "+v"(nl2[qb]), "+v"(nd[qb]));
   }
-  f32x16 nl2x[FOLD ? QB : 1], ndx[FOLD ? QB : 1];  // the starting values of the accumulations
-  if (FOLD) {
+  f32x16 nl2x[FOLD ? QB : 1], ndx[FOLD_D ? QB : 1];   // the starting values of the accumulations
+  if constexpr (FOLD) {
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) { nl2x[qb][v] = nl2[qb]; ndx[qb][v] = nd[qb]; }
-      asm volatile("" : "+v"(nl2x[qb]), "+v"(ndx[qb]));
+      for (int v = 0; v < 16; ++v) nl2x[qb][v] = nl2[qb];
+      asm volatile("" : "+v"(nl2x[qb]));
     }
   }
+  if constexpr (FOLD_D) {
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) ndx[qb][v] = nd[qb];
+      asm volatile("" : "+v"(ndx[qb]));
+    }
+  }
+  // Ragged key count: Q as given for the last tile, and its scores in units before the scale.
+  auto unfold_q = [&]() __attribute__((always_inline)) {
+    if constexpr (FOLD) {
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {
+        int r = i_wave0 + 32 * qb + (int)(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) & 31u);
+        asm volatile("" : "+v"(r));                // (worked out anew: nothing of it stays in a register through the loop)
+        const int rc = min(r, rows_lim - 1);
+        const int hq_l = PACK ? hq + rc / d.Sq : hq, i = PACK ? rc % d.Sq : rc;
+        const uint16_t* const q = (const uint16_t*)a.q + b * d.q_sb + hq_l * d.q_sh + (long)i * d.q_ss;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const u32x4 x = *(const u32x4*)(q + 16 * ks + 8 * g), zero4 = {0, 0, 0, 0};
+          qf[qb][ks] = __builtin_bit_cast(bf16x8, r < rows_lim ? x : zero4);
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) nl2x[qb][v] *= 1.f / c2;
+      }
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {            // (in place, and settled, before a matrix instruction reads them)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(qf[qb][ks]));
+        asm volatile("s_nop 7" : "+v"(nl2x[qb]));
+      }
+    }
+  };
 
   // ---- tiles this workgroup needs (media mask: tiles visible to none of its rows are skipped).
   // The window of the bitmap that its rows and key range can touch is copied to LDS, and the
@@ -433,7 +472,7 @@ bwd_dq_bf16_kernel(BwdArgs a) {
           else if (ks == 0) mfma_first(s[qb], ka[cu], qf[qb][ks]);
           else mfma_next(s[qb], ka[cu], qf[qb][ks]);
         } else {
-          if (ks == 0 && FOLD) mfma_from(p[qb], va[cu], gf[qb][ks], ndx[qb]);
+          if (ks == 0 && FOLD_D) mfma_from(p[qb], va[cu], gf[qb][ks], ndx[qb]);
           else if (ks == 0) mfma_first(p[qb], va[cu], gf[qb][ks]);
           else mfma_next(p[qb], va[cu], gf[qb][ks]);
         }
@@ -467,7 +506,8 @@ bwd_dq_bf16_kernel(BwdArgs a) {
       }
     }
   };
-  // dense, ragged key count: the exponents of keys that the tile before the last has seen -> -inf
+  // dense, ragged key count: the last tile's scores -> exponents (its Q is not folded, see unfold_q), those of
+  // keys that the tile before has seen -> -inf
   const int t_ragged = !GENERAL && LIST == 0 && d.Skv % TN != 0 ? n_tiles - 1 : -1, low0 = n_tiles * TN - d.Skv;
   auto mask_ragged = [&](f32x16 (&s)[QB], int t, int hb) __attribute__((always_inline)) {
     if (!GENERAL && LIST == 0 && t == t_ragged) {
@@ -476,7 +516,7 @@ bwd_dq_bf16_kernel(BwdArgs a) {
       for (int v = 0; v < 16; ++v) {
         const bool out = 32 * hb + 8 * (v / 4) + 4 * g + (v % 4) < low0;
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) s[qb][v] = out ? -INFINITY : s[qb][v];
+        for (int qb = 0; qb < QB; ++qb) s[qb][v] = out ? -INFINITY : s[qb][v] * c2;
       }
     }
   };
@@ -509,8 +549,8 @@ bwd_dq_bf16_kernel(BwdArgs a) {
     }
   };
   // Conversion of scores into the dS operands, element x of a half (x = 0..31: query block
-  // qb = x / 16, register v = x % 16): p = exp2(s c2 - L2), dS = p (dP - delta) -- with FOLD both
-  // differences were formed by the accumulation already -- packed in pairs as bf16 into word
+  // qb = x / 16, register v = x % 16): p = exp2(s c2 - L2), dS = p (dP - delta) -- with FOLD and
+  // FOLD_D the differences were formed by the accumulation already -- packed in pairs as bf16 into word
   // (v % 8) / 2 of operand v / 8 of the query block.
   // An element is started (its exp2) in one place and finished (multiply, packing) in the next, so
   // that between the matrix instructions of the pipelined loop the exponential's result is never
@@ -523,7 +563,7 @@ bwd_dq_bf16_kernel(BwdArgs a) {
   };
   auto conv_finish = [&](int x, Carry& cy, const f32x16 (&p)[QB], u32x4 (&dsw)[QB][2]) __attribute__((always_inline)) {
     const int qb = x / 16, v = x % 16;
-    const float ds = cy.ex * (FOLD ? p[qb][v] : p[qb][v] + nd[qb]);
+    const float ds = cy.ex * (FOLD_D ? p[qb][v] : p[qb][v] + nd[qb]);
     if (v % 2 == 0) { cy.ds = ds; return; }
     const unsigned w2 = pack2_bf16(cy.ds, ds);
     dsw[qb][v / 8][(v % 8) / 2] = (LIST != 2 || ((vcur >> qb) & 1)) ? w2 : 0u;
@@ -642,6 +682,7 @@ bwd_dq_bf16_kernel(BwdArgs a) {
   if (nt > 0) {
     vcur = vis_at(0);
     if constexpr (LIST == 3) vt = tile_vis(e[0], 0);
+    if (!GENERAL && LIST == 0 && t_begin == t_ragged) unfold_q();
     score(smem, 0, s0, p0, nothing, first_kv(smem, 0), no_tail);
     mask_scores(e[0], 0, s0);
     settle_scores(s0);
@@ -708,6 +749,7 @@ bwd_dq_bf16_kernel(BwdArgs a) {
     convert(s1, p1, ds1);
     if constexpr (LIST == 3) mask_words(ds1, 1, vt);
     if (more) vcur = vis_at(T + 1);
+    if (!GENERAL && LIST == 0 && more && t_begin + T + 1 == t_ragged) unfold_q();
     if (more) { score(stage(T + 1), 0, s0, p0, nothing, first_kv(stage(T + 1), 0), no_tail); mask_scores(e[1], 0, s0); }
     contract(stage(T), 1, ds1);
     if (more) {
@@ -815,11 +857,17 @@ hipError_t launch(const BwdArgs& a, long grid, hipStream_t s) {
 
 }  // namespace
 
+// Key counts that the dense kernel takes without a mask: whole tiles, or so many that the ones it takes with a
+// folded Q (all but a ragged last one) are whole tiles in the general kernel's place as well.  Up to
+// 127 ragged keys the general kernel reads Q as given throughout: dQ of 512 rows against 100 keys with 1 %
+// outliers is off by 2.7e-3, with a folded Q by 3.9e-3; both take a launch's time.
+static bool dq_dense_keys(const Dims& d) { return d.Skv % TN == 0 || d.Skv >= 2 * TN; }
+
 int bwd_bf16_pick_split(const Dims& d, int n_cu, bool masked) {
   // one workgroup per CU; split the KV axis until the grid covers the chip (four times as many
   // workgroups with a media mask, whose visible work differs from one query tile to the next)
   // (the dense kernel tiles the rows of a whole group of query heads, the general one each head's)
-  const bool dense = !masked && d.Skv >= TN;
+  const bool dense = !masked && dq_dense_keys(d);
   const long base = dense ? (long)d.B * d.Hkv * (((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM)
                           : (long)d.B * d.Hq * ((d.Sq + QM - 1) / QM);
   const int n_tiles = (d.Skv + TN - 1) / TN;
@@ -898,7 +946,7 @@ hipError_t launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s) {
     const hipError_t e = launch_one(p1, false, s);
     return e != hipSuccess ? e : launch_one(p2, true, s);
   }
-  return launch_one(a, d.Skv < TN, s);
+  return launch_one(a, !dq_dense_keys(d), s);
 }
 
 // the masks that the forward takes by words too: see launch_bwd_dq_bf16 for the order of choice
