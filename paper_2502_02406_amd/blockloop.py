@@ -30,6 +30,13 @@ class MediaMask:
     kv_block: int
 
 
+def _covers(t: torch.Tensor, like: torch.Tensor) -> bool:
+    """t has an element wherever `like` has one (addressed with like's strides and element size)."""
+    return t.shape == like.shape and t.dtype == like.dtype or (
+        t.dim() == like.dim() and t.element_size() == like.element_size()
+        and all(a >= b for a, b in zip(t.shape, like.shape)))
+
+
 class BlockLoop:
     def __init__(self, q_shape, kv_shape, dtype: torch.dtype, n_blocks: int = 1,
                  mask: Optional[MediaMask] = None, softmax_scale: float = 0.0,
@@ -79,31 +86,40 @@ class BlockLoop:
         nkb = (self.blk + self.mask.kv_block - 1) // self.mask.kv_block
         return B.make_mask(self.mask.allow, self.mask.q_chunk, self.mask.kv_block, n * per, nkb)
 
-    def _blocks(self, q, k):
-        """The problem of every block (they differ in where their keys start only) and the bytes from one
-        block's keys to the next's."""
+    def _blocks(self, q, k, like_k, like_q=()):
+        """The problem that the blocks share (they differ in where their keys start and, the last one, in how
+        many they are: _keys_of) and the bytes from one block's keys to the next's.  The library gets
+        addresses: what it is told to read or write has to be there."""
         if not q.is_cuda:
             raise RuntimeError("BlockLoop needs device tensors")
-        p = B.make_problem(q, k, self.scale)
-        if self.n_blocks > 1:
-            p.Skv = self.blk
-        return p, self.blk * k.stride(2) * k.element_size()
+        if not all(_covers(t, k) for t in like_k) or not all(_covers(t, q) for t in like_q):
+            raise ValueError("V, dK and dV have to be as large as K; O and dO as large as Q")
+        rows = q.shape[0] * q.shape[1] * q.shape[2]
+        if rows > self.lse.numel() or 1 + sum((n - 1) * s for n, s in zip(q.shape, q.stride())) > self.o.numel():
+            raise ValueError("Q is larger than this loop's results")
+        return B.make_problem(q, k, self.scale), self.blk * k.stride(2) * k.element_size()
+
+    def _keys_of(self, n: int, k) -> int:
+        """Keys of block n: as many as K has left (a K shorter than the loop was made for ends earlier)."""
+        return max(0, min(self.blk, k.shape[2] - n * self.blk))
 
     def forward(self, q, k, v) -> Tuple[torch.Tensor, torch.Tensor]:
         """Returns (O in the input dtype, L float32); both are buffers owned by this object."""
         # (the running O of the block loop is written with Q's strides by the first visit and read as
         # a contiguous tensor by the others)
         assert self.n_blocks == 1 or q.is_contiguous(), "the block loop needs a contiguous Q"
-        p, step = self._blocks(q, k)
+        p, step = self._blocks(q, k, (v,))
         call = B.Calls(p, q.dtype, self.ws)
         qp, kp, vp, lp = q.data_ptr(), k.data_ptr(), v.data_ptr(), self.lse.data_ptr()
         if self.n_blocks == 1:
             call.fwd(qp, kp, vp, self._mask_for(0), self.o.data_ptr(), self.o.dtype, lp)
             return self.o, self.lse
         op = self.o_acc.data_ptr()
+        p.Skv = self._keys_of(0, k)
         # merging with the identity (0, -inf) is a no-op: the first visit writes the state directly
         call.fwd(qp, kp, vp, self._mask_for(0), op, torch.float32, lp)
         for n in range(1, self.n_blocks):       # the FlashAttention call and Rescale of Algorithm 1 in one call
+            p.Skv = self._keys_of(n, k)
             call.fwd_merge(qp, kp + n * step, vp + n * step, self._mask_for(n), op, lp)
         if self.o_acc is not self.o:
             B.lvx_xattn_merge([self.o_acc], [self.lse], self.o, self.lse)    # round to the output dtype
@@ -113,8 +129,10 @@ class BlockLoop:
         """dk/dv (same shape and strides as k) are overwritten; returns dQ in the input dtype."""
         assert dk.stride() == k.stride() and dv.stride() == k.stride() and v.stride() == k.stride()
         assert o.stride() == q.stride() and d_o.stride() == q.stride()
+        p, step = self._blocks(q, k, (v, dk, dv), (o, d_o))
+        if lse.numel() < q.shape[0] * q.shape[1] * q.shape[2]:
+            raise ValueError("L has to have a value for every row of Q")
         self.dq_accum.zero_()
-        p, step = self._blocks(q, k)
         call = B.Calls(p, q.dtype, self.ws)
         qp, kp, vp, dkp, dvp = q.data_ptr(), k.data_ptr(), v.data_ptr(), dk.data_ptr(), dv.data_ptr()
         op, lp, gp, ap = o.data_ptr(), lse.data_ptr(), d_o.data_ptr(), self.dq_accum.data_ptr()
@@ -122,6 +140,7 @@ class BlockLoop:
             # delta = rowsum(dO * O) depends on the query block only: the first visit computes it
             # into the workspace, the others reuse it
             stages = (B.LVX_BWD_ALL if n == 0 else (B.LVX_BWD_DKDV | B.LVX_BWD_DQ)) | self.bwd_flags
+            p.Skv = self._keys_of(n, k)
             call.bwd(qp, kp + n * step, vp + n * step, op, lp, gp, self._mask_for(n), ap, dkp + n * step, dvp + n * step, stages)
         if self.dq is not self.dq_accum:
             B.lvx_xattn_dq_finalize(p, self.dq_accum, self.dq)
