@@ -37,6 +37,11 @@ def _covers(t: torch.Tensor, like: torch.Tensor) -> bool:
         and all(a >= b for a, b in zip(t.shape, like.shape)))
 
 
+def _same_strides(t: torch.Tensor, like: torch.Tensor) -> bool:
+    """Equal where they address anything: the stride of a single batch or head does not."""
+    return all(a == b for n, a, b in zip(like.shape, t.stride(), like.stride()) if n > 1)
+
+
 class BlockLoop:
     def __init__(self, q_shape, kv_shape, dtype: torch.dtype, n_blocks: int = 1,
                  mask: Optional[MediaMask] = None, softmax_scale: float = 0.0,
@@ -127,7 +132,7 @@ class BlockLoop:
 
     def backward(self, q, k, v, o, lse, d_o, dk, dv) -> torch.Tensor:
         """dk/dv (same shape and strides as k) are overwritten; returns dQ in the input dtype."""
-        assert dk.stride() == k.stride() and dv.stride() == k.stride() and v.stride() == k.stride()
+        assert dk.stride() == k.stride() and dv.stride() == k.stride() and _same_strides(v, k)
         assert o.stride() == q.stride() and d_o.stride() == q.stride()
         p, step = self._blocks(q, k, (v, dk, dv), (o, d_o))
         if lse.numel() < q.shape[0] * q.shape[1] * q.shape[2]:

@@ -92,3 +92,14 @@ def test_tensors_that_the_kernels_would_leave_are_refused(lib, short, n_blocks):
     with pytest.raises(ValueError):
         loop.backward(*(t[n] for n in ("q", "k", "v", "o", "lse", "do", "dk", "dv")))
     assert not lib.calls
+
+
+def test_stride_of_a_single_batch_means_nothing(lib):
+    # V as two of the five heads of a longer buffer: only its batch stride differs from K's
+    q, k, v, o, lse, do, dk, dv = tensors(2048)
+    v = Dev(torch.zeros((1, 5, 2048, 64), dtype=torch.bfloat16)[:, 1:3])
+    assert v.stride()[1:] == k.stride()[1:] and v.stride(0) != k.stride(0)
+    make().backward(q, k, v, o, lse, do, dk, dv)
+    assert len(lib.calls) == 2
+    with pytest.raises(AssertionError):          # (a head stride does mean something)
+        make().backward(q, k, Dev(torch.zeros((1, 2, 2049, 64), dtype=torch.bfloat16)[:, :, :2048]), o, lse, do, dk, dv)
