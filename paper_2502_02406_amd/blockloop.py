@@ -42,6 +42,12 @@ def _same_strides(t: torch.Tensor, like: torch.Tensor) -> bool:
     return all(a == b for n, a, b in zip(like.shape, t.stride(), like.stride()) if n > 1)
 
 
+def _apart(buf: torch.Tensor, *ts):
+    """The tensors, as copies where they lie in `buf`: a result handed out that comes back as an input."""
+    first, last = buf.data_ptr(), buf.data_ptr() + buf.numel() * buf.element_size()
+    return tuple(t.new_empty_strided(t.size(), t.stride()).copy_(t.detach()) if first <= t.data_ptr() < last else t for t in ts)
+
+
 class BlockLoop:
     def __init__(self, q_shape, kv_shape, dtype: torch.dtype, n_blocks: int = 1,
                  mask: Optional[MediaMask] = None, softmax_scale: float = 0.0,
@@ -63,7 +69,8 @@ class BlockLoop:
         self.lse = torch.empty(rows, **f32)
         self.o = torch.empty(q_shape, dtype=dtype, device=device)
         # Running O_j of Algorithm 1 (L_j lives in self.lse) and the dQ sums.  Both are float32: a float32
-        # problem's are its results already, with nothing left to round.
+        # problem's are its results already, with nothing left to round (they are written while the inputs
+        # are still read, which _apart sees to where an input is an earlier result).
         self.dq_accum = torch.empty(q_shape, **f32)
         if dtype == torch.float32:
             self.o_acc, self.dq = self.o, self.dq_accum
@@ -114,6 +121,8 @@ class BlockLoop:
         # a contiguous tensor by the others)
         assert self.n_blocks == 1 or q.is_contiguous(), "the block loop needs a contiguous Q"
         p, step = self._blocks(q, k, (v,))
+        if self.n_blocks > 1 and self.o_acc is self.o:
+            q, k, v = _apart(self.o, q, k, v)
         call = B.Calls(p, q.dtype, self.ws)
         qp, kp, vp, lp = q.data_ptr(), k.data_ptr(), v.data_ptr(), self.lse.data_ptr()
         if self.n_blocks == 1:
@@ -137,6 +146,8 @@ class BlockLoop:
         p, step = self._blocks(q, k, (v, dk, dv), (o, d_o))
         if lse.numel() < q.shape[0] * q.shape[1] * q.shape[2]:
             raise ValueError("L has to have a value for every row of Q")
+        if self.dq is self.dq_accum:
+            q, k, v, o, lse, d_o = _apart(self.dq, q, k, v, o, lse, d_o)
         self.dq_accum.zero_()
         call = B.Calls(p, q.dtype, self.ws)
         qp, kp, vp, dkp, dvp = q.data_ptr(), k.data_ptr(), v.data_ptr(), dk.data_ptr(), dv.data_ptr()

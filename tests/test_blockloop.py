@@ -103,3 +103,39 @@ def test_stride_of_a_single_batch_means_nothing(lib):
     assert len(lib.calls) == 2
     with pytest.raises(AssertionError):          # (a head stride does mean something)
         make().backward(q, k, Dev(torch.zeros((1, 2, 2049, 64), dtype=torch.bfloat16)[:, :, :2048]), o, lse, do, dk, dv)
+
+
+def test_float32_results_as_the_next_call_s_inputs(lib):
+    # float32 results are the running state itself, which the first visit writes while the others still
+    # read their inputs: what the library reads lies elsewhere
+    f32 = torch.float32
+    loop = make(f32)
+    loop.o, loop.dq_accum = Dev(loop.o), Dev(loop.dq_accum)
+    loop.o_acc, loop.dq = loop.o, loop.dq_accum
+    q, k, v, o, lse, do, dk, dv = tensors(2048, f32)
+    inside = lambda x, t: 0 <= x - t.data_ptr() < t.numel() * 4
+    loop.forward(loop.forward(q, k, v)[0], k, v)
+    reads = [a for c in lib.calls if "fwd" in c[0] for a in c[3][1:4]]
+    assert len(reads) == 12 and not any(inside(a, loop.o) for a in reads)
+    lib.calls.clear()
+    loop.backward(q, k, v, o, lse, loop.backward(q, k, v, o, lse, do, dk, dv), dk, dv)
+    reads = [a for c in lib.calls for a in c[3][1:7]]
+    assert len(reads) == 24 and not any(inside(a, loop.dq_accum) for a in reads)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_results_as_inputs(dtype):
+    # a result handed on as the next call's Q or dO is read whole, whatever the call writes first
+    g = torch.Generator().manual_seed(4)
+    q, do = (torch.randn((1, 4, 64, 64), generator=g).to(dtype).cuda() for _ in range(2))
+    k, v = (torch.randn((1, 2, 256, 64), generator=g).to(dtype).cuda() for _ in range(2))
+    a, b = (BlockLoop(tuple(q.shape), tuple(k.shape), dtype, 2) for _ in range(2))
+    dk, dv = torch.empty_like(k), torch.empty_like(v)
+    o, _ = a.forward(q, k, v)
+    want = b.forward(o.clone(), k, v)[0].clone()
+    assert torch.equal(a.forward(o, k, v)[0], want)
+    o, lse = (t.clone() for t in b.forward(q, k, v))
+    dq = a.backward(q, k, v, o, lse, do, dk, dv)
+    want = [t.clone() for t in (b.backward(q, k, v, o, lse, dq.clone(), dk, dv), dk, dv)]
+    assert all(torch.equal(x, y) for x, y in zip((a.backward(q, k, v, o, lse, dq, dk, dv), dk, dv), want))
