@@ -452,13 +452,16 @@ fwd_bf16_kernel(FwdArgs a) {
     if (__builtin_expect(__any(need), 0)) {
       asm volatile("" ::: "memory");               // keep this a real, rarely taken branch
       drain_oacc();
+      // (LIST = 3: a score that its row does not see may be what sent the wave here, NaN or +infinity, which no
+      // reference turns into 0; it is -infinity from here on)
+      if constexpr (LIST == 3) mask_words(s, hb, vis);
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
         if (LIST == 2 && !((vb >> qb) & 1)) continue;          // (scores the rows do not see raise nothing)
         float r_new = fmaxf(r[qb], row_max(s[qb]));
         float alpha = __builtin_amdgcn_exp2f(r[qb] - r_new);
         if constexpr (LIST == 3) {
-          // (scores the row does not see raise nothing; a row that has added up nothing yet takes its
+          // (a row that does not see the half keeps its reference; one that has added up nothing yet takes its
           // first visible half's maximum, be it lower than what it started from)
           const bool seen = (half_word(vis, hb, qb) >> ql) & 1u;
           const bool fresh = xhalf_sum(l_run[qb]) == 0.f;

@@ -1,6 +1,10 @@
-"""A NaN in one key is a NaN in every result of the query rows that see it, and in no other: the float32
-kernels (one block and a running state) and the forward for few rows (one workgroup, splits with their
-combine, a running state), whose combines leave out parts without keys but not parts without a value."""
+"""Scores, values and gradients that are not finite.
+
+A NaN in one key is a NaN in every result of the query rows that see it, and in no other: the float32
+kernels (one block and a running state), the forward for few rows (one workgroup, splits with their
+combine, a running state), whose combines leave out parts without keys but not parts without a value, and
+the bf16 forward under masks by words.  Keys whose scores are -infinity have no weight.  What a tile repeats
+or pads with (a ragged key or row count) adds nothing, be it infinite."""
 import pytest
 import torch
 
@@ -41,3 +45,32 @@ def test_infinite_gradient_of_a_row_without_keys():
     do[0, 1, 20] = float("inf")
     assert torch.equal(loop.backward(q, k, v, o, lse, do, dk, dv), clean)
     assert not clean[0, 1, 16:24].any()
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("D", [64, 96, 128])
+@pytest.mark.parametrize("q_chunk,kv_block", [(48, 128), (16, 100), (2, 64)])
+def test_bad_key_in_a_frame_that_others_do_not_see(q_chunk, kv_block, D, bad):
+    # chunk c sees the frames c and c + 1 (mod 12): O and L of the rows that do not see the bad key's frame
+    # are as without it, but for the rounding of another reference: 2^-8 of a probability, 2^-9 of O
+    from paper_2502_02406_amd.blockloop import BlockLoop, MediaMask
+    g = torch.Generator().manual_seed(8)
+    Sq, nf = 300, 12
+    q = torch.randn((1, 2, Sq, D), generator=g).bfloat16().cuda()
+    k, v = (torch.randn((1, 1, nf * kv_block, D), generator=g).bfloat16().cuda() for _ in range(2))
+    chunk = torch.arange(-(-Sq // q_chunk))
+    allow = torch.zeros((len(chunk), nf), dtype=torch.uint8)
+    allow[chunk, chunk % nf] = allow[chunk, (chunk + 1) % nf] = 1
+    loop = BlockLoop(tuple(q.shape), tuple(k.shape), torch.bfloat16, 1, MediaMask(allow.cuda(), q_chunk, kv_block))
+    o0, l0 = (t.float() for t in loop.forward(q, k, v))
+    for frame in (0, 3, nf - 1):
+        for at in (0, kv_block - 1):
+            k2 = k.clone()
+            k2[0, 0, frame * kv_block + at, 5] = bad
+            o, lse = (t.float() for t in loop.forward(q, k2, v))
+            sees = allow[:, frame].bool().repeat_interleave(q_chunk)[:Sq].cuda()
+            what = f"frame {frame} key {at}"
+            assert ((lse - l0)[:, :, ~sees].abs() <= 2.0 ** -8).all(), what
+            assert ((o - o0)[:, :, ~sees].abs() <= 2.0 ** -6 * o0.abs().max()).all(), what
+            if bad != bad:
+                assert torch.isnan(o[:, :, sees]).all(), what
