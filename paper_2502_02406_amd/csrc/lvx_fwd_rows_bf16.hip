@@ -162,7 +162,7 @@ __global__ void __launch_bounds__(256) fwd_rows_bf16_kernel(FwdArgs a) {
       float mx = s[nb][0];
 #pragma unroll
       for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[nb][v]);
-      mx = xhalf_max(mx);                          // (a unit has at least one key: finite)
+      mx = fmaxf(xhalf_max(mx), -1e30f);           // (a row whose scores are all -infinity needs a finite reference)
       if (__any((mx - m_ref[nb]) * c2 > LAZY)) {
         const float m_new = fmaxf(m_ref[nb], mx);
         const float alpha = __builtin_amdgcn_exp2f((m_ref[nb] - m_new) * c2);     // m_ref = -inf -> 0

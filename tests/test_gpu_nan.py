@@ -74,3 +74,22 @@ def test_bad_key_in_a_frame_that_others_do_not_see(q_chunk, kv_block, D, bad):
             assert ((o - o0)[:, :, ~sees].abs() <= 2.0 ** -6 * o0.abs().max()).all(), what
             if bad != bad:
                 assert torch.isnan(o[:, :, sees]).all(), what
+
+
+@pytest.mark.parametrize("first,last", [(0, 40), (0, 5999), (32, 64), (100, 5000)])
+@pytest.mark.parametrize("D", [64, 96, 128])
+@pytest.mark.parametrize("n_blocks", [1, 2])
+def test_few_rows_against_keys_without_weight(n_blocks, D, first, last):
+    from paper_2502_02406_amd.blockloop import BlockLoop
+    g = torch.Generator().manual_seed(9)
+    q = torch.randn((1, 4, 3, D), generator=g).bfloat16().cuda()
+    k, v = (torch.randn((1, 2, 6000, D), generator=g).bfloat16().cuda() for _ in range(2))
+    q[..., 3] = q[..., 3].abs() + 0.5
+    q[:, :, 1, 3] = 0.5
+    k[:, :, first:last, 3] = float("-inf")
+    o, lse = BlockLoop(tuple(q.shape), tuple(k.shape), torch.bfloat16, n_blocks).forward(q, k, v)
+    kd, vd = (t.double().repeat_interleave(2, 1) for t in (k, v))
+    s = q.double() @ kd.transpose(2, 3) * D ** -0.5
+    want = torch.softmax(s, -1) @ vd
+    assert torch.allclose(o.double(), want, rtol=2e-2, atol=1e-2)
+    assert torch.allclose(lse.double(), torch.logsumexp(s, -1), rtol=0, atol=1e-3)
