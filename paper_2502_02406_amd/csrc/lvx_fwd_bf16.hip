@@ -586,12 +586,27 @@ fwd_bf16_kernel(FwdArgs a) {
     }
   };
 
+  // The rows of V that the moved last tile repeats are cleared once it has landed (their weight is 0, but 0 times
+  // an infinite value is not); the next barrier hands them on.
+  auto clear_repeated = [&](int t, char* st) __attribute__((always_inline)) {
+    if (RAGGED && t == n_tiles - 1 && d.Skv % TN != 0) {
+      asm volatile("" ::: "memory");
+      for (int x = tid; x < (n_tiles * TN - d.Skv) * CPR; x += 256)
+        *(u32x4*)(st + SM::TILE + tile_off<D>(x / CPR, 0, x % CPR * 16)) = u32x4{0, 0, 0, 0};
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+  };
+
   f32x16 s0[QB], s1[QB];                           // scores of even / odd halves
   u32x4 p0[QB][2] = {}, p1[QB][2] = {};            // packed P^T operands of even / odd halves
   Carry cy;
   TileVis vt = {};                                 // LIST = 3: of tile T
   if (nt > 0) {
     if constexpr (LIST == 3) vt = tile_vis(e[0], 0);
+    if (RAGGED && nt == 1) {
+      clear_repeated(LIST == 3 ? e[0] : t_begin, smem);
+      wg_barrier();
+    }
     score(smem, 0, s0, nothing, first_k(smem, 0), no_tail);
     settle_scores(s0);
     mask_ragged(s0, t_begin, 0);
@@ -667,6 +682,7 @@ fwd_bf16_kernel(FwdArgs a) {
       commit(s0, p0, vb_n, vn, 0);
       if constexpr (LIST == 3) { vt = vn; set_rq_lanes(vt, 1); }
     }
+    if (T + 2 == nt) clear_repeated(LIST == 3 ? e[1] : t_begin + T + 1, stage(T + 1));
     mid(std::false_type{}, T + 4 < nt, stage(T), T % NSTG);
     if (more) { score(stage(T + 1), 1, s1, nothing, first_k(stage(T + 1), 1), no_tail); }
     shift_e();

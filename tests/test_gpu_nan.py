@@ -93,3 +93,25 @@ def test_few_rows_against_keys_without_weight(n_blocks, D, first, last):
     want = torch.softmax(s, -1) @ vd
     assert torch.allclose(o.double(), want, rtol=2e-2, atol=1e-2)
     assert torch.allclose(lse.double(), torch.logsumexp(s, -1), rtol=0, atol=1e-3)
+
+
+@pytest.mark.parametrize("D", [64, 96, 128])
+@pytest.mark.parametrize("Skv,j", [(100, 60), (64 * 3 + 20, 64 * 3 - 10), (64 * 40 + 1, 64 * 40 - 63), (64 * 12 + 63, 64 * 12 - 1)])
+@pytest.mark.parametrize("masked", [False, True])
+def test_infinite_value_of_a_key_that_the_last_tile_repeats(masked, Skv, j, D):
+    from paper_2502_02406_amd.blockloop import BlockLoop, MediaMask
+    g = torch.Generator().manual_seed(10)
+    q = torch.randn((1, 4, 150, D), generator=g).bfloat16().cuda()
+    k, v = (torch.randn((1, 2, Skv, D), generator=g).bfloat16().cuda() for _ in range(2))
+    mask = None
+    if masked:
+        allow = torch.zeros((4, -(-Skv // 70)), dtype=torch.uint8)
+        allow[:, -2:] = allow[:, j // 70:j // 70 + 1] = allow[1:, 0:1] = 1
+        mask = MediaMask(allow.cuda(), 40, 70)
+    loop = BlockLoop(tuple(q.shape), tuple(k.shape), torch.bfloat16, 1, mask)
+    clean = loop.forward(q, k, v)[0].clone()
+    v[0, 0, j, 7] = float("inf")
+    o = loop.forward(q, k, v)[0]
+    assert (o[:, :2, :, 7] == float("inf")).all()
+    clean[:, :2, :, 7] = float("inf")
+    assert torch.equal(o, clean)
