@@ -68,6 +68,13 @@ template <int D> __device__ __forceinline__ void put_tile(float* tile, const Pie
 #pragma unroll
   for (int it = 0; it < D / 8; ++it) *(f32x4*)(tile + row_of_piece<D>(it, lane) * pitch_of(D) + col_of_piece<D>(it, lane)) = p.x[it];
 }
+// rows `first` .. 31 of a tile in LDS become 0: those past the last row, where something without a weight would be
+// multiplied that need not be finite
+template <int D> __device__ __forceinline__ void clear_rows(float* tile, int first, int lane) {
+#pragma unroll 1
+  for (int x = first * (D / 4) + lane; x < 32 * (D / 4); x += 64)
+    *(f32x4*)(tile + x / (D / 4) * pitch_of(D) + x % (D / 4) * 4) = f32x4{0.f, 0.f, 0.f, 0.f};
+}
 // a lane's row of the stationary side, 16 bytes per step group i: dims 8 i + 4 g ...
 template <int D> struct RowOps { f32x4 x[D / 8]; };
 template <int D> __device__ __forceinline__ RowOps<D> row_ops(const float* tile, int l31, int g) {
@@ -174,6 +181,7 @@ __global__ void __launch_bounds__(64 * waves_of(D)) fwd_f32_kernel(FwdArgs a) {
     const int n = d.Skv - j0;
     put_tile<D>(kt, kp, lane);
     put_tile<D>(vt, vp, lane);
+    if (n < 32) clear_rows<D>(vt, n, lane);
     if (n > 32 * NW) request(j0 + 32 * NW);
     f32x16 s = products<D>(kt, q, ql, g);
     if (MASKED || n < 32) {
@@ -376,7 +384,8 @@ __device__ void bwd_dkdv_f32(const BwdArgs& a, int tile, int hk, int b, char* sm
     }
     const int rr = min(r0 + kl, rows - 1);
     const float x = g == 0 ? a.lse[row_b + rr] : a.delta[row_b + rr];
-    sp = g == 0 ? (x == -INFINITY || r0 + kl >= rows ? -INFINITY : -x) : x;
+    const bool past = r0 + kl >= rows;
+    sp = g == 0 ? (x == -INFINITY || past ? -INFINITY : -x) : past ? 0.f : x;
   };
 #pragma unroll
   for (int x = tid; x < 32 * (D / 4); x += 64 * NW) {
@@ -395,6 +404,7 @@ __device__ void bwd_dkdv_f32(const BwdArgs& a, int tile, int hk, int b, char* sm
   for (int r0 = 32 * wave; r0 < rows; r0 += 32 * NW) {
     put_tile<D>(qt, qp, lane);
     put_tile<D>(gt, gp, lane);
+    if (rows - r0 < 32) clear_rows<D>(gt, rows - r0, lane);
     st[lane] = sp;
     const int rn = r0 + 32 * NW;
     const bool more = rn < rows, plain = rn + 32 <= rows && rn / d.Sq == (rn + 31) / d.Sq;

@@ -115,3 +115,25 @@ def test_infinite_value_of_a_key_that_the_last_tile_repeats(masked, Skv, j, D):
     assert (o[:, :2, :, 7] == float("inf")).all()
     clean[:, :2, :, 7] = float("inf")
     assert torch.equal(o, clean)
+
+
+@pytest.mark.parametrize("D", [64, 96, 128])
+@pytest.mark.parametrize("Sq,Skv", [(40, 100), (7, 33), (33, 290)])
+def test_infinities_in_the_last_key_and_row(Sq, Skv, D):
+    # float32, no multiples of the 32-row tiles: an infinite V of the last key, an infinite dO of the last row
+    from paper_2502_02406_amd.blockloop import BlockLoop
+    g = torch.Generator().manual_seed(11)
+    q, do = (torch.randn((1, 3, Sq, D), generator=g).cuda() for _ in range(2))
+    k, v = (torch.randn((1, 1, Skv, D), generator=g).cuda() for _ in range(2))
+    loop = BlockLoop(tuple(q.shape), tuple(k.shape), torch.float32, 1)
+    o, lse = (t.clone() for t in loop.forward(q, k, v))
+    dk, dv = torch.empty_like(k), torch.empty_like(v)
+    loop.backward(q, k, v, o, lse, do, dk, dv)
+    want = dv.clone()
+    v2, do2 = v.clone(), do.clone()
+    v2[0, 0, -1, 7] = do2[0, 2, -1, 3] = float("inf")
+    o2 = loop.forward(q, k, v2)[0]
+    o[..., 7] = want[..., 3] = float("inf")
+    assert torch.equal(o2, o)
+    loop.backward(q, k, v, o.nan_to_num(posinf=0.0), lse, do2, dk, dv)
+    assert torch.equal(dv, want)
