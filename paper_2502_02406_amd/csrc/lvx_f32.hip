@@ -220,6 +220,13 @@ __global__ void __launch_bounds__(64 * waves_of(D)) fwd_f32_kernel(FwdArgs a) {
   float* const l_next = st_l + NW * 32;
   const float l_row = xhalf_sum(l);
   if (g == 0) { st_m[wave * 32 + ql] = m; st_l[wave * 32 + ql] = l_row; }
+  if (MASKED && __any(l_row == 0.f)) {             // (a row that saw no key of this wave's has weight 0: so must be what it holds)
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int x = 0; x < 16; ++x) acc[db][x] = l_row == 0.f ? 0.f : acc[db][x];
+  }
   put_block<D>(kt, acc, ql, g);
   __syncthreads();
   const long row_b = ((long)b * d.Hq + hk * d.G) * d.Sq;       // L rows of the group follow each other

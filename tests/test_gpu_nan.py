@@ -137,3 +137,20 @@ def test_infinities_in_the_last_key_and_row(Sq, Skv, D):
     assert torch.equal(o2, o)
     loop.backward(q, k, v, o.nan_to_num(posinf=0.0), lse, do2, dk, dv)
     assert torch.equal(dv, want)
+
+
+@pytest.mark.parametrize("blind", [0, 1])
+def test_rows_that_see_nothing_of_a_block_with_a_bad_value(blind):
+    # float32, two blocks: rows 0 .. 31 see nothing of block `blind`, whose V holds a NaN
+    from paper_2502_02406_amd.blockloop import BlockLoop, MediaMask
+    g = torch.Generator().manual_seed(12)
+    q = torch.randn((1, 2, 64, 64), generator=g).cuda()
+    k, v = (torch.randn((1, 1, 400, 64), generator=g).cuda() for _ in range(2))
+    allow = torch.ones((2, 2), dtype=torch.uint8)
+    allow[0, blind] = 0
+    loop = BlockLoop(tuple(q.shape), tuple(k.shape), torch.float32, 2, MediaMask(allow.cuda(), 32, 200))
+    clean, l0 = (t.clone() for t in loop.forward(q, k, v))
+    v[0, 0, 200 * blind + 77, 4] = float("nan")
+    o, lse = loop.forward(q, k, v)
+    assert torch.equal(o[:, :, :32], clean[:, :, :32]) and torch.equal(lse, l0)
+    assert torch.isnan(o[:, :, 32:, 4]).all()
