@@ -308,7 +308,7 @@ __host__ __device__ inline long xcd_grid(int n_heads, int items_per_head) {
 // interleave: the parts of a head take its items in turn instead of a run each, for items whose
 // work falls or rises along the head (key tiles under a causal mask): with runs, one XCD would get
 // the long items of a head and another the short ones.
-__device__ __forceinline__ bool xcd_decode(long pid, int n_heads, int items_per_head, HeadWork* w,
+__host__ __device__ __forceinline__ bool xcd_decode(long pid, int n_heads, int items_per_head, HeadWork* w,
                                            bool interleave = false) {
   const int S = xcd_parts(n_heads);
   const int per_vh = (items_per_head + S - 1) / S;
@@ -321,9 +321,16 @@ __device__ __forceinline__ bool xcd_decode(long pid, int n_heads, int items_per_
   w->item = item;
   return item < items_per_head;
 }
+// Entry of a list of `total` that workgroup pid takes when every XCD (pid mod 8) takes a run of the list, no XCD
+// one of more than an entry beyond another's; false: none.  The grid has a multiple of 8 workgroups, total or more.
+__host__ __device__ __forceinline__ bool xcd_run(long pid, long total, long* entry) {
+  const long x = pid % 8;
+  *entry = total * x / 8 + pid / 8;
+  return *entry < total * (x + 1) / 8;
+}
 // The same for the tiles of a matrix product (head = row tile, item = column tile), of which there may be any
 // number of rows: where the parts above come out uneven, each XCD takes a run of the list (row tile, column tile)
-// instead, so that no XCD has more than one tile beyond another and the column tiles of a row tile still meet in
+// instead, so that no XCD has more than one tile beyond another (xcd_run) and the column tiles of a row tile still meet in
 // one L2 (but for a row tile that two runs share).  An odd number of row tiles with 4 column tiles left four
 // XCDs idle: projection of 17958 tokens x 512 features x 1024 columns 63 -> 36 us, its dx 86 -> 35; 60001 x
 // 1024 x 1024 263 -> 125 and 237 -> 126 us.  Even parts stay as they are: there runs gain nothing (131072 x 512 x
@@ -332,12 +339,13 @@ __host__ __device__ inline bool tile_runs(int n_rt, int n_ct) { return n_ct % xc
 __host__ __device__ inline long tile_grid(int n_rt, int n_ct) {
   return tile_runs(n_rt, n_ct) ? ((long)n_rt * n_ct + 7) / 8 * 8 : xcd_grid(n_rt, n_ct);
 }
-__device__ __forceinline__ bool tile_decode(long pid, int n_rt, int n_ct, HeadWork* w) {
+__host__ __device__ __forceinline__ bool tile_decode(long pid, int n_rt, int n_ct, HeadWork* w) {
   if (!tile_runs(n_rt, n_ct)) return xcd_decode(pid, n_rt, n_ct, w);
-  const long tiles = (long)n_rt * n_ct, tile = pid % 8 * ((tiles + 7) / 8) + pid / 8;
+  long tile;
+  const bool on = xcd_run(pid, (long)n_rt * n_ct, &tile);
   w->head = (int)(tile / n_ct);
   w->item = (int)(tile % n_ct);
-  return tile < tiles;
+  return on;
 }
 
 }  // namespace lvx

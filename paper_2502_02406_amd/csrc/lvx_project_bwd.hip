@@ -121,9 +121,10 @@ project_bwd_bf16_kernel(ProjBwdArgs a) {
     // tiles of a part, which read the same tokens, meet in its L2.  With a tile's parts on one XCD instead
     // every tile fetched its panels of G and x for itself: 131072 tokens x 1024 columns x 512 features, 8
     // tiles x 32 parts, forward + gradients 488 -> 463 us.
-    const int tiles = n_rt * n_ct, total = tiles * a.dw_parts, per = (total + 7) / 8;
-    const int x = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-    if (x >= total) return;                          // (the grid has 8 per workgroups)
+    const int tiles = n_rt * n_ct;
+    long entry;
+    if (!xcd_run(blockIdx.x, (long)tiles * a.dw_parts, &entry)) return;
+    const int x = (int)entry;
     tpart = x / tiles;
     hw.head = x % tiles / n_ct;
     hw.item = x % n_ct;
