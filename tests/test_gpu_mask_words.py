@@ -56,3 +56,33 @@ def test_rows_whose_keys_score_far_below_the_first_tile(D):
     torch.cuda.synchronize()
     Oref, Lref = oracle.fwd(*(W.as_f32_numpy(x[n]) for n in ("q", "k", "v")), mask=oracle.Mask(allow.numpy(), w.q_chunk, w.kv_block))
     check_fwd(O, L, Oref, Lref, TOL["bf16"], w.name)
+
+
+def test_a_key_that_scores_far_above_the_rest_costs_nothing():
+    # The first key of each frame scores 150 units of log2 above the others, which leaves one half-wave of every row without a sum
+    # worth the name for good.  Asking such lanes again in every half took 2.1 times as long; the same run twice
+    # differs by a few per cent.
+    import torch
+    from paper_2502_02406_amd.blockloop import BlockLoop, MediaMask
+    g = torch.Generator(device="cuda").manual_seed(13)
+    q = torch.randn((1, 16, 1024, 128), generator=g, device="cuda").bfloat16()
+    k, v = (torch.randn((1, 16, 16384, 128), generator=g, device="cuda").bfloat16() for _ in range(2))
+    q[..., 0] = 4.0
+    loop = BlockLoop(tuple(q.shape), tuple(k.shape), torch.bfloat16, 1,
+                     MediaMask(torch.ones((22, 16), dtype=torch.uint8, device="cuda"), 48, 1024))
+
+    def ms():
+        times = []
+        for _ in range(8):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(5):
+                loop.forward(q, k, v)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b) / 5)
+        return min(times)
+
+    even = ms()
+    k[:, :, ::1024, 0] = 300.0       # (of every frame: every split of the keys has one)
+    assert ms() <= 1.4 * even
