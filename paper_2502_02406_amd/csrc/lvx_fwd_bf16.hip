@@ -596,14 +596,16 @@ fwd_bf16_kernel(FwdArgs a) {
     }
   };
 
-  // The rows of V that the moved last tile repeats are cleared once it has landed (their weight is 0, but 0 times
-  // an infinite value is not); the next barrier hands them on.
+  // The rows of V that the moved last tile repeats are cleared before it is contracted (their weight is 0, but 0
+  // times an infinite value is not).
   auto clear_repeated = [&](int t, char* st) __attribute__((always_inline)) {
     if (RAGGED && t == n_tiles - 1 && d.Skv % TN != 0) {
       asm volatile("" ::: "memory");
+#pragma unroll 1
       for (int x = tid; x < (n_tiles * TN - d.Skv) * CPR; x += 256)
         *(u32x4*)(st + SM::TILE + tile_off<D>(x / CPR, 0, x % CPR * 16)) = u32x4{0, 0, 0, 0};
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      wg_barrier();
     }
   };
 
@@ -613,10 +615,6 @@ fwd_bf16_kernel(FwdArgs a) {
   TileVis vt = {};                                 // LIST = 3: of tile T
   if (nt > 0) {
     if constexpr (LIST == 3) vt = tile_vis(e[0], 0);
-    if (RAGGED && nt == 1) {
-      clear_repeated(LIST == 3 ? e[0] : t_begin, smem);
-      wg_barrier();
-    }
     score(smem, 0, s0, nothing, first_k(smem, 0), no_tail);
     settle_scores(s0);
     mask_ragged(s0, t_begin, 0);
@@ -676,6 +674,7 @@ fwd_bf16_kernel(FwdArgs a) {
     const int vb_t = vis_at(T), vb_n = more ? vis_at(T + 1) : 0;
     TileVis vn = {};
     if constexpr (LIST == 3) { if (more) vn = tile_vis(e[1], (T + 1) % NSTG); }
+    if (!more) clear_repeated(LIST == 3 ? e[0] : t_begin + T, stage(T));
     contract(stage(T), 0, p0);
     settle_scores(s1);                             // (outside the pipelined loop the wait comes first, as a real dependence)
     mask_ragged(s1, t_begin + T, 1);
@@ -692,7 +691,6 @@ fwd_bf16_kernel(FwdArgs a) {
       commit(s0, p0, vb_n, vn, 0);
       if constexpr (LIST == 3) { vt = vn; set_rq_lanes(vt, 1); }
     }
-    if (T + 2 == nt) clear_repeated(LIST == 3 ? e[1] : t_begin + T + 1, stage(T + 1));
     mid(std::false_type{}, T + 4 < nt, stage(T), T % NSTG);
     if (more) { score(stage(T + 1), 1, s1, nothing, first_k(stage(T + 1), 1), no_tail); }
     shift_e();
