@@ -132,8 +132,8 @@ size_t fwd_ws(const Dims& d, int n_split) {
   const size_t rows = (size_t)d.B * d.Hq * d.Sq;
   return align_up(rows * d.D * sizeof(float) * n_split) + align_up(rows * sizeof(float) * n_split);
 }
-// lvx_xattn_fwd_merge: the splits' partial results (bf16 kernels that split the key range), or one
-// float32 partial result (float32 kernels, which have no fused epilogue)
+// lvx_xattn_fwd_merge: the splits' partial results (bf16 kernels that split the key range).  The float32
+// kernels, which merge in their epilogue, leave theirs alone; callers give them room for a partial result all the same.
 size_t fwd_merge_ws(const Dims& d, lvx_dtype dtype, int n_split) {
   return fwd_ws(d, dtype == LVX_F32 ? 2 : n_split);      // (fwd_ws(d, 2) holds more than one partial result)
 }
@@ -267,7 +267,7 @@ lvx_status lvx_xattn_fwd_merge(const lvx_problem* p, lvx_dtype dtype, const void
   a.d = make_dims(p);
   if (dtype == LVX_F32 && (a.d.q_ss != a.d.D || a.d.q_sh != (long)a.d.Sq * a.d.D ||
                            a.d.q_sb != (long)a.d.Hq * a.d.Sq * a.d.D))
-    return LVX_ERR_STRIDE;      // the float32 kernels write their result with Q's strides
+    return LVX_ERR_STRIDE;      // (part of the interface, although the kernel would read any)
   a.mask = make_mask(mask);
   a.q = q; a.k = k; a.v = v; a.o_is_f32 = 1;
   a.partial = 0; a.part0 = 0; a.pass = 0;

@@ -147,7 +147,7 @@ hipError_t launch_project_bwd(const ProjBwdArgs& a, int is_f32, hipStream_t s);
 // one; lvx_xattn_workspace_bytes returns the larger of the two cases); 0 for invalid arguments.
 size_t fwd_workspace_need(const lvx_problem* p, lvx_dtype dtype, const lvx_mask* mask);
 
-// kernels for float32 tensors (plain FMA, correctness-grade)
+// kernels for float32 tensors (float32 matrix instruction; the key range is never split)
 hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t s);
 hipError_t launch_bwd_f32(const BwdArgs& a, unsigned stages, hipStream_t s);   // stages: 2 = dK/dV, 4 = dQ
 // kernels for bfloat16 tensors (MFMA)
