@@ -69,12 +69,12 @@ constexpr int XE = LVX_FWD_XE;                  // elements of a half converted 
 // lane by lane, by one select with such a word as the lane mask.  A half that a key block's end
 // cuts for some row of the wave takes the branch that raises the reference: its scores get
 // -infinity where the words say so and it is converted again from the registers they are still in,
-// so the steady loop has no other branch than before.  A row's first visible half, whose reference
-// comes from keys it does not see, goes the same way when its sum shows that it is far too high.
+// so the steady loop has one other branch: a half that holds the first keys that some row sees gives
+// that row its reference and is converted again (once per row, and the rows of a chunk together).
 // Bound by the same issue slots as the dense loop, plus about 45 instructions a tile.  2048 rows x 28
-// heads in chunks of 64 against 32 frames of 729 keys, causal, D = 128: 0.82 -> 0.45 ms (780 TFLOP/s of
-// visible pairs); 4096 rows x 8 heads in chunks of 2, each seeing one of 2048 frames of 64 keys,
-// D = 64: 0.78 -> 0.13 ms for 268 MB of K and V.
+// heads in chunks of 64 against 32 frames of 729 keys, causal, D = 128: 0.82 -> 0.42 ms (830 TFLOP/s of
+// visible pairs); 4096 rows x 8 heads in chunks of 2, each seeing one of 2048 frames of 64 keys, D = 64:
+// 0.80 -> 0.17 ms for 268 MB of K and V, 0.026 of them for the references: every tile is some row's first.
 template <int D, int LIST = 0>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 fwd_bf16_kernel(FwdArgs a) {
@@ -426,20 +426,19 @@ fwd_bf16_kernel(FwdArgs a) {
       for (int x = 0; x < 16; ++x) s[qb][x] = (keys >> (8 * (x / 4) + (x % 4))) & 1u ? s[qb][x] : -INFINITY;
     }
   };
-  // LIST = 3: a row whose sum of its first visible half is smaller than TOO_HIGH has a reference far above its
-  // scores.  Rows that have a sum already are not asked: a lane holds only its share of it, which stays small for good
-  // where the other half-wave's keys hold the mass (asked every time, 16 heads x 2048 rows x 32768 keys of which the
-  // first scores far above the rest took 1.14 ms, now 0.52).
-  constexpr float TOO_HIGH = 0x1p-60f;
-  auto too_high = [&](const TileVis& vis, int hb) __attribute__((always_inline)) -> unsigned long long {   // lanes
-    unsigned long long high = 0;
+  // LIST = 3: rows that see half hb and have no sum yet
+  auto first_seen = [&](const TileVis& vis, int hb, int qb) __attribute__((always_inline)) -> unsigned {
+    const unsigned long long none = __ballot(l_run[qb] == 0.f);
+    return half_word(vis, hb, qb) & (unsigned)none & (unsigned)(none >> 32);
+  };
+  // ... a row's largest score among the keys of half hb that it sees
+  auto seen_max = [&](const f32x16& sv, int hb, int qb, const TileVis& vis) __attribute__((always_inline)) -> float {
+    if (!half_cut(vis, hb)) return (half_word(vis, hb, qb) >> ql) & 1u ? row_max(sv) : -INFINITY;
+    const unsigned keys = lane_keys(vis, hb, qb, ql, g);
+    float m = -INFINITY;
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      const unsigned long long none = __ballot(l_run[qb] == 0.f);
-      const unsigned w = half_word(vis, hb, qb) & (unsigned)none & (unsigned)(none >> 32);
-      high |= __ballot(l_half[qb] < TOO_HIGH) & (((unsigned long long)w << 32) | w);
-    }
-    return high;
+    for (int x = 0; x < 16; ++x) m = fmaxf(m, (keys >> (8 * (x / 4) + (x % 4))) & 1u ? sv[x] : -INFINITY);
+    return xhalf_max(m) * c2;
   };
   auto too_large = [&]() __attribute__((always_inline)) -> unsigned long long {
     bool large = false;
@@ -448,15 +447,32 @@ fwd_bf16_kernel(FwdArgs a) {
     return __ballot(large);
   };
   // (vb: LIST = 2, row blocks that see the tile; vis, hb: LIST = 3, the half's words)
-  auto commit = [&](f32x16 (&s)[QB], u32x4 (&pw)[QB][2], int vb, const TileVis& vis, int hb) __attribute__((always_inline)) {
+  // (s_next: LIST = 3 and hb = 0, the scores of the tile's other half)
+  auto commit = [&](f32x16 (&s)[QB], u32x4 (&pw)[QB][2], int vb, const TileVis& vis, int hb, f32x16 (&s_next)[QB]) __attribute__((always_inline)) {
     unsigned long long need = too_large();
     if constexpr (LIST == 3) {
-      need |= too_high(vis, hb);
-      if (__builtin_expect(half_cut(vis, hb), 0)) {
+      // Rows that see their first keys: the reference becomes their largest score of the tile, both halves, so that
+      // the largest probability is 1 and loses nothing in bf16, as in the general kernel (with what other keys had left
+      // as reference O of rows that see 64 keys each was off by 2.33e-3, so by 2.11e-3).
+      const unsigned first[QB] = {first_seen(vis, hb, 0), first_seen(vis, hb, 1)};
+      const bool cut = half_cut(vis, hb);
+      if (__builtin_expect(cut || (first[0] | first[1]) != 0, 0)) {
         asm volatile("" ::: "memory");
-        mask_words(s, hb, vis);
-        convert(s, pw);
-        need = too_large() | too_high(vis, hb);
+        if (cut) mask_words(s, hb, vis);
+        if (hb == 0 && (first[0] | first[1]) != 0) settle_scores(s_next);
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+          if (!cut && first[qb] == 0) continue;
+          if (first[qb] != 0) {
+            const float m = hb == 0 ? fmaxf(seen_max(s[qb], 0, qb, vis), seen_max(s_next[qb], 1, qb, vis)) : seen_max(s[qb], 1, qb, vis);
+            r[qb] = ((first[qb] >> ql) & 1u) && m != -INFINITY ? m : r[qb];
+          }
+          set_rq_lanes(vis, hb);
+          Carry cy;
+#pragma unroll
+          for (int x = 0; x < 16; ++x) conv_elem(16 * qb + x, cy, s, pw);
+        }
+        need = too_large();
       }
     }
     if (__builtin_expect(need != 0, 0)) {
@@ -471,12 +487,11 @@ fwd_bf16_kernel(FwdArgs a) {
         float r_new = fmaxf(r[qb], row_max(s[qb]));
         float alpha = __builtin_amdgcn_exp2f(r[qb] - r_new);
         if constexpr (LIST == 3) {
-          // (a row that does not see the half keeps its reference; one that has added up nothing yet takes its
-          // first visible half's maximum, be it lower than what it started from)
+          // (a row that does not see the half keeps its reference; one without a sum has nothing to shrink, and what it
+          // starts from may be infinite)
           const bool seen = (half_word(vis, hb, qb) >> ql) & 1u;
           const bool fresh = xhalf_sum(l_run[qb]) == 0.f;
-          const float m = row_max(s[qb]);
-          r_new = !seen || m == -INFINITY ? r[qb] : fresh ? m : fmaxf(r[qb], m);
+          r_new = seen ? r_new : r[qb];
           alpha = fresh ? 0.f : __builtin_amdgcn_exp2f(r[qb] - r_new);
         }
         r[qb] = r_new;
@@ -628,9 +643,10 @@ fwd_bf16_kernel(FwdArgs a) {
     set_rq(vis_at(0));
     if constexpr (LIST == 3) set_rq_lanes(vt, 0);
     convert(s0, p0);
-    commit(s0, p0, vis_at(0), vt, 0);
+    if constexpr (LIST == 3) score(smem, 1, s1, nothing, first_k(smem, 1), no_tail);
+    commit(s0, p0, vis_at(0), vt, 0, s1);
     if constexpr (LIST == 3) set_rq_lanes(vt, 1);
-    score(smem, 1, s1, nothing, first_k(smem, 1), no_tail);
+    if constexpr (LIST != 3) score(smem, 1, s1, nothing, first_k(smem, 1), no_tail);
   }
   int T = 0;
   int id_next = LIST && cursor < t_end ? tlist[cursor] : 0;     // LIST: number of the next tile to copy
@@ -647,7 +663,7 @@ fwd_bf16_kernel(FwdArgs a) {
     asm volatile("" : "+v"(fk));                   // (waited for here, where the compiler still knows what is in flight)
     score_convert(sb, 0, s0, s1, p1, cy, fk, [&]() __attribute__((always_inline)) { fvt = first_vt(sa, 1); }, nothing);
     asm volatile("" : "+v"(fvt));
-    commit(s1, p1, vb_t, vt, 1);
+    commit(s1, p1, vb_t, vt, 1, s0);
     set_rq(vb_n);                                  // from here on: scores of tile T + 1
     if constexpr (LIST == 3) set_rq_lanes(vn, 0);
     contract_convert(sa, 1, p1, s0, p0, cy, fvt, [&]() __attribute__((always_inline)) { fk = first_k(sb, 1); });
@@ -665,7 +681,7 @@ fwd_bf16_kernel(FwdArgs a) {
                     if (m % EVERY == EVERY - 1 && m / EVERY < NDMA) issue_part(t_new, sa, m / EVERY, T % NSTG);
                   });
     asm volatile("" : "+v"(fvt));
-    commit(s0, p0, vb_n, vn, 0);
+    commit(s0, p0, vb_n, vn, 0, s1);
     if constexpr (LIST == 3) { vt = vn; set_rq_lanes(vt, 1); }
     shift_e();
   }
@@ -679,7 +695,7 @@ fwd_bf16_kernel(FwdArgs a) {
     settle_scores(s1);                             // (outside the pipelined loop the wait comes first, as a real dependence)
     mask_ragged(s1, t_begin + T, 1);
     convert(s1, p1);
-    commit(s1, p1, vb_t, vt, 1);                   // (a raise comes before anything relative to the new reference is added)
+    commit(s1, p1, vb_t, vt, 1, s0);                 // (a raise comes before anything relative to the new reference is added)
     if (more) { score(stage(T + 1), 0, s0, nothing, first_k(stage(T + 1), 0), no_tail); }
     contract(stage(T), 1, p1);
     if (more) {
@@ -688,11 +704,12 @@ fwd_bf16_kernel(FwdArgs a) {
       set_rq(vb_n);
       if constexpr (LIST == 3) set_rq_lanes(vn, 0);
       convert(s0, p0);
-      commit(s0, p0, vb_n, vn, 0);
+      if constexpr (LIST == 3) score(stage(T + 1), 1, s1, nothing, first_k(stage(T + 1), 1), no_tail);
+      commit(s0, p0, vb_n, vn, 0, s1);
       if constexpr (LIST == 3) { vt = vn; set_rq_lanes(vt, 1); }
     }
     mid(std::false_type{}, T + 4 < nt, stage(T), T % NSTG);
-    if (more) { score(stage(T + 1), 1, s1, nothing, first_k(stage(T + 1), 1), no_tail); }
+    if (LIST != 3 && more) { score(stage(T + 1), 1, s1, nothing, first_k(stage(T + 1), 1), no_tail); }
     shift_e();
   }
 

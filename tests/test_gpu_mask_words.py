@@ -86,3 +86,30 @@ def test_a_key_that_scores_far_above_the_rest_costs_nothing():
     even = ms()
     k[:, :, ::1024, 0] = 300.0       # (of every frame: every split of the keys has one)
     assert ms() <= 1.4 * even
+
+
+@pytest.mark.parametrize("D", [64, 96, 128])
+@pytest.mark.parametrize("q_chunk,kv_block", [(2, 64), (16, 64), (24, 100), (2, 729)])
+def test_the_largest_probability_is_not_rounded(q_chunk, kv_block, D):
+    # Every row sees one frame, in which one key (in any half of a tile) scores 40 above the rest and otherwise like
+    # no other frame's: its probability is 1 and O its V.  Rounded to bf16 relative to some other reference it would
+    # be off by up to 2^-9.  The float32 bound: the reference (64 .. 128 in units of log2) is rounded, by 2^-18 at most,
+    # which the sum sees and the bf16 probability does not: 2^-18 ln 2 of O; as much again for the sum, its inverse and
+    # the combine of the splits (some units of 2^-24), and the rest of the frame (e^-40).
+    import torch
+    from paper_2502_02406_amd import binding as B
+    from paper_2502_02406_amd.blockloop import BlockLoop, MediaMask
+    g = torch.Generator().manual_seed(14)
+    Sq, nf = 24 * q_chunk, 24
+    q = 0.1 * torch.randn((1, 2, Sq, D), generator=g)
+    k, v = (0.1 * torch.randn((1, 1, nf * kv_block, D), generator=g) for _ in range(2))
+    top = torch.arange(nf) * kv_block + torch.randint(0, kv_block, (nf,), generator=g)
+    q[..., 0] = 1.0
+    k[0, 0, top, 0] = D ** 0.5 * (42.0 + 3.0 * torch.rand(nf, generator=g))
+    q, k, v = (t.bfloat16().cuda() for t in (q, k, v))
+    loop = BlockLoop(tuple(q.shape), tuple(k.shape), torch.bfloat16, 1,
+                     MediaMask(torch.eye(nf, dtype=torch.uint8).cuda(), q_chunk, kv_block))
+    o = torch.empty(q.shape, dtype=torch.float32, device="cuda")
+    B.lvx_xattn_fwd(B.make_problem(q, k, 0.0), q, k, v, loop._mask_for(0), o, loop.lse, loop.ws)
+    want = v[0, 0, top.repeat_interleave(q_chunk).cuda()].float()
+    assert ((o - want).abs() <= 2.0 ** -17 * 0.6932 * want.abs() + 1e-12).all()
