@@ -74,7 +74,7 @@ constexpr int XE = LVX_FWD_XE;                  // elements of a half converted 
 // Bound by the same issue slots as the dense loop, plus about 45 instructions a tile.  2048 rows x 28
 // heads in chunks of 64 against 32 frames of 729 keys, causal, D = 128: 0.82 -> 0.42 ms (830 TFLOP/s of
 // visible pairs); 4096 rows x 8 heads in chunks of 2, each seeing one of 2048 frames of 64 keys, D = 64:
-// 0.80 -> 0.17 ms for 268 MB of K and V, 0.026 of them for the references: every tile is some row's first.
+// 0.80 -> 0.16 ms for 268 MB of K and V, 0.02 of them for the references: every tile is some row's first.
 template <int D, int LIST = 0>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 fwd_bf16_kernel(FwdArgs a) {
@@ -431,14 +431,23 @@ fwd_bf16_kernel(FwdArgs a) {
     const unsigned long long none = __ballot(l_run[qb] == 0.f);
     return half_word(vis, hb, qb) & (unsigned)none & (unsigned)(none >> 32);
   };
-  // ... a row's largest score among the keys of half hb that it sees
-  auto seen_max = [&](const f32x16& sv, int hb, int qb, const TileVis& vis) __attribute__((always_inline)) -> float {
-    if (!half_cut(vis, hb)) return (half_word(vis, hb, qb) >> ql) & 1u ? row_max(sv) : -INFINITY;
+  // ... this lane's largest score among the keys of half hb that its row sees
+  auto lane_max = [&](const f32x16& sv) __attribute__((always_inline)) -> float {
+    float m = fmaxf(fmaxf(sv[0], sv[1]), sv[2]);
+#pragma unroll
+    for (int v = 3; v < 15; v += 2) m = fmaxf(fmaxf(m, sv[v]), sv[v + 1]);
+    return fmaxf(m, sv[15]);
+  };
+  auto lane_max_seen = [&](const f32x16& sv, int hb, int qb, const TileVis& vis) __attribute__((always_inline)) -> float {
+    // (half_cut as a word: selects, no branches)
+    const unsigned two = (vis.a[0] ^ vis.b[0]) | (vis.a[1] ^ vis.b[1]);
+    const unsigned cut = ((unsigned)(vis.edge - 32 * hb - 1) < 31u ? two : 0u) | (vis.low > 32 * hb ? 1u : 0u);
+    if (__builtin_expect(cut == 0, 1)) return (half_word(vis, hb, qb) >> ql) & 1u ? lane_max(sv) : -INFINITY;
     const unsigned keys = lane_keys(vis, hb, qb, ql, g);
     float m = -INFINITY;
 #pragma unroll
     for (int x = 0; x < 16; ++x) m = fmaxf(m, (keys >> (8 * (x / 4) + (x % 4))) & 1u ? sv[x] : -INFINITY);
-    return xhalf_max(m) * c2;
+    return m;
   };
   auto too_large = [&]() __attribute__((always_inline)) -> unsigned long long {
     bool large = false;
@@ -464,7 +473,9 @@ fwd_bf16_kernel(FwdArgs a) {
         for (int qb = 0; qb < QB; ++qb) {
           if (!cut && first[qb] == 0) continue;
           if (first[qb] != 0) {
-            const float m = hb == 0 ? fmaxf(seen_max(s[qb], 0, qb, vis), seen_max(s_next[qb], 1, qb, vis)) : seen_max(s[qb], 1, qb, vis);
+            float m = lane_max(s[qb]);             // (its keys that the row does not see are masked, or there are none)
+            if (hb == 0) m = fmaxf(m, lane_max_seen(s_next[qb], 1, qb, vis));
+            m = xhalf_max(m) * c2;
             r[qb] = ((first[qb] >> ql) & 1u) && m != -INFINITY ? m : r[qb];
           }
           set_rq_lanes(vis, hb);
