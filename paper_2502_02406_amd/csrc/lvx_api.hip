@@ -93,9 +93,6 @@ int fwd_two_pass_split(int n_split, int reserve) {   // each launch's split coun
   const int cap = (LVX_MAX_PARTS - reserve) / 2;      // `reserve` others) go into one combine
   return n_split < cap ? n_split : cap;
 }
-bool fwd_two_pass(const Dims& d, lvx_dtype dtype, const MaskDev& m) {
-  return dtype == LVX_BF16 && fwd_bf16_two_pass_fits(d, m) && !fwd_bf16_takes_rows(d, m);
-}
 hipError_t launch_fwd_bf16_two_pass(FwdArgs a, hipStream_t s) {
   a.partial = 1;
   a.pass = 1;
@@ -107,26 +104,6 @@ hipError_t launch_fwd_bf16_two_pass(FwdArgs a, hipStream_t s) {
   return launch_fwd_bf16(a, s);
 }
 
-// How a forward call runs: the KV splits of each launch, whether a media mask makes it two launches,
-// the partial results the combine then reads, and the bytes of MaskRows' words the kernel reads.
-// `reserve` parts of the combine are taken already (lvx_xattn_fwd_merge: the running state).
-struct FwdPlan { int n_split; bool two; int n_parts; size_t rows_bytes; };
-FwdPlan fwd_plan(const Dims& d, lvx_dtype dtype, const MaskDev& m, int reserve) {
-  const bool masked = m.allow != nullptr, bf16 = dtype == LVX_BF16;
-  FwdPlan f;
-  f.n_split = fwd_split(d, dtype, masked);
-  if (f.n_split > LVX_MAX_PARTS - reserve) f.n_split = LVX_MAX_PARTS - reserve;
-  f.two = masked && fwd_two_pass(d, dtype, m);
-  if (f.two) f.n_split = fwd_two_pass_split(f.n_split, reserve);
-  const bool rows = masked && bf16 && fwd_bf16_takes_rows(d, m);
-  f.rows_bytes = rows ? align_up(mask_rows_bytes(d, mask_rows_of(d, m))) : 0;
-  // (one launch over tile lists: its workgroups start longest first, which evens the load out
-  // with half the splits the other masked forms want)
-  if (masked && bf16 && (rows || fwd_bf16_one_pass_fits(d, m)) && f.n_split > 1) f.n_split /= 2;
-  f.n_parts = f.two ? 2 * f.n_split : f.n_split;
-  return f;
-}
-
 size_t fwd_ws(const Dims& d, int n_split) {
   if (n_split <= 1) return ALIGN;   // never zero, so that a valid workspace pointer is always passed
   const size_t rows = (size_t)d.B * d.Hq * d.Sq;
@@ -136,6 +113,33 @@ size_t fwd_ws(const Dims& d, int n_split) {
 // kernels, which merge in their epilogue, leave theirs alone; callers give them room for a partial result all the same.
 size_t fwd_merge_ws(const Dims& d, lvx_dtype dtype, int n_split) {
   return fwd_ws(d, dtype == LVX_F32 ? 2 : n_split);      // (fwd_ws(d, 2) holds more than one partial result)
+}
+// How a forward call runs: the KV splits of each launch, whether a media mask makes it two launches,
+// the partial results the combine then reads, the bytes of MaskRows' words the kernel reads, and the
+// workspace it all takes.  `reserve` parts of the combine are taken already (lvx_xattn_fwd_merge: the
+// running state).
+struct FwdPlan { int n_split; bool two; int n_parts; size_t rows_bytes, need; };
+FwdPlan fwd_plan_with(const Dims& d, lvx_dtype dtype, const MaskDev& m, int reserve, bool rows) {
+  const bool masked = m.allow != nullptr, bf16 = dtype == LVX_BF16;
+  FwdPlan f;
+  f.n_split = fwd_split(d, dtype, masked);
+  if (f.n_split > LVX_MAX_PARTS - reserve) f.n_split = LVX_MAX_PARTS - reserve;
+  f.two = masked && bf16 && !rows && fwd_bf16_two_pass_fits(d, m);
+  if (f.two) f.n_split = fwd_two_pass_split(f.n_split, reserve);
+  f.rows_bytes = rows ? align_up(mask_rows_bytes(d, mask_rows_of(d, m))) : 0;
+  // (one launch over tile lists: its workgroups start longest first, which evens the load out
+  // with half the splits the other masked forms want)
+  if (masked && bf16 && (rows || fwd_bf16_one_pass_fits(d, m)) && f.n_split > 1) f.n_split /= 2;
+  f.n_parts = f.two ? 2 * f.n_split : f.n_split;
+  f.need = (reserve ? fwd_merge_ws(d, dtype, f.n_parts) : fwd_ws(d, f.n_parts)) + f.rows_bytes;
+  return f;
+}
+// ... in a workspace of `room` bytes.  Words that do not fit (262144 rows against 131072 keys in blocks of 64: 68
+// MB, where the general kernel needs nothing) leave the call to the kernels that do without.
+FwdPlan fwd_plan(const Dims& d, lvx_dtype dtype, const MaskDev& m, int reserve, size_t room) {
+  const bool rows = m.allow != nullptr && dtype == LVX_BF16 && fwd_bf16_takes_rows(d, m);
+  const FwdPlan f = fwd_plan_with(d, dtype, m, reserve, rows);
+  return rows && f.need > room ? fwd_plan_with(d, dtype, m, reserve, false) : f;
 }
 int sq_padded(const Dims& d) { return (d.Sq + 31) / 32 * 32; }
 bool has_stats_ovl(const Dims& d) { return d.Sq % 32 != 0 && d.Sq >= 32; }
@@ -161,11 +165,9 @@ size_t bwd_ws(const Dims& d, int n_slices, bool fused) {   // ... + the fused ke
 }  // namespace
 
 namespace lvx {
-size_t fwd_workspace_need(const lvx_problem* p, lvx_dtype dtype, const lvx_mask* mask) {
+size_t fwd_workspace_need(const lvx_problem* p, lvx_dtype dtype, const lvx_mask* mask, size_t room) {
   if (check_problem(p, dtype) != LVX_OK || check_mask(p, mask) != LVX_OK) return 0;
-  const Dims d = make_dims(p);
-  const FwdPlan f = fwd_plan(d, dtype, make_mask(mask), 0);
-  return fwd_ws(d, f.n_parts) + f.rows_bytes;
+  return fwd_plan(make_dims(p), dtype, make_mask(mask), 0, room).need;
 }
 }  // namespace lvx
 
@@ -222,12 +224,11 @@ lvx_status lvx_xattn_fwd(const lvx_problem* p, lvx_dtype dtype, const void* q, c
   a.q = q; a.k = k; a.v = v; a.o = o; a.o_is_f32 = o_dtype == LVX_F32; a.lse = lse;
   a.merge_into = 0;
   a.partial = 0; a.part0 = 0; a.pass = 0;
-  const FwdPlan plan = fwd_plan(a.d, dtype, a.mask, 0);
+  const FwdPlan plan = fwd_plan(a.d, dtype, a.mask, 0, workspace_bytes);
   a.n_split = plan.n_split;
   const int n_parts = plan.n_parts;
   a.o_part = nullptr; a.lse_part = nullptr;
-  const size_t need = fwd_ws(a.d, n_parts) + plan.rows_bytes;
-  if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < need) return LVX_ERR_WORKSPACE;
+  if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < plan.need) return LVX_ERR_WORKSPACE;
   a.rows = MaskRows{};
   a.rows_ws = plan.rows_bytes > 0 ? (char*)workspace + fwd_ws(a.d, n_parts) : nullptr;
   hipStream_t s = (hipStream_t)hip_stream;
@@ -271,11 +272,10 @@ lvx_status lvx_xattn_fwd_merge(const lvx_problem* p, lvx_dtype dtype, const void
   a.mask = make_mask(mask);
   a.q = q; a.k = k; a.v = v; a.o_is_f32 = 1;
   a.partial = 0; a.part0 = 0; a.pass = 0;
-  const FwdPlan plan = fwd_plan(a.d, dtype, a.mask, 1);          // (the running state is one more part of the combine)
+  const FwdPlan plan = fwd_plan(a.d, dtype, a.mask, 1, workspace_bytes);          // (the running state is one more part of the combine)
   a.n_split = plan.n_split;
   a.o_part = nullptr; a.lse_part = nullptr;
-  const size_t need = fwd_merge_ws(a.d, dtype, plan.n_parts) + plan.rows_bytes;
-  if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < need) return LVX_ERR_WORKSPACE;
+  if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < plan.need) return LVX_ERR_WORKSPACE;
   a.rows = MaskRows{};
   a.rows_ws = plan.rows_bytes > 0 ? (char*)workspace + fwd_merge_ws(a.d, dtype, plan.n_parts) : nullptr;
   hipStream_t s = (hipStream_t)hip_stream;

@@ -144,8 +144,9 @@ bool project_bwd_bf16_supported(const ProjBwdArgs& a);   // shapes the matrix-co
 hipError_t launch_project_bwd(const ProjBwdArgs& a, int is_f32, hipStream_t s);
 
 // Bytes of workspace that lvx_xattn_fwd needs for exactly this call (with this mask or without
-// one; lvx_xattn_workspace_bytes returns the larger of the two cases); 0 for invalid arguments.
-size_t fwd_workspace_need(const lvx_problem* p, lvx_dtype dtype, const lvx_mask* mask);
+// one; lvx_xattn_workspace_bytes returns the larger of the two cases) when it is given `room`; 0 for
+// invalid arguments.
+size_t fwd_workspace_need(const lvx_problem* p, lvx_dtype dtype, const lvx_mask* mask, size_t room);
 
 // kernels for float32 tensors (float32 matrix instruction; the key range is never split)
 hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t s);

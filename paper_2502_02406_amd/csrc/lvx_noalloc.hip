@@ -37,7 +37,7 @@ extern "C" lvx_status lvx_xattn_fwd_static(const lvx_problem* p, lvx_dtype dtype
                                            const void* k, const void* v, const lvx_mask* mask,
                                            void* o, lvx_dtype o_dtype, float* lse, void* hip_stream) {
   // what this very call needs (invalid arguments give 0: lvx_xattn_fwd below then names the error)
-  const size_t need = lvx::fwd_workspace_need(p, dtype, mask);
+  const size_t need = lvx::fwd_workspace_need(p, dtype, mask, LVX_STATIC_SCRATCH_BYTES);
   if (need > (size_t)LVX_STATIC_SCRATCH_BYTES) return LVX_ERR_WORKSPACE;
   void* ws = nullptr;
   if (scratch_of_current_device(&ws) != hipSuccess) return LVX_ERR_HIP;

@@ -113,3 +113,32 @@ def test_the_largest_probability_is_not_rounded(q_chunk, kv_block, D):
     B.lvx_xattn_fwd(B.make_problem(q, k, 0.0), q, k, v, loop._mask_for(0), o, loop.lse, loop.ws)
     want = v[0, 0, top.repeat_interleave(q_chunk).cuda()].float()
     assert ((o - want).abs() <= 2.0 ** -17 * 0.6932 * want.abs() + 1e-12).all()
+
+
+@pytest.mark.parametrize("merge", [False, True])
+def test_words_that_do_not_fit_the_workspace(merge):
+    # 16 heads x 64 row tiles fill the chip without splits, so that the kernels that do without words need 256 bytes of
+    # workspace: with less than the words take (35 KB) such a call runs on them.  Tolerances: those of bf16.
+    import torch
+    from paper_2502_02406_amd import binding as B
+    from paper_2502_02406_amd.blockloop import BlockLoop, MediaMask
+    g = torch.Generator().manual_seed(15)
+    q = (0.5 * torch.randn((1, 16, 16384, 64), generator=g)).bfloat16().cuda()
+    k, v = (0.5 * torch.randn((1, 16, 1024, 64), generator=g).bfloat16().cuda() for _ in range(2))
+    allow = (torch.rand((4096, 16), generator=g) < 0.5).to(torch.uint8)
+    loop = BlockLoop(tuple(q.shape), tuple(k.shape), torch.bfloat16, 1, MediaMask(allow.cuda(), 4, 64))
+    p, m = B.make_problem(q, k, 0.0), loop._mask_for(0)
+    call = B.lvx_xattn_fwd_merge if merge else B.lvx_xattn_fwd
+
+    def run(ws):
+        o, lse = torch.zeros(q.shape, device="cuda"), torch.full(q.shape[:3], float("-inf"), device="cuda")
+        call(p, q, k, v, m, o, lse, ws)
+        return o, lse
+
+    o, lse = run(loop.ws)
+    o2, lse2 = run(torch.empty(4096, dtype=torch.uint8, device="cuda"))
+    seen = torch.isfinite(lse)
+    assert torch.equal(seen, torch.isfinite(lse2)) and not o2[~seen].any()
+    assert (o - o2).abs().max() <= 1e-2 and (lse - lse2)[seen].abs().max() <= 1e-3
+    with pytest.raises(B.LvxError):
+        run(torch.empty(128, dtype=torch.uint8, device="cuda"))
