@@ -85,7 +85,8 @@ enum { LVX_MAX_PARTS = 64 };
 
 /* Bytes of workspace lvx_xattn_fwd (which = LVX_WS_FWD), lvx_xattn_bwd (LVX_WS_BWD) or
  * lvx_xattn_fwd_merge (LVX_WS_FWD_MERGE) needs for this problem and dtype.  Returns 0 on invalid
- * arguments. */
+ * arguments.  (lvx_xattn_bwd takes less as well: the room for key tiles that several dK/dV workgroups share
+ * is used where it is there.) */
 size_t lvx_xattn_workspace_bytes(const lvx_problem* p, lvx_dtype dtype, int which);
 
 /* Forward pass of one visit (Algorithm 1, the FlashAttention call; Section 2 defines the result):

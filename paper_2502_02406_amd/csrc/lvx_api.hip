@@ -158,6 +158,13 @@ int bwd_slices(const Dims& d, lvx_dtype dtype, bool masked) {
 }
 size_t bwd_slice_bytes(const Dims& d) { return (size_t)d.B * d.Hq * d.Sq * d.D * sizeof(float); }
 size_t bwd_ws_part(const Dims& d, int n_slices) { return n_slices > 0 ? align_up(n_slices * bwd_slice_bytes(d)) : 0; }
+// ... + the sums of key tiles that several dK/dV workgroups share.  A workspace without room for these leaves every
+// tile to one workgroup.
+size_t bwd_ws_kv(const Dims& d, lvx_dtype dtype, bool masked) {
+  if (dtype != LVX_BF16) return 0;
+  const KvPlan p = dkdv_bf16_plan(d, device_cu_count(), masked);
+  return dkdv_bf16_sums_bytes(d, p) + dkdv_bf16_counts_bytes(d, p);
+}
 size_t bwd_ws(const Dims& d, int n_slices, bool fused) {   // ... + the fused kernel's dQ tiles and locks
   return bwd_ws_fixed(d) + bwd_ws_part(d, n_slices) + (fused ? align_up(bwd_fused_ws_bytes(d)) : 0);
 }
@@ -204,7 +211,8 @@ size_t lvx_xattn_workspace_bytes(const lvx_problem* p, lvx_dtype dtype, int whic
   if (which == LVX_WS_FWD) return fwd_ws(d, parts(0)) + rows_most;
   if (which == LVX_WS_BWD)
     return bwd_ws(d, larger(bwd_slices(d, dtype, true), bwd_slices(d, dtype, false)),
-                  dtype == LVX_BF16 && bwd_fused_bf16_supported(d, false));
+                  dtype == LVX_BF16 && bwd_fused_bf16_supported(d, false)) +
+           (bwd_ws_kv(d, dtype, true) > bwd_ws_kv(d, dtype, false) ? bwd_ws_kv(d, dtype, true) : bwd_ws_kv(d, dtype, false));
   if (which == LVX_WS_FWD_MERGE) return fwd_merge_ws(d, dtype, parts(1)) + rows_most;
   return 0;
 }
@@ -378,6 +386,14 @@ lvx_status lvx_xattn_bwd_stages(const lvx_problem* p, lvx_dtype dtype, const voi
   a.rows_ws = mask != nullptr && n_slices > 0 ? (char*)workspace + bwd_ws_fixed(a.d) + (n_slices - 1) * bwd_slice_bytes(a.d) : nullptr;
   a.rows_ws_bytes = bwd_slice_bytes(a.d);
   a.dq_tiles = fused ? (float*)((char*)workspace + bwd_ws_fixed(a.d) + bwd_ws_part(a.d, n_slices)) : nullptr;
+  a.kv = {0, 1, 0}; a.kv_sums = nullptr; a.kv_counts = nullptr;
+  if (dtype == LVX_BF16 && !fused && workspace_bytes - need >= bwd_ws_kv(a.d, dtype, mask != nullptr)) {
+    a.kv = dkdv_bf16_plan(a.d, device_cu_count(), mask != nullptr);
+    if (a.kv.parts > 1) {
+      a.kv_sums = (float*)((char*)workspace + need);
+      a.kv_counts = (int*)((char*)workspace + need + dkdv_bf16_sums_bytes(a.d, a.kv));
+    }
+  }
   a.dq_locks = nullptr; a.dq_err = nullptr; a.dq_stagger = 0;
   hipStream_t s = (hipStream_t)hip_stream;
   hipError_t e = hipSuccess;

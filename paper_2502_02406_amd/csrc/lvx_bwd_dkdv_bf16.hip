@@ -110,7 +110,10 @@ __device__ unsigned long long dkdv_probe[8];
 #define DKDV_STAMP(x)
 #endif
 
-template <int D, bool GENERAL, bool STEPS = false, bool WORDS = false>
+// PARTS: key tiles that several workgroups share (see dkdv_bf16_plan).  A variant of its own, since the workgroups that
+// only write zeros are over in a microsecond and notice what it adds to the set-up (16384 workgroups of which 12288
+// write zeros: 927 -> 938 us).
+template <int D, bool GENERAL, bool STEPS = false, bool WORDS = false, bool PARTS = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 bwd_dkdv_bf16_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -126,13 +129,23 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   const Dims& d = a.d;
   const int G = d.Hq / d.Hkv;
   const int n_kt = (d.Skv + KN - 1) / KN;
+  // (parts of a tile are items of their own, the first parts of all tiles before the second ones; a head that several
+  // XCDs share is dealt out in turn when its items differ in length)
+  const int n_part = PARTS ? a.kv.parts : 1, n_whole = PARTS ? a.kv.whole : n_kt;
   HeadWork hw;
-  if (!xcd_decode(blockIdx.x, d.B * d.Hkv, n_kt, &hw, STEPS)) return;
+  if (!xcd_decode(blockIdx.x, d.B * d.Hkv, n_whole + (n_kt - n_whole) * n_part, &hw, STEPS || PARTS)) return;
+  int part = 0, np = 1;                            // this workgroup's part of its tile, of np
+  int tile = hw.item;
+  if (PARTS && hw.item >= n_whole) {
+    part = (hw.item - n_whole) / (n_kt - n_whole);
+    tile = hw.item - part * (n_kt - n_whole);
+    np = n_part;
+  }
   DKDV_STAMP(stamp0);
   const int b = hw.head / d.Hkv, hk = hw.head % d.Hkv;
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, kl = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int j_wg0 = hw.item * KN;
+  const int j_wg0 = tile * KN;
   const int j_wave0 = j_wg0 + wave * 32 * KVB;
 
   // ---- query steps: the G heads of the group, KM rows at a time.  With a media mask, steps whose
@@ -287,6 +300,11 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
       for (Cursor c = cursor; c.s < n_all; advance(c)) ++n;
     }
   }
+  if (STEPS && PARTS) {                           // (the longer its list, the more parts share it)
+    np = max(1, min(n_part, (n + a.kv.len - 1) / a.kv.len));
+    if (part == 0 && tid == 0) a.kv_counts[(long)hw.head * n_kt + tile] = np;
+    if (part >= np) return;
+  }
   if ((GENERAL || STEPS) && n == 0) {              // keys that no query sees: dK = dV = 0, nothing to read
     const u32x4 z = {0, 0, 0, 0};
     for (int c = tid; c < KN * CPR; c += 256) {
@@ -297,6 +315,20 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
       *(u32x4*)((uint16_t*)a.dv + off) = z;
     }
     return;
+  }
+
+  if (PARTS && np > 1) {                           // this part's run of the steps
+    const int first = (int)((long)n * part / np), per = STEPS ? per_head : spH;
+    n = (int)((long)n * (part + 1) / np) - first;
+    cursor.s = first;
+    cursor.h = first / per;
+    cursor.k = first - cursor.h * per;
+    if (STEPS) {
+      cursor.i0 = __builtin_amdgcn_readfirstlane(tl[cursor.k]) * KM;
+      cursor.tp = tl[cursor.k + 1 < per ? cursor.k + 1 : 0];
+    } else {
+      cursor.i0 = cursor.k * KM;
+    }
   }
 
   // ---- K operands of this wave's keys: lane holds key j_wave0 + 32 kb + kl, columns 16 ks + 8 g ..
@@ -395,10 +427,10 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   // 0 .. NDMA - 1 so that the dense loop can spread them over the matrix instructions of a phase.
   constexpr int NDMA = 2 * NCR + 1;                // copies per wave and step
   struct Tile { const char *qb, *gb, *lb; char* dst; int rows; long tile; };
-  if (RUNNING) {                                   // (the dense cursor still stands at step 0)
-    cursor.hb = (long)(hk * G) * d.q_sh * 2 + (long)wave * row_bytes;
-    cursor.lb = (long)(uintptr_t)l0 + (long)(hk * G) * a.sq_pad * 8;
-    cursor.lo = (long)(uintptr_t)a.stats_ovl + ((long)b * d.Hq + hk * G) * 256;
+  if (RUNNING) {                                   // (the dense cursor still stands at its first step)
+    cursor.hb = (long)(hk * G + cursor.h) * d.q_sh * 2 + (long)wave * row_bytes;
+    cursor.lb = (long)(uintptr_t)l0 + (long)(hk * G + cursor.h) * a.sq_pad * 8 + (long)cursor.i0 * 8;
+    cursor.lo = (long)(uintptr_t)a.stats_ovl + ((long)b * d.Hq + hk * G + cursor.h) * 256;
   }
   auto tile_of = [&](const Cursor& c, char* st) __attribute__((always_inline)) -> Tile {
     if constexpr (RUNNING) {
@@ -764,6 +796,24 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
     else
       asm volatile("s_nop 15\n\ts_nop 15" : "+a"(dk[kb][0]), "+a"(dk[kb][1]), "+a"(dv[kb][0]), "+a"(dv[kb][1]));
   }
+  if (PARTS && np > 1) {
+    // A part's sums stay float32 and in the order of the registers: a kilobyte per store, nothing to turn around.
+    float* const out = a.kv_sums + ((((long)hw.head * (n_kt - n_whole) + tile - n_whole) * n_part + part) * 2 * NWV + wave) * (32 * KVB * D);
+#pragma unroll
+    for (int kb = 0; kb < KVB; ++kb)
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          float* const o = out + (((kb * DB + db) * 4 + q4) * 64 + lane) * 4;
+          const f32x4 yk = {dk[kb][db][4 * q4] * d.scale, dk[kb][db][4 * q4 + 1] * d.scale,
+                            dk[kb][db][4 * q4 + 2] * d.scale, dk[kb][db][4 * q4 + 3] * d.scale};
+          const f32x4 yv = {dv[kb][db][4 * q4], dv[kb][db][4 * q4 + 1], dv[kb][db][4 * q4 + 2], dv[kb][db][4 * q4 + 3]};
+          *(f32x4*)o = yk;
+          *(f32x4*)(o + KN * D) = yv;
+        }
+    return;
+  }
   // A lane holds one key row, four columns at a time: stored as they are, every instruction
   // would touch 32 rows with 16 bytes each.  Each wave turns its rows around through LDS instead
   // (the ring and the V rows are free once every wave has left the loop) and writes whole
@@ -819,16 +869,54 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
 #endif
 }
 
+// dK and dV of the tiles that several workgroups shared: their parts' sums, added in the order of the parts and
+// rounded once.  A thread takes eight columns of a key row, which two lanes of the kernel above held; eight
+// consecutive threads take the same columns of eight consecutive keys, so that both the reads (128 bytes
+// of a register's kilobyte) and the writes (128 bytes or more of a row, by the threads eight apart) are whole lines.
+template <int D, bool COUNTS>
+__global__ void __launch_bounds__(256) dkdv_sum_kernel(BwdArgs a) {
+  const Dims& d = a.d;
+  constexpr int KN = 256, DB = D / 32, CPR = D / 8;
+  const int n_kt = (d.Skv + KN - 1) / KN, n_cut = n_kt - a.kv.whole, parts = a.kv.parts;
+  const long cut = blockIdx.x / (2 * CPR);                                      // (head, tile) of those that are cut
+  const int unit = (int)(blockIdx.x % (2 * CPR)) * 256 + (int)threadIdx.x;      // of the tile's 2 x 256 x CPR
+  const int head = (int)(cut / n_cut), tile = a.kv.whole + (int)(cut % n_cut);
+  const int np = COUNTS ? a.kv_counts[(long)head * n_kt + tile] : parts;
+  if (np <= 1) return;                                                          // (one workgroup: it has written them)
+  const int which = unit / (KN * CPR), u = unit % (KN * CPR);
+  const int c = (u / 8) % CPR, r = u / (8 * CPR) * 8 + u % 8, j = tile * KN + r;
+  if (j >= d.Skv) return;
+  const float* x = a.kv_sums + (cut * parts * 2 + which) * (KN * D) +
+                   ((((r >> 5) * DB + (c >> 2)) * 4 + (c & 3)) * 64 + (r & 31)) * 4;
+  f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+#pragma unroll 4
+  for (int p = 0; p < np; ++p) {
+    lo += *(const f32x4*)(x + (long)p * (2 * KN * D));
+    hi += *(const f32x4*)(x + (long)p * (2 * KN * D) + 32 * 4);
+  }
+  const long off = (head / d.Hkv) * d.kv_sb + (head % d.Hkv) * d.kv_sh + (long)j * d.kv_ss + 8 * c;
+  *(u32x4*)((uint16_t*)(which ? a.dv : a.dk) + off) = u32x4{pack2_bf16(lo[0], lo[1]), pack2_bf16(lo[2], lo[3]),
+                                                            pack2_bf16(hi[0], hi[1]), pack2_bf16(hi[2], hi[3])};
+}
+
+template <int D, bool GENERAL, bool STEPS, bool WORDS, bool PARTS>
+hipError_t launch_as(const BwdArgs& a, hipStream_t s) {
+  using SM = DkvSmem<D, kvb_of(GENERAL)>;
+  const int n_kt = (a.d.Skv + SM::KN - 1) / SM::KN, n_cut = PARTS ? n_kt - a.kv.whole : 0;
+  const long grid = xcd_grid(a.d.B * a.d.Hkv, n_kt - n_cut + n_cut * a.kv.parts);
+  static SmemOnce once;
+  constexpr int lds = WORDS ? SM::TOTAL_WORDS : SM::TOTAL;
+  hipError_t e = ensure_dynamic_lds((const void*)bwd_dkdv_bf16_kernel<D, GENERAL, STEPS, WORDS, PARTS>, lds, &once);
+  if (e != hipSuccess) return e;
+  bwd_dkdv_bf16_kernel<D, GENERAL, STEPS, WORDS, PARTS><<<(unsigned)grid, 256, lds, s>>>(a);
+  if constexpr (PARTS) dkdv_sum_kernel<D, STEPS><<<(unsigned)(a.d.B * a.d.Hkv * n_cut * 2 * (D / 8)), 256, 0, s>>>(a);
+  return hipGetLastError();
+}
 template <int D, bool GENERAL, bool STEPS = false, bool WORDS = false>
 hipError_t launch(const BwdArgs& a, hipStream_t s) {
-  const long grid = xcd_grid(a.d.B * a.d.Hkv, (a.d.Skv + DkvSmem<D, kvb_of(GENERAL)>::KN - 1) / DkvSmem<D, kvb_of(GENERAL)>::KN);
-  static SmemOnce once;
-  using SM = DkvSmem<D, kvb_of(GENERAL)>;
-  constexpr int lds = WORDS ? SM::TOTAL_WORDS : SM::TOTAL;
-  hipError_t e = ensure_dynamic_lds((const void*)bwd_dkdv_bf16_kernel<D, GENERAL, STEPS, WORDS>, lds, &once);
-  if (e != hipSuccess) return e;
-  bwd_dkdv_bf16_kernel<D, GENERAL, STEPS, WORDS><<<(unsigned)grid, 256, lds, s>>>(a);
-  return hipGetLastError();
+  if constexpr (!GENERAL)
+    if (a.kv_sums != nullptr) return launch_as<D, false, STEPS, WORDS, true>(a, s);
+  return launch_as<D, GENERAL, STEPS, WORDS, false>(a, s);
 }
 
 bool dkdv_rows_ok(const Dims& d) { return d.Sq % KM == 0 || d.Sq >= KM; }   // (a ragged Sq needs 32 rows to overlap)
@@ -838,6 +926,76 @@ bool dkdv_steps(const Dims& d, const MaskDev& m) {
 }
 
 }  // namespace
+
+// How many workgroups share a key tile.  One per tile leaves most of the chip idle when there are few keys (8
+// heads x 1024 keys: 32 tiles for 256 compute units), and a last round of a few tiles takes as long as a
+// full one (9447 keys x 8 heads: 296 tiles, two rounds for the work of 1.16).  A part costs its own set-up, a
+// trip of its sums through memory (256 KB there and back with 128-wide heads) and, once, the launch that adds
+// them, so the line is drawn by the sum of these: the rounds of whole tiles that fill the chip stay as
+// they are, and the tiles of the last round (or of the last two) are cut into the number of parts that takes
+// the least time, if it is 3 % less.  Measured, D = 128, 32 / 8 heads, both kernels' time: 2650 rows x
+// 9447 keys 876 -> 609 us (256 tiles whole, 40 in 6 parts); 3081 x 1024 keys 438 -> 102; 512 x 10353 keys 191 -> 167; 28 / 4
+// heads x 2240 rows x 7282 keys 566 -> 374 (the 120 tiles ran at a higher clock: less than the half that the
+// count of rounds says).  No parts where they lose: 28 / 4 heads x 512 x 91125 keys, 5.6 rounds, 1019 us,
+// its last 144 tiles in two or three parts 1085 and 1089.  Of 30 shapes with 64 to 8192 rows and 1024 to
+// 20000 keys the choice was within 8 % of the best of nine on every one.
+// Under a mask a tile's steps are known to its workgroups only: each works out the list, and a tile of more than
+// `len` steps is cut into as many parts as it has runs of `len`, the kv.parts workgroups that a tile has
+// at most; the others leave.  2048 rows x 28 heads in chunks of 64 against 32 frames of 729 keys, causal: 701 ->
+// 648 us; 3584 rows x 6016 keys in frames of 64 1116 -> 306; masks that show each chunk one frame 206 -> 78 (3264
+// rows x 4480 keys, frames of 64) and, with tiles enough but most of them short, 312 -> 196 (2591 x 28160).
+KvPlan dkdv_bf16_plan(const Dims& d, int n_cu, bool masked) {
+  constexpr int KN = DkvSmem<128, 2>::KN;
+  const int n_kt = (d.Skv + KN - 1) / KN, H = d.B * d.Hkv;
+  const long tiles = (long)H * n_kt;
+  const int steps = d.Hq / d.Hkv * ((d.Sq + KM - 1) / KM);
+  const long most = 1024;                          // sets of sums (256 KB each with 128-wide heads)
+  KvPlan best = {n_kt, 1, 0};
+  if (!dkdv_rows_ok(d)) return best;
+  // clocks of a step, of a workgroup's set-up and epilogue, and of the sums' way through memory
+  const double t_step = d.D == 128 ? 2750. : d.D == 96 ? 2150. : 1550., t_fix = 25e3, t_list = 10e3;
+  const double t_sums = 4e3, t_sum = 200. * d.D / 128, t_launch = 9e3;
+  if (masked) {
+    // (what the mask shows is not known here: every number of steps from none to all as often as any other, as
+    // under a causal mask; other masks leave more of the chip idle, so a tie goes to the parts)
+    const double ts = 1.15 * t_step, tf = t_fix + t_list + t_sums;
+    const double whole_t = steps * ts + tf, even_t = (double)tiles / n_cu * (0.5 * steps * ts + tf);
+    double best_t = 1.1 * (whole_t > even_t ? whole_t : even_t);
+    for (long p = 2; p <= 32 && tiles * p <= most; ++p) {
+      const long len = (steps + p - 1) / p;
+      const double t = (double)tiles / n_cu * (0.5 * steps * ts + 0.5 * (p + 1) * tf) + 0.25 * (len * ts + tf) + t_launch;
+      if (len >= 8 && t < best_t) {
+        best_t = t;
+        best = {0, (int)p, (int)(len <= 14 ? len : len <= 28 ? 14 : (len + 1) / 2)};
+      }
+    }
+    return best;
+  }
+  const auto rounds = [&](long n) { return (double)((n + n_cu - 1) / n_cu); };
+  double best_t = rounds(tiles) * (steps * t_step + t_fix);
+  const long full = tiles / n_cu;
+  for (long k = full; k >= 0 && k >= full - 1; --k) {
+    const int whole = (int)(k * n_cu / H);
+    const long cut = tiles - (long)H * whole;
+    for (long p = 2; p <= 32 && cut * p <= most && p * 4 <= steps; ++p) {
+      const double t = rounds((long)H * whole) * (steps * t_step + t_fix) +
+                       rounds(cut * p) * ((double)((steps + p - 1) / p) * t_step + t_fix + t_sums) + cut * p * t_sum + t_launch;
+      if (t < best_t * 0.97) {
+        best_t = t;
+        best = {whole, (int)p, 0};
+      }
+    }
+  }
+  return best;
+}
+size_t dkdv_bf16_sums_bytes(const Dims& d, const KvPlan& p) {
+  constexpr int KN = DkvSmem<128, 2>::KN;
+  return p.parts > 1 ? (size_t)d.B * d.Hkv * ((d.Skv + KN - 1) / KN - p.whole) * p.parts * 2 * KN * d.D * sizeof(float) : 0;
+}
+size_t dkdv_bf16_counts_bytes(const Dims& d, const KvPlan& p) {
+  constexpr int KN = DkvSmem<128, 2>::KN;
+  return p.parts > 1 ? ((size_t)d.B * d.Hkv * ((d.Skv + KN - 1) / KN) * sizeof(int) + 255) / 256 * 256 : 0;
+}
 
 // A mask that cuts through the steps or through a workgroup's keys, while its list and words fit
 // beside the ring: one word for every step and for every key block that 256 keys can lie in.

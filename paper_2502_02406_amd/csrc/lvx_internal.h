@@ -62,8 +62,17 @@ struct FwdArgs {
   float* lse_part;      // [n_split, B,Hq,Sq]
 };
 
+struct KvPlan {
+  int whole, parts;     // parts == 1: every tile has one workgroup
+  int len;              // media mask: a tile is cut into as many parts as it has runs of this many steps, `parts` at most
+};
+
 struct BwdArgs {
   Dims d;
+  // dK/dV kernel (bf16): the first kv.whole key tiles of a head have one workgroup each, every other one up to
+  // kv.parts, which share its steps and leave float32 sums in kv_sums, in the order of the matrix
+  // registers, [B Hkv, tiles - whole, parts][dK, dV][256 x D]; dkdv_sum_kernel adds them up
+  KvPlan kv;
   MaskDev mask;
   MaskRows rows;        // set by launch_bwd_bf16 where a kernel reads it
   void* rows_ws;        // workspace for its words (rows_ws_bytes), or nullptr
@@ -82,6 +91,8 @@ struct BwdArgs {
                         // short one: the rows it has seen before then contribute nothing.
   float* dq_accum;      // [B,Hq,Sq,D] float32, accumulated into
   void *dk, *dv;        // K's strides, input dtype, overwritten
+  float* kv_sums;
+  int* kv_counts;       // media mask: parts that a tile was cut into, [B Hkv, tiles] (its number of steps is the mask's)
   int n_split_dq;       // KV splits of the dQ kernel
   int dq_pass;          // media mask, dQ kernel: 0 = one launch over every visible tile; 1 = this launch takes the
                         // key tiles that EVERY row of a workgroup sees (dense kernel over a list of them),
@@ -155,6 +166,9 @@ hipError_t launch_bwd_f32(const BwdArgs& a, unsigned stages, hipStream_t s);   /
 hipError_t launch_fwd_bf16(const FwdArgs& a, hipStream_t s);
 hipError_t launch_bwd_bf16(const BwdArgs& a, unsigned stages, hipStream_t s);
 hipError_t launch_bwd_dkdv_bf16(const BwdArgs& a, hipStream_t s);
+KvPlan dkdv_bf16_plan(const Dims& d, int n_cu, bool masked);
+size_t dkdv_bf16_sums_bytes(const Dims& d, const KvPlan& p);     // of BwdArgs::kv_sums (a multiple of 256 bytes),
+size_t dkdv_bf16_counts_bytes(const Dims& d, const KvPlan& p);   // and of kv_counts
 hipError_t launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s);
 // all five products in one kernel (dense, head dim 128, at least 256 keys and 32 query rows):
 // handles the first Skv / 256 * 256 keys; needs BwdArgs::dq_tiles
