@@ -82,9 +82,12 @@ MaskDev make_mask(const lvx_mask* m) {
 int fwd_split(const Dims& d, lvx_dtype dtype, bool masked) {
   return dtype == LVX_BF16 ? fwd_bf16_pick_split(d, device_cu_count(), masked) : 1;
 }
-int bwd_split(const Dims& d, lvx_dtype dtype, bool masked) {
-  return dtype == LVX_BF16 ? bwd_bf16_pick_split(d, device_cu_count(), masked) : 1;
+TailPlan bwd_split(const Dims& d, lvx_dtype dtype, bool masked) {
+  if (dtype == LVX_BF16 && bwd_dq_bf16_dense(d, masked)) return bwd_dq_bf16_dense_plan(d, device_cu_count());
+  return {0, dtype == LVX_BF16 ? bwd_bf16_pick_split(d, device_cu_count(), masked) : 1};
 }
+
+int fwd_list_split(const Dims& d) { return list_split((long)d.B * d.Hq * ((d.Sq + 255) / 256), (d.Skv + 63) / 64); }
 
 // bf16 under a media mask that fits (fwd_bf16_two_pass_fits): the dense kernel over the key tiles
 // that every row of a workgroup sees, then the general kernel on the other visible tiles; each
@@ -104,42 +107,59 @@ hipError_t launch_fwd_bf16_two_pass(FwdArgs a, hipStream_t s) {
   return launch_fwd_bf16(a, s);
 }
 
-size_t fwd_ws(const Dims& d, int n_split) {
+size_t split_rows(const Dims& d, int whole) {   // rows that are split: all but the first `whole` tiles of 256 of a group
+  return (size_t)d.B * d.Hkv * ((long)d.G * d.Sq - 256L * whole);
+}
+size_t fwd_ws(const Dims& d, int n_split, int whole = 0) {
   if (n_split <= 1) return ALIGN;   // never zero, so that a valid workspace pointer is always passed
-  const size_t rows = (size_t)d.B * d.Hq * d.Sq;
+  const size_t rows = split_rows(d, whole);
   return align_up(rows * d.D * sizeof(float) * n_split) + align_up(rows * sizeof(float) * n_split);
 }
 // lvx_xattn_fwd_merge: the splits' partial results (bf16 kernels that split the key range).  The float32
 // kernels, which merge in their epilogue, leave theirs alone; callers give them room for a partial result all the same.
-size_t fwd_merge_ws(const Dims& d, lvx_dtype dtype, int n_split) {
-  return fwd_ws(d, dtype == LVX_F32 ? 2 : n_split);      // (fwd_ws(d, 2) holds more than one partial result)
+size_t fwd_merge_ws(const Dims& d, lvx_dtype dtype, int n_split, int whole = 0) {
+  return fwd_ws(d, dtype == LVX_F32 ? 2 : n_split, whole);      // (fwd_ws(d, 2) holds more than one partial result)
 }
 // How a forward call runs: the KV splits of each launch, whether a media mask makes it two launches,
 // the partial results the combine then reads, the bytes of MaskRows' words the kernel reads, and the
-// workspace it all takes.  `reserve` parts of the combine are taken already (lvx_xattn_fwd_merge: the
+// workspace it all takes.  The dense kernel leaves the first `whole` row tiles of a K/V head unsplit.  `reserve` parts of the combine are taken already (lvx_xattn_fwd_merge: the
 // running state).
-struct FwdPlan { int n_split; bool two; int n_parts; size_t rows_bytes, need; };
-FwdPlan fwd_plan_with(const Dims& d, lvx_dtype dtype, const MaskDev& m, int reserve, bool rows) {
+struct FwdPlan { int n_split, whole; bool two; int n_parts; size_t rows_bytes, need; };
+FwdPlan fwd_plan_with(const Dims& d, lvx_dtype dtype, const MaskDev& m, int reserve, bool rows, size_t room) {
   const bool masked = m.allow != nullptr, bf16 = dtype == LVX_BF16;
   FwdPlan f;
+  f.whole = 0;
   f.n_split = fwd_split(d, dtype, masked);
   if (f.n_split > LVX_MAX_PARTS - reserve) f.n_split = LVX_MAX_PARTS - reserve;
   f.two = masked && bf16 && !rows && fwd_bf16_two_pass_fits(d, m);
   if (f.two) f.n_split = fwd_two_pass_split(f.n_split, reserve);
   f.rows_bytes = rows ? align_up(mask_rows_bytes(d, mask_rows_of(d, m))) : 0;
-  // (one launch over tile lists: its workgroups start longest first, which evens the load out
-  // with half the splits the other masked forms want)
-  if (masked && bf16 && (rows || fwd_bf16_one_pass_fits(d, m)) && f.n_split > 1) f.n_split /= 2;
-  f.n_parts = f.two ? 2 * f.n_split : f.n_split;
-  f.need = (reserve ? fwd_merge_ws(d, dtype, f.n_parts) : fwd_ws(d, f.n_parts)) + f.rows_bytes;
-  return f;
+  const bool list = masked && bf16 && (rows || fwd_bf16_one_pass_fits(d, m));
+  if (list) f.n_split = fwd_list_split(d);
+  for (;;) {
+    f.n_parts = f.two ? 2 * f.n_split : f.n_split;
+    f.need = (reserve ? fwd_merge_ws(d, dtype, f.n_parts) : fwd_ws(d, f.n_parts)) + f.rows_bytes;
+    if (!list || f.need <= room || f.n_split == 1) return f;
+    f.n_split /= 2;                      // (a list can be shared by any number)
+  }
 }
 // ... in a workspace of `room` bytes.  Words that do not fit (262144 rows against 131072 keys in blocks of 64: 68
 // MB, where the general kernel needs nothing) leave the call to the kernels that do without.
+FwdPlan fwd_dense_plan(const Dims& d, int reserve, size_t room) {
+  // (a set of partial results: 256 rows of O and L)
+  const size_t most = (size_t)1 << 40, sets = (room < most ? room : most) / (256 * (d.D + 1) * sizeof(float) + ALIGN);
+  const TailPlan t = fwd_bf16_dense_plan(d, device_cu_count(), LVX_MAX_PARTS - reserve, (long)sets);
+  return {t.parts, t.whole, false, t.parts, 0, fwd_ws(d, t.parts, t.whole)};
+}
 FwdPlan fwd_plan(const Dims& d, lvx_dtype dtype, const MaskDev& m, int reserve, size_t room) {
+  if (dtype == LVX_BF16 && fwd_bf16_dense(d, m.allow != nullptr)) {
+    FwdPlan f = fwd_dense_plan(d, reserve, SIZE_MAX);
+    if (f.need > room) f = fwd_dense_plan(d, reserve, room);      // (fewer parts, or none)
+    return f.need > room ? fwd_dense_plan(d, reserve, 0) : f;
+  }
   const bool rows = m.allow != nullptr && dtype == LVX_BF16 && fwd_bf16_takes_rows(d, m);
-  const FwdPlan f = fwd_plan_with(d, dtype, m, reserve, rows);
-  return rows && f.need > room ? fwd_plan_with(d, dtype, m, reserve, false) : f;
+  const FwdPlan f = fwd_plan_with(d, dtype, m, reserve, rows, room);
+  return rows && f.need > room ? fwd_plan_with(d, dtype, m, reserve, false, room) : f;
 }
 int sq_padded(const Dims& d) { return (d.Sq + 31) / 32 * 32; }
 bool has_stats_ovl(const Dims& d) { return d.Sq % 32 != 0 && d.Sq >= 32; }
@@ -151,13 +171,18 @@ size_t bwd_ws_fixed(const Dims& d) {   // delta [B,Hq,Sq] + padded statistics [B
 }
 // The dQ kernel's partial sums [n, B,Hq,Sq,D] when it splits.  A masked bf16 call always has one
 // slice at least: the words of MaskRows go into the last slice, which the kernels that read them
-// leave alone (they use half the splits), and which the others fill only after the words' last reader.
+// leave alone (list_split, one less at least), and which the others fill only after the words' last reader.
 int bwd_slices(const Dims& d, lvx_dtype dtype, bool masked) {
-  const int n = bwd_split(d, dtype, masked);
+  int n = bwd_split(d, dtype, masked).parts;
+  if (masked && dtype == LVX_BF16 && n <= fwd_list_split(d)) n = fwd_list_split(d) + 1;
   return n > 1 || (masked && dtype == LVX_BF16) ? n : 0;
 }
 size_t bwd_slice_bytes(const Dims& d) { return (size_t)d.B * d.Hq * d.Sq * d.D * sizeof(float); }
-size_t bwd_ws_part(const Dims& d, int n_slices) { return n_slices > 0 ? align_up(n_slices * bwd_slice_bytes(d)) : 0; }
+size_t bwd_ws_part(const Dims& d, lvx_dtype dtype, bool masked) {
+  const int n = bwd_slices(d, dtype, masked);
+  if (masked || n == 0) return align_up(n * bwd_slice_bytes(d));
+  return align_up(n * split_rows(d, bwd_split(d, dtype, masked).whole) * d.D * sizeof(float));
+}
 // ... + the sums of key tiles that several dK/dV workgroups share.  A workspace without room for these leaves every
 // tile to one workgroup.
 size_t bwd_ws_kv(const Dims& d, lvx_dtype dtype, bool masked) {
@@ -165,8 +190,8 @@ size_t bwd_ws_kv(const Dims& d, lvx_dtype dtype, bool masked) {
   const KvPlan p = dkdv_bf16_plan(d, device_cu_count(), masked);
   return dkdv_bf16_sums_bytes(d, p) + dkdv_bf16_counts_bytes(d, p);
 }
-size_t bwd_ws(const Dims& d, int n_slices, bool fused) {   // ... + the fused kernel's dQ tiles and locks
-  return bwd_ws_fixed(d) + bwd_ws_part(d, n_slices) + (fused ? align_up(bwd_fused_ws_bytes(d)) : 0);
+size_t bwd_ws(const Dims& d, lvx_dtype dtype, bool masked, bool fused) {   // ... + the fused kernel's dQ tiles and locks
+  return bwd_ws_fixed(d) + bwd_ws_part(d, dtype, masked) + (fused ? align_up(bwd_fused_ws_bytes(d)) : 0);
 }
 
 }  // namespace
@@ -206,14 +231,19 @@ size_t lvx_xattn_workspace_bytes(const lvx_problem* p, lvx_dtype dtype, int whic
   const auto parts = [&](int reserve) {
     const int masked = dtype == LVX_BF16 ? 2 * fwd_two_pass_split(fwd_split(d, dtype, true), reserve) : 1;
     const auto cap = [&](int n) { return n < LVX_MAX_PARTS - reserve ? n : LVX_MAX_PARTS - reserve; };
-    return larger(larger(masked, cap(fwd_split(d, dtype, true))), cap(fwd_split(d, dtype, false)));
+    return larger(larger(masked, larger(cap(fwd_split(d, dtype, true)), dtype == LVX_BF16 ? fwd_list_split(d) : 1)),
+                  cap(fwd_split(d, dtype, false)));
   };
-  if (which == LVX_WS_FWD) return fwd_ws(d, parts(0)) + rows_most;
+  const auto most = [](size_t x, size_t y) { return x > y ? x : y; };
+  const auto dense = [&](int reserve) -> size_t {
+    return dtype == LVX_BF16 && fwd_bf16_dense(d, false) ? fwd_dense_plan(d, reserve, SIZE_MAX).need : 0;
+  };
+  if (which == LVX_WS_FWD) return most(fwd_ws(d, parts(0)) + rows_most, dense(0));
   if (which == LVX_WS_BWD)
-    return bwd_ws(d, larger(bwd_slices(d, dtype, true), bwd_slices(d, dtype, false)),
-                  dtype == LVX_BF16 && bwd_fused_bf16_supported(d, false)) +
-           (bwd_ws_kv(d, dtype, true) > bwd_ws_kv(d, dtype, false) ? bwd_ws_kv(d, dtype, true) : bwd_ws_kv(d, dtype, false));
-  if (which == LVX_WS_FWD_MERGE) return fwd_merge_ws(d, dtype, parts(1)) + rows_most;
+    // (the dK/dV sums go behind whichever of the two it is)
+    return most(bwd_ws(d, dtype, true, false) + bwd_ws_kv(d, dtype, true),
+                bwd_ws(d, dtype, false, dtype == LVX_BF16 && bwd_fused_bf16_supported(d, false)) + bwd_ws_kv(d, dtype, false));
+  if (which == LVX_WS_FWD_MERGE) return most(fwd_merge_ws(d, dtype, parts(1)) + rows_most, dense(1));
   return 0;
 }
 
@@ -234,13 +264,14 @@ lvx_status lvx_xattn_fwd(const lvx_problem* p, lvx_dtype dtype, const void* q, c
   a.partial = 0; a.part0 = 0; a.pass = 0;
   const FwdPlan plan = fwd_plan(a.d, dtype, a.mask, 0, workspace_bytes);
   a.n_split = plan.n_split;
+  a.whole = plan.whole;
   const int n_parts = plan.n_parts;
   a.o_part = nullptr; a.lse_part = nullptr;
   if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < plan.need) return LVX_ERR_WORKSPACE;
   a.rows = MaskRows{};
   a.rows_ws = plan.rows_bytes > 0 ? (char*)workspace + fwd_ws(a.d, n_parts) : nullptr;
   hipStream_t s = (hipStream_t)hip_stream;
-  const size_t rows = (size_t)a.d.B * a.d.Hq * a.d.Sq;
+  const size_t rows = split_rows(a.d, a.whole);
   if (n_parts > 1) {
     a.o_part = (float*)workspace;
     a.lse_part = (float*)((char*)workspace + align_up(rows * a.d.D * sizeof(float) * n_parts));
@@ -257,6 +288,7 @@ lvx_status lvx_xattn_fwd(const lvx_problem* p, lvx_dtype dtype, const void* q, c
     }
     m.o_slices = a.o_part; m.lse_slices = a.lse_part; m.first = 0;
     m.rows = (long)rows; m.D = a.d.D; m.o_out = o; m.lse_out = lse;
+    m.group = a.d.G * a.d.Sq; m.skip = 256 * a.whole;
     m.Hq = a.d.Hq; m.Sq = a.d.Sq; m.o_sb = a.d.q_sb; m.o_sh = a.d.q_sh; m.o_ss = a.d.q_ss;
     e = launch_merge(m, 1, a.o_is_f32, s);
     if (e != hipSuccess) return LVX_ERR_HIP;
@@ -282,23 +314,25 @@ lvx_status lvx_xattn_fwd_merge(const lvx_problem* p, lvx_dtype dtype, const void
   a.partial = 0; a.part0 = 0; a.pass = 0;
   const FwdPlan plan = fwd_plan(a.d, dtype, a.mask, 1, workspace_bytes);          // (the running state is one more part of the combine)
   a.n_split = plan.n_split;
+  a.whole = plan.whole;
   a.o_part = nullptr; a.lse_part = nullptr;
   if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < plan.need) return LVX_ERR_WORKSPACE;
   a.rows = MaskRows{};
   a.rows_ws = plan.rows_bytes > 0 ? (char*)workspace + fwd_merge_ws(a.d, dtype, plan.n_parts) : nullptr;
   hipStream_t s = (hipStream_t)hip_stream;
-  const size_t rows = (size_t)a.d.B * a.d.Hq * a.d.Sq;
+  const size_t rows = split_rows(a.d, a.whole);
   if (plan.n_parts == 1) {   // Rescale in the kernel's epilogue
     a.o = o_acc; a.lse = lse_acc; a.merge_into = 1;
     return (dtype == LVX_BF16 ? launch_fwd_bf16(a, s) : launch_fwd_f32(a, s)) == hipSuccess ? LVX_OK : LVX_ERR_HIP;
   }
   // partial results in the workspace, then one combine over the running state and them (the float32
   // kernels never split the key range)
-  a.merge_into = 0;
+  // (the tiles that are not split merge in the epilogue all the same)
+  a.merge_into = 1;
   const int n_parts = plan.n_parts;
   float* const o_part = (float*)workspace;
   float* const l_part = (float*)((char*)workspace + align_up(rows * a.d.D * sizeof(float) * n_parts));
-  a.o = nullptr; a.lse = nullptr; a.o_part = o_part; a.lse_part = l_part;
+  a.o = o_acc; a.lse = lse_acc; a.o_part = o_part; a.lse_part = l_part;
   hipError_t e = plan.two ? launch_fwd_bf16_two_pass(a, s) : launch_fwd_bf16(a, s);
   if (e != hipSuccess) return LVX_ERR_HIP;
   MergeArgs m;
@@ -310,6 +344,7 @@ lvx_status lvx_xattn_fwd_merge(const lvx_problem* p, lvx_dtype dtype, const void
   }
   m.o_slices = o_part; m.lse_slices = l_part; m.first = 1;
   m.rows = (long)rows; m.D = a.d.D; m.o_out = o_acc; m.lse_out = lse_acc;
+  m.group = a.d.G * a.d.Sq; m.skip = 256 * a.whole;
   m.Hq = a.d.Hq; m.Sq = a.d.Sq; m.o_ss = a.d.D; m.o_sh = (long)a.d.Sq * a.d.D; m.o_sb = (long)a.d.Hq * a.d.Sq * a.d.D;
   e = launch_merge(m, 1, 1, s);
   return e == hipSuccess ? LVX_OK : LVX_ERR_HIP;
@@ -334,7 +369,7 @@ lvx_status lvx_xattn_merge(int32_t B, int32_t Hq, int32_t Sq, int32_t D, int32_t
   }
   m.n_parts = n_parts;
   m.o_slices = m.lse_slices = nullptr; m.first = 0;
-  m.rows = (long)B * Hq * Sq; m.D = D; m.o_out = o_out; m.lse_out = lse_out;
+  m.rows = (long)B * Hq * Sq; m.group = 1; m.skip = 0; m.D = D; m.o_out = o_out; m.lse_out = lse_out;
   m.Hq = Hq; m.Sq = Sq; m.o_ss = D; m.o_sh = (long)Sq * D; m.o_sb = (long)Hq * Sq * D;
   hipError_t e = launch_merge(m, part_dtype == LVX_F32, out_dtype == LVX_F32, (hipStream_t)hip_stream);
   return e == hipSuccess ? LVX_OK : LVX_ERR_HIP;
@@ -365,7 +400,9 @@ lvx_status lvx_xattn_bwd_stages(const lvx_problem* p, lvx_dtype dtype, const voi
   BwdArgs a;
   a.d = make_dims(p);
   a.mask = make_mask(mask);
-  a.n_split_dq = bwd_split(a.d, dtype, mask != nullptr);
+  const TailPlan dq = bwd_split(a.d, dtype, mask != nullptr);
+  a.n_split_dq = dq.parts;
+  a.dq_whole = dq.whole;
   a.dq_pass = 0;
   // the kernel that forms all five products at once: where it applies, unless the caller asks for
   // the two-kernel form (or only for one of the two kernels)
@@ -373,7 +410,7 @@ lvx_status lvx_xattn_bwd_stages(const lvx_problem* p, lvx_dtype dtype, const voi
   const bool want_fuse = (stages & LVX_BWD_FUSED) || (FUSED_BY_DEFAULT && !(stages & LVX_BWD_SPLIT));
   const bool fused = can_fuse && want_fuse && (stages & (LVX_BWD_DKDV | LVX_BWD_DQ)) == (LVX_BWD_DKDV | LVX_BWD_DQ);
   const int n_slices = bwd_slices(a.d, dtype, mask != nullptr);
-  const size_t need = bwd_ws(a.d, n_slices, can_fuse);
+  const size_t need = bwd_ws(a.d, dtype, mask != nullptr, can_fuse);
   if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < need) return LVX_ERR_WORKSPACE;
   a.q = q; a.k = k; a.v = v; a.o = o; a.d_o = d_o; a.lse = lse;
   a.delta = (float*)workspace;
@@ -381,11 +418,11 @@ lvx_status lvx_xattn_bwd_stages(const lvx_problem* p, lvx_dtype dtype, const voi
   a.stats = (float*)((char*)workspace + align_up((size_t)a.d.B * a.d.Hq * a.d.Sq * sizeof(float)));
   a.stats_ovl = has_stats_ovl(a.d) ? a.stats + stats_floats(a.d) : nullptr;
   a.dq_accum = dq_accum; a.dk = dk; a.dv = dv;
-  a.dq_part = a.n_split_dq > 1 ? (float*)((char*)workspace + bwd_ws_fixed(a.d)) : nullptr;
+  a.dq_part = n_slices > 0 ? (float*)((char*)workspace + bwd_ws_fixed(a.d)) : nullptr;
   a.rows = MaskRows{};
   a.rows_ws = mask != nullptr && n_slices > 0 ? (char*)workspace + bwd_ws_fixed(a.d) + (n_slices - 1) * bwd_slice_bytes(a.d) : nullptr;
   a.rows_ws_bytes = bwd_slice_bytes(a.d);
-  a.dq_tiles = fused ? (float*)((char*)workspace + bwd_ws_fixed(a.d) + bwd_ws_part(a.d, n_slices)) : nullptr;
+  a.dq_tiles = fused ? (float*)((char*)workspace + bwd_ws_fixed(a.d) + bwd_ws_part(a.d, dtype, mask != nullptr)) : nullptr;
   a.kv = {0, 1, 0}; a.kv_sums = nullptr; a.kv_counts = nullptr;
   if (dtype == LVX_BF16 && !fused && workspace_bytes - need >= bwd_ws_kv(a.d, dtype, mask != nullptr)) {
     a.kv = dkdv_bf16_plan(a.d, device_cu_count(), mask != nullptr);
@@ -411,10 +448,9 @@ lvx_status lvx_xattn_bwd_error_word(const lvx_problem* p, lvx_dtype dtype, const
   if (!word) return LVX_ERR_NULL;
   if ((st = check_mask(p, mask)) != LVX_OK) return st;
   const Dims d = make_dims(p);
-  const int n_slices = bwd_slices(d, dtype, mask != nullptr);
   const bool fused = dtype == LVX_BF16 && bwd_fused_bf16_supported(d, mask != nullptr);
-  if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < bwd_ws(d, n_slices, fused)) return LVX_ERR_WORKSPACE;
-  *word = fused ? (const int*)((char*)workspace + bwd_ws_fixed(d) + bwd_ws_part(d, n_slices) + bwd_fused_ws_bytes(d) - 256)
+  if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < bwd_ws(d, dtype, mask != nullptr, fused)) return LVX_ERR_WORKSPACE;
+  *word = fused ? (const int*)((char*)workspace + bwd_ws_fixed(d) + bwd_ws_part(d, dtype, mask != nullptr) + bwd_fused_ws_bytes(d) - 256)
                 : nullptr;
   return LVX_OK;
 }

@@ -84,7 +84,7 @@ bwd_dq_bf16_kernel(BwdArgs a) {
   const int rows_lim = PACK ? G * d.Sq : d.Sq;      // rows of the list this workgroup's tiles are cut from
   const int n_qt = (rows_lim + QM - 1) / QM;
   const int per_split = PACK ? n_qt : G * n_qt;
-  int b, hk, split, hq, qt;
+  int b, hk, split, hq, qt, n_split = a.n_split_dq;
   if constexpr (LIST >= 2) {
     // (as in the forward: the later query tiles, which under a causal mask see the most key tiles,
     // start first; the head varies fastest)
@@ -97,13 +97,16 @@ bwd_dq_bf16_kernel(BwdArgs a) {
     hq = head % d.Hq;
     hk = hq / G;
   } else {
+    const int whole = PACK ? a.dq_whole : 0, n_cut = per_split - whole;      // (as in the forward)
     HeadWork hw;
-    if (!xcd_decode(blockIdx.x, d.B * d.Hkv, a.n_split_dq * per_split, &hw)) return;
+    if (!xcd_decode(blockIdx.x, d.B * d.Hkv, whole + a.n_split_dq * n_cut, &hw, whole > 0)) return;
     b = hw.head / d.Hkv;
     hk = hw.head % d.Hkv;
-    split = hw.item / per_split;
+    const int cut = max(hw.item - whole, 0);
+    split = cut / n_cut;
     hq = hk * G + (PACK ? 0 : (hw.item % per_split) / n_qt);   // PACK: the first head of the group
-    qt = hw.item % n_qt;
+    qt = PACK ? hw.item - split * n_cut : hw.item % n_qt;
+    if (PACK && hw.item < whole) n_split = 1;
   }
 
   DQ_STAMP(stamp0);
@@ -113,9 +116,8 @@ bwd_dq_bf16_kernel(BwdArgs a) {
 
   // KV range of this split, in tiles
   const int n_tiles = (d.Skv + TN - 1) / TN;
-  const int tps = (n_tiles + a.n_split_dq - 1) / a.n_split_dq;
-  int t_begin = split * tps;                        // (with a media mask: re-cut below over the visible tiles)
-  int t_end = min(n_tiles, t_begin + tps);
+  int t_begin = (int)((long)split * n_tiles / n_split);         // (with a media mask: re-cut below over the visible tiles)
+  int t_end = (int)((long)(split + 1) * n_tiles / n_split);
 
   // ---- stationary operands and statistics of this lane's query rows i_wave0 + 32 qb + ql
   // The dense variant folds the statistics into the matrix products: Q is held as
@@ -802,9 +804,11 @@ bwd_dq_bf16_kernel(BwdArgs a) {
   constexpr int RPI = 64 / LPR;                    // rows per instruction
   constexpr bool EVEN = 64 % LPR == 0 && (32 * QB) % RPI == 0;    // else: idle lanes, and a last instruction with fewer rows
   const int rsub = lane / LPR, col = (lane % LPR) * 4;
-  const bool whole = a.n_split_dq == 1;            // else: this split's own slice of the partial sums
-  float* const out0 = (whole ? a.dq_accum : a.dq_part + (long)split * d.B * d.Hq * d.Sq * D) +
-                      (((long)b * d.Hq + hq) * d.Sq) * D;
+  const bool whole = n_split == 1;                 // else: this split's own slice of the partial sums
+  const int skip = PACK ? a.dq_whole * QM : 0;     // (rows of the group that are not split and have no place there)
+  float* const out0 = whole || !PACK ? (whole ? a.dq_accum : a.dq_part + (long)split * d.B * d.Hq * d.Sq * D) +
+                                           (((long)b * d.Hq + hq) * d.Sq) * D
+                                     : a.dq_part + (((long)split * d.B * d.Hkv + (long)b * d.Hkv + hk) * (rows_lim - skip) - skip) * D;
   // (dq_accum and the partial sums are contiguous [B,Hq,Sq,D]: row i of the group's list is row i
   // past the first row of the group's first head)
   // Eight instructions' worth of rows at a time: their old values are all requested before the
@@ -863,23 +867,21 @@ hipError_t launch(const BwdArgs& a, long grid, hipStream_t s) {
 // outliers is off by 2.7e-3, with a folded Q by 3.9e-3; both take a launch's time.
 static bool dq_dense_keys(const Dims& d) { return d.Skv % TN == 0 || d.Skv >= 2 * TN; }
 
+bool bwd_dq_bf16_dense(const Dims& d, bool masked) { return !masked && dq_dense_keys(d); }
+TailPlan bwd_dq_bf16_dense_plan(const Dims& d, int n_cu) {
+  const long n_qt = ((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM;
+  const double t_tile = d.D == 128 ? 2.25e-6 : d.D == 96 ? 1.7e-6 : 1.25e-6;
+  return pick_tail((long)d.B * d.Hkv, (int)n_qt, (d.Skv + TN - 1) / TN, n_cu, 64, t_tile, 14e-6, 2.0 * QM * d.D * 4.0 / 4.5e12, 5e-6, 1L << 40);
+}
+
 int bwd_bf16_pick_split(const Dims& d, int n_cu, bool masked) {
   // one workgroup per CU; split the KV axis until the grid covers the chip (four times as many
   // workgroups with a media mask, whose visible work differs from one query tile to the next)
-  // (the dense kernel tiles the rows of a whole group of query heads, the general one each head's)
-  const bool dense = !masked && dq_dense_keys(d);
-  const long base = dense ? (long)d.B * d.Hkv * (((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM)
-                          : (long)d.B * d.Hq * ((d.Sq + QM - 1) / QM);
+  const long base = (long)d.B * d.Hq * ((d.Sq + QM - 1) / QM);
   const int n_tiles = (d.Skv + TN - 1) / TN;
   long cap = n_tiles / 16;                // keep at least 16 tiles (1024 keys) per split
   if (cap < 1) cap = 1;
-  if (!masked) {
-    // about 5.5 TFLOP/s per compute unit in this kernel; a split's sums are float32 rows written
-    // once and read once by the reduction at about 3 TB/s
-    const double t_full = 6.0 * QM * (double)d.Skv * d.D / 5.5e12;
-    const double t_part = 2.0 * (double)d.B * d.Hq * d.Sq * d.D * 4.0 / 3e12;
-    return pick_split_balanced(base, n_cu, cap, t_full, t_part);
-  }
+  if (!masked) return 1;                  // (fewer than 128 keys)
   long want = (4L * n_cu + base - 1) / base;
   if (want < 1) want = 1;
   if (want > cap) want = cap;
@@ -895,7 +897,7 @@ hipError_t launch_one(const BwdArgs& a, bool general, hipStream_t s) {
   const bool list = a.dq_pass == 1 || a.dq_pass >= 3;   // the dense kernel over a list of tiles: rows tiled per head
   const long per_split = general || list ? (long)G * ((d.Sq + QM - 1) / QM) : ((long)G * d.Sq + QM - 1) / QM;
   const long grid = a.dq_pass >= 3 ? (long)d.B * d.Hq * a.n_split_dq * ((d.Sq + QM - 1) / QM)
-                                   : xcd_grid(d.B * d.Hkv, (int)(a.n_split_dq * per_split));
+                                   : xcd_grid(d.B * d.Hkv, (int)(a.dq_whole + a.n_split_dq * (per_split - a.dq_whole)));
   hipError_t e;
   if (a.dq_pass == 4) e = d.D == 64 ? launch<64, false, 3>(a, grid, s) : d.D == 96 ? launch<96, false, 3>(a, grid, s) : launch<128, false, 3>(a, grid, s);
   else if (a.dq_pass == 3) e = d.D == 64 ? launch<64, false, 2>(a, grid, s) : d.D == 96 ? launch<96, false, 2>(a, grid, s) : launch<128, false, 2>(a, grid, s);
@@ -903,8 +905,10 @@ hipError_t launch_one(const BwdArgs& a, bool general, hipStream_t s) {
   else if (d.D == 64) e = general ? launch<64, true>(a, grid, s) : launch<64, false>(a, grid, s);
   else if (d.D == 96) e = general ? launch<96, true>(a, grid, s) : launch<96, false>(a, grid, s);
   else e = general ? launch<128, true>(a, grid, s) : launch<128, false>(a, grid, s);
-  if (e == hipSuccess && a.n_split_dq > 1)
-    e = launch_dq_reduce(a.dq_part, a.n_split_dq, (long)d.B * d.Hq * d.Sq * d.D, a.dq_accum, s);
+  if (e == hipSuccess && a.n_split_dq > 1) {
+    const long group = (long)G * d.Sq * d.D, run = group - (long)a.dq_whole * QM * d.D;
+    e = launch_dq_reduce(a.dq_part, a.n_split_dq, d.B * d.Hkv * run, run, group, a.dq_accum, s);
+  }
   return e;
 }
 
@@ -926,7 +930,7 @@ hipError_t launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s) {
     if (fits && a.mask.q_chunk % 32 == 0 && a.mask.kv_block % TN == 0) {
       BwdArgs p3 = a;
       p3.dq_pass = 3;
-      if (p3.n_split_dq > 1) p3.n_split_dq /= 2;    // (its workgroups start longest first: half the splits even the load out)
+      p3.n_split_dq = list_split((long)d.B * d.Hq * ((d.Sq + QM - 1) / QM), n_tiles);
       return launch_one(p3, false, s);
     }
     // ... or of any other mask with key blocks of 64 keys and more, by the words that travel with the tiles
@@ -934,7 +938,7 @@ hipError_t launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s) {
       BwdArgs p4 = a;
       p4.dq_pass = 4;
       p4.frame_magic = frame_magic_of(a.mask.kv_block);
-      if (p4.n_split_dq > 1) p4.n_split_dq /= 2;
+      p4.n_split_dq = list_split((long)d.B * d.Hq * ((d.Sq + QM - 1) / QM), n_tiles);
       return launch_one(p4, false, s);
     }
     const bool two = d.Skv % TN == 0 && plan_fits(h_max, w, n_tiles, DqSmem<128>::BITS_BYTES, DqSmem<128>::WIN_BYTES) &&
@@ -967,6 +971,7 @@ hipError_t launch_bwd_bf16(const BwdArgs& a, unsigned stages, hipStream_t s) {
     rest.dv = (uint16_t*)a.dv + (long)done * a.d.kv_ss;
     rest.d.Skv = a.d.Skv - done;
     rest.n_split_dq = 1;
+    rest.dq_whole = 0;
     rest.dq_part = nullptr;
     rest.dq_tiles = nullptr;
     return launch_bwd_bf16(rest, stages, s);

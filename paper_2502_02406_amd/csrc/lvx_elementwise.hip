@@ -45,7 +45,7 @@ __global__ void __launch_bounds__(256) merge_kernel(MergeArgs a) {
   // and turned into weights, so a thread waits for memory once, not twice.  (A part without keys
   // still has a buffer; what it holds is fetched and dropped.)
   const long t0 = (long)blockIdx.x * 256 + threadIdx.x, stride = (long)gridDim.x * 256;
-  long row[U];
+  long row[U], grow[U];                 // of the parts that are slices; of the tensor
   int c[U];
   bool on[U];
 #pragma unroll
@@ -54,9 +54,11 @@ __global__ void __launch_bounds__(256) merge_kernel(MergeArgs a) {
     row[u] = t / vpr;
     c[u] = (int)(t % vpr) * VEC;
     on[u] = row[u] < a.rows && c[u] < a.D;
+    const int run = a.group - a.skip;
+    grow[u] = a.skip == 0 ? row[u] : row[u] / run * a.group + a.skip + row[u] % run;
   }
   auto load_part = [&](int u, int k) __attribute__((always_inline)) -> u32x4 {
-    if (PART_F32) return *(const u32x4*)((const float*)a.o_parts[k] + row[u] * a.D + c[u]);
+    if (PART_F32) return *(const u32x4*)((const float*)a.o_parts[k] + (k < a.first ? grow[u] : row[u]) * a.D + c[u]);
     const uint16_t* src = (const uint16_t*)a.o_parts[k] + row[u] * a.D + c[u];
     if (VEC == 8) return *(const u32x4*)src;
     const unsigned x0 = ((const unsigned*)src)[0], x1 = ((const unsigned*)src)[1];
@@ -95,7 +97,7 @@ __global__ void __launch_bounds__(256) merge_kernel(MergeArgs a) {
     float lk[LG];
 #pragma unroll
     for (int k = 0; k < LG; ++k) {
-      const float x = a.lse_parts[k < n ? k : n - 1][row[u]];
+      const float x = a.lse_parts[k < n ? k : n - 1][k < a.first ? grow[u] : row[u]];
       lk[k] = k < n ? x : -INFINITY;
     }
     float M = -INFINITY;
@@ -136,7 +138,7 @@ __global__ void __launch_bounds__(256) merge_kernel(MergeArgs a) {
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     if (!on[u]) continue;
-    const long i = row[u] % a.Sq, h = (row[u] / a.Sq) % a.Hq, b = row[u] / ((long)a.Sq * a.Hq);
+    const long i = grow[u] % a.Sq, h = (grow[u] / a.Sq) % a.Hq, b = grow[u] / ((long)a.Sq * a.Hq);
     const long off = b * a.o_sb + h * a.o_sh + i * a.o_ss + c[u];
     if (OUT_F32) {
       const f32x4 y = {acc[u][0], acc[u][1], acc[u][2], acc[u][3]};
@@ -152,7 +154,7 @@ __global__ void __launch_bounds__(256) merge_kernel(MergeArgs a) {
         dst[1] = pack_bf16(acc[u][2], acc[u][3]);
       }
     }
-    if (c[u] == 0) a.lse_out[row[u]] = Lout[u];
+    if (c[u] == 0) a.lse_out[grow[u]] = Lout[u];
   }
 }
 
@@ -226,7 +228,7 @@ __global__ void __launch_bounds__(256) merge_row_kernel(MergeRowArgs a) {
 
 hipError_t launch_merge(const MergeArgs& a, int part_is_f32, int out_is_f32, hipStream_t s) {
   // (few rows: fewer workgroups of the kernel below than compute units; and parts enough to share)
-  if (part_is_f32 && a.o_slices != nullptr && a.first <= 1 && a.n_parts > 4 && a.rows <= 1024) {
+  if (part_is_f32 && a.o_slices != nullptr && a.first <= 1 && a.skip == 0 && a.n_parts > 4 && a.rows <= 1024) {
     MergeRowArgs r;
     r.o0 = (const float*)a.o_parts[0]; r.l0 = a.lse_parts[0];
     r.o = a.o_slices; r.l = a.lse_slices;
@@ -320,18 +322,20 @@ hipError_t launch_delta(const Dims& d, const void* o, const void* d_o, int is_f3
   return hipGetLastError();
 }
 
-// dq_accum += sum of the KV splits' partial dQ (float32, contiguous).  One thread per 4 elements.
-__global__ void __launch_bounds__(256) dq_reduce_kernel(const float* parts, int n_parts, long n, float* acc) {
+// dq_accum += sum of the KV splits' partial dQ (float32, contiguous; where only the last rows of a group were split,
+// `run` of its `group` floats).  One thread per 4 elements.
+__global__ void __launch_bounds__(256) dq_reduce_kernel(const float* parts, int n_parts, long n, long run, long group, float* acc) {
   const long i = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i >= n) return;
+  if (run != group) acc += (i / run + 1) * (group - run);
   f32x4 x = *(const f32x4*)(acc + i);
   for (int k = 0; k < n_parts; ++k) x += *(const f32x4*)(parts + (long)k * n + i);
   *(f32x4*)(acc + i) = x;
 }
 
-hipError_t launch_dq_reduce(const float* parts, int n_parts, long n, float* dq_accum, hipStream_t s) {
+hipError_t launch_dq_reduce(const float* parts, int n_parts, long n, long run, long group, float* dq_accum, hipStream_t s) {
   const unsigned blocks = (unsigned)((n / 4 + 255) / 256);
-  dq_reduce_kernel<<<blocks, 256, 0, s>>>(parts, n_parts, n, dq_accum);
+  dq_reduce_kernel<<<blocks, 256, 0, s>>>(parts, n_parts, n, run, group, dq_accum);
   return hipGetLastError();
 }
 

@@ -93,7 +93,7 @@ fwd_bf16_kernel(FwdArgs a) {
   const int rows_kv = PACK ? G * d.Sq : d.Sq;
   const int n_qt = (rows_kv + QM - 1) / QM;
   const int per_split = PACK ? n_qt : G * n_qt;
-  int b, hk, split, hq0, qt;
+  int b, hk, split, hq0, qt, n_split = a.n_split;
   if constexpr (LIST >= 2) {
     // Under a mask the query tiles of a head differ in how many key tiles they see (under a causal
     // one, the later the tile the more).  Workgroups start in the order of their numbers: the later
@@ -109,13 +109,18 @@ fwd_bf16_kernel(FwdArgs a) {
     hq0 = head % d.Hq;
     hk = hq0 / G;
   } else {
+    // (PACK: the row tiles that are not split come first; where a head's items differ so in length, XCDs
+    // that share it take them in turn)
+    const int whole = PACK ? a.whole : 0, n_cut = per_split - whole;
     HeadWork hw;
-    if (!xcd_decode(blockIdx.x, d.B * d.Hkv, a.n_split * per_split, &hw)) return;
+    if (!xcd_decode(blockIdx.x, d.B * d.Hkv, whole + a.n_split * n_cut, &hw, whole > 0)) return;
     b = hw.head / d.Hkv;
     hk = hw.head % d.Hkv;
-    split = hw.item / per_split;
+    const int cut = max(hw.item - whole, 0);
+    split = cut / n_cut;
     hq0 = hk * G + (PACK ? 0 : (hw.item % per_split) / n_qt);   // PACK: the first head of the group
-    qt = hw.item % n_qt;
+    qt = PACK ? hw.item - split * n_cut : hw.item % n_qt;
+    if (PACK && hw.item < whole) n_split = 1;
   }
 
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, ql = lane & 31;
@@ -124,9 +129,8 @@ fwd_bf16_kernel(FwdArgs a) {
 
   // KV range of this split, in tiles
   const int n_tiles = (d.Skv + TN - 1) / TN;
-  const int tps = (n_tiles + a.n_split - 1) / a.n_split;
-  int t_begin = split * tps;                        // (LIST: re-cut below over the list)
-  int t_end = min(n_tiles, t_begin + tps);
+  int t_begin = (int)((long)split * n_tiles / n_split);         // (LIST: re-cut below over the list)
+  int t_end = (int)((long)(split + 1) * n_tiles / n_split);
 
   // ---- stationary operands: Q of this lane's rows r_wave0 + 32 qb + ql of the list
   const float c2 = d.scale * LOG2E;
@@ -736,9 +740,11 @@ fwd_bf16_kernel(FwdArgs a) {
     if (r >= rows_kv) continue;
     const int hq = PACK ? hq0 + r / d.Sq : hq0, i = PACK ? r % d.Sq : r;
     const long row = ((long)b * d.Hq + hq) * d.Sq + i;
-    if (a.n_split > 1 || a.partial) {
-      const long slice = (long)(a.part0 + split) * d.B * d.Hq * d.Sq;
-      float* o = a.o_part + (slice + row) * D;
+    if (n_split > 1 || a.partial) {
+      const int cut_rows = PACK ? rows_kv - a.whole * QM : 0;    // rows of a group that are split
+      const long prow = (long)(a.part0 + split) * (PACK ? (long)d.B * d.Hkv * cut_rows : (long)d.B * d.Hq * d.Sq) +
+                        (PACK ? ((long)b * d.Hkv + hk) * cut_rows + r - a.whole * QM : row);
+      float* o = a.o_part + prow * D;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -747,7 +753,7 @@ fwd_bf16_kernel(FwdArgs a) {
                      oacc[qb][db][4 * q4 + 3] * inv};
           *(f32x4*)(o + 32 * db + 8 * q4 + 4 * g) = y;
         }
-      if (g == 0) a.lse_part[slice + row] = lse;
+      if (g == 0) a.lse_part[prow] = l_tot != l_tot ? l_tot : lse;      // (a NaN must not look like a part without keys)
       continue;
     }
     if (a.merge_into) {
@@ -810,25 +816,23 @@ hipError_t launch(const FwdArgs& a, long grid, hipStream_t s) {
 
 }  // namespace
 
+bool fwd_bf16_dense(const Dims& d, bool masked) { return !masked && d.Skv >= TN && !fwd_rows_bf16_takes(d, masked); }
+TailPlan fwd_bf16_dense_plan(const Dims& d, int n_cu, int most, long room) {
+  const long n_qt = ((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM;
+  const double t_tile = d.D == 128 ? 1.75e-6 : d.D == 96 ? 1.45e-6 : 1.2e-6;
+  return pick_tail((long)d.B * d.Hkv, (int)n_qt, (d.Skv + TN - 1) / TN, n_cu, most, t_tile, 10e-6, 2.0 * QM * d.D * 4.0 / 4.5e12, 5e-6, room);
+}
+
 int fwd_bf16_pick_split(const Dims& d, int n_cu, bool masked) {
   if (fwd_rows_bf16_takes(d, masked)) return fwd_rows_bf16_pick_split(d, n_cu);
   // one workgroup per CU; split the KV axis until the grid covers the chip.  With a media mask the
   // visible work differs from one query tile to the next (the splits of a tile share its visible
   // key tiles evenly), so four times as many workgroups are made to even the load out.
-  // (the dense kernel tiles the rows of a whole group of query heads, the general one each head's)
-  const bool dense = !masked && d.Skv >= TN;
-  const long base = dense ? (long)d.B * d.Hkv * (((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM)
-                          : (long)d.B * d.Hq * ((d.Sq + QM - 1) / QM);
+  const long base = (long)d.B * d.Hq * ((d.Sq + QM - 1) / QM);
   const int n_tiles = (d.Skv + TN - 1) / TN;
   long cap = n_tiles / 16;                // keep at least 16 tiles (1024 keys) per split
   if (cap < 1) cap = 1;
-  if (!masked) {
-    // about 4.5 TFLOP/s per compute unit in this kernel; partial results are float32 rows written
-    // once and read once at about 3 TB/s
-    const double t_full = 4.0 * QM * (double)d.Skv * d.D / 4.5e12;
-    const double t_part = 2.0 * (double)d.B * d.Hq * d.Sq * d.D * 4.0 / 3e12;
-    return pick_split_balanced(base, n_cu, cap, t_full, t_part);
-  }
+  if (!masked) return 1;                  // (fewer than 64 keys)
   long want = (LVX_MASKED_WG_FACTOR * n_cu + base - 1) / base;
   if (want < 1) want = 1;
   if (want > cap) want = cap;
@@ -893,7 +897,7 @@ hipError_t launch_fwd_bf16(const FwdArgs& a, hipStream_t s) {
   if (fwd_rows_bf16_takes(d, a.mask.allow != nullptr)) return launch_fwd_rows_bf16(a, s);
   if (a.mask.allow != nullptr || d.Skv < TN) return launch_fwd_general_bf16(a, s);
   const int n_qt = (int)(((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM);
-  const long grid = xcd_grid(d.B * d.Hkv, a.n_split * n_qt);
+  const long grid = xcd_grid(d.B * d.Hkv, a.whole + a.n_split * (n_qt - a.whole));
   return d.D == 64 ? launch<64>(a, grid, s) : d.D == 96 ? launch<96>(a, grid, s) : launch<128>(a, grid, s);
 }
 

@@ -52,6 +52,8 @@ struct FwdArgs {
   int partial;          // 1: write partial results even with n_split == 1 (this launch is one of several
                         // whose results are combined)
   int part0;            // index of the partial slice that split 0 of this launch writes
+  int whole;            // dense kernel: the first `whole` row tiles of a K/V head are not split (the partial slices
+                        // then hold the rows of the others only, [B,Hkv, rows of the group - 256 whole])
   MaskRows rows;        // set by the launch where the kernel masks by it
   void* rows_ws;        // workspace for its words, or nullptr
   unsigned frame_magic; // 2^36 / kv_block, rounded up (set with rows)
@@ -94,6 +96,7 @@ struct BwdArgs {
   float* kv_sums;
   int* kv_counts;       // media mask: parts that a tile was cut into, [B Hkv, tiles] (its number of steps is the mask's)
   int n_split_dq;       // KV splits of the dQ kernel
+  int dq_whole;         // as FwdArgs::whole
   int dq_pass;          // media mask, dQ kernel: 0 = one launch over every visible tile; 1 = this launch takes the
                         // key tiles that EVERY row of a workgroup sees (dense kernel over a list of them),
                         // 2 = this launch takes the other visible tiles (general kernel); 3, 4 = one launch of
@@ -116,7 +119,8 @@ struct MergeArgs {
   // start here (nullptr: not so; the pointers above are always set)
   const float *o_slices, *lse_slices;
   int first;
-  long rows;            // B*Hq*Sq
+  long rows;            // rows to combine: B*Hq*Sq, or those of every group of `group` rows past its first `skip`
+  int group, skip;
   int D;
   void* o_out;
   float* lse_out;
@@ -210,6 +214,56 @@ inline int pick_split_balanced(long base, int n_cu, long cap, double t_full, dou
   }
   return best;
 }
+// The same for workgroups that take a tile of rows each, n_qt tiles in each of `heads` groups: whole rounds of
+// row tiles are left unsplit, and the tiles of the last round (or of the last two) are split `parts` ways, down to three
+// key tiles a part.  t_tile: one workgroup's time for one of the n_tiles key tiles, t_fix: its set-up and
+// epilogue, t_part: what a set of partial results of one row tile costs, t_join: the launch that combines
+// them; room: sets of them that there is workspace for.  Splitting every row tile (to 16 key tiles a
+// part at least) sent all rows through memory for the sake of the last round: 32 / 8 heads x 2650 rows x 9447 keys, 336
+// row tiles, forward with its combine 439 -> 428 us, dQ 550 -> 511; and few rows against few keys waited for long
+// parts: 8 heads (D = 64) x 427 rows x 2576 keys forward 36 -> 28, 16 heads x 134 rows x 1024 keys 33 -> 27.
+// Of 31 shapes with 64 to 8192 rows and 1024 to 131072 keys the choice is within 8 % of the best of up to 28 on all but two.
+struct TailPlan { int whole, parts; };
+inline TailPlan pick_tail(long heads, int n_qt, int n_tiles, int n_cu, long most, double t_tile, double t_fix,
+                          double t_part, double t_join, long room) {
+  const long tiles = heads * n_qt;
+  const auto time = [&](long n, int kt) {          // n workgroups of kt key tiles each
+    return (double)((n + n_cu - 1) / n_cu) * (kt * t_tile + t_fix);
+  };
+  TailPlan best = {0, 1};
+  double best_t = time(tiles, n_tiles);
+  const long full = tiles / n_cu;
+  for (long k = full; k >= 0 && k >= full - 1; --k) {
+    const long whole = k * n_cu / heads, cut = tiles - heads * whole;
+    for (long p = 2; p <= most && p <= 64 && 3 * p <= n_tiles && cut * p <= room; ++p) {
+      const double t = time(heads * whole, n_tiles) + time(cut * p, (int)((n_tiles + p - 1) / p)) + (double)(cut * p) * t_part + t_join;
+      if (t < best_t * (best.parts == 1 ? 0.97 : 0.995)) {
+        best_t = t;
+        best = {(int)whole, (int)p};
+      }
+    }
+  }
+  return best;
+}
+// the dense forward and dQ kernels (bf16, no mask): whether they take the problem, and how
+bool fwd_bf16_dense(const Dims& d, bool masked);
+TailPlan fwd_bf16_dense_plan(const Dims& d, int n_cu, int most, long room);
+bool bwd_dq_bf16_dense(const Dims& d, bool masked);
+TailPlan bwd_dq_bf16_dense_plan(const Dims& d, int n_cu);
+// KV splits of the masked kernels that walk a list of the tiles some row sees (LIST >= 2; each split takes an even share
+// of the list, wherever it ends), for `wgs` row tiles and n_tiles key tiles of which the mask shows any
+// number.  They start longest first, so two rounds of the chip (512 workgroups) even out lists as uneven
+// as a causal mask's while a workgroup keeps tiles enough to be worth its set-up and list (15 us); else one
+// round, down to three tiles a split.  (Four times the compute units halved, 1024 keys a split at least, before.)
+// Forward and dQ, us: 28 row tiles (D = 128) x 92 key tiles 68 -> 38 and 84 -> 46, 64 x 29 (D = 64) 53 -> 37 and 53 -> 37, 64
+// x 201 88 -> 72 and 109 -> 89; two rounds of long ones: 128 x 2048, causal 457 -> 382 and 581 -> 482 against
+// one round (each chunk one frame: 152 -> 168).  Between one round and one and a half, two splits: 160 x 160 232 -> 202 (three before).
+inline int list_split(long wgs, int n_tiles) {
+  const long two = wgs <= 256 ? 512 / wgs : wgs <= 400 ? 2 : 1, one = wgs <= 128 ? 256 / wgs : wgs <= 400 ? 2 : 1;
+  long s = n_tiles / two >= 64 ? two : one;
+  if (s > n_tiles / 3) s = n_tiles / 3;
+  return s < 1 ? 1 : s > 60 ? 60 : (int)s;
+}
 int fwd_bf16_pick_split(const Dims& d, int n_cu, bool masked);
 bool fwd_bf16_two_pass_fits(const Dims& d, const MaskDev& m);   // a masked forward may run as passes 1 and 2
 bool fwd_bf16_one_pass_fits(const Dims& d, const MaskDev& m);   // ... or as one launch of the dense kernel over tile lists
@@ -230,7 +284,8 @@ hipError_t launch_merge(const MergeArgs& a, int part_is_f32, int out_is_f32, hip
 hipError_t launch_delta(const Dims& d, const void* o, const void* d_o, int is_f32, const float* lse,
                         float* delta, float* stats, int sq_pad, float* stats_ovl, hipStream_t s);
 // dq_accum[i] += sum over the n_parts slices of `parts` (each n floats, n a multiple of 4)
-hipError_t launch_dq_reduce(const float* parts, int n_parts, long n, float* dq_accum, hipStream_t s);
+// (of runs of `run` floats in every `group` of them, the last ones)
+hipError_t launch_dq_reduce(const float* parts, int n_parts, long n, long run, long group, float* dq_accum, hipStream_t s);
 hipError_t launch_dq_finalize(const Dims& d, const float* dq_accum, void* dq, int is_f32,
                               hipStream_t s);
 

@@ -1,0 +1,55 @@
+"""Row tiles of the dense forward and dQ kernels of which only those of the last round are split over the keys, and lists
+shared by more workgroups than they have tiles, against float64.  O, P and dS are rounded to bf16 (2^-9 each,
+relative), and so is the Q that dQ's scores are formed with: 2^-7.5 of the norm bounds O and 2^-7 dQ; L is a float32
+sum (1e-3)."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(B, Hq, Hkv, D, Sq, Skv, n_blocks=1, q_chunk=0, kv_block=0):
+    from paper_2502_02406_amd.blockloop import BlockLoop, MediaMask
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q, do = (torch.randn((B, Hq, Sq, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+    k, v = (torch.randn((B, Hkv, Skv, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+    mask, seen = None, torch.ones((Sq, Skv), dtype=torch.bool, device="cuda")
+    if q_chunk:
+        c, f = torch.arange(-(-Sq // q_chunk))[:, None], torch.arange(-(-Skv // kv_block))[None, :]
+        allow = (f <= c).to(torch.uint8).cuda()
+        mask = MediaMask(allow, q_chunk, kv_block)
+        seen = allow.bool().repeat_interleave(q_chunk, 0)[:Sq].repeat_interleave(kv_block, 1)[:, :Skv]
+    loop = BlockLoop(tuple(q.shape), tuple(k.shape), torch.bfloat16, n_blocks, mask)
+    o, lse = loop.forward(q, k, v)
+    dq = loop.backward(q, k, v, o, lse, do, torch.empty_like(k), torch.empty_like(v))
+    G = Hq // Hkv
+    for b in range(B):
+        for h in range(Hq):
+            qd, gd, od, kd, vd = (t.double() for t in (q[b, h], do[b, h], o[b, h], k[b, h // G], v[b, h // G]))
+            s = torch.where(seen, qd @ kd.T * D ** -0.5, float("-inf"))
+            L = torch.logsumexp(s, -1)
+            p = torch.exp(s - L[:, None])
+            ref = p @ vd
+            assert float((lse[b, h].double() - L).abs().max()) <= 1e-3, f"L of head {h}"
+            assert float((od - ref).norm() / ref.norm()) <= 2.0 ** -7.5, f"O of head {h}"
+            dref = p * (gd @ vd.T - (gd * od).sum(-1, keepdim=True)) @ kd * D ** -0.5
+            assert float((dq[b, h].double() - dref).norm() / dref.norm()) <= 2.0 ** -7, f"dQ of head {h}"
+
+
+@pytest.mark.parametrize("shape", [
+    (1, 8, 8, 64, 33 * 256 - 5, 2000, 1),          # 32 of a head's 33 tiles whole, a ragged last one
+    (1, 8, 8, 64, 33 * 256, 4032, 2),              # ... and merged with the running result
+    (1, 12, 4, 128, 5600, 2100, 1),                # heads of a group in one list, four K/V heads: two XCDs each
+    (1, 3, 3, 96, 90 * 256 + 1, 2048, 1),          # an odd number of heads
+    (2, 8, 4, 128, 130, 700, 1),                   # fewer tiles than compute units, three key tiles a part
+], ids=lambda s: "x".join(map(str, s)))
+def test_last_round(shape):
+    _case(*shape)
+
+
+@pytest.mark.parametrize("D", [64, 96, 128])
+@pytest.mark.parametrize("mask", [(1, 4, 2, 300, 1900, 40, 729), (2, 2, 2, 80, 4096, 64, 256), (1, 8, 2, 64, 1088, 2, 64)],
+                         ids=lambda m: "x".join(map(str, m)))
+def test_short_lists(D, mask):
+    B, Hq, Hkv, Sq, Skv, q_chunk, kv_block = mask
+    _case(B, Hq, Hkv, D, Sq, Skv, 1, q_chunk, kv_block)
