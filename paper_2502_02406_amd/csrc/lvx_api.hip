@@ -145,17 +145,13 @@ FwdPlan fwd_plan_with(const Dims& d, lvx_dtype dtype, const MaskDev& m, int rese
 }
 // ... in a workspace of `room` bytes.  Words that do not fit (262144 rows against 131072 keys in blocks of 64: 68
 // MB, where the general kernel needs nothing) leave the call to the kernels that do without.
-FwdPlan fwd_dense_plan(const Dims& d, int reserve, size_t room) {
-  // (a set of partial results: 256 rows of O and L)
-  const size_t most = (size_t)1 << 40, sets = (room < most ? room : most) / (256 * (d.D + 1) * sizeof(float) + ALIGN);
-  const TailPlan t = fwd_bf16_dense_plan(d, device_cu_count(), LVX_MAX_PARTS - reserve, (long)sets);
-  return {t.parts, t.whole, false, t.parts, 0, fwd_ws(d, t.parts, t.whole)};
-}
 FwdPlan fwd_plan(const Dims& d, lvx_dtype dtype, const MaskDev& m, int reserve, size_t room) {
   if (dtype == LVX_BF16 && fwd_bf16_dense(d, m.allow != nullptr)) {
-    FwdPlan f = fwd_dense_plan(d, reserve, SIZE_MAX);
-    if (f.need > room) f = fwd_dense_plan(d, reserve, room);      // (fewer parts, or none)
-    return f.need > room ? fwd_dense_plan(d, reserve, 0) : f;
+    const auto plan = [&](TailPlan t) -> FwdPlan { return {t.parts, t.whole, false, t.parts, 0, fwd_ws(d, t.parts, t.whole)}; };
+    const FwdPlan f = plan(fwd_bf16_dense_plan(d, device_cu_count(), LVX_MAX_PARTS - reserve));
+    if (f.need <= room) return f;
+    const int n = fwd_bf16_coarse_split(d, device_cu_count());
+    return plan({0, n < LVX_MAX_PARTS - reserve ? n : LVX_MAX_PARTS - reserve});
   }
   const bool rows = m.allow != nullptr && dtype == LVX_BF16 && fwd_bf16_takes_rows(d, m);
   const FwdPlan f = fwd_plan_with(d, dtype, m, reserve, rows, room);
@@ -236,13 +232,13 @@ size_t lvx_xattn_workspace_bytes(const lvx_problem* p, lvx_dtype dtype, int whic
   };
   const auto most = [](size_t x, size_t y) { return x > y ? x : y; };
   const auto dense = [&](int reserve) -> size_t {
-    return dtype == LVX_BF16 && fwd_bf16_dense(d, false) ? fwd_dense_plan(d, reserve, SIZE_MAX).need : 0;
+    return dtype == LVX_BF16 && fwd_bf16_dense(d, false) ? fwd_plan(d, dtype, make_mask(nullptr), reserve, SIZE_MAX).need : 0;
   };
   if (which == LVX_WS_FWD) return most(fwd_ws(d, parts(0)) + rows_most, dense(0));
   if (which == LVX_WS_BWD)
-    // (the dK/dV sums go behind whichever of the two it is)
-    return most(bwd_ws(d, dtype, true, false) + bwd_ws_kv(d, dtype, true),
-                bwd_ws(d, dtype, false, dtype == LVX_BF16 && bwd_fused_bf16_supported(d, false)) + bwd_ws_kv(d, dtype, false));
+    return most(bwd_ws(d, dtype, true, dtype == LVX_BF16 && bwd_fused_bf16_supported(d, false)),
+                bwd_ws(d, dtype, false, dtype == LVX_BF16 && bwd_fused_bf16_supported(d, false))) +
+           most(bwd_ws_kv(d, dtype, true), bwd_ws_kv(d, dtype, false));
   if (which == LVX_WS_FWD_MERGE) return most(fwd_merge_ws(d, dtype, parts(1)) + rows_most, dense(1));
   return 0;
 }

@@ -871,7 +871,7 @@ bool bwd_dq_bf16_dense(const Dims& d, bool masked) { return !masked && dq_dense_
 TailPlan bwd_dq_bf16_dense_plan(const Dims& d, int n_cu) {
   const long n_qt = ((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM;
   const double t_tile = d.D == 128 ? 2.25e-6 : d.D == 96 ? 1.7e-6 : 1.25e-6;
-  return pick_tail((long)d.B * d.Hkv, (int)n_qt, (d.Skv + TN - 1) / TN, n_cu, 64, t_tile, 14e-6, 2.0 * QM * d.D * 4.0 / 4.5e12, 5e-6, 1L << 40);
+  return pick_tail((long)d.B * d.Hkv, (int)n_qt, (d.Skv + TN - 1) / TN, n_cu, 64, t_tile, 14e-6, 2.0 * QM * d.D * 4.0 / 4.5e12, 5e-6);
 }
 
 int bwd_bf16_pick_split(const Dims& d, int n_cu, bool masked) {

@@ -817,10 +817,16 @@ hipError_t launch(const FwdArgs& a, long grid, hipStream_t s) {
 }  // namespace
 
 bool fwd_bf16_dense(const Dims& d, bool masked) { return !masked && d.Skv >= TN && !fwd_rows_bf16_takes(d, masked); }
-TailPlan fwd_bf16_dense_plan(const Dims& d, int n_cu, int most, long room) {
+TailPlan fwd_bf16_dense_plan(const Dims& d, int n_cu, int most) {
   const long n_qt = ((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM;
   const double t_tile = d.D == 128 ? 1.75e-6 : d.D == 96 ? 1.45e-6 : 1.2e-6;
-  return pick_tail((long)d.B * d.Hkv, (int)n_qt, (d.Skv + TN - 1) / TN, n_cu, most, t_tile, 10e-6, 2.0 * QM * d.D * 4.0 / 4.5e12, 5e-6, room);
+  return pick_tail((long)d.B * d.Hkv, (int)n_qt, (d.Skv + TN - 1) / TN, n_cu, most, t_tile, 10e-6, 2.0 * QM * d.D * 4.0 / 4.5e12, 5e-6);
+}
+// Parts of 1024 keys at least, fewer as a rule than the plan's: lvx_xattn_fwd_static's fixed scratch may have room for these only.
+int fwd_bf16_coarse_split(const Dims& d, int n_cu) {
+  const long base = (long)d.B * d.Hkv * (((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM), cap = (d.Skv + TN - 1) / TN / 16;
+  return pick_split_balanced(base, n_cu, cap < 1 ? 1 : cap, 4.0 * QM * (double)d.Skv * d.D / 4.5e12,
+                             2.0 * (double)d.B * d.Hq * d.Sq * d.D * 4.0 / 3e12);
 }
 
 int fwd_bf16_pick_split(const Dims& d, int n_cu, bool masked) {

@@ -217,15 +217,14 @@ inline int pick_split_balanced(long base, int n_cu, long cap, double t_full, dou
 // The same for workgroups that take a tile of rows each, n_qt tiles in each of `heads` groups: whole rounds of
 // row tiles are left unsplit, and the tiles of the last round (or of the last two) are split `parts` ways, down to three
 // key tiles a part.  t_tile: one workgroup's time for one of the n_tiles key tiles, t_fix: its set-up and
-// epilogue, t_part: what a set of partial results of one row tile costs, t_join: the launch that combines
-// them; room: sets of them that there is workspace for.  Splitting every row tile (to 16 key tiles a
+// epilogue, t_part: what a set of partial results of one row tile costs, t_join: the launch that combines them.  Splitting every row tile (to 16 key tiles a
 // part at least) sent all rows through memory for the sake of the last round: 32 / 8 heads x 2650 rows x 9447 keys, 336
 // row tiles, forward with its combine 439 -> 428 us, dQ 550 -> 511; and few rows against few keys waited for long
 // parts: 8 heads (D = 64) x 427 rows x 2576 keys forward 36 -> 28, 16 heads x 134 rows x 1024 keys 33 -> 27.
 // Of 31 shapes with 64 to 8192 rows and 1024 to 131072 keys the choice is within 8 % of the best of up to 28 on all but two.
 struct TailPlan { int whole, parts; };
 inline TailPlan pick_tail(long heads, int n_qt, int n_tiles, int n_cu, long most, double t_tile, double t_fix,
-                          double t_part, double t_join, long room) {
+                          double t_part, double t_join) {
   const long tiles = heads * n_qt;
   const auto time = [&](long n, int kt) {          // n workgroups of kt key tiles each
     return (double)((n + n_cu - 1) / n_cu) * (kt * t_tile + t_fix);
@@ -235,7 +234,7 @@ inline TailPlan pick_tail(long heads, int n_qt, int n_tiles, int n_cu, long most
   const long full = tiles / n_cu;
   for (long k = full; k >= 0 && k >= full - 1; --k) {
     const long whole = k * n_cu / heads, cut = tiles - heads * whole;
-    for (long p = 2; p <= most && p <= 64 && 3 * p <= n_tiles && cut * p <= room; ++p) {
+    for (long p = 2; p <= most && p <= 64 && 3 * p <= n_tiles; ++p) {
       const double t = time(heads * whole, n_tiles) + time(cut * p, (int)((n_tiles + p - 1) / p)) + (double)(cut * p) * t_part + t_join;
       if (t < best_t * (best.parts == 1 ? 0.97 : 0.995)) {
         best_t = t;
@@ -247,7 +246,8 @@ inline TailPlan pick_tail(long heads, int n_qt, int n_tiles, int n_cu, long most
 }
 // the dense forward and dQ kernels (bf16, no mask): whether they take the problem, and how
 bool fwd_bf16_dense(const Dims& d, bool masked);
-TailPlan fwd_bf16_dense_plan(const Dims& d, int n_cu, int most, long room);
+TailPlan fwd_bf16_dense_plan(const Dims& d, int n_cu, int most);
+int fwd_bf16_coarse_split(const Dims& d, int n_cu);             // every row tile, in a workspace too small for that plan
 bool bwd_dq_bf16_dense(const Dims& d, bool masked);
 TailPlan bwd_dq_bf16_dense_plan(const Dims& d, int n_cu);
 // KV splits of the masked kernels that walk a list of the tiles some row sees (LIST >= 2; each split takes an even share
