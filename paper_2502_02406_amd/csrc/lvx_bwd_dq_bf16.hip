@@ -21,6 +21,7 @@
 #include "lvx_internal.h"
 #include "lvx_mfma.h"
 #include "lvx_kv_ring.h"
+#include "lvx_mask_stream.h"
 
 #include <type_traits>
 
@@ -43,6 +44,90 @@ __device__ unsigned long long dq_probe[8];
 #else
 #define DQ_STAMP(x)
 #endif
+
+// Row tile qt of one head under a mask that shows its row blocks little (mask_streams, lvx_mask_stream.h): wave w takes
+// row blocks 2 w and 2 w + 1.  K is read by rows (S) and transposed (dQ), V by rows only.
+template <int D>
+__device__ __forceinline__ void dq_mask_stream(const BwdArgs& a, char* smem, int b, int hk, int hq, int qt, int split,
+                                               unsigned long long any, int wave, int lane) {
+  constexpr int KS = D / 16, DB = D / 32;
+  using U = KeyUnit<D>;
+  const Dims& d = a.d;
+  const int g = lane >> 5, ql = lane & 31;
+  KeyStream<D> ks(a.k, a.v, d, b, hk, smem, wave, lane, a.mask.kv_block, true);
+  const UnitReads<D> kr(lane, false);
+  const float c2 = d.scale * LOG2E;
+  for (int rb = 2 * wave; rb < 2 * wave + 2; ++rb) {
+    const int i0 = qt * QM + 32 * rb;
+    if (i0 >= d.Sq) return;
+    const int i = min(i0 + ql, d.Sq - 1);
+    bf16x8 qf[KS], gf[KS];
+    const long off = b * d.q_sb + hq * d.q_sh + (long)i * d.q_ss;
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      qf[k] = *(const bf16x8*)((const uint16_t*)a.q + off + 16 * k + 8 * g);
+      gf[k] = *(const bf16x8*)((const uint16_t*)a.d_o + off + 16 * k + 8 * g);
+    }
+    const long slot = (((long)b * d.Hq + hq) * a.sq_pad + (i & ~31)) * 2 + (i & 31);
+    float nl2 = a.stats[slot], nd = a.stats[slot + 32];        // -L log2(e) (-inf: no probability mass) and -delta
+    const int n = ks.start(a.rows, b, qt, rb, any, split, a.n_split_dq);
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      asm volatile("" : "+a"(qf[k]));
+      asm volatile("" : "+a"(gf[k]));
+    }
+    asm volatile("" : "+v"(nl2), "+v"(nd));
+    f32x16 dq[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) { dq[db] = zero16(); asm volatile("" : "+a"(dq[db])); }
+    asm volatile("s_nop 7" ::: "memory");
+    int st = 0;
+    for (int p = 0; p < n; ++p) {
+      ks.arrive(n - 1 - p);
+      char* const t = ks.stage0 + st * U::STAGE;
+      f32x16 s, dp;
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        const bf16x8 ka = kr.plain(t, k), va = kr.plain(t + U::TILE, k);
+        if (k == 0) { mfma_first(s, ka, qf[0]); mfma_first(dp, va, gf[0]); }
+        else { mfma_next(s, ka, qf[k]); mfma_next(dp, va, gf[k]); }
+      }
+      const auto un = ks.unit();
+      asm volatile("s_nop 15\n\ts_nop 15" : "+v"(s), "+v"(dp));
+      mask_unit(s, un.keys, un.word, ql, g);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {               // (a pair that does not count adds 0, whatever its dP)
+        const float x = __builtin_amdgcn_exp2f(fmaf(s[v], c2, nl2)) * (dp[v] + nd);
+        s[v] = s[v] == -INFINITY ? 0.f : x;
+      }
+#pragma unroll
+      for (int t2 = 0; t2 < 2; ++t2) {
+        const bf16x8 df = cvt_operand(s, 8 * t2);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) mfma_acc(dq[db], unit_tr<D>(kr, t, db, t2), df);
+      }
+      ks.release(st);
+      st = st + 1 == ks.NST ? 0 : st + 1;
+    }
+    settle_acc(dq);
+    if (i0 + ql >= d.Sq) continue;
+    const long row = ((long)b * d.Hq + hq) * d.Sq + i;
+    const bool whole = a.n_split_dq == 1;          // else: this split's own slice of the partial sums
+    float* const out = whole ? a.dq_accum + row * D : a.dq_part + ((long)split * d.B * d.Hq * d.Sq + row) * D;
+    f32x4 old[DB * 4] = {};
+    if (whole) {
+#pragma unroll
+      for (int x = 0; x < DB * 4; ++x) old[x] = *(const f32x4*)(out + 32 * (x / 4) + 8 * (x % 4) + 4 * g);
+    }
+#pragma unroll
+    for (int x = 0; x < DB * 4; ++x) {
+      f32x4 y = old[x];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) y[e] += dq[x / 4][4 * (x % 4) + e] * d.scale;
+      *(f32x4*)(out + 32 * (x / 4) + 8 * (x % 4) + 4 * g) = y;
+    }
+  }
+}
 
 // GENERAL = false: dense attention (no mask code, so that the steady-state loop is one basic block; a
 // key count that is no multiple of 64 moves the last tile back to end with the last key, and the keys it
@@ -112,6 +197,13 @@ bwd_dq_bf16_kernel(BwdArgs a) {
   DQ_STAMP(stamp0);
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, ql = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if constexpr (LIST == 3) {
+    unsigned long long any;
+    if (mask_streams(a.rows, b, qt, lane, &any)) {
+      dq_mask_stream<D>(a, smem, b, hk, hq, qt, split, any, wave, lane);
+      return;
+    }
+  }
   const int i_wave0 = qt * QM + wave * 32 * QB;     // first row (of the head, or of the group's list) of this wave
 
   // KV range of this split, in tiles
@@ -851,7 +943,7 @@ bwd_dq_bf16_kernel(BwdArgs a) {
 template <int D, bool GENERAL, int LIST = 0>
 hipError_t launch(const BwdArgs& a, long grid, hipStream_t s) {
   static SmemOnce once;
-  constexpr int lds = DqSmem<D>::TOTAL + (LIST == 3 ? NSTG * 256 : 0);
+  constexpr int lds = LIST == 3 ? mask_words_lds<D>() : DqSmem<D>::TOTAL;
   static_assert(lds <= 160 * 1024, "the layout fits a compute unit");
   hipError_t e = ensure_dynamic_lds((const void*)bwd_dq_bf16_kernel<D, GENERAL, LIST>, lds, &once);
   if (e != hipSuccess) return e;

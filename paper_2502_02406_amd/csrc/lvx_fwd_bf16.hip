@@ -27,6 +27,7 @@
 #include "lvx_internal.h"
 #include "lvx_mfma.h"
 #include "lvx_kv_ring.h"
+#include "lvx_mask_stream.h"
 
 #include <type_traits>
 
@@ -44,6 +45,129 @@ constexpr float LAZY_SUM = 64.0f;      // a lane's 16 probabilities of a half ma
 #define LVX_MASKED_WG_FACTOR 4L
 #endif
 constexpr int XE = LVX_FWD_XE;                  // elements of a half converted during the contraction (of 32)
+
+// Row tile qt of one head under a mask that shows its row blocks little (mask_streams, lvx_mask_stream.h): wave w
+// takes row blocks 2 w and 2 w + 1.  The reference of a row is the largest score it has seen, always: its
+// probability is 1, which bf16 holds exactly, and the few units of a row make the raises few.
+template <int D>
+__device__ __forceinline__ void fwd_mask_stream(const FwdArgs& a, char* smem, int b, int hk, int hq, int qt, int split,
+                                                unsigned long long any, int wave, int lane) {
+  constexpr int KS = D / 16, DB = D / 32;
+  using U = KeyUnit<D>;
+  const Dims& d = a.d;
+  const int g = lane >> 5, ql = lane & 31;
+  KeyStream<D> ks(a.k, a.v, d, b, hk, smem, wave, lane, a.mask.kv_block, false);
+  const UnitReads<D> kr(lane, false), vr(lane, true);
+  const float c2 = d.scale * LOG2E;
+  for (int rb = 2 * wave; rb < 2 * wave + 2; ++rb) {
+    const int i0 = qt * QM + 32 * rb;
+    if (i0 >= d.Sq) return;
+    const int i = min(i0 + ql, d.Sq - 1);
+    bf16x8 qf[KS];
+    const uint16_t* const q = (const uint16_t*)a.q + b * d.q_sb + hq * d.q_sh + (long)i * d.q_ss;
+#pragma unroll
+    for (int k = 0; k < KS; ++k) qf[k] = *(const bf16x8*)(q + 16 * k + 8 * g);
+    const int n = ks.start(a.rows, b, qt, rb, any, split, a.n_split);
+#pragma unroll
+    for (int k = 0; k < KS; ++k) asm volatile("" : "+a"(qf[k]));
+    f32x16 oacc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) { oacc[db] = zero16(); asm volatile("" : "+a"(oacc[db])); }
+    asm volatile("s_nop 7" ::: "memory");
+    float m = -INFINITY, l = 0.f;                  // reference (raw scores), this lane's share of the sum
+    int st = 0;
+    for (int p = 0; p < n; ++p) {
+      ks.arrive(n - 1 - p);
+      char* const t = ks.stage0 + st * U::STAGE;
+      bf16x8 ka[KS];
+#pragma unroll
+      for (int k = 0; k < KS; ++k) ka[k] = kr.plain(t, k);
+      const auto un = ks.unit();
+      f32x16 s;
+      mfma_first(s, ka[0], qf[0]);
+#pragma unroll
+      for (int k = 1; k < KS; ++k) mfma_next(s, ka[k], qf[k]);
+      settle_unit(s);
+      mask_unit(s, un.keys, un.word, ql, g);
+      float mx = s[0];
+#pragma unroll
+      for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+      mx = fmaxf(xhalf_max(mx), -1e30f);           // (a row whose scores are all -infinity needs a finite reference)
+      if (__any(mx > m)) {
+        settle_acc(oacc);
+        const float m_new = fmaxf(m, mx), alpha = __builtin_amdgcn_exp2f((m - m_new) * c2);     // m = -inf -> 0
+        m = m_new;
+        l *= alpha;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) oacc[db][v] *= alpha;
+          asm volatile("s_nop 7" : "+a"(oacc[db]));
+        }
+      }
+      const float mc = m * c2;
+      float sum = 0.f;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], c2, -mc));
+        sum += s[v];
+      }
+      l += sum;
+      ks.clear_past(t + U::TILE);
+#pragma unroll
+      for (int t2 = 0; t2 < 2; ++t2) {
+        const bf16x8 pf = cvt_operand(s, 8 * t2);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) mfma_acc(oacc[db], unit_tr<D>(vr, t + U::TILE, db, t2), pf);
+      }
+      ks.release(st);
+      st = st + 1 == ks.NST ? 0 : st + 1;
+    }
+    settle_acc(oacc);
+    const float l_tot = xhalf_sum(l);
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    const float lse = l_tot != 0.f ? m * d.scale + logf(l_tot) : -INFINITY;    // (NaN scores: NaN, which no combine drops)
+    if (i0 + ql >= d.Sq) continue;
+    const long row = ((long)b * d.Hq + hq) * d.Sq + i;
+    const bool part = a.n_split > 1 || a.partial;
+    float w0 = 0.f, w1 = inv, L1 = lse;
+    if (!part && a.merge_into) {                   // Rescale of Algorithm 1 with the running (O, L) of this row
+      const float L0 = a.lse[row], M = fmaxf(L0, lse);
+      w1 = 0.f;
+      L1 = -INFINITY;
+      if (M != -INFINITY) {
+        L1 = M + logf(expf(L0 - M) + expf(lse - M));
+        w0 = expf(L0 - L1);
+        w1 = expf(lse - L1) * inv;
+      }
+    }
+    const long prow = (long)(a.part0 + split) * d.B * d.Hq * d.Sq + row;
+    const long off = b * d.q_sb + hq * d.q_sh + (long)i * d.q_ss;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int col = 32 * db + 8 * q4 + 4 * g;
+        f32x4 y = {oacc[db][4 * q4] * w1, oacc[db][4 * q4 + 1] * w1, oacc[db][4 * q4 + 2] * w1, oacc[db][4 * q4 + 3] * w1};
+        if (part) {
+          *(f32x4*)(a.o_part + prow * D + col) = y;
+        } else if (a.merge_into) {
+          float* const o = (float*)a.o + row * D + col;
+          const f32x4 old = *(const f32x4*)o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[e] += w0 * old[e];
+          *(f32x4*)o = y;
+        } else if (a.o_is_f32) {
+          *(f32x4*)((float*)a.o + off + col) = y;
+        } else {
+          const u32x2 z = {pack2_bf16(y[0], y[1]), pack2_bf16(y[2], y[3])};
+          *(u32x2*)((uint16_t*)a.o + off + col) = z;
+        }
+      }
+    // (both half-waves of the row have read L before: the loads precede this store in program order)
+    if (g == 0) (part ? a.lse_part[prow] : a.lse[row]) = L1;
+  }
+}
 
 // Dense attention, no mask code, so that nothing stands between the phases of the pipeline (other
 // masks: lvx_fwd_general_bf16.hip).  A key count that is no multiple of 64 needs none either: the last
@@ -74,7 +198,8 @@ constexpr int XE = LVX_FWD_XE;                  // elements of a half converted 
 // Bound by the same issue slots as the dense loop, plus about 45 instructions a tile.  2048 rows x 28
 // heads in chunks of 64 against 32 frames of 729 keys, causal, D = 128: 0.82 -> 0.42 ms (830 TFLOP/s of
 // visible pairs); 4096 rows x 8 heads in chunks of 2, each seeing one of 2048 frames of 64 keys, D = 64:
-// 0.80 -> 0.16 ms for 268 MB of K and V, 0.02 of them for the references: every tile is some row's first.
+// 0.80 -> 0.16 ms for 268 MB of K and V, 0.02 of them for the references: every tile is some row's first
+// (such tiles are streamed since: fwd_mask_stream).
 template <int D, int LIST = 0>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 fwd_bf16_kernel(FwdArgs a) {
@@ -125,6 +250,13 @@ fwd_bf16_kernel(FwdArgs a) {
 
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, ql = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if constexpr (LIST == 3) {
+    unsigned long long any;
+    if (mask_streams(a.rows, b, qt, lane, &any)) {
+      fwd_mask_stream<D>(a, smem, b, hk, hq0, qt, split, any, wave, lane);
+      return;
+    }
+  }
   const int r_wave0 = qt * QM + wave * 32 * QB;     // first row (of the group's list) of this wave
 
   // KV range of this split, in tiles
@@ -806,7 +938,7 @@ fwd_bf16_kernel(FwdArgs a) {
 template <int D, int LIST = 0>
 hipError_t launch(const FwdArgs& a, long grid, hipStream_t s) {
   static SmemOnce once;
-  constexpr int lds = KvSmem<D>::TOTAL + (LIST == 3 ? NSTG * 256 : 0);
+  constexpr int lds = LIST == 3 ? mask_words_lds<D>() : KvSmem<D>::TOTAL;
   static_assert(lds <= 160 * 1024, "the layout fits a compute unit");
   const hipError_t e = ensure_dynamic_lds((const void*)fwd_bf16_kernel<D, LIST>, lds, &once);
   if (e != hipSuccess) return e;

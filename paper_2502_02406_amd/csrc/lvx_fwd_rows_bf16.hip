@@ -16,12 +16,8 @@
 // 31 -> 7.3 us (256 workgroups with 25 units of keys each, where the dense kernel's split stops at 48 of
 // 16 tiles).  With the combine: 238 -> 181 us and 42.4 -> 12.8 us a call; 64 rows (16 x 4 heads) against 65536 keys
 // 86 -> 62 us; 8 batches x 16 heads against 20000 keys 281 -> 222 us.
-//
-// Tiles are kept unpadded, the 16-byte chunks of a row permuted by the row (by the source addresses
-// of the copies, which may be anything): K so that one chunk of 16 consecutive rows covers all
-// banks, V so that 64 bytes of four consecutive rows do.
 #include "lvx_internal.h"
-#include "lvx_mfma.h"
+#include "lvx_key_units.h"
 
 namespace lvx {
 
@@ -30,23 +26,13 @@ namespace {
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LAZY = 6.0f;           // raise the reference only when a row tops it by 2^LAZY
 constexpr int NWV = 4;                 // waves per workgroup
-constexpr int UK = 32;                 // keys per unit
 constexpr int NST = 2;                 // stages per wave
 
-template <int D> struct RowsSmem {
-  static constexpr int CPR = D / 8;                 // 16-byte chunks of data per row
-  static constexpr int CH = D == 64 ? 8 : 16;       // chunk places per row (96-wide heads: four unused)
-  static constexpr int ROWB = CH * 16;
-  static constexpr int TILE = UK * ROWB;
-  static constexpr int NC = TILE / 1024;            // wave-level copies per tile
-  static constexpr int STAGE = 2 * TILE;            // K, then V
-  static constexpr int WAVE = NST * STAGE;
+template <int D> struct RowsSmem : KeyUnit<D> {
+  static constexpr int WAVE = NST * KeyUnit<D>::STAGE;
   static constexpr int STATS = NWV * WAVE;          // combine: [waves][64 rows] references and sums
   static constexpr int TOTAL = STATS + NWV * 64 * 8;
 };
-// where chunk c of row r stands
-template <int D> __device__ __forceinline__ int k_swz(int r) { return D == 64 ? (r >> 1) & 7 : r & 15; }
-template <int D> __device__ __forceinline__ int v_swz(int r) { return D == 64 ? 4 * ((r >> 1) & 1) : 4 * (r & 3); }
 
 template <int D, int NB>
 __global__ void __launch_bounds__(256) fwd_rows_bf16_kernel(FwdArgs a) {
@@ -69,11 +55,8 @@ __global__ void __launch_bounds__(256) fwd_rows_bf16_kernel(FwdArgs a) {
   const char* const k0 = (const char*)a.k + (b * d.kv_sb + hk * d.kv_sh) * 2;
   const char* const v0 = (const char*)a.v + (b * d.kv_sb + hk * d.kv_sh) * 2;
   const unsigned row_bytes = (unsigned)(d.kv_ss * 2);
-  // copy n fills 64 chunk places in a row: lane l place 64 n + l = (row, place) of the tile
-  auto copy_off = [&](int n, int swz_of_v, int last_row) __attribute__((always_inline)) -> unsigned {
-    const int slot = 64 * n + lane, r = slot / CH;
-    const int c = (slot % CH) ^ (swz_of_v ? v_swz<D>(r) : k_swz<D>(r));
-    return (unsigned)min(r, last_row) * row_bytes + (unsigned)min(c, CPR - 1) * 16;
+  auto copy_off = [&](int n, int of_v, int last_row) __attribute__((always_inline)) -> unsigned {
+    return unit_copy_off<D>(n, of_v, last_row, row_bytes, lane);
   };
   unsigned offk[NC], offv[NC];
 #pragma unroll
