@@ -135,6 +135,12 @@ lvx_status lvx_xattn_fwd_merge(const lvx_problem* p, lvx_dtype dtype, const void
                                const void* v, const lvx_mask* mask, float* o_acc, float* lse_acc,
                                void* workspace, size_t workspace_bytes, void* hip_stream);
 
+/* The last visit of a block loop (LVX_BF16 only, LVX_ERR_DTYPE otherwise): lvx_xattn_fwd_merge whose merged O is
+ * rounded and written to o (Q's strides, which may be Q itself) instead of o_acc; o_acc then holds nothing of use. */
+lvx_status lvx_xattn_fwd_merge_last(const lvx_problem* p, lvx_dtype dtype, const void* q, const void* k,
+                                    const void* v, const lvx_mask* mask, float* o_acc, float* lse_acc, void* o,
+                                    void* workspace, size_t workspace_bytes, void* hip_stream);
+
 /* Backward pass of one visit: gradients of loss = sum(O * dO) for the K/V block passed, with the
  * attention probabilities recomputed as p_ij = exp(scale * <Q_i, K_j> - L_i) from the saved L
  * (Section 3.2 saves only x, O and L; Table 1 counts the five matrix products).
@@ -164,6 +170,18 @@ lvx_status lvx_xattn_bwd_stages(const lvx_problem* p, lvx_dtype dtype, const voi
                                 const lvx_mask* mask, float* dq_accum, void* dk, void* dv,
                                 void* workspace, size_t workspace_bytes, void* hip_stream,
                                 unsigned stages);
+
+/* One visit of a block loop's backward pass: lvx_xattn_bwd, but
+ *   first != 0: dq_accum is overwritten, not added to (no zeroing before the first block), and delta = rowsum(dO * O)
+ *               is left in the workspace, which the following visits of the same query block with
+ *               first == 0 read there (same workspace, same Q, O, L and dO; blocks of no more keys);
+ *   dq != NULL: this is the last visit; the sum is rounded into dq (type `dtype`, Q's strides) and dq_accum holds
+ *               nothing of use.  LVX_BF16 only (LVX_ERR_DTYPE otherwise): float32 sums are the result.
+ * Never the one-kernel form. */
+lvx_status lvx_xattn_bwd_visit(const lvx_problem* p, lvx_dtype dtype, const void* q, const void* k,
+                               const void* v, const void* o, const float* lse, const void* d_o,
+                               const lvx_mask* mask, float* dq_accum, void* dk, void* dv,
+                               void* workspace, size_t workspace_bytes, void* hip_stream, int first, void* dq);
 
 /* Where lvx_xattn_bwd reports that it could not finish dQ.  For dense bf16 problems with D = 128 the
  * backward forms all five products of Table 1 in one kernel whose workgroups add their dQ tiles

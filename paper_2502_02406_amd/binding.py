@@ -25,8 +25,8 @@ LVX_BWD_FUSED, LVX_BWD_SPLIT = 8, 16
 
 LVX_STATIC_SCRATCH_BYTES = 64 << 20
 
-EXPORTS = ("lvx_xattn_workspace_bytes", "lvx_xattn_fwd", "lvx_xattn_fwd_static", "lvx_xattn_fwd_merge", "lvx_xattn_merge", "lvx_xattn_bwd",
-           "lvx_xattn_bwd_stages", "lvx_xattn_bwd_error_word", "lvx_xattn_dq_finalize", "lvx_xattn_project", "lvx_xattn_project_bwd", "lvx_strerror")
+EXPORTS = ("lvx_xattn_workspace_bytes", "lvx_xattn_fwd", "lvx_xattn_fwd_static", "lvx_xattn_fwd_merge", "lvx_xattn_fwd_merge_last", "lvx_xattn_merge", "lvx_xattn_bwd",
+           "lvx_xattn_bwd_stages", "lvx_xattn_bwd_visit", "lvx_xattn_bwd_error_word", "lvx_xattn_dq_finalize", "lvx_xattn_project", "lvx_xattn_project_bwd", "lvx_strerror")
 
 
 class LvxError(RuntimeError):
@@ -77,6 +77,8 @@ def load() -> C.CDLL:
         lib.lvx_xattn_fwd_merge.argtypes = [C.POINTER(lvx_problem), C.c_int, C.c_void_p, C.c_void_p,
                                             C.c_void_p, C.POINTER(lvx_mask), C.c_void_p, C.c_void_p,
                                             C.c_void_p, C.c_size_t, C.c_void_p]
+        lib.lvx_xattn_fwd_merge_last.restype = C.c_int
+        lib.lvx_xattn_fwd_merge_last.argtypes = lib.lvx_xattn_fwd_merge.argtypes[:8] + [C.c_void_p] + lib.lvx_xattn_fwd_merge.argtypes[8:]
         lib.lvx_xattn_merge.restype = C.c_int
         lib.lvx_xattn_merge.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32,
                                         C.POINTER(C.c_void_p), C.POINTER(C.c_void_p), C.c_int,
@@ -88,6 +90,8 @@ def load() -> C.CDLL:
                                       C.c_void_p, C.c_size_t, C.c_void_p]
         lib.lvx_xattn_bwd_stages.restype = C.c_int
         lib.lvx_xattn_bwd_stages.argtypes = lib.lvx_xattn_bwd.argtypes + [C.c_uint]
+        lib.lvx_xattn_bwd_visit.restype = C.c_int
+        lib.lvx_xattn_bwd_visit.argtypes = lib.lvx_xattn_bwd.argtypes + [C.c_int, C.c_void_p]
         lib.lvx_xattn_bwd_error_word.restype = C.c_int
         lib.lvx_xattn_bwd_error_word.argtypes = [C.POINTER(lvx_problem), C.c_int, C.POINTER(lvx_mask), C.c_void_p,
                                                  C.c_size_t, C.POINTER(C.c_void_p)]
@@ -250,6 +254,7 @@ class Calls:
     def __init__(self, p: lvx_problem, dtype: torch.dtype, workspace: torch.Tensor):
         lib = load()
         self._f, self._m, self._b = lib.lvx_xattn_fwd, lib.lvx_xattn_fwd_merge, lib.lvx_xattn_bwd_stages
+        self._l, self._v = lib.lvx_xattn_fwd_merge_last, lib.lvx_xattn_bwd_visit
         self._p, self._dt = C.byref(p), dtype_code(dtype)
         self._ws, self._n = workspace.data_ptr(), workspace.numel() * workspace.element_size()
         self._s = _stream()
@@ -261,6 +266,15 @@ class Calls:
     def fwd_merge(self, q: int, k: int, v: int, mask: Optional[lvx_mask], o_acc: int, lse_acc: int) -> None:
         _check(self._m(self._p, self._dt, q, k, v, C.byref(mask) if mask is not None else None, o_acc, lse_acc,
                        self._ws, self._n, self._s), "lvx_xattn_fwd_merge")
+
+    def fwd_merge_last(self, q: int, k: int, v: int, mask: Optional[lvx_mask], o_acc: int, lse_acc: int, o: int) -> None:
+        _check(self._l(self._p, self._dt, q, k, v, C.byref(mask) if mask is not None else None, o_acc, lse_acc, o,
+                       self._ws, self._n, self._s), "lvx_xattn_fwd_merge_last")
+
+    def bwd_visit(self, q: int, k: int, v: int, o: int, lse: int, d_o: int, mask: Optional[lvx_mask], dq_accum: int,
+                  dk: int, dv: int, first: bool, dq: Optional[int]) -> None:
+        _check(self._v(self._p, self._dt, q, k, v, o, lse, d_o, C.byref(mask) if mask is not None else None, dq_accum,
+                       dk, dv, self._ws, self._n, self._s, int(first), dq), "lvx_xattn_bwd_visit")
 
     def bwd(self, q: int, k: int, v: int, o: int, lse: int, d_o: int, mask: Optional[lvx_mask], dq_accum: int,
             dk: int, dv: int, stages: int) -> None:

@@ -134,9 +134,10 @@ class BlockLoop:
         call.fwd(qp, kp, vp, self._mask_for(0), op, torch.float32, lp)
         for n in range(1, self.n_blocks):       # the FlashAttention call and Rescale of Algorithm 1 in one call
             p.Skv = self._keys_of(n, k)
-            call.fwd_merge(qp, kp + n * step, vp + n * step, self._mask_for(n), op, lp)
-        if self.o_acc is not self.o:
-            B.lvx_xattn_merge([self.o_acc], [self.lse], self.o, self.lse)    # round to the output dtype
+            if n == self.n_blocks - 1 and self.o_acc is not self.o:          # ... which rounds to the output dtype, the last time
+                call.fwd_merge_last(qp, kp + n * step, vp + n * step, self._mask_for(n), op, lp, self.o.data_ptr())
+            else:
+                call.fwd_merge(qp, kp + n * step, vp + n * step, self._mask_for(n), op, lp)
         return self.o, self.lse
 
     def backward(self, q, k, v, o, lse, d_o, dk, dv) -> torch.Tensor:
@@ -148,10 +149,18 @@ class BlockLoop:
             raise ValueError("L has to have a value for every row of Q")
         if self.dq is self.dq_accum:
             q, k, v, o, lse, d_o = _apart(self.dq, q, k, v, o, lse, d_o)
-        self.dq_accum.zero_()
         call = B.Calls(p, q.dtype, self.ws)
         qp, kp, vp, dkp, dvp = q.data_ptr(), k.data_ptr(), v.data_ptr(), dk.data_ptr(), dv.data_ptr()
         op, lp, gp, ap = o.data_ptr(), lse.data_ptr(), d_o.data_ptr(), self.dq_accum.data_ptr()
+        if not self.bwd_flags & B.LVX_BWD_FUSED:
+            # (the first visit overwrites the dQ sums and leaves delta in the workspace, the last one rounds the sums)
+            last = self.dq.data_ptr() if self.dq is not self.dq_accum else None
+            for n in range(self.n_blocks):
+                p.Skv = self._keys_of(n, k)
+                call.bwd_visit(qp, kp + n * step, vp + n * step, op, lp, gp, self._mask_for(n), ap, dkp + n * step, dvp + n * step,
+                               n == 0, last if n == self.n_blocks - 1 else None)
+            return self.dq
+        self.dq_accum.zero_()
         for n in range(self.n_blocks):
             # delta = rowsum(dO * O) depends on the query block only: the first visit computes it
             # into the workspace, the others reuse it
@@ -207,8 +216,12 @@ class RecomputeLayer:
                 return lp.o, lp.lse
             if n == 0:
                 B.lvx_xattn_fwd(p, self.q, self.k, self.v, None, self.o_acc, lp.lse, lp.ws)
-            else:
+            elif n < self.n_blocks - 1 or self.q.dtype == torch.float32:
                 B.lvx_xattn_fwd_merge(p, self.q, self.k, self.v, None, self.o_acc, lp.lse, lp.ws)
+            else:
+                B.Calls(p, self.q.dtype, lp.ws).fwd_merge_last(self.q.data_ptr(), self.k.data_ptr(), self.v.data_ptr(), None,
+                                                               self.o_acc.data_ptr(), lp.lse.data_ptr(), lp.o.data_ptr())
+                return lp.o, lp.lse
         B.lvx_xattn_merge([self.o_acc], [lp.lse], lp.o, lp.lse)
         return lp.o, lp.lse
 
@@ -216,17 +229,18 @@ class RecomputeLayer:
         """(dx, dy in the input dtype, dW_Q, dW_KV float32) from x, y, (O, L) and dO alone."""
         lp = self.loop
         B.lvx_xattn_project(x, wq, [self.q])                       # Q again
-        lp.dq_accum.zero_()
         self.dwq.zero_()
         self.dwkv.zero_()
         p = B.make_problem(self.q, self.k, lp.scale)
+        assert o.stride() == self.q.stride() and d_o.stride() == self.q.stride()
+        call = B.Calls(p, self.q.dtype, lp.ws)
+        last = lp.dq.data_ptr() if lp.dq is not lp.dq_accum else None
         for n in range(self.n_blocks):
             yb = self._kv_of_block(y, wkv, n)                       # K, V of the block again
-            stages = B.LVX_BWD_ALL if n == 0 else (B.LVX_BWD_DKDV | B.LVX_BWD_DQ)
-            B.lvx_xattn_bwd(p, self.q, self.k, self.v, o, lse, d_o, None, lp.dq_accum, self.dk, self.dv, lp.ws, stages)
+            call.bwd_visit(self.q.data_ptr(), self.k.data_ptr(), self.v.data_ptr(), o.data_ptr(), lse.data_ptr(), d_o.data_ptr(), None,
+                           lp.dq_accum.data_ptr(), self.dk.data_ptr(), self.dv.data_ptr(), n == 0,
+                           last if n == self.n_blocks - 1 else None)
             B.lvx_xattn_project_bwd(yb, wkv, [self.dk, self.dv],
                                     dx=self.dy[:, n * self.blk:(n + 1) * self.blk], dw=self.dwkv)
-        if lp.dq is not lp.dq_accum:
-            B.lvx_xattn_dq_finalize(p, lp.dq_accum, lp.dq)
         B.lvx_xattn_project_bwd(x, wq, [lp.dq], dx=self.dx, dw=self.dwq)
         return self.dx, self.dy, self.dwq, self.dwkv

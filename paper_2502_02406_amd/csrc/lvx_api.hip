@@ -257,6 +257,7 @@ lvx_status lvx_xattn_fwd(const lvx_problem* p, lvx_dtype dtype, const void* q, c
   a.mask = make_mask(mask);
   a.q = q; a.k = k; a.v = v; a.o = o; a.o_is_f32 = o_dtype == LVX_F32; a.lse = lse;
   a.merge_into = 0;
+  a.o_last = nullptr;
   a.partial = 0; a.part0 = 0; a.pass = 0;
   const FwdPlan plan = fwd_plan(a.d, dtype, a.mask, 0, workspace_bytes);
   a.n_split = plan.n_split;
@@ -292,9 +293,9 @@ lvx_status lvx_xattn_fwd(const lvx_problem* p, lvx_dtype dtype, const void* q, c
   return LVX_OK;
 }
 
-lvx_status lvx_xattn_fwd_merge(const lvx_problem* p, lvx_dtype dtype, const void* q, const void* k,
-                               const void* v, const lvx_mask* mask, float* o_acc, float* lse_acc,
-                               void* workspace, size_t workspace_bytes, void* hip_stream) {
+static lvx_status fwd_merge(const lvx_problem* p, lvx_dtype dtype, const void* q, const void* k, const void* v,
+                            const lvx_mask* mask, float* o_acc, float* lse_acc, void* o_last, void* workspace,
+                            size_t workspace_bytes, void* hip_stream) {
   lvx_status st = check_problem(p, dtype);
   if (st != LVX_OK) return st;
   if (!q || !k || !v || !o_acc || !lse_acc) return LVX_ERR_NULL;
@@ -307,6 +308,7 @@ lvx_status lvx_xattn_fwd_merge(const lvx_problem* p, lvx_dtype dtype, const void
     return LVX_ERR_STRIDE;      // (part of the interface, although the kernel would read any)
   a.mask = make_mask(mask);
   a.q = q; a.k = k; a.v = v; a.o_is_f32 = 1;
+  a.o_last = o_last;
   a.partial = 0; a.part0 = 0; a.pass = 0;
   const FwdPlan plan = fwd_plan(a.d, dtype, a.mask, 1, workspace_bytes);          // (the running state is one more part of the combine)
   a.n_split = plan.n_split;
@@ -342,8 +344,27 @@ lvx_status lvx_xattn_fwd_merge(const lvx_problem* p, lvx_dtype dtype, const void
   m.rows = (long)rows; m.D = a.d.D; m.o_out = o_acc; m.lse_out = lse_acc;
   m.group = a.d.G * a.d.Sq; m.skip = 256 * a.whole;
   m.Hq = a.d.Hq; m.Sq = a.d.Sq; m.o_ss = a.d.D; m.o_sh = (long)a.d.Sq * a.d.D; m.o_sb = (long)a.d.Hq * a.d.Sq * a.d.D;
-  e = launch_merge(m, 1, 1, s);
+  if (o_last != nullptr) {
+    m.o_out = o_last;
+    m.o_sb = a.d.q_sb; m.o_sh = a.d.q_sh; m.o_ss = a.d.q_ss;
+  }
+  e = launch_merge(m, 1, o_last == nullptr, s);
   return e == hipSuccess ? LVX_OK : LVX_ERR_HIP;
+}
+
+lvx_status lvx_xattn_fwd_merge(const lvx_problem* p, lvx_dtype dtype, const void* q, const void* k,
+                               const void* v, const lvx_mask* mask, float* o_acc, float* lse_acc,
+                               void* workspace, size_t workspace_bytes, void* hip_stream) {
+  return fwd_merge(p, dtype, q, k, v, mask, o_acc, lse_acc, nullptr, workspace, workspace_bytes, hip_stream);
+}
+
+lvx_status lvx_xattn_fwd_merge_last(const lvx_problem* p, lvx_dtype dtype, const void* q, const void* k,
+                                    const void* v, const lvx_mask* mask, float* o_acc, float* lse_acc, void* o,
+                                    void* workspace, size_t workspace_bytes, void* hip_stream) {
+  if (!o) return LVX_ERR_NULL;
+  if (!aligned16(o)) return LVX_ERR_STRIDE;
+  if (dtype == LVX_F32) return LVX_ERR_DTYPE;      // (a float32 running result is the result)
+  return fwd_merge(p, dtype, q, k, v, mask, o_acc, lse_acc, o, workspace, workspace_bytes, hip_stream);
 }
 
 lvx_status lvx_xattn_merge(int32_t B, int32_t Hq, int32_t Sq, int32_t D, int32_t n_parts,
@@ -379,11 +400,10 @@ lvx_status lvx_xattn_bwd(const lvx_problem* p, lvx_dtype dtype, const void* q, c
                               workspace_bytes, hip_stream, LVX_BWD_ALL);
 }
 
-lvx_status lvx_xattn_bwd_stages(const lvx_problem* p, lvx_dtype dtype, const void* q, const void* k,
-                                const void* v, const void* o, const float* lse, const void* d_o,
-                                const lvx_mask* mask, float* dq_accum, void* dk, void* dv,
-                                void* workspace, size_t workspace_bytes, void* hip_stream,
-                                unsigned stages) {
+static lvx_status bwd_visit(const lvx_problem* p, lvx_dtype dtype, const void* q, const void* k, const void* v,
+                            const void* o, const float* lse, const void* d_o, const lvx_mask* mask, float* dq_accum,
+                            void* dk, void* dv, void* workspace, size_t workspace_bytes, void* hip_stream, unsigned stages,
+                            bool first, void* dq_last) {
   lvx_status st = check_problem(p, dtype);
   if (st != LVX_OK) return st;
   if ((stages & LVX_BWD_ALL) == 0 || (stages & ~(unsigned)(LVX_BWD_ALL | LVX_BWD_FUSED | LVX_BWD_SPLIT))) return LVX_ERR_SHAPE;
@@ -414,6 +434,7 @@ lvx_status lvx_xattn_bwd_stages(const lvx_problem* p, lvx_dtype dtype, const voi
   a.stats = (float*)((char*)workspace + align_up((size_t)a.d.B * a.d.Hq * a.d.Sq * sizeof(float)));
   a.stats_ovl = has_stats_ovl(a.d) ? a.stats + stats_floats(a.d) : nullptr;
   a.dq_accum = dq_accum; a.dk = dk; a.dv = dv;
+  a.dq_first = first; a.dq_last = dq_last;
   a.dq_part = n_slices > 0 ? (float*)((char*)workspace + bwd_ws_fixed(a.d)) : nullptr;
   a.rows = MaskRows{};
   a.rows_ws = mask != nullptr && n_slices > 0 ? (char*)workspace + bwd_ws_fixed(a.d) + (n_slices - 1) * bwd_slice_bytes(a.d) : nullptr;
@@ -435,6 +456,25 @@ lvx_status lvx_xattn_bwd_stages(const lvx_problem* p, lvx_dtype dtype, const voi
   if (stages & (LVX_BWD_DKDV | LVX_BWD_DQ))
     e = dtype == LVX_BF16 ? launch_bwd_bf16(a, stages & LVX_BWD_ALL, s) : launch_bwd_f32(a, stages & LVX_BWD_ALL, s);
   return e == hipSuccess ? LVX_OK : LVX_ERR_HIP;
+}
+
+lvx_status lvx_xattn_bwd_stages(const lvx_problem* p, lvx_dtype dtype, const void* q, const void* k,
+                                const void* v, const void* o, const float* lse, const void* d_o,
+                                const lvx_mask* mask, float* dq_accum, void* dk, void* dv,
+                                void* workspace, size_t workspace_bytes, void* hip_stream,
+                                unsigned stages) {
+  return bwd_visit(p, dtype, q, k, v, o, lse, d_o, mask, dq_accum, dk, dv, workspace, workspace_bytes, hip_stream, stages, false,
+                   nullptr);
+}
+
+lvx_status lvx_xattn_bwd_visit(const lvx_problem* p, lvx_dtype dtype, const void* q, const void* k,
+                               const void* v, const void* o, const float* lse, const void* d_o,
+                               const lvx_mask* mask, float* dq_accum, void* dk, void* dv,
+                               void* workspace, size_t workspace_bytes, void* hip_stream, int first, void* dq) {
+  if (dq && dtype == LVX_F32) return LVX_ERR_DTYPE;      // (float32 sums are the result)
+  if (dq && !aligned16(dq)) return LVX_ERR_STRIDE;
+  return bwd_visit(p, dtype, q, k, v, o, lse, d_o, mask, dq_accum, dk, dv, workspace, workspace_bytes, hip_stream,
+                   (first ? LVX_BWD_ALL : LVX_BWD_DKDV | LVX_BWD_DQ) | LVX_BWD_SPLIT, first != 0, dq);
 }
 
 lvx_status lvx_xattn_bwd_error_word(const lvx_problem* p, lvx_dtype dtype, const lvx_mask* mask,

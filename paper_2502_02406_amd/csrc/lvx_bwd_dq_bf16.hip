@@ -115,7 +115,7 @@ __device__ __forceinline__ void dq_mask_stream(const BwdArgs& a, char* smem, int
     const bool whole = a.n_split_dq == 1;          // else: this split's own slice of the partial sums
     float* const out = whole ? a.dq_accum + row * D : a.dq_part + ((long)split * d.B * d.Hq * d.Sq + row) * D;
     f32x4 old[DB * 4] = {};
-    if (whole) {
+    if (whole && !a.dq_first) {
 #pragma unroll
       for (int x = 0; x < DB * 4; ++x) old[x] = *(const f32x4*)(out + 32 * (x / 4) + 8 * (x % 4) + 4 * g);
     }
@@ -124,7 +124,13 @@ __device__ __forceinline__ void dq_mask_stream(const BwdArgs& a, char* smem, int
       f32x4 y = old[x];
 #pragma unroll
       for (int e = 0; e < 4; ++e) y[e] += dq[x / 4][4 * (x % 4) + e] * d.scale;
-      *(f32x4*)(out + 32 * (x / 4) + 8 * (x % 4) + 4 * g) = y;
+      const int col = 32 * (x / 4) + 8 * (x % 4) + 4 * g;
+      if (whole && a.dq_last) {
+        const u32x2 z = {pack2_bf16(y[0], y[1]), pack2_bf16(y[2], y[3])};
+        *(u32x2*)((uint16_t*)a.dq_last + off + col) = z;
+      } else {
+        *(f32x4*)(out + col) = y;
+      }
     }
   }
 }
@@ -909,8 +915,8 @@ bwd_dq_bf16_kernel(BwdArgs a) {
   // re-read it and store nothing.
   constexpr int NB = 8;
   for (int r00 = 0; r00 < 32 * QB; r00 += NB * RPI) {
-    f32x4 old[NB];
-    if (whole) {
+    f32x4 old[NB] = {};
+    if (whole && !a.dq_first) {
 #pragma unroll
       for (int u = 0; u < NB; ++u) {
         const int i = min(i_wave0 + r00 + u * RPI + rsub, rows_lim - 1);
@@ -924,7 +930,13 @@ bwd_dq_bf16_kernel(BwdArgs a) {
       if (!ok) continue;
       f32x4 y = *(const f32x4*)(tbuf + r * RP + col * 4);
       if (whole) y += old[u];
-      *(f32x4*)(out0 + (long)i * D + col) = y;
+      if (whole && a.dq_last) {
+        const int h = PACK ? hq + i / d.Sq : hq, ih = PACK ? i % d.Sq : i;
+        const u32x2 z = {pack2_bf16(y[0], y[1]), pack2_bf16(y[2], y[3])};
+        *(u32x2*)((uint16_t*)a.dq_last + b * d.q_sb + h * d.q_sh + (long)ih * d.q_ss + col) = z;
+      } else {
+        *(f32x4*)(out0 + (long)i * D + col) = y;
+      }
     }
   }
 #ifdef LVX_DQ_PROBE
@@ -999,7 +1011,7 @@ hipError_t launch_one(const BwdArgs& a, bool general, hipStream_t s) {
   else e = general ? launch<128, true>(a, grid, s) : launch<128, false>(a, grid, s);
   if (e == hipSuccess && a.n_split_dq > 1) {
     const long group = (long)G * d.Sq * d.D, run = group - (long)a.dq_whole * QM * d.D;
-    e = launch_dq_reduce(a.dq_part, a.n_split_dq, d.B * d.Hkv * run, run, group, a.dq_accum, s);
+    e = launch_dq_reduce(d, a.dq_part, a.n_split_dq, d.B * d.Hkv * run, run, group, a.dq_accum, a.dq_first, a.dq_last, s);
   }
   return e;
 }
@@ -1039,6 +1051,8 @@ hipError_t launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s) {
     BwdArgs p1 = a, p2 = a;
     p1.dq_pass = 1;
     p2.dq_pass = 2;
+    p1.dq_last = nullptr;
+    p2.dq_first = 0;
     const hipError_t e = launch_one(p1, false, s);
     return e != hipSuccess ? e : launch_one(p2, true, s);
   }

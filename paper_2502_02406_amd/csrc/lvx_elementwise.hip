@@ -324,18 +324,37 @@ hipError_t launch_delta(const Dims& d, const void* o, const void* d_o, int is_f3
 
 // dq_accum += sum of the KV splits' partial dQ (float32, contiguous; where only the last rows of a group were split,
 // `run` of its `group` floats).  One thread per 4 elements.
-__global__ void __launch_bounds__(256) dq_reduce_kernel(const float* parts, int n_parts, long n, long run, long group, float* acc) {
+// LAST: the sum is the result, rounded to bf16 with Q's strides.
+template <bool FIRST, bool LAST>
+__global__ void __launch_bounds__(256) dq_reduce_kernel(Dims d, const float* parts, int n_parts, long n, long run, long group, float* acc,
+                                                        uint16_t* dq) {
   const long i = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i >= n) return;
-  if (run != group) acc += (i / run + 1) * (group - run);
-  f32x4 x = *(const f32x4*)(acc + i);
+  const long at = run != group ? i + (i / run + 1) * (group - run) : i;
+  f32x4 x = {0.f, 0.f, 0.f, 0.f};
+  if (!FIRST) x = *(const f32x4*)(acc + at);
+#pragma unroll 4
   for (int k = 0; k < n_parts; ++k) x += *(const f32x4*)(parts + (long)k * n + i);
-  *(f32x4*)(acc + i) = x;
+  if (!LAST) {
+    *(f32x4*)(acc + at) = x;
+    return;
+  }
+  const long row = at / d.D;
+  const int c = (int)(at % d.D);
+  const long ih = row % d.Sq, h = (row / d.Sq) % d.Hq, b = row / ((long)d.Sq * d.Hq);
+  unsigned* const dst = (unsigned*)(dq + b * d.q_sb + h * d.q_sh + ih * d.q_ss + c);
+  dst[0] = pack_bf16(x[0], x[1]);
+  dst[1] = pack_bf16(x[2], x[3]);
 }
 
-hipError_t launch_dq_reduce(const float* parts, int n_parts, long n, long run, long group, float* dq_accum, hipStream_t s) {
+hipError_t launch_dq_reduce(const Dims& d, const float* parts, int n_parts, long n, long run, long group, float* dq_accum, bool first,
+                            void* dq_last, hipStream_t s) {
   const unsigned blocks = (unsigned)((n / 4 + 255) / 256);
-  dq_reduce_kernel<<<blocks, 256, 0, s>>>(parts, n_parts, n, run, group, dq_accum);
+  uint16_t* const dq = (uint16_t*)dq_last;
+  if (first && dq) dq_reduce_kernel<true, true><<<blocks, 256, 0, s>>>(d, parts, n_parts, n, run, group, dq_accum, dq);
+  else if (first) dq_reduce_kernel<true, false><<<blocks, 256, 0, s>>>(d, parts, n_parts, n, run, group, dq_accum, dq);
+  else if (dq) dq_reduce_kernel<false, true><<<blocks, 256, 0, s>>>(d, parts, n_parts, n, run, group, dq_accum, dq);
+  else dq_reduce_kernel<false, false><<<blocks, 256, 0, s>>>(d, parts, n_parts, n, run, group, dq_accum, dq);
   return hipGetLastError();
 }
 

@@ -341,7 +341,8 @@ __device__ void bwd_dq_f32(const BwdArgs& a, int tile, int hk, int b, char* smem
     const int r = x / (D / 4), c = x % (D / 4) * 4;
     if (r0 + r >= rows) continue;
     float* const o = a.dq_accum + (row_b + r0 + r) * D + c;    // (rows are owned by one workgroup)
-    f32x4 old = *(const f32x4*)o;
+    f32x4 old = {0.f, 0.f, 0.f, 0.f};
+    if (!a.dq_first) old = *(const f32x4*)o;
     f32x4 y = *(const f32x4*)(lds + r * P + c);
 #pragma unroll
     for (int w = 1; w < NW; ++w) y += *(const f32x4*)(lds + w * 2 * T + r * P + c);

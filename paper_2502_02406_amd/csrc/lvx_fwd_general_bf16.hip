@@ -434,7 +434,12 @@ fwd_general_bf16_kernel(FwdArgs a) {
         const f32x4 x = *(const f32x4*)dst;
         f32x4 y = {w0 * x[0] + w1 * oacc[db][4 * q4], w0 * x[1] + w1 * oacc[db][4 * q4 + 1],
                    w0 * x[2] + w1 * oacc[db][4 * q4 + 2], w0 * x[3] + w1 * oacc[db][4 * q4 + 3]};
-        *(f32x4*)dst = y;
+        if (a.o_last) {
+          const u32x2 z = {pack2_bf16(y[0], y[1]), pack2_bf16(y[2], y[3])};
+          *(u32x2*)((uint16_t*)a.o_last + b * d.q_sb + hq * d.q_sh + (long)i_lane * d.q_ss + 32 * db + 8 * q4 + 4 * g) = z;
+        } else {
+          *(f32x4*)dst = y;
+        }
       }
     // (both half-waves of the row have read L0 above: the loads precede this store in program order)
     if (g == 0) a.lse[row] = L1;

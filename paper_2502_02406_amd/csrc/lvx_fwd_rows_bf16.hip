@@ -245,7 +245,12 @@ __global__ void __launch_bounds__(256) fwd_rows_bf16_kernel(FwdArgs a) {
       float* const o = (float*)a.o + row * D + 4 * c;
       const f32x4 old = *(const f32x4*)o;
       const f32x4 z = {w0 * old[0] + w1 * y[0], w0 * old[1] + w1 * y[1], w0 * old[2] + w1 * y[2], w0 * old[3] + w1 * y[3]};
-      *(f32x4*)o = z;
+      if (a.o_last) {
+        const u32x2 x2 = {pack2_bf16(z[0], z[1]), pack2_bf16(z[2], z[3])};
+        *(u32x2*)((uint16_t*)a.o_last + b * d.q_sb + hq * d.q_sh + (long)i * d.q_ss + 4 * c) = x2;
+      } else {
+        *(f32x4*)o = z;
+      }
     } else {
       const long off = b * d.q_sb + hq * d.q_sh + (long)i * d.q_ss + 4 * c;
       if (a.o_is_f32) {

@@ -50,6 +50,7 @@ struct FwdArgs {
   int o_is_f32;         // 1: o is float32, 0: o has the input dtype
   int merge_into;       // 1 (n_split == 1 only): o (float32, CONTIGUOUS [B,Hq,Sq,D]) and lse hold a running
                         // result; the kernel leaves in them the Rescale of it with this visit's result
+  void* o_last;         // with merge_into, or nullptr: the last visit's O goes here (input dtype, Q's strides) instead
   float* lse;           // [B,Hq,Sq]
   int n_split;          // number of KV splits handled by separate workgroups
   int partial;          // 1: write partial results even with n_split == 1 (this launch is one of several
@@ -95,6 +96,8 @@ struct BwdArgs {
                         // walks the rows 32 at a time takes rows Sq-32 .. Sq-1 as its last step instead of a
                         // short one: the rows it has seen before then contribute nothing.
   float* dq_accum;      // [B,Hq,Sq,D] float32, accumulated into
+  int dq_first;         // 1: ... overwritten instead (the first visit)
+  void* dq_last;        // or nullptr: the last visit's sum goes here (input dtype, Q's strides) instead
   void *dk, *dv;        // K's strides, input dtype, overwritten
   float* kv_sums;
   int* kv_counts;       // media mask: parts that a tile was cut into, [B Hkv, tiles] (its number of steps is the mask's)
@@ -288,7 +291,9 @@ hipError_t launch_delta(const Dims& d, const void* o, const void* d_o, int is_f3
                         float* delta, float* stats, int sq_pad, float* stats_ovl, hipStream_t s);
 // dq_accum[i] += sum over the n_parts slices of `parts` (each n floats, n a multiple of 4)
 // (of runs of `run` floats in every `group` of them, the last ones)
-hipError_t launch_dq_reduce(const float* parts, int n_parts, long n, long run, long group, float* dq_accum, hipStream_t s);
+// (`first`: not added to what is there; dq_last: written there in bf16, with Q's strides)
+hipError_t launch_dq_reduce(const Dims& d, const float* parts, int n_parts, long n, long run, long group, float* dq_accum, bool first,
+                            void* dq_last, hipStream_t s);
 hipError_t launch_dq_finalize(const Dims& d, const float* dq_accum, void* dq, int is_f32,
                               hipStream_t s);
 

@@ -1,0 +1,62 @@
+"""The block loop's first and last visits: nothing that the running buffers held before counts, and the last visit's
+rounded result is what the separate conversion makes of the running one.  (The sums are formed in the same order
+and rounded once either way: equal, but for a running 0 that is added.)"""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,n_blocks,Hq,Hkv,Sq,Skv,q_chunk,kv_block", [
+    (torch.bfloat16, 1, 4, 2, 150, 700, 0, 0),             # one workgroup's rows split over the keys
+    (torch.bfloat16, 2, 4, 2, 150, 1400, 0, 0),
+    (torch.bfloat16, 3, 8, 8, 2000, 3 * 192, 0, 0),        # not split
+    (torch.bfloat16, 2, 8, 2, 3, 4000, 0, 0),              # few rows
+    (torch.bfloat16, 1, 4, 2, 100, 50, 0, 0),              # fewer keys than a tile: the general kernels
+    (torch.bfloat16, 2, 4, 2, 256, 2048, 64, 128),         # masks by tile lists, by words (dense and streamed), in two launches
+    (torch.bfloat16, 2, 4, 2, 300, 2 * 729, 48, 729),
+    (torch.bfloat16, 2, 4, 2, 300, 2048, 2, 64),
+    (torch.bfloat16, 2, 4, 2, 300, 2048, 24, 16),
+    (torch.bfloat16, 2, 4, 2, 300, 600, 7, 20),
+    (torch.float32, 2, 4, 2, 150, 300, 0, 0),
+    (torch.float32, 2, 4, 2, 100, 320, 8, 32),
+])
+@pytest.mark.parametrize("D", [64, 96, 128])
+def test_running_buffers(D, dtype, n_blocks, Hq, Hkv, Sq, Skv, q_chunk, kv_block):
+    from paper_2502_02406_amd import binding as L
+    from paper_2502_02406_amd.blockloop import BlockLoop, MediaMask
+    g = torch.Generator(device="cuda").manual_seed(2)
+    q, do = (torch.randn((1, Hq, Sq, D), generator=g, device="cuda").to(dtype) for _ in range(2))
+    k, v = (torch.randn((1, Hkv, Skv, D), generator=g, device="cuda").to(dtype) for _ in range(2))
+    mask = None
+    if q_chunk:
+        nq, nk = -(-Sq // q_chunk), -(-Skv // kv_block)
+        f, c = torch.arange(nk)[None, :], torch.arange(nq)[:, None]
+        mask = MediaMask(((f % nq == c) | (f == 0) & (c % 3 != 1)).to(torch.uint8).cuda(), q_chunk, kv_block)   # some rows see nothing of a block
+    loop = BlockLoop(tuple(q.shape), tuple(k.shape), dtype, n_blocks, mask)
+    for t in (loop.o, loop.lse, loop.dq_accum, loop.dq, loop.o_acc):
+        if t is not None:
+            t.fill_(float("nan"))
+    o, lse = loop.forward(q, k, v)
+    # the same visits, with the running result rounded by a call of its own
+    p, step = loop._blocks(q, k, (v,))
+    call = L.Calls(p, q.dtype, loop.ws)
+    o_acc, l_acc = torch.zeros(q.shape, dtype=torch.float32, device="cuda"), torch.full(q.shape[:3], float("-inf"), device="cuda")
+    a = [t.data_ptr() for t in (q, k, v)]
+    for n in range(n_blocks):
+        p.Skv = loop._keys_of(n, k)
+        at = [a[1] + n * step, a[2] + n * step]
+        if n == 0:
+            call.fwd(a[0], *at, loop._mask_for(0), o_acc.data_ptr(), torch.float32, l_acc.data_ptr())
+        else:
+            call.fwd_merge(a[0], *at, loop._mask_for(n), o_acc.data_ptr(), l_acc.data_ptr())
+    assert torch.equal(lse, l_acc) and torch.equal(o, o_acc.to(dtype))
+    dk, dv = torch.empty_like(k), torch.empty_like(v)
+    dq = loop.backward(q, k, v, o, lse, do, dk, dv)
+    acc, dk2, dv2 = torch.zeros_like(o_acc), torch.empty_like(k), torch.empty_like(v)
+    b = [t.data_ptr() for t in (o, lse, do)]
+    for n in range(n_blocks):
+        p.Skv = loop._keys_of(n, k)
+        call.bwd(a[0], a[1] + n * step, a[2] + n * step, *b, loop._mask_for(n), acc.data_ptr(), dk2.data_ptr() + n * step,
+                 dv2.data_ptr() + n * step, L.LVX_BWD_ALL if n == 0 else L.LVX_BWD_DKDV | L.LVX_BWD_DQ)
+    assert torch.equal(dq, acc.to(dtype)) and torch.equal(dk, dk2) and torch.equal(dv, dv2)
