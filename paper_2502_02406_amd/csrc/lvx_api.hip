@@ -254,6 +254,7 @@ lvx_status lvx_xattn_fwd(const lvx_problem* p, lvx_dtype dtype, const void* q, c
   if ((st = check_mask(p, mask)) != LVX_OK) return st;
   FwdArgs a;
   a.d = make_dims(p);
+  a.n_cu = device_cu_count();
   a.mask = make_mask(mask);
   a.q = q; a.k = k; a.v = v; a.o = o; a.o_is_f32 = o_dtype == LVX_F32; a.lse = lse;
   a.merge_into = 0;
@@ -303,6 +304,7 @@ static lvx_status fwd_merge(const lvx_problem* p, lvx_dtype dtype, const void* q
   if ((st = check_mask(p, mask)) != LVX_OK) return st;
   FwdArgs a;
   a.d = make_dims(p);
+  a.n_cu = device_cu_count();
   if (dtype == LVX_F32 && (a.d.q_ss != a.d.D || a.d.q_sh != (long)a.d.Sq * a.d.D ||
                            a.d.q_sb != (long)a.d.Hq * a.d.Sq * a.d.D))
     return LVX_ERR_STRIDE;      // (part of the interface, although the kernel would read any)
@@ -415,6 +417,7 @@ static lvx_status bwd_visit(const lvx_problem* p, lvx_dtype dtype, const void* q
   if ((st = check_mask(p, mask)) != LVX_OK) return st;
   BwdArgs a;
   a.d = make_dims(p);
+  a.n_cu = device_cu_count();
   a.mask = make_mask(mask);
   const TailPlan dq = bwd_split(a.d, dtype, mask != nullptr);
   a.n_split_dq = dq.parts;

@@ -58,6 +58,7 @@ struct FwdArgs {
   int part0;            // index of the partial slice that split 0 of this launch writes
   int whole;            // dense kernel: the first `whole` row tiles of a K/V head are not split (the partial slices
                         // then hold the rows of the others only, [B,Hkv, rows of the group - 256 whole])
+  int n_cu;             // compute units of the device (float32: picks the width of a workgroup)
   MaskRows rows;        // set by the launch where the kernel masks by it
   void* rows_ws;        // workspace for its words, or nullptr
   unsigned frame_magic; // 2^36 / kv_block, rounded up (set with rows)
@@ -80,6 +81,7 @@ struct BwdArgs {
   // registers, [B Hkv, tiles - whole, parts][dK, dV][256 x D]; dkdv_sum_kernel adds them up
   KvPlan kv;
   MaskDev mask;
+  int n_cu;             // compute units of the device (float32: picks the width of a workgroup)
   MaskRows rows;        // set by launch_bwd_bf16 where a kernel reads it
   void* rows_ws;        // workspace for its words (rows_ws_bytes), or nullptr
   size_t rows_ws_bytes;
