@@ -159,7 +159,7 @@ __global__ void __launch_bounds__(256) merge_kernel(MergeArgs a) {
 }
 
 // The same for few rows and many parts (a serving step's split-KV combine: 32 rows, 32 .. 64 parts of
-// float32): one workgroup per row, whose threads share the PARTS as well as the columns -- thread groups
+// float32; a short query block's): one workgroup per row, whose threads share the PARTS as well as the columns -- thread groups
 // of 16 or 32 lanes take every NG-th part, all their loads on their way at once, and meet in LDS.  The
 // kernel above gives such a problem one thread per 16 bytes of output, 4 workgroups in all, each thread
 // walking through the parts four at a time.  Bound by one trip to memory and the launch: the parts'
@@ -227,8 +227,10 @@ __global__ void __launch_bounds__(256) merge_row_kernel(MergeRowArgs a) {
 }
 
 hipError_t launch_merge(const MergeArgs& a, int part_is_f32, int out_is_f32, hipStream_t s) {
-  // (few rows: fewer workgroups of the kernel below than compute units; and parts enough to share)
-  if (part_is_f32 && a.o_slices != nullptr && a.first <= 1 && a.skip == 0 && a.n_parts > 4 && a.rows <= 1024) {
+  // (few rows: the kernel below gives them one thread per 16 bytes, too few to wait for many parts; and parts enough to share.
+  // Forward with its combine, us, this kernel against that one: 2048 rows x 128 x 32 parts 63 and 77, x 8 parts 31
+  // and 39; 4096 rows 99 and 102, 36 and 39; 8192 rows 172 and 163, 53 and 46)
+  if (part_is_f32 && a.o_slices != nullptr && a.first <= 1 && a.skip == 0 && a.n_parts > 4 && a.rows <= 4096) {
     MergeRowArgs r;
     r.o0 = (const float*)a.o_parts[0]; r.l0 = a.lse_parts[0];
     r.o = a.o_slices; r.l = a.lse_slices;
