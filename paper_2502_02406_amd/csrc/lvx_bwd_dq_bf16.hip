@@ -46,7 +46,7 @@ __device__ unsigned long long dq_probe[8];
 #endif
 
 // Row tile qt of one head under a mask that shows its row blocks little (mask_streams, lvx_mask_stream.h): wave w takes
-// row blocks 2 w and 2 w + 1.  K is read by rows (S) and transposed (dQ), V by rows only.
+// row blocks w and w + 4.  K is read by rows (S) and transposed (dQ), V by rows only.
 template <int D>
 __device__ __forceinline__ void dq_mask_stream(const BwdArgs& a, char* smem, int b, int hk, int hq, int qt, int split,
                                                unsigned long long any, int wave, int lane) {
@@ -57,7 +57,7 @@ __device__ __forceinline__ void dq_mask_stream(const BwdArgs& a, char* smem, int
   KeyStream<D> ks(a.k, a.v, d, b, hk, smem, wave, lane, a.mask.kv_block, true);
   const UnitReads<D> kr(lane, false);
   const float c2 = d.scale * LOG2E;
-  for (int rb = 2 * wave; rb < 2 * wave + 2; ++rb) {
+  for (int rb = wave; rb < QM / 32; rb += NWV) {
     const int i0 = qt * QM + 32 * rb;
     if (i0 >= d.Sq) return;
     const int i = min(i0 + ql, d.Sq - 1);

@@ -47,7 +47,7 @@ constexpr float LAZY_SUM = 64.0f;      // a lane's 16 probabilities of a half ma
 constexpr int XE = LVX_FWD_XE;                  // elements of a half converted during the contraction (of 32)
 
 // Row tile qt of one head under a mask that shows its row blocks little (mask_streams, lvx_mask_stream.h): wave w
-// takes row blocks 2 w and 2 w + 1.  The reference of a row is the largest score it has seen, always: its
+// takes row blocks w and w + 4.  The reference of a row is the largest score it has seen, always: its
 // probability is 1, which bf16 holds exactly, and the few units of a row make the raises few.
 template <int D>
 __device__ __forceinline__ void fwd_mask_stream(const FwdArgs& a, char* smem, int b, int hk, int hq, int qt, int split,
@@ -59,7 +59,7 @@ __device__ __forceinline__ void fwd_mask_stream(const FwdArgs& a, char* smem, in
   KeyStream<D> ks(a.k, a.v, d, b, hk, smem, wave, lane, a.mask.kv_block, false);
   const UnitReads<D> kr(lane, false), vr(lane, true);
   const float c2 = d.scale * LOG2E;
-  for (int rb = 2 * wave; rb < 2 * wave + 2; ++rb) {
+  for (int rb = wave; rb < QM / 32; rb += NWV) {
     const int i0 = qt * QM + 32 * rb;
     if (i0 >= d.Sq) return;
     const int i = min(i0 + ql, d.Sq - 1);

@@ -28,7 +28,7 @@ struct MaskRows {
   const unsigned long long* any;
   long any_stride_b;
   int any_words;
-  // counts[(b n_qt + qt) any_words + x], byte w: pairs of (row block 2 w or 2 w + 1 of tile qt, key block 64 x ..
+  // counts[(b n_qt + qt) any_words + x], byte w: pairs of (row block w or w + 4 of tile qt, key block 64 x ..
   // 64 x + 63) in which some row sees the key block
   const unsigned* counts;
 };

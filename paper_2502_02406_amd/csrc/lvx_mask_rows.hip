@@ -52,7 +52,7 @@ __global__ void __launch_bounds__(512) mask_rows_kernel(MaskDev m, MaskRows r, i
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       const unsigned x = tile[k][lane];
-      count += (unsigned)__popcll(__ballot(x != 0)) << (8 * (k / 2));
+      count += (unsigned)__popcll(__ballot(x != 0)) << (8 * (k % 4));
       bits |= x;
     }
     const unsigned long long on = __ballot(bits != 0);
