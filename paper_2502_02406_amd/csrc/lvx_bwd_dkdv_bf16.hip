@@ -96,8 +96,8 @@ template <int D> constexpr int dkdv_step_list_cap() {
 // ones cost the general kernel below more than masking everything costs here (it also owns only
 // 128 keys per workgroup, half the reuse of every operand).  Key tiles are dealt to the XCDs in
 // turn, since the early ones of a causal mask have the most steps.  2048 rows x 28 heads in chunks
-// of 64 against 32 frames of 729 keys, causal, D = 128: 2.73 -> 0.75 ms, of which 0.68 is the longest
-// workgroup (448 steps); 4096 rows x 8 heads in chunks of 2, each seeing one of 2048 frames of 64
+// of 64 against 32 frames of 729 keys, causal, D = 128: 2.73 -> 0.75 ms, 0.65 with tiles in parts (dkdv_bf16_plan), 0.61 with the
+// extract written out; 4096 rows x 8 heads in chunks of 2, each seeing one of 2048 frames of 64
 // keys, D = 64: 0.54 -> 0.17 ms (reads and writes 268 MB each).
 // Measurement builds only (python -m paper_2502_02406_amd.build --define LVX_DKDV_PROBE=1): every
 // workgroup with steps to run adds the clocks of its three phases (set-up until the first tiles and
@@ -340,6 +340,12 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   // each.
   const float c2 = d.scale * LOG2E;
   bf16x8 kf[KVB][KS];
+  // V's operands of the wave's keys are the same in every step too: in registers where there is room beside the
+  // accumulators (a third of a step's LDS reads; 64-wide heads, 4096 rows x 8 heads x 65536 keys 955 -> 915 us, 96-wide, 2048 x
+  // 32 x 32768 1263 -> 1225, with the operands handed on as words, below), from LDS with 128-wide heads, whose
+  // accumulators fill half of the file, and with words and 96-wide heads, where the set-up would spill.
+  constexpr bool V_REGS = !GENERAL && (D == 64 || (D == 96 && !WORDS));
+  bf16x8 vf[V_REGS ? KVB : 1][V_REGS ? KS : 1];
   char* const vres = smem + NSTG * SM::STAGE;
   auto load_kv = [&]() __attribute__((always_inline)) {
     // A lane needs ITS key row (16 bytes of it per k-step): fetched directly, every load
@@ -509,13 +515,17 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   // starting values of the accumulations, which are the statistics of the query rows -- S starts
   // at -L log2 e and dP at -delta, so that neither difference needs a vector instruction.  The
   // dense loop fetches them while the previous phase still computes.
-  struct FirstY { bf16x8 qa, ga, va[KVB]; f32x16 nl, nd; };
+  // (operands as words: handed on as bf16 elements, each register is put together again from its halves)
+  struct FirstY { u32x4 qa, ga, va[KVB]; f32x16 nl, nd; };
   auto first_y = [&](const char* __restrict__ t, const char* __restrict__ vw) __attribute__((always_inline)) -> FirstY {
     FirstY f;
-    f.qa = *(const bf16x8*)(t + ilv_off<D>(kl, 0, 8 * g));
-    f.ga = *(const bf16x8*)(t + ilv_off<D>(kl, KM, 8 * g));
+    f.qa = *(const u32x4*)(t + ilv_off<D>(kl, 0, 8 * g));
+    f.ga = *(const u32x4*)(t + ilv_off<D>(kl, KM, 8 * g));
 #pragma unroll
-    for (int kb = 0; kb < KVB; ++kb) f.va[kb] = *(const bf16x8*)(vw + kb * 32 * SM::P);
+    for (int kb = 0; kb < KVB; ++kb) {
+      if constexpr (V_REGS) f.va[kb] = __builtin_bit_cast(u32x4, vf[kb][0]);
+      else f.va[kb] = *(const u32x4*)(vw + kb * 32 * SM::P);
+    }
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
       const f32x4 nl = *(const f32x4*)(t + SM::STAT_OFF + (8 * q4 + 4 * g) * 4);
@@ -532,7 +542,7 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
                    f32x16 (&p)[KVB], auto&& per_unit, const FirstY& f, auto&& tail) __attribute__((always_inline)) {
     const char* qrow = t + ilv_off<D>(kl, 0, 8 * g);
     const char* grow = t + ilv_off<D>(kl, KM, 8 * g);
-    bf16x8 qa[2], ga[2], va[2][KVB];               // two operand sets, used alternately
+    u32x4 qa[2], ga[2], va[2][KVB];                // two operand sets, used alternately
     qa[0] = f.qa;
     ga[0] = f.ga;
 #pragma unroll
@@ -541,16 +551,19 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
     for (int ks = 0; ks < KS; ++ks) {
       const int cu = ks & 1, nx = cu ^ 1;
       if (ks + 1 < KS) {
-        qa[nx] = *(const bf16x8*)(qrow + (ks + 1) * 32);
-        ga[nx] = *(const bf16x8*)(grow + (ks + 1) * 32);
+        qa[nx] = *(const u32x4*)(qrow + (ks + 1) * 32);
+        ga[nx] = *(const u32x4*)(grow + (ks + 1) * 32);
 #pragma unroll
-        for (int kb = 0; kb < KVB; ++kb) va[nx][kb] = *(const bf16x8*)(vw + kb * 32 * SM::P + (ks + 1) * 32);
+        for (int kb = 0; kb < KVB; ++kb) {
+          if constexpr (V_REGS) va[nx][kb] = __builtin_bit_cast(u32x4, vf[kb][ks + 1]);
+          else va[nx][kb] = *(const u32x4*)(vw + kb * 32 * SM::P + (ks + 1) * 32);
+        }
       }
 #pragma unroll
       for (int j = 0; j < 2 * KVB; ++j) {          // S of both key blocks, then dP
         const int kb = j % KVB;
-        if (j < KVB) s[kb] = mfma32(qa[cu], kf[kb][ks], ks == 0 ? f.nl : s[kb]);
-        else p[kb] = mfma32(ga[cu], va[cu][kb], ks == 0 ? f.nd : p[kb]);
+        if (j < KVB) s[kb] = mfma32(__builtin_bit_cast(bf16x8, qa[cu]), kf[kb][ks], ks == 0 ? f.nl : s[kb]);
+        else p[kb] = mfma32(__builtin_bit_cast(bf16x8, ga[cu]), __builtin_bit_cast(bf16x8, va[cu][kb]), ks == 0 ? f.nd : p[kb]);
         per_unit(ks * 2 * KVB + j);                // vector work in the shadow of this instruction
         if (ks * 2 * KVB + j == 2 * KVB * KS - 3) tail();
         __builtin_amdgcn_sched_barrier(0);
@@ -608,7 +621,12 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
     float pr = cy.ex;
     // (WORDS: a probability is kept or becomes zero by one bit of the word; whatever the scores of
     // a pair that is not visible gave, nothing of them is left in P, and dS = 0 dP)
-    if (WORDS) pr = __uint_as_float(__float_as_uint(pr) & (unsigned)__builtin_amdgcn_sbfe((int)wcur[kb], 8 * q4 + e, 1));
+    if (WORDS) {
+      // (written out: the compiler makes a compare, a select and idle states of the same expression)
+      unsigned keep;
+      asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(keep) : "v"(wcur[kb]), "n"(8 * q4 + e));
+      pr = __uint_as_float(__float_as_uint(pr) & keep);
+    }
     const float ds = pr * p[kb][v];
     if (e % 2 == 0) { cy.pr = pr; cy.ds = ds; return; }
     pwo[kb][q4 >> 1][2 * (q4 & 1) + e / 2] = pack2_bf16(cy.pr, pr);
@@ -705,6 +723,15 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   __syncthreads();                                 // V rows and the first tiles are in LDS
   DKDV_STAMP(stamp1);
   const char* const vw = vres + (wave * 32 * KVB + kl) * SM::P + g * 16;
+  if constexpr (V_REGS) {
+#pragma unroll
+    for (int kb = 0; kb < KVB; ++kb)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        vf[kb][ks] = *(const bf16x8*)(vw + kb * 32 * SM::P + ks * 32);
+        asm volatile("" : "+v"(vf[kb][ks]));
+      }
+  }
 
   f32x16 s[KVB], p[KVB];
   u32x4 pf0[KVB][2] = {}, sf0[KVB][2] = {}, pf1[KVB][2] = {}, sf1[KVB][2] = {};   // packed P and dS operands
@@ -736,7 +763,6 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   // the score phase in turn fetches the first operands of the next contraction (step i + 1) and
   // sends out the copies of step i + 4 one at a time between its matrix instructions.
   FirstX fx = first_x(smem);
-  FirstY fy;
   auto full_iter = [&](char* st_copy, const char* __restrict__ t0, const char* __restrict__ t1,
                        const char* __restrict__ t2, const char* __restrict__ vw_, const u32x4 (&pfi)[KVB][2],
                        const u32x4 (&sfi)[KVB][2], u32x4 (&pfo)[KVB][2], u32x4 (&sfo)[KVB][2]) __attribute__((always_inline)) {
@@ -746,6 +772,7 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
       mid(std::false_type{}, true, st_copy);
       score(t2, vw_, s, p, nothing, first_y(t2, vw_), next_x);
     } else {
+      FirstY fy;
       contract_convert(t0, pfi, sfi, s, p, pfo, sfo, fx, [&](int m) __attribute__((always_inline)) {
         if (m == NM_X - 4) {
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (nothing is in flight here any more)
