@@ -85,13 +85,15 @@ project_bf16_kernel(ProjArgs a) {
   }
   const char* const xg = (const char*)a.x + m0 * (long)xrow_b;
   const char* const wg = (const char*)a.w + ((long)n0 + 64 * wave) * wrow_b;
+  const unsigned smem_u = lds_base(smem);
   auto issue_part = [&](int kt, int part) __attribute__((always_inline)) {
-    char* const st = smem + (kt % NSLOT) * SLOT_B;
+    // (the slot as an LDS address: a cast from the generic pointer carries a null test, two scalar instructions a copy)
+    const unsigned st = smem_u + (unsigned)((kt % NSLOT) * SLOT_B);
     if (part < XC) {
-      dma16s(xg + (long)kt * ROWB, xo[part], st + (8 * XC * wave + 8 * part) * ROWB);
+      dma16u(xg + (long)kt * ROWB, xo[part], st + (unsigned)((8 * XC * wave + 8 * part) * ROWB));
     } else {
       const int j = part - XC;
-      dma16s(wg + (long)(8 * j) * wrow_b + (long)kt * ROWB, wo[j & 1], st + TILE_B + (64 * wave + 8 * j) * ROWB);
+      dma16u(wg + (long)(8 * j) * wrow_b + (long)kt * ROWB, wo[j & 1], st + (unsigned)(TILE_B + (64 * wave + 8 * j) * ROWB));
     }
   };
 

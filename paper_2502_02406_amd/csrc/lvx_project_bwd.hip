@@ -99,7 +99,11 @@ __device__ __forceinline__ void div_tokens(int m, int S, float inv_S, int* b, in
 // MODE 0: dx = G W (rows = tokens, columns = features e, contraction over n)
 // MODE 1: dw += G^T X (rows = columns n of the projection, columns = e, contraction over tokens)
 // RB: 32-row blocks of the result per wave (4: tiles of 256 rows; 2: of 128 rows)
-// GA (MODE 0): heads are multiples of 64 wide, so that a tile pair's 64 columns of G are one line
+// GA: MODE 0: heads are multiples of 64 wide, so that a tile pair's 64 columns of G are one line; MODE 1: the 64 tokens of a
+// tile pair lie in one batch (dw_one_batch), so that their rows of G are one stretch and a copy's address is
+// an addition and a minimum per lane.  The general form divides every lane's token by S: about 200 vector instructions, 40 of them
+// multiplications at a quarter of the rate, on top of the 64 matrix instructions of a pair: dW of 32768 tokens x 4096 features x
+// 2048 columns 463 us, 431 without them; 2048 tokens x 4096 x 4096 84 and 77; 131072 x 512 x 1024 142 and 134.
 template <int MODE, int RB, bool GA = true>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 project_bwd_bf16_kernel(ProjBwdArgs a) {
@@ -196,6 +200,7 @@ project_bwd_bf16_kernel(ProjBwdArgs a) {
   }
   const unsigned wrow_b = (unsigned)(a.E * 2), xrow_b = (unsigned)(a.ldx * 2);
   const unsigned smem_u = lds_base(smem);
+  const unsigned x_lane = (unsigned)(16 * wave + lh) * xrow_b;         // MODE 1: the lane's row of x in copy 0
 
   // MODE 0: the head and column that tile pair kt of G starts at, advanced pair by pair (the G
   // copies of the pairs are issued in ascending order, copy 8 of a pair first)
@@ -206,6 +211,17 @@ project_bwd_bf16_kernel(ProjBwdArgs a) {
   // the pair, i.e. column g_c + 8 chunk of the output, in head / at column (that / D, that % D)
   unsigned g_lane0 = 0u, g_lane1 = 0u;               // (j even / odd)
   const float inv_D = 1.0f / (float)a.D;
+  // MODE 1, GA: where the next pair's tokens start in G, g_c the first one's number in its batch; the last row that a lane of the pair
+  // at hand may read; g_lane0 the lane's row in copy 0
+  const unsigned g_row_b = (unsigned)(a.D * 2);
+  const char* g_next = nullptr;
+  unsigned g_last = 0u;
+  if (MODE == 1 && GA) {
+    const int m0 = k0 * BK, b0 = m0 / a.S;
+    g_c = m0 - b0 * a.S;
+    g_next = g_tile_base + ((long)b0 * a.H * a.S + g_c) * g_row_b;
+    g_lane0 = (unsigned)(16 * wave + b_rin) * g_row_b;
+  }
 
   auto issue_part = [&](int kt, int part) __attribute__((always_inline)) {
     const unsigned st = smem_u + (unsigned)((kt % NSLOT) * SLOT_B);
@@ -217,10 +233,9 @@ project_bwd_bf16_kernel(ProjBwdArgs a) {
         dma16u(base, (unsigned)lh * wrow_b + kr_chunk[j & 1], dst);
       } else {
         const long m_first = (long)PROBE_PAIR(k0 + kt) * BK;
-        const int last = (int)(a.M - 1 - m_first);   // rows past it re-read it, and are cleared in LDS
-        const int r = 16 * wave + 2 * j + lh;
+        const int last = (int)min(a.M - 1 - m_first, 63L);   // rows past it re-read it, and are cleared in LDS
         const char* base = (const char*)a.x + (m_first * a.ldx + e0) * 2;
-        dma16u(base, (unsigned)(r < last ? r : last) * xrow_b + kr_chunk[j & 1], dst);
+        dma16u(base, min(x_lane + (unsigned)(2 * j) * xrow_b, (unsigned)last * xrow_b) + kr_chunk[j & 1], dst);
       }
     } else if (MODE == 0) {                          // B side: G, 256 tokens x 64 columns
       if (part == 8) {
@@ -241,6 +256,17 @@ project_bwd_bf16_kernel(ProjBwdArgs a) {
       }
       dma16u(g_pair_base, g_row[j] + (GA ? 0u : (j & 1) ? g_lane1 : g_lane0),
              st + (unsigned)(TILE_B + (16 * RB * wave + 8 * j) * RK_ROWB));
+    } else if (GA) {                                 // B side: G, 64 tokens of one batch x TR columns
+      const int jb = part - 8;
+      if (jb == 0) {                                 // (pairs come in ascending order, this copy first)
+        g_pair_base = g_next;
+        g_last = (unsigned)min(a.M - 1 - (long)(k0 + kt) * BK, 63L) * g_row_b;
+        g_c += BK;
+        g_next += 64 * (long)g_row_b;
+        if (g_c >= a.S) { g_c = 0; g_next += (long)(a.H - 1) * head_b; }
+      }
+      dma16u(g_pair_base, min(g_lane0 + (unsigned)(RPI * jb) * g_row_b, g_last) + g_col[jb & 1],
+             st + (unsigned)(TILE_B + (16 * wave + RPI * jb) * BROWB));
     } else {                                         // B side: G, 64 tokens x TR columns
       const int jb = part - 8;
       const long m_first = (long)PROBE_PAIR(k0 + kt) * BK;
@@ -589,11 +615,28 @@ template <int RB, bool GA> hipError_t launch_dx(const ProjBwdArgs& a, hipStream_
   project_bwd_bf16_kernel<0, RB, GA><<<(unsigned)grid, 256, SMEM_B, s>>>(a);
   return hipGetLastError();
 }
+template <int RB, bool GA> hipError_t launch_dw_as(const ProjBwdArgs& a, unsigned grid, hipStream_t s) {
+  static SmemOnce once;
+  const hipError_t e = ensure_dynamic_lds((const void*)project_bwd_bf16_kernel<1, RB, GA>, SMEM_B, &once);
+  if (e != hipSuccess) return e;
+  project_bwd_bf16_kernel<1, RB, GA><<<grid, 256, SMEM_B, s>>>(a);
+  return hipGetLastError();
+}
+// whether every 64 tokens from a multiple of 64 on are of one batch
+bool dw_one_batch(const ProjBwdArgs& a) {
+#ifdef LVX_PROJ_PROBE
+  return false;                                    // (the general form's addresses are the ones that build changes)
+#else
+  return a.M == a.S || a.S % BK == 0;
+#endif
+}
+template <int RB> hipError_t launch_dw(const ProjBwdArgs& a, unsigned grid, hipStream_t s) {
+  return dw_one_batch(a) ? launch_dw_as<RB, true>(a, grid, s) : launch_dw_as<RB, false>(a, grid, s);
+}
 }  // namespace
 
 hipError_t launch_project_bwd(const ProjBwdArgs& a, int is_f32, hipStream_t s) {
   const bool mfma_w = !is_f32 && mfma_common(a), mfma_x = mfma_w;
-  static SmemOnce once_w, once_w2;
   ProjBwdArgs rest = a;                              // what is left for the plain kernels
   if (mfma_x) rest.dx = nullptr;
   if (mfma_w) rest.dw = nullptr;
@@ -620,19 +663,17 @@ hipError_t launch_project_bwd(const ProjBwdArgs& a, int is_f32, hipStream_t s) {
         if (parts >= 2) w.dw_parts = (int)parts;
       }
       if (tiles * 4 > (long)a.n_cu * 3 || w.dw_parts > 1) {
-        const hipError_t e = ensure_dynamic_lds((const void*)project_bwd_bf16_kernel<1, 4>, SMEM_B, &once_w);
-        if (e != hipSuccess) return e;
         w.dw_tiles_grid = (unsigned)xcd_grid(a.N / T, a.E / T);
         const unsigned grid = w.dw_parts >= DW_SUMS ? (unsigned)((tiles * w.dw_parts + 7) / 8 * 8)
                                                     : w.dw_tiles_grid * (unsigned)w.dw_parts;
-        project_bwd_bf16_kernel<1, 4><<<grid, 256, SMEM_B, s>>>(w);
+        const hipError_t e = launch_dw<4>(w, grid, s);
+        if (e != hipSuccess) return e;
         if (w.dw_parts >= DW_SUMS)
           dw_add_sums_kernel<<<(unsigned)(tiles * (T * T / 1024)), 256, 0, s>>>(a.dw, a.E, a.N / T, a.E / T, w.dw_parts);
       } else {
-        const hipError_t e = ensure_dynamic_lds((const void*)project_bwd_bf16_kernel<1, 2>, SMEM_B, &once_w2);
-        if (e != hipSuccess) return e;
         w.dw_tiles_grid = (unsigned)xcd_grid(a.N / 128, a.E / T);
-        project_bwd_bf16_kernel<1, 2><<<w.dw_tiles_grid, 256, SMEM_B, s>>>(w);
+        const hipError_t e = launch_dw<2>(w, w.dw_tiles_grid, s);
+        if (e != hipSuccess) return e;
       }
     }
     const hipError_t e = hipGetLastError();
