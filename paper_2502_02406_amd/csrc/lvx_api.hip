@@ -82,11 +82,6 @@ MaskDev make_mask(const lvx_mask* m) {
 int fwd_split(const Dims& d, lvx_dtype dtype, bool masked) {
   return dtype == LVX_BF16 ? fwd_bf16_pick_split(d, device_cu_count(), masked) : 1;
 }
-TailPlan bwd_split(const Dims& d, lvx_dtype dtype, bool masked) {
-  if (dtype == LVX_BF16 && bwd_dq_bf16_dense(d, masked)) return bwd_dq_bf16_dense_plan(d, device_cu_count());
-  return {0, dtype == LVX_BF16 ? bwd_bf16_pick_split(d, device_cu_count(), masked) : 1};
-}
-
 int fwd_list_split(const Dims& d) { return list_split((long)d.B * d.Hq * ((d.Sq + 255) / 256), (d.Skv + 63) / 64); }
 
 // bf16 under a media mask that fits (fwd_bf16_two_pass_fits): the dense kernel over the key tiles
@@ -120,6 +115,7 @@ size_t fwd_ws(const Dims& d, int n_split, int whole = 0) {
 size_t fwd_merge_ws(const Dims& d, lvx_dtype dtype, int n_split, int whole = 0) {
   return fwd_ws(d, dtype == LVX_F32 ? 2 : n_split, whole);      // (fwd_ws(d, 2) holds more than one partial result)
 }
+int cap_parts(int n, int reserve) { return n < LVX_MAX_PARTS - reserve ? n : LVX_MAX_PARTS - reserve; }
 // How a forward call runs: the KV splits of each launch, whether a media mask makes it two launches,
 // the partial results the combine then reads, the bytes of MaskRows' words the kernel reads, and the
 // workspace it all takes.  The dense kernel leaves the first `whole` row tiles of a K/V head unsplit.  `reserve` parts of the combine are taken already (lvx_xattn_fwd_merge: the
@@ -150,8 +146,7 @@ FwdPlan fwd_plan(const Dims& d, lvx_dtype dtype, const MaskDev& m, int reserve, 
     const auto plan = [&](TailPlan t) -> FwdPlan { return {t.parts, t.whole, false, t.parts, 0, fwd_ws(d, t.parts, t.whole)}; };
     const FwdPlan f = plan(fwd_bf16_dense_plan(d, device_cu_count(), LVX_MAX_PARTS - reserve));
     if (f.need <= room) return f;
-    const int n = fwd_bf16_coarse_split(d, device_cu_count());
-    return plan({0, n < LVX_MAX_PARTS - reserve ? n : LVX_MAX_PARTS - reserve});
+    return plan({0, cap_parts(fwd_bf16_coarse_split(d, device_cu_count()), reserve)});
   }
   const bool rows = m.allow != nullptr && dtype == LVX_BF16 && fwd_bf16_takes_rows(d, m);
   const FwdPlan f = fwd_plan_with(d, dtype, m, reserve, rows, room);
@@ -165,19 +160,34 @@ size_t bwd_ws_fixed(const Dims& d) {   // delta [B,Hq,Sq] + padded statistics [B
   return align_up((size_t)d.B * d.Hq * d.Sq * sizeof(float)) +
          align_up((stats_floats(d) + (has_stats_ovl(d) ? (size_t)d.B * d.Hq * 64 : 0)) * sizeof(float));
 }
-// The dQ kernel's partial sums [n, B,Hq,Sq,D] when it splits.  A masked bf16 call always has one
+// How the dQ kernels split the key range, and the workspace of a backward call: `list` splits under masks that
+// run over lists, else dq; partial sums [n_slices, split rows, D].  A masked bf16 call always has one
 // slice at least: the words of MaskRows go into the last slice, which the kernels that read them
-// leave alone (list_split, one less at least), and which the others fill only after the words' last reader.
-int bwd_slices(const Dims& d, lvx_dtype dtype, bool masked) {
-  int n = bwd_split(d, dtype, masked).parts;
-  if (masked && dtype == LVX_BF16 && n <= fwd_list_split(d)) n = fwd_list_split(d) + 1;
-  return n > 1 || (masked && dtype == LVX_BF16) ? n : 0;
-}
+// leave alone (`list` is one less at least), and which the others fill only after the words' last reader.
+struct BwdPlan { TailPlan dq; int list, n_slices; size_t part, need; };
 size_t bwd_slice_bytes(const Dims& d) { return (size_t)d.B * d.Hq * d.Sq * d.D * sizeof(float); }
-size_t bwd_ws_part(const Dims& d, lvx_dtype dtype, bool masked) {
-  const int n = bwd_slices(d, dtype, masked);
-  if (masked || n == 0) return align_up(n * bwd_slice_bytes(d));
-  return align_up(n * split_rows(d, bwd_split(d, dtype, masked).whole) * d.D * sizeof(float));
+bool can_fuse(const Dims& d, lvx_dtype dtype, bool masked) { return dtype == LVX_BF16 && bwd_fused_bf16_supported(d, masked); }
+BwdPlan bwd_plan_with(const Dims& d, lvx_dtype dtype, bool masked, bool fused, bool coarse) {
+  BwdPlan p = {{0, 1}, 1, 0, 0, 0};
+  if (dtype == LVX_BF16) {
+    const int n_cu = device_cu_count();
+    if (!bwd_dq_bf16_dense(d, masked)) p.dq.parts = bwd_bf16_pick_split(d, n_cu, masked);
+    else if (coarse) p.dq.parts = bwd_dq_bf16_coarse_split(d, n_cu);
+    else p.dq = bwd_dq_bf16_dense_plan(d, n_cu);
+    const int n = p.dq.parts;
+    if (masked) p.list = !coarse ? fwd_list_split(d) : n > 1 ? n / 2 : 1;
+    p.n_slices = !masked ? (n > 1 ? n : 0) : n > p.list || coarse ? n : p.list + 1;
+    p.part = align_up(p.n_slices * split_rows(d, p.dq.whole) * d.D * sizeof(float));
+  }
+  p.need = bwd_ws_fixed(d) + p.part + (fused ? align_up(bwd_fused_ws_bytes(d)) : 0);   // ... + the fused kernel's dQ tiles and locks
+  return p;
+}
+// ... in a workspace of `room` bytes.  Fewer keys or rows may want more parts than what the workspace was made for (a block
+// loop whose K is shorter: 16 heads x 29 rows against 4982 keys in the room of 4996): the coarse
+// splits need no more than those of a larger problem, and the query has room for either.
+BwdPlan bwd_plan(const Dims& d, lvx_dtype dtype, bool masked, bool fused, size_t room) {
+  const BwdPlan p = bwd_plan_with(d, dtype, masked, fused, false);
+  return p.need <= room ? p : bwd_plan_with(d, dtype, masked, fused, true);
 }
 // ... + the sums of key tiles that several dK/dV workgroups share.  A workspace without room for these leaves every
 // tile to one workgroup.
@@ -186,10 +196,6 @@ size_t bwd_ws_kv(const Dims& d, lvx_dtype dtype, bool masked) {
   const KvPlan p = dkdv_bf16_plan(d, device_cu_count(), masked);
   return dkdv_bf16_sums_bytes(d, p) + dkdv_bf16_counts_bytes(d, p);
 }
-size_t bwd_ws(const Dims& d, lvx_dtype dtype, bool masked, bool fused) {   // ... + the fused kernel's dQ tiles and locks
-  return bwd_ws_fixed(d) + bwd_ws_part(d, dtype, masked) + (fused ? align_up(bwd_fused_ws_bytes(d)) : 0);
-}
-
 }  // namespace
 
 namespace lvx {
@@ -226,19 +232,22 @@ size_t lvx_xattn_workspace_bytes(const lvx_problem* p, lvx_dtype dtype, int whic
   const size_t rows_most = dtype == LVX_BF16 ? align_up(fwd_bf16_rows_bytes_most(d)) : 0;
   const auto parts = [&](int reserve) {
     const int masked = dtype == LVX_BF16 ? 2 * fwd_two_pass_split(fwd_split(d, dtype, true), reserve) : 1;
-    const auto cap = [&](int n) { return n < LVX_MAX_PARTS - reserve ? n : LVX_MAX_PARTS - reserve; };
+    const auto cap = [&](int n) { return cap_parts(n, reserve); };
     return larger(larger(masked, larger(cap(fwd_split(d, dtype, true)), dtype == LVX_BF16 ? fwd_list_split(d) : 1)),
                   cap(fwd_split(d, dtype, false)));
   };
   const auto most = [](size_t x, size_t y) { return x > y ? x : y; };
   const auto dense = [&](int reserve) -> size_t {
-    return dtype == LVX_BF16 && fwd_bf16_dense(d, false) ? fwd_plan(d, dtype, make_mask(nullptr), reserve, SIZE_MAX).need : 0;
+    return dtype == LVX_BF16 && fwd_bf16_dense(d, false) ? most(fwd_plan(d, dtype, make_mask(nullptr), reserve, SIZE_MAX).need,
+                                                                fwd_ws(d, cap_parts(fwd_bf16_coarse_split(d, device_cu_count()), reserve))) : 0;
+  };
+  const auto bwd = [&](bool masked) -> size_t {
+    const bool fused = can_fuse(d, dtype, false);
+    return most(bwd_plan_with(d, dtype, masked, fused, false).need, bwd_plan_with(d, dtype, masked, fused, true).need);
   };
   if (which == LVX_WS_FWD) return most(fwd_ws(d, parts(0)) + rows_most, dense(0));
   if (which == LVX_WS_BWD)
-    return most(bwd_ws(d, dtype, true, dtype == LVX_BF16 && bwd_fused_bf16_supported(d, false)),
-                bwd_ws(d, dtype, false, dtype == LVX_BF16 && bwd_fused_bf16_supported(d, false))) +
-           most(bwd_ws_kv(d, dtype, true), bwd_ws_kv(d, dtype, false));
+    return most(bwd(true), bwd(false)) + most(bwd_ws_kv(d, dtype, true), bwd_ws_kv(d, dtype, false));
   if (which == LVX_WS_FWD_MERGE) return most(fwd_merge_ws(d, dtype, parts(1)) + rows_most, dense(1));
   return 0;
 }
@@ -419,17 +428,18 @@ static lvx_status bwd_visit(const lvx_problem* p, lvx_dtype dtype, const void* q
   a.d = make_dims(p);
   a.n_cu = device_cu_count();
   a.mask = make_mask(mask);
-  const TailPlan dq = bwd_split(a.d, dtype, mask != nullptr);
-  a.n_split_dq = dq.parts;
-  a.dq_whole = dq.whole;
   a.dq_pass = 0;
   // the kernel that forms all five products at once: where it applies, unless the caller asks for
   // the two-kernel form (or only for one of the two kernels)
-  const bool can_fuse = dtype == LVX_BF16 && bwd_fused_bf16_supported(a.d, mask != nullptr);
+  const bool may_fuse = can_fuse(a.d, dtype, mask != nullptr);
   const bool want_fuse = (stages & LVX_BWD_FUSED) || (FUSED_BY_DEFAULT && !(stages & LVX_BWD_SPLIT));
-  const bool fused = can_fuse && want_fuse && (stages & (LVX_BWD_DKDV | LVX_BWD_DQ)) == (LVX_BWD_DKDV | LVX_BWD_DQ);
-  const int n_slices = bwd_slices(a.d, dtype, mask != nullptr);
-  const size_t need = bwd_ws(a.d, dtype, mask != nullptr, can_fuse);
+  const bool fused = may_fuse && want_fuse && (stages & (LVX_BWD_DKDV | LVX_BWD_DQ)) == (LVX_BWD_DKDV | LVX_BWD_DQ);
+  const BwdPlan plan = bwd_plan(a.d, dtype, mask != nullptr, may_fuse, workspace_bytes);
+  a.n_split_dq = plan.dq.parts;
+  a.dq_whole = plan.dq.whole;
+  a.dq_list = plan.list;
+  const int n_slices = plan.n_slices;
+  const size_t need = plan.need;
   if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < need) return LVX_ERR_WORKSPACE;
   a.q = q; a.k = k; a.v = v; a.o = o; a.d_o = d_o; a.lse = lse;
   a.delta = (float*)workspace;
@@ -442,7 +452,7 @@ static lvx_status bwd_visit(const lvx_problem* p, lvx_dtype dtype, const void* q
   a.rows = MaskRows{};
   a.rows_ws = mask != nullptr && n_slices > 0 ? (char*)workspace + bwd_ws_fixed(a.d) + (n_slices - 1) * bwd_slice_bytes(a.d) : nullptr;
   a.rows_ws_bytes = bwd_slice_bytes(a.d);
-  a.dq_tiles = fused ? (float*)((char*)workspace + bwd_ws_fixed(a.d) + bwd_ws_part(a.d, dtype, mask != nullptr)) : nullptr;
+  a.dq_tiles = fused ? (float*)((char*)workspace + bwd_ws_fixed(a.d) + plan.part) : nullptr;
   a.kv = {0, 1, 0}; a.kv_sums = nullptr; a.kv_counts = nullptr;
   if (dtype == LVX_BF16 && !fused && workspace_bytes - need >= bwd_ws_kv(a.d, dtype, mask != nullptr)) {
     a.kv = dkdv_bf16_plan(a.d, device_cu_count(), mask != nullptr);
@@ -487,9 +497,10 @@ lvx_status lvx_xattn_bwd_error_word(const lvx_problem* p, lvx_dtype dtype, const
   if (!word) return LVX_ERR_NULL;
   if ((st = check_mask(p, mask)) != LVX_OK) return st;
   const Dims d = make_dims(p);
-  const bool fused = dtype == LVX_BF16 && bwd_fused_bf16_supported(d, mask != nullptr);
-  if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < bwd_ws(d, dtype, mask != nullptr, fused)) return LVX_ERR_WORKSPACE;
-  *word = fused ? (const int*)((char*)workspace + bwd_ws_fixed(d) + bwd_ws_part(d, dtype, mask != nullptr) + bwd_fused_ws_bytes(d) - 256)
+  const bool fused = can_fuse(d, dtype, mask != nullptr);
+  const BwdPlan plan = bwd_plan(d, dtype, mask != nullptr, fused, workspace_bytes);
+  if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < plan.need) return LVX_ERR_WORKSPACE;
+  *word = fused ? (const int*)((char*)workspace + bwd_ws_fixed(d) + plan.part + bwd_fused_ws_bytes(d) - 256)
                 : nullptr;
   return LVX_OK;
 }

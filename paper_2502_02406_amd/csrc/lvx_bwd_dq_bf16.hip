@@ -978,6 +978,12 @@ TailPlan bwd_dq_bf16_dense_plan(const Dims& d, int n_cu) {
   return pick_tail((long)d.B * d.Hkv, (int)n_qt, (d.Skv + TN - 1) / TN, n_cu, 64, t_tile, 14e-6, 2.0 * QM * d.D * 4.0 / 4.5e12, 5e-6);
 }
 
+int bwd_dq_bf16_coarse_split(const Dims& d, int n_cu) {
+  const long base = (long)d.B * d.Hkv * (((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM), cap = (d.Skv + TN - 1) / TN / 16;
+  return pick_split_balanced(base, n_cu, cap < 1 ? 1 : cap, 6.0 * QM * (double)d.Skv * d.D / 5.5e12,
+                             2.0 * (double)d.B * d.Hq * d.Sq * d.D * 4.0 / 3e12);
+}
+
 int bwd_bf16_pick_split(const Dims& d, int n_cu, bool masked) {
   // one workgroup per CU; split the KV axis until the grid covers the chip (four times as many
   // workgroups with a media mask, whose visible work differs from one query tile to the next)
@@ -1034,7 +1040,7 @@ hipError_t launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s) {
     if (fits && a.mask.q_chunk % 32 == 0 && a.mask.kv_block % TN == 0) {
       BwdArgs p3 = a;
       p3.dq_pass = 3;
-      p3.n_split_dq = list_split((long)d.B * d.Hq * ((d.Sq + QM - 1) / QM), n_tiles);
+      p3.n_split_dq = a.dq_list;
       return launch_one(p3, false, s);
     }
     // ... or of any other mask with key blocks of 64 keys and more, by the words that travel with the tiles
@@ -1042,7 +1048,7 @@ hipError_t launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s) {
       BwdArgs p4 = a;
       p4.dq_pass = 4;
       p4.frame_magic = frame_magic_of(a.mask.kv_block);
-      p4.n_split_dq = list_split((long)d.B * d.Hq * ((d.Sq + QM - 1) / QM), n_tiles);
+      p4.n_split_dq = a.dq_list;
       return launch_one(p4, false, s);
     }
     const bool two = d.Skv % TN == 0 && plan_fits(h_max, w, n_tiles, DqSmem<128>::BITS_BYTES, DqSmem<128>::WIN_BYTES) &&

@@ -105,6 +105,7 @@ struct BwdArgs {
   int* kv_counts;       // media mask: parts that a tile was cut into, [B Hkv, tiles] (its number of steps is the mask's)
   int n_split_dq;       // KV splits of the dQ kernel
   int dq_whole;         // as FwdArgs::whole
+  int dq_list;          // KV splits of its launches over the tiles some row sees (dq_pass 3, 4)
   int dq_pass;          // media mask, dQ kernel: 0 = one launch over every visible tile; 1 = this launch takes the
                         // key tiles that EVERY row of a workgroup sees (dense kernel over a list of them),
                         // 2 = this launch takes the other visible tiles (general kernel); 3, 4 = one launch of
@@ -258,6 +259,7 @@ TailPlan fwd_bf16_dense_plan(const Dims& d, int n_cu, int most);
 int fwd_bf16_coarse_split(const Dims& d, int n_cu);             // every row tile, in a workspace too small for that plan
 bool bwd_dq_bf16_dense(const Dims& d, bool masked);
 TailPlan bwd_dq_bf16_dense_plan(const Dims& d, int n_cu);
+int bwd_dq_bf16_coarse_split(const Dims& d, int n_cu);
 // KV splits of the masked kernels that walk a list of the tiles some row sees (LIST >= 2; each split takes an even share
 // of the list, wherever it ends), for `wgs` row tiles and n_tiles key tiles of which the mask shows any
 // number.  They start longest first, so two rounds of the chip (512 workgroups) even out lists as uneven

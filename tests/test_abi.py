@@ -210,6 +210,16 @@ def test_workspace_sizes_and_strerror(lib):
     assert B.strerror(-99) == "unknown status"
 
 
+@pytest.mark.parametrize("B_,Hq,Hkv,D,Sq,Skv,fewer", [(1, 128, 16, 64, 14, 1567, 1530), (2, 16, 2, 128, 29, 4996, 4982),
+                                                        (1, 4, 2, 96, 72, 29102, 23990), (1, 56, 8, 96, 64, 1928, 1865)])
+def test_workspace_holds_for_fewer_keys(lib, B_, Hq, Hkv, D, Sq, Skv, fewer):
+    p, less = (problem(B=B_, Hq=Hq, Hkv=Hkv, D=D, Sq=Sq, Skv=n) for n in (Skv, fewer))
+    word = C.c_void_p()
+    for which in (p, less):
+        assert lib.lvx_xattn_bwd_error_word(C.byref(which), B.LVX_BF16, None, FAKE, B.lvx_xattn_workspace_bytes(p, B.LVX_BF16, B.LVX_WS_BWD),
+                                            C.byref(word)) == 0
+
+
 def test_binding_refuses_cpu_tensors():
     import torch
     if torch.cuda.is_available():

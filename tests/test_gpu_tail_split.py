@@ -8,7 +8,7 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-def _case(B, Hq, Hkv, D, Sq, Skv, n_blocks=1, q_chunk=0, kv_block=0):
+def _case(B, Hq, Hkv, D, Sq, Skv, n_blocks=1, q_chunk=0, kv_block=0, made_for=0):
     from paper_2502_02406_amd.blockloop import BlockLoop, MediaMask
     g = torch.Generator(device="cuda").manual_seed(3)
     q, do = (torch.randn((B, Hq, Sq, D), generator=g, device="cuda").bfloat16() for _ in range(2))
@@ -19,7 +19,7 @@ def _case(B, Hq, Hkv, D, Sq, Skv, n_blocks=1, q_chunk=0, kv_block=0):
         allow = (f <= c).to(torch.uint8).cuda()
         mask = MediaMask(allow, q_chunk, kv_block)
         seen = allow.bool().repeat_interleave(q_chunk, 0)[:Sq].repeat_interleave(kv_block, 1)[:, :Skv]
-    loop = BlockLoop(tuple(q.shape), tuple(k.shape), torch.bfloat16, n_blocks, mask)
+    loop = BlockLoop(tuple(q.shape), (B, Hkv, made_for or Skv, D), torch.bfloat16, n_blocks, mask)
     o, lse = loop.forward(q, k, v)
     dq = loop.backward(q, k, v, o, lse, do, torch.empty_like(k), torch.empty_like(v))
     G = Hq // Hkv
@@ -53,3 +53,10 @@ def test_last_round(shape):
 def test_short_lists(D, mask):
     B, Hq, Hkv, Sq, Skv, q_chunk, kv_block = mask
     _case(B, Hq, Hkv, D, Sq, Skv, 1, q_chunk, kv_block)
+
+
+@pytest.mark.parametrize("shape", [(1, 128, 16, 64, 14, 1530, 1567), (2, 16, 2, 128, 29, 4982, 4996), (1, 4, 2, 96, 72, 23990, 29102)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_fewer_keys_than_the_workspace_was_made_for(shape):
+    """... for which the plan of these keys would want more parts: dQ is split as far as there is room."""
+    _case(*shape[:6], made_for=shape[6])
