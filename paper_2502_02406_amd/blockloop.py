@@ -69,8 +69,8 @@ class BlockLoop:
         self.lse = torch.empty(rows, **f32)
         self.o = torch.empty(q_shape, dtype=dtype, device=device)
         # Running O_j of Algorithm 1 (L_j lives in self.lse) and the dQ sums.  Both are float32: a float32
-        # problem's are its results already, with nothing left to round (they are written while the inputs
-        # are still read, which _apart sees to where an input is an earlier result).
+        # problem's are its results already, with nothing left to round.  The last visit writes the results (float32: every
+        # visit) while the inputs are still read, which _apart sees to where an input is an earlier result.
         self.dq_accum = torch.empty(q_shape, **f32)
         if dtype == torch.float32:
             self.o_acc, self.dq = self.o, self.dq_accum
@@ -121,7 +121,7 @@ class BlockLoop:
         # a contiguous tensor by the others)
         assert self.n_blocks == 1 or q.is_contiguous(), "the block loop needs a contiguous Q"
         p, step = self._blocks(q, k, (v,))
-        if self.n_blocks > 1 and self.o_acc is self.o:
+        if self.n_blocks > 1:
             q, k, v = _apart(self.o, q, k, v)
         call = B.Calls(p, q.dtype, self.ws)
         qp, kp, vp, lp = q.data_ptr(), k.data_ptr(), v.data_ptr(), self.lse.data_ptr()
@@ -147,8 +147,7 @@ class BlockLoop:
         p, step = self._blocks(q, k, (v, dk, dv), (o, d_o))
         if lse.numel() < q.shape[0] * q.shape[1] * q.shape[2]:
             raise ValueError("L has to have a value for every row of Q")
-        if self.dq is self.dq_accum:
-            q, k, v, o, lse, d_o = _apart(self.dq, q, k, v, o, lse, d_o)
+        q, k, v, o, lse, d_o = _apart(self.dq, q, k, v, o, lse, d_o)
         call = B.Calls(p, q.dtype, self.ws)
         qp, kp, vp, dkp, dvp = q.data_ptr(), k.data_ptr(), v.data_ptr(), dk.data_ptr(), dv.data_ptr()
         op, lp, gp, ap = o.data_ptr(), lse.data_ptr(), d_o.data_ptr(), self.dq_accum.data_ptr()

@@ -60,3 +60,25 @@ def test_running_buffers(D, dtype, n_blocks, Hq, Hkv, Sq, Skv, q_chunk, kv_block
         call.bwd(a[0], a[1] + n * step, a[2] + n * step, *b, loop._mask_for(n), acc.data_ptr(), dk2.data_ptr() + n * step,
                  dv2.data_ptr() + n * step, L.LVX_BWD_ALL if n == 0 else L.LVX_BWD_DKDV | L.LVX_BWD_DQ)
     assert torch.equal(dq, acc.to(dtype)) and torch.equal(dk, dk2) and torch.equal(dv, dv2)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_results_come_back_as_inputs(dtype):
+    """O and dQ, buffers of the loop, as the next call's operands: the last visit writes them while others are still read."""
+    from paper_2502_02406_amd.blockloop import BlockLoop
+    g = torch.Generator(device="cuda").manual_seed(4)
+    q, k, v, do = (torch.randn((1, 4, 640, 64), generator=g, device="cuda").to(dtype) for _ in range(4))
+    loop = BlockLoop(tuple(q.shape), tuple(k.shape), dtype, 2)
+    dk, dv = torch.empty_like(k), torch.empty_like(v)
+    o, lse = (t.clone() for t in loop.forward(q, k, v))
+    for back in ((q, loop.o, v), (q, k, loop.o), (loop.o, loop.o, loop.o)):
+        loop.o.copy_(o)
+        want = loop.forward(*(t.clone() for t in back))[0].clone()
+        loop.o.copy_(o)
+        assert torch.equal(loop.forward(*back)[0], want)
+    x = loop.backward(q, k, v, o, lse, do, dk, dv).clone()
+    for back in ((q, loop.dq, v, o, lse, do), (q, k, loop.dq, o, lse, do), (q, k, v, o, lse, loop.dq), (loop.dq, k, v, loop.dq, lse, loop.dq)):
+        loop.dq.copy_(x)
+        want = [t.clone() for t in (loop.backward(*(t.clone() for t in back), dk, dv), dk, dv)]
+        loop.dq.copy_(x)
+        assert all(torch.equal(a, b) for a, b in zip((loop.backward(*back, dk, dv), dk, dv), want))
