@@ -9,8 +9,6 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 
 __device__ __forceinline__ float bf16_lo(unsigned u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned u) { return __uint_as_float(u & 0xffff0000u); }
-// the larger, or the NaN (a part without a value must not look like one without keys)
-__device__ __forceinline__ float max_or_nan(float a, float b) { return b > a || b != b ? b : a; }
 __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
   typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
   bf16x2 r;

@@ -303,7 +303,7 @@ __global__ void __launch_bounds__(64 * waves_of(D)) fwd_f32_kernel(FwdArgs a) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) y[e] += f * ow[e];
     }
-    const float inv = z > 0.f ? 1.f / z : 0.f, lse = z > 0.f ? M + logf(z) : -INFINITY;
+    const float inv = z > 0.f ? 1.f / z : 0.f, lse = z != 0.f ? M + logf(z) : -INFINITY;    // (NaN scores: NaN, which no combine drops)
     if (r0 + r >= rows) continue;
 #pragma unroll
     for (int e = 0; e < 4; ++e) y[e] *= inv;

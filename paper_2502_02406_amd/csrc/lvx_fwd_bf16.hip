@@ -132,7 +132,7 @@ __device__ __forceinline__ void fwd_mask_stream(const FwdArgs& a, char* smem, in
     const bool part = a.n_split > 1 || a.partial;
     float w0 = 0.f, w1 = inv, L1 = lse;
     if (!part && a.merge_into) {                   // Rescale of Algorithm 1 with the running (O, L) of this row
-      const float L0 = a.lse[row], M = fmaxf(L0, lse);
+      const float L0 = a.lse[row], M = max_or_nan(L0, lse);
       w1 = 0.f;
       L1 = -INFINITY;
       if (M != -INFINITY) {
@@ -872,7 +872,7 @@ fwd_bf16_kernel(FwdArgs a) {
   for (int qb = 0; qb < QB; ++qb) {
     const float l_tot = xhalf_sum(l_run[qb]);
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    const float lse = l_tot > 0.f ? r[qb] * (1.f / LOG2E) + logf(l_tot) : -INFINITY;
+    const float lse = l_tot != 0.f ? r[qb] * (1.f / LOG2E) + logf(l_tot) : -INFINITY;    // (NaN scores: NaN, which no combine drops)
     const int r = r_wave0 + 32 * qb + ql;
     if (r >= rows_kv) continue;
     const int hq = PACK ? hq0 + r / d.Sq : hq0, i = PACK ? r % d.Sq : r;
@@ -890,14 +890,14 @@ fwd_bf16_kernel(FwdArgs a) {
                      oacc[qb][db][4 * q4 + 3] * inv};
           *(f32x4*)(o + 32 * db + 8 * q4 + 4 * g) = y;
         }
-      if (g == 0) a.lse_part[prow] = l_tot != l_tot ? l_tot : lse;      // (a NaN must not look like a part without keys)
+      if (g == 0) a.lse_part[prow] = lse;
       continue;
     }
     if (a.merge_into) {
       // Rescale of Algorithm 1 with the running (O, L) of this row: L' = ln(e^L + e^dL),
       // O' = e^(L - L') O + e^(dL - L') dO, where dO = acc / l is this visit's result
       const float L0 = a.lse[row];
-      const float M = fmaxf(L0, lse);
+      const float M = max_or_nan(L0, lse);
       float w0 = 0.f, w1 = 0.f, L1 = -INFINITY;
       if (M != -INFINITY) {
         const float e0 = expf(L0 - M), e1 = expf(lse - M);

@@ -396,7 +396,7 @@ fwd_general_bf16_kernel(FwdArgs a) {
   // ---- epilogue: O = acc / l, L = m * scale + ln l
   const float l_tot = xhalf_sum(l_run);
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  const float lse = l_tot > 0.f ? m_ref * d.scale + logf(l_tot) : -INFINITY;
+  const float lse = l_tot != 0.f ? m_ref * d.scale + logf(l_tot) : -INFINITY;    // (NaN scores: NaN, which no combine drops)
   if (i_lane >= d.Sq) return;
   const long row = ((long)b * d.Hq + hq) * d.Sq + i_lane;
   if (a.n_split > 1 || a.partial) {
@@ -417,7 +417,7 @@ fwd_general_bf16_kernel(FwdArgs a) {
     // Rescale of Algorithm 1 with the running (O, L) of this row: L' = ln(e^L + e^dL),
     // O' = e^(L - L') O + e^(dL - L') dO, where dO = acc / l is this visit's result
     const float L0 = a.lse[row];
-    const float M = fmaxf(L0, lse);
+    const float M = max_or_nan(L0, lse);
     float w0 = 0.f, w1 = 0.f, L1 = -INFINITY;
     if (M != -INFINITY) {
       const float e0 = expf(L0 - M), e1 = expf(lse - M);

@@ -235,7 +235,7 @@ __global__ void __launch_bounds__(256) fwd_rows_bf16_kernel(FwdArgs a) {
     } else if (a.merge_into) {
       // Rescale of Algorithm 1 with the running (O, L) of this row (every thread of a row reads L
       // before the barrier, one of them replaces it after it)
-      const float L0 = a.lse[row], Mx = fmaxf(L0, lse);
+      const float L0 = a.lse[row], Mx = max_or_nan(L0, lse);
       float w0 = 0.f, w1 = 0.f;
       if (Mx != -INFINITY) {
         const float L1 = Mx + logf(expf(L0 - Mx) + expf(lse - Mx));
@@ -272,7 +272,7 @@ __global__ void __launch_bounds__(256) fwd_rows_bf16_kernel(FwdArgs a) {
         if (st_l[w * 64 + r] != 0.f) l += __builtin_amdgcn_exp2f((st_m[w * 64 + r] - M) * c2) * st_l[w * 64 + r];
       const float lse = l != 0.f ? M * d.scale + logf(l) : -INFINITY;   // (NaN scores: NaN, which no combine drops)
       const long row = ((long)b * d.Hq + hk * G + r / d.Sq) * d.Sq + r % d.Sq;
-      const float L0 = a.lse[row], Mx = fmaxf(L0, lse);
+      const float L0 = a.lse[row], Mx = max_or_nan(L0, lse);
       a.lse[row] = Mx == -INFINITY ? -INFINITY : Mx + logf(expf(L0 - Mx) + expf(lse - Mx));
     }
   }

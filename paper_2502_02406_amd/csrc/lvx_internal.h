@@ -33,6 +33,9 @@ struct MaskRows {
   const unsigned* counts;
 };
 
+// the larger, or the NaN (a result without a value must not look like one without keys)
+__device__ __forceinline__ float max_or_nan(float a, float b) { return b > a || b != b ? b : a; }
+
 // Shape, strides (in elements) and scale shared by every kernel.
 struct Dims {
   int B, Hq, Hkv, Sq, Skv, D;

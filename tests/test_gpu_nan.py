@@ -154,3 +154,46 @@ def test_rows_that_see_nothing_of_a_block_with_a_bad_value(blind):
     o, lse = loop.forward(q, k, v)
     assert torch.equal(o[:, :, :32], clean[:, :, :32]) and torch.equal(lse, l0)
     assert torch.isnan(o[:, :, 32:, 4]).all()
+
+
+@pytest.mark.parametrize("D,dtype,Hq,Hkv,Sq,Skv,q_chunk,kv_block", [
+    (64, torch.bfloat16, 8, 8, 33 * 256 - 5, 2000, 0, 0),      # dense: row tiles left whole beside split ones
+    (128, torch.bfloat16, 4, 2, 300, 150, 0, 0),               # ... not split
+    (128, torch.bfloat16, 4, 2, 3, 60, 0, 0),                  # few rows
+    (64, torch.bfloat16, 2, 1, 300, 320, 24, 64),              # words, streamed (not split)
+    (64, torch.bfloat16, 2, 1, 300, 640, 256, 100),            # words, dense loop
+    (64, torch.bfloat16, 2, 1, 300, 640, 256, 128),            # lists
+    (96, torch.bfloat16, 2, 1, 300, 320, 24, 16),              # general kernel
+    (64, torch.float32, 2, 1, 100, 320, 8, 32),
+    (64, torch.float32, 2, 1, 100, 320, 0, 0),
+])
+def test_nan_key_is_a_nan_statistic(D, dtype, Hq, Hkv, Sq, Skv, q_chunk, kv_block):
+    """L as well as O, by itself and merged with a running result of no keys or of some: an L of -infinity would be
+    dropped by the next combine as that of rows without keys."""
+    from paper_2502_02406_amd import binding as L
+    g = torch.Generator().manual_seed(13)
+    q = torch.randn((1, Hq, Sq, D), generator=g).to(dtype).cuda()
+    k, v = (torch.randn((1, Hkv, Skv, D), generator=g).to(dtype).cuda() for _ in range(2))
+    j = Skv // 3
+    k[0, 0, j, 3] = float("nan")
+    mask, sees = None, torch.ones(Sq, dtype=torch.bool, device="cuda")
+    if q_chunk:
+        c, f = torch.arange(-(-Sq // q_chunk))[:, None], torch.arange(-(-Skv // kv_block))[None, :]
+        allow = ((f - c) % 5 == 0).to(torch.uint8).cuda()
+        mask = L.make_mask(allow, q_chunk, kv_block)
+        sees = allow[:, j // kv_block].bool().repeat_interleave(q_chunk)[:Sq]
+    p = L.make_problem(q, k)
+    n = max(L.lvx_xattn_workspace_bytes(p, L.dtype_code(dtype), w) for w in (L.LVX_WS_FWD, L.LVX_WS_FWD_MERGE))
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    o, lse = torch.empty_like(q), torch.empty((1, Hq, Sq), device="cuda")
+    L.lvx_xattn_fwd(p, q, k, v, mask, o, lse, ws)
+    heads = slice(0, Hq // Hkv)
+    assert torch.isnan(o[0, heads][:, sees]).all() and torch.isnan(lse[0, heads][:, sees]).all()
+    assert not torch.isnan(lse[0, Hq // Hkv:]).any()
+    assert not torch.isnan(lse[:, :, ~sees]).any()
+    for start in (float("-inf"), 1.0):
+        acc, l_acc = torch.zeros(q.shape, device="cuda"), torch.full((1, Hq, Sq), start, device="cuda")
+        L.lvx_xattn_fwd_merge(p, q, k, v, mask, acc, l_acc, ws)
+        assert torch.isnan(acc[0, heads][:, sees]).all() and torch.isnan(l_acc[0, heads][:, sees]).all(), start
+        L.lvx_xattn_merge([acc], [l_acc], o, l_acc)
+        assert torch.isnan(o[0, heads][:, sees]).all(), start
