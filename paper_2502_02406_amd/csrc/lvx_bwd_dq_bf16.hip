@@ -100,6 +100,7 @@ __device__ __forceinline__ void dq_mask_stream(const BwdArgs& a, char* smem, int
         const float x = __builtin_amdgcn_exp2f(fmaf(s[v], c2, nl2)) * (dp[v] + nd);
         s[v] = s[v] == -INFINITY ? 0.f : x;
       }
+      ks.clear_past(t, un);
 #pragma unroll
       for (int t2 = 0; t2 < 2; ++t2) {
         const bf16x8 df = cvt_operand(s, 8 * t2);

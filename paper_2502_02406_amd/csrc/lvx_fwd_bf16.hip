@@ -113,7 +113,7 @@ __device__ __forceinline__ void fwd_mask_stream(const FwdArgs& a, char* smem, in
         sum += s[v];
       }
       l += sum;
-      ks.clear_past(t + U::TILE);
+      ks.clear_past(t + U::TILE, un);
 #pragma unroll
       for (int t2 = 0; t2 < 2; ++t2) {
         const bf16x8 pf = cvt_operand(s, 8 * t2);

@@ -152,12 +152,12 @@ template <int D> struct KeyStream {
     const int key0 = __builtin_amdgcn_readfirstlane((int)x.x) * kv_block + u * UK;
     return {min(kv_block - u * UK, Skv - key0), (unsigned)__builtin_amdgcn_readfirstlane((int)x.y)};
   }
-  // rows of the unit past the last key become 0, of a tile that is multiplied by weights of 0 there
-  __device__ __forceinline__ void clear_past(char* tile) {
-    const int there = Skv - (__builtin_amdgcn_readfirstlane((int)list[e].x) * kv_block + u * UK);
-    if (there >= UK) return;
+  // rows of the unit past its key block or the last key become 0, of a tile that is multiplied by weights of 0 there (what
+  // the next key block holds may be infinite, and no row of the tile has to see it)
+  __device__ __forceinline__ void clear_past(char* tile, const Unit& un) {
+    if (un.keys >= UK) return;
     asm volatile("" ::: "memory");
-    for (int x = max(there, 0) * U::CH + lane; x < UK * U::CH; x += 64) *(u32x4*)(tile + x * 16) = u32x4{0, 0, 0, 0};
+    for (int x = max(un.keys, 0) * U::CH + lane; x < UK * U::CH; x += 64) *(u32x4*)(tile + x * 16) = u32x4{0, 0, 0, 0};
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   }
   // every read of the stage has returned: the unit NST further on takes it

@@ -197,3 +197,30 @@ def test_nan_key_is_a_nan_statistic(D, dtype, Hq, Hkv, Sq, Skv, q_chunk, kv_bloc
         assert torch.isnan(acc[0, heads][:, sees]).all() and torch.isnan(l_acc[0, heads][:, sees]).all(), start
         L.lvx_xattn_merge([acc], [l_acc], o, l_acc)
         assert torch.isnan(o[0, heads][:, sees]).all(), start
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("D", [64, 96, 128])
+@pytest.mark.parametrize("kv_block", [66, 64 + 33])
+def test_bad_keys_behind_a_streamed_frame(kv_block, D, bad):
+    """Each row block sees a frame of its own (streamed); the keys behind the last of them, which nobody sees and no tile of
+    64 keys holds together with one that is seen, are bad: a unit of 32 keys reaches into them."""
+    from paper_2502_02406_amd.blockloop import BlockLoop, MediaMask
+    g = torch.Generator().manual_seed(14)
+    nf = 3 * 64
+    end = next(f for f in range(8, nf) if f * kv_block % 64 == 0)
+    q, do = (torch.randn((1, 2, 256, D), generator=g).bfloat16().cuda() for _ in range(2))
+    k, v = (torch.randn((1, 1, nf * kv_block, D), generator=g).bfloat16().cuda() for _ in range(2))
+    allow = torch.zeros((8, nf), dtype=torch.uint8)
+    allow[torch.arange(8), end - 8 + torch.arange(8)] = 1
+    loop = BlockLoop(tuple(q.shape), tuple(k.shape), torch.bfloat16, 1, MediaMask(allow.cuda(), 32, kv_block))
+    out = []
+    for fill in (None, bad):
+        if fill is not None:
+            k[:, :, end * kv_block:] = v[:, :, end * kv_block:] = fill
+        dk, dv = torch.empty_like(k), torch.empty_like(v)
+        o, lse = loop.forward(q, k, v)
+        dq = loop.backward(q, k, v, o, lse, do, dk, dv)
+        out.append([t.clone() for t in (o, lse, dq, dk[:, :, :end * kv_block], dv[:, :, :end * kv_block])])
+    for name, a, b in zip(("O", "L", "dQ", "dK", "dV"), *out):
+        assert torch.equal(a, b), name
