@@ -85,8 +85,9 @@ enum { LVX_MAX_PARTS = 64 };
 
 /* Bytes of workspace lvx_xattn_fwd (which = LVX_WS_FWD), lvx_xattn_bwd (LVX_WS_BWD) or
  * lvx_xattn_fwd_merge (LVX_WS_FWD_MERGE) needs for this problem and dtype.  Returns 0 on invalid
- * arguments.  (lvx_xattn_bwd takes less as well: the room for key tiles that several dK/dV workgroups share
- * is used where it is there.) */
+ * arguments.  A workspace of this size also serves the same heads and batches with fewer query rows, fewer keys or
+ * both (the key range is then split into as many parts as there is room for).  (lvx_xattn_bwd takes less as
+ * well: the room for key tiles that several dK/dV workgroups share is used where it is there.) */
 size_t lvx_xattn_workspace_bytes(const lvx_problem* p, lvx_dtype dtype, int which);
 
 /* Forward pass of one visit (Algorithm 1, the FlashAttention call; Section 2 defines the result):
@@ -102,8 +103,8 @@ lvx_status lvx_xattn_fwd(const lvx_problem* p, lvx_dtype dtype, const void* q, c
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, result and kernels as
  * lvx_xattn_fwd, but no workspace: the KV splits' partial results go into a device array of
  * LVX_STATIC_SCRATCH_BYTES that the library holds on every GPU it runs on until the process ends.
- * Problems whose lvx_xattn_workspace_bytes(p, dtype, LVX_WS_FWD) exceeds that size are refused with
- * LVX_ERR_WORKSPACE before anything is launched.  Allocates nothing.  The stream must belong to
+ * Problems whose lvx_xattn_workspace_bytes(p, dtype, LVX_WS_FWD) exceeds that size take fewer parts where those fit
+ * and are refused with LVX_ERR_WORKSPACE, before anything is launched, where they do not.  Allocates nothing.  The stream must belong to
  * the current device.  Every call on a GPU shares that GPU's array: two calls that overlap in
  * time on one GPU (different streams, or different host threads) race; calls on one stream do not. */
 enum { LVX_STATIC_SCRATCH_BYTES = 64 << 20 };

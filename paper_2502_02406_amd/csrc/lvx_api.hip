@@ -135,8 +135,10 @@ FwdPlan fwd_plan_with(const Dims& d, lvx_dtype dtype, const MaskDev& m, int rese
   for (;;) {
     f.n_parts = f.two ? 2 * f.n_split : f.n_split;
     f.need = (reserve ? fwd_merge_ws(d, dtype, f.n_parts) : fwd_ws(d, f.n_parts)) + f.rows_bytes;
-    if (!list || f.need <= room || f.n_split == 1) return f;
-    f.n_split /= 2;                      // (a list can be shared by any number)
+    if (f.need <= room || f.n_split == 1) return f;
+    // (a list can be shared by any number, and so can the keys of the other forms: fewer keys or rows may want more
+    // parts than those that the workspace was made for, 28 x 1 row against 6369 keys in the room of 6597)
+    f.n_split = list ? f.n_split / 2 : f.n_split - 1;
   }
 }
 // ... in a workspace of `room` bytes.  Words that do not fit (262144 rows against 131072 keys in blocks of 64: 68
@@ -146,7 +148,11 @@ FwdPlan fwd_plan(const Dims& d, lvx_dtype dtype, const MaskDev& m, int reserve, 
     const auto plan = [&](TailPlan t) -> FwdPlan { return {t.parts, t.whole, false, t.parts, 0, fwd_ws(d, t.parts, t.whole)}; };
     const FwdPlan f = plan(fwd_bf16_dense_plan(d, device_cu_count(), LVX_MAX_PARTS - reserve));
     if (f.need <= room) return f;
-    return plan({0, cap_parts(fwd_bf16_coarse_split(d, device_cu_count()), reserve)});
+    // (coarse parts, or down to half of them: those of fewer keys or rows may be a few more than a larger problem's)
+    const int coarse = cap_parts(fwd_bf16_coarse_split(d, device_cu_count()), reserve);
+    int n = coarse;
+    while (n > (coarse + 1) / 2 && plan({0, n}).need > room) --n;
+    return plan({0, n});
   }
   const bool rows = m.allow != nullptr && dtype == LVX_BF16 && fwd_bf16_takes_rows(d, m);
   const FwdPlan f = fwd_plan_with(d, dtype, m, reserve, rows, room);
@@ -167,13 +173,14 @@ size_t bwd_ws_fixed(const Dims& d) {   // delta [B,Hq,Sq] + padded statistics [B
 struct BwdPlan { TailPlan dq; int list, n_slices; size_t part, need; };
 size_t bwd_slice_bytes(const Dims& d) { return (size_t)d.B * d.Hq * d.Sq * d.D * sizeof(float); }
 bool can_fuse(const Dims& d, lvx_dtype dtype, bool masked) { return dtype == LVX_BF16 && bwd_fused_bf16_supported(d, masked); }
-BwdPlan bwd_plan_with(const Dims& d, lvx_dtype dtype, bool masked, bool fused, bool coarse) {
+BwdPlan bwd_plan_with(const Dims& d, lvx_dtype dtype, bool masked, bool fused, bool coarse, int most = LVX_MAX_PARTS) {
   BwdPlan p = {{0, 1}, 1, 0, 0, 0};
   if (dtype == LVX_BF16) {
     const int n_cu = device_cu_count();
     if (!bwd_dq_bf16_dense(d, masked)) p.dq.parts = bwd_bf16_pick_split(d, n_cu, masked);
     else if (coarse) p.dq.parts = bwd_dq_bf16_coarse_split(d, n_cu);
     else p.dq = bwd_dq_bf16_dense_plan(d, n_cu);
+    if (p.dq.parts > most) p.dq.parts = most;
     const int n = p.dq.parts;
     if (masked) p.list = !coarse ? fwd_list_split(d) : n > 1 ? n / 2 : 1;
     p.n_slices = !masked ? (n > 1 ? n : 0) : n > p.list || coarse ? n : p.list + 1;
@@ -183,11 +190,14 @@ BwdPlan bwd_plan_with(const Dims& d, lvx_dtype dtype, bool masked, bool fused, b
   return p;
 }
 // ... in a workspace of `room` bytes.  Fewer keys or rows may want more parts than what the workspace was made for (a block
-// loop whose K is shorter: 16 heads x 29 rows against 4982 keys in the room of 4996): the coarse
-// splits need no more than those of a larger problem, and the query has room for either.
+// loop whose K is shorter: 16 heads x 29 rows against 4982 keys in the room of 4996): coarse splits, and
+// of these as many as there is room for, down to none (under a mask one slice, which a call with more rows has too).
 BwdPlan bwd_plan(const Dims& d, lvx_dtype dtype, bool masked, bool fused, size_t room) {
-  const BwdPlan p = bwd_plan_with(d, dtype, masked, fused, false);
-  return p.need <= room ? p : bwd_plan_with(d, dtype, masked, fused, true);
+  BwdPlan p = bwd_plan_with(d, dtype, masked, fused, false);
+  if (p.need <= room) return p;
+  p = bwd_plan_with(d, dtype, masked, fused, true);
+  while (p.need > room && p.dq.parts > 1) p = bwd_plan_with(d, dtype, masked, fused, true, p.dq.parts - 1);
+  return p;
 }
 // ... + the sums of key tiles that several dK/dV workgroups share.  A workspace without room for these leaves every
 // tile to one workgroup.

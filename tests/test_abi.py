@@ -220,6 +220,36 @@ def test_workspace_holds_for_fewer_keys(lib, B_, Hq, Hkv, D, Sq, Skv, fewer):
                                             C.byref(word)) == 0
 
 
+def test_workspace_holds_for_fewer_keys_and_rows(lib):
+    """Any smaller problem of the same heads is taken (and gets as far as the launch, which fails without a device) in the
+    workspace that the query gives for the larger one: few rows, dense and masked, forward, merge and backward."""
+    import random
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("host-only check")
+    rng = random.Random(11)
+    cases = [(1, 28, 4, 96, 1, 6597, 1, 6369, 0), (1, 7, 1, 128, 8, 4913, 8, 4848, 0), (2, 4, 4, 64, 797, 79528, 758, 79528, 64),
+             (1, 16, 4, 128, 3212, 124162, 2723, 124162, 0), (1, 32, 4, 128, 20, 106729, 20, 95666, 0)]
+    for _ in range(1500):
+        h, sq, skv = rng.choice((1, 4, 8, 16)), int(2 ** rng.uniform(0, 13)), int(2 ** rng.uniform(6, 17))
+        cases.append((rng.choice((1, 2)), h * rng.choice((1, 4, 7)), h, rng.choice((64, 96, 128)), sq, skv,
+                      rng.choice((sq, rng.randint(1, sq), sq - rng.randint(0, min(63, sq - 1)))),
+                      rng.choice((skv, rng.randint(1, skv), max(1, int(skv * rng.uniform(0.8, 1))))), rng.choice((0, 0, 16, 64, 100, 729))))
+    for c in cases:
+        B_, Hq, Hkv, D, Sq, Skv, rows, keys, kv_block = c
+        p, less = problem(B=B_, Hq=Hq, Hkv=Hkv, D=D, Sq=Sq, Skv=Skv), problem(B=B_, Hq=Hq, Hkv=Hkv, D=D, Sq=rows, Skv=keys)
+        m = None
+        if kv_block:
+            m = B.lvx_mask()
+            m.allow, m.q_chunk, m.kv_block, m.n_q_chunks, m.n_kv_blocks = FAKE, 32, kv_block, -(-Sq // 32), -(-Skv // kv_block)
+            m.stride_q, m.stride_b = m.n_kv_blocks, 0
+            m = C.byref(m)
+        n = [B.lvx_xattn_workspace_bytes(p, B.LVX_BF16, w) for w in (B.LVX_WS_FWD, B.LVX_WS_FWD_MERGE, B.LVX_WS_BWD)]
+        assert fwd(lib, less, mask=m, ws_bytes=n[0]) != -6, c
+        assert lib.lvx_xattn_fwd_merge(C.byref(less), B.LVX_BF16, FAKE, FAKE, FAKE, m, FAKE, FAKE, FAKE, n[1], None) != -6, c
+        assert lib.lvx_xattn_bwd_error_word(C.byref(less), B.LVX_BF16, m, FAKE, n[2], C.byref(C.c_void_p())) == 0, c
+
+
 def test_binding_refuses_cpu_tensors():
     import torch
     if torch.cuda.is_available():

@@ -55,8 +55,9 @@ def test_short_lists(D, mask):
     _case(B, Hq, Hkv, D, Sq, Skv, 1, q_chunk, kv_block)
 
 
-@pytest.mark.parametrize("shape", [(1, 128, 16, 64, 14, 1530, 1567), (2, 16, 2, 128, 29, 4982, 4996), (1, 4, 2, 96, 72, 23990, 29102)],
+@pytest.mark.parametrize("shape", [(1, 128, 16, 64, 14, 1530, 1567), (2, 16, 2, 128, 29, 4982, 4996), (1, 4, 2, 96, 72, 23990, 29102),
+                                   (1, 28, 4, 96, 1, 6369, 6597), (1, 7, 1, 128, 8, 4848, 4913)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_fewer_keys_than_the_workspace_was_made_for(shape):
-    """... for which the plan of these keys would want more parts: dQ is split as far as there is room."""
+    """... for which the plan of these keys would want more parts: they are split as far as there is room."""
     _case(*shape[:6], made_for=shape[6])
