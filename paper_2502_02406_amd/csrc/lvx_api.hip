@@ -199,12 +199,16 @@ BwdPlan bwd_plan(const Dims& d, lvx_dtype dtype, bool masked, bool fused, size_t
   while (p.need > room && p.dq.parts > 1) p = bwd_plan_with(d, dtype, masked, fused, true, p.dq.parts - 1);
   return p;
 }
-// ... + the sums of key tiles that several dK/dV workgroups share.  A workspace without room for these leaves every
-// tile to one workgroup.
+// How the dK/dV kernel shares key tiles among workgroups where there are `room` bytes for their sums (and, under a
+// mask, the tiles' numbers of parts): as many parts as fit.
+KvPlan kv_plan(const Dims& d, lvx_dtype dtype, bool masked, size_t room) {
+  if (dtype != LVX_BF16) return {0, 1, 0};
+  const size_t counts = dkdv_bf16_counts_bytes(d), set = dkdv_bf16_set_bytes(d);
+  return dkdv_bf16_plan(d, device_cu_count(), masked, room > counts ? (long)((room - counts) / set) : 0);
+}
 size_t bwd_ws_kv(const Dims& d, lvx_dtype dtype, bool masked) {
-  if (dtype != LVX_BF16) return 0;
-  const KvPlan p = dkdv_bf16_plan(d, device_cu_count(), masked);
-  return dkdv_bf16_sums_bytes(d, p) + dkdv_bf16_counts_bytes(d, p);
+  const KvPlan p = kv_plan(d, dtype, masked, SIZE_MAX);
+  return p.parts > 1 ? dkdv_bf16_sums_bytes(d, p) + dkdv_bf16_counts_bytes(d) : 0;
 }
 }  // namespace
 
@@ -464,8 +468,8 @@ static lvx_status bwd_visit(const lvx_problem* p, lvx_dtype dtype, const void* q
   a.rows_ws_bytes = bwd_slice_bytes(a.d);
   a.dq_tiles = fused ? (float*)((char*)workspace + bwd_ws_fixed(a.d) + plan.part) : nullptr;
   a.kv = {0, 1, 0}; a.kv_sums = nullptr; a.kv_counts = nullptr;
-  if (dtype == LVX_BF16 && !fused && workspace_bytes - need >= bwd_ws_kv(a.d, dtype, mask != nullptr)) {
-    a.kv = dkdv_bf16_plan(a.d, device_cu_count(), mask != nullptr);
+  if (!fused) {
+    a.kv = kv_plan(a.d, dtype, mask != nullptr, workspace_bytes - need);
     if (a.kv.parts > 1) {
       a.kv_sums = (float*)((char*)workspace + need);
       a.kv_counts = (int*)((char*)workspace + need + dkdv_bf16_sums_bytes(a.d, a.kv));

@@ -971,12 +971,12 @@ bool dkdv_steps(const Dims& d, const MaskDev& m) {
 // at most; the others leave.  2048 rows x 28 heads in chunks of 64 against 32 frames of 729 keys, causal: 701 ->
 // 648 us; 3584 rows x 6016 keys in frames of 64 1116 -> 306; masks that show each chunk one frame 206 -> 78 (3264
 // rows x 4480 keys, frames of 64) and, with tiles enough but most of them short, 312 -> 196 (2591 x 28160).
-KvPlan dkdv_bf16_plan(const Dims& d, int n_cu, bool masked) {
+KvPlan dkdv_bf16_plan(const Dims& d, int n_cu, bool masked, long most_sets) {
   constexpr int KN = DkvSmem<128, 2>::KN;
   const int n_kt = (d.Skv + KN - 1) / KN, H = d.B * d.Hkv;
   const long tiles = (long)H * n_kt;
   const int steps = d.Hq / d.Hkv * ((d.Sq + KM - 1) / KM);
-  const long most = 1024;                          // sets of sums (256 KB each with 128-wide heads)
+  const long most = most_sets < 1024 ? most_sets : 1024;         // sets of sums (256 KB each with 128-wide heads)
   KvPlan best = {n_kt, 1, 0};
   if (!dkdv_rows_ok(d)) return best;
   // clocks of a step, of a workgroup's set-up and epilogue, and of the sums' way through memory
@@ -1015,13 +1015,14 @@ KvPlan dkdv_bf16_plan(const Dims& d, int n_cu, bool masked) {
   }
   return best;
 }
+size_t dkdv_bf16_set_bytes(const Dims& d) { return (size_t)2 * DkvSmem<128, 2>::KN * d.D * sizeof(float); }
 size_t dkdv_bf16_sums_bytes(const Dims& d, const KvPlan& p) {
   constexpr int KN = DkvSmem<128, 2>::KN;
-  return p.parts > 1 ? (size_t)d.B * d.Hkv * ((d.Skv + KN - 1) / KN - p.whole) * p.parts * 2 * KN * d.D * sizeof(float) : 0;
+  return p.parts > 1 ? (size_t)d.B * d.Hkv * ((d.Skv + KN - 1) / KN - p.whole) * p.parts * dkdv_bf16_set_bytes(d) : 0;
 }
-size_t dkdv_bf16_counts_bytes(const Dims& d, const KvPlan& p) {
+size_t dkdv_bf16_counts_bytes(const Dims& d) {
   constexpr int KN = DkvSmem<128, 2>::KN;
-  return p.parts > 1 ? ((size_t)d.B * d.Hkv * ((d.Skv + KN - 1) / KN) * sizeof(int) + 255) / 256 * 256 : 0;
+  return ((size_t)d.B * d.Hkv * ((d.Skv + KN - 1) / KN) * sizeof(int) + 255) / 256 * 256;
 }
 
 // A mask that cuts through the steps or through a workgroup's keys, while its list and words fit

@@ -182,9 +182,10 @@ hipError_t launch_bwd_f32(const BwdArgs& a, unsigned stages, hipStream_t s);   /
 hipError_t launch_fwd_bf16(const FwdArgs& a, hipStream_t s);
 hipError_t launch_bwd_bf16(const BwdArgs& a, unsigned stages, hipStream_t s);
 hipError_t launch_bwd_dkdv_bf16(const BwdArgs& a, hipStream_t s);
-KvPlan dkdv_bf16_plan(const Dims& d, int n_cu, bool masked);
+KvPlan dkdv_bf16_plan(const Dims& d, int n_cu, bool masked, long most_sets);   // with room for that many sets of a tile's sums
+size_t dkdv_bf16_set_bytes(const Dims& d);
 size_t dkdv_bf16_sums_bytes(const Dims& d, const KvPlan& p);     // of BwdArgs::kv_sums (a multiple of 256 bytes),
-size_t dkdv_bf16_counts_bytes(const Dims& d, const KvPlan& p);   // and of kv_counts
+size_t dkdv_bf16_counts_bytes(const Dims& d);                    // and of kv_counts
 hipError_t launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s);
 // all five products in one kernel (dense, head dim 128, at least 256 keys and 32 query rows):
 // handles the first Skv / 256 * 256 keys; needs BwdArgs::dq_tiles

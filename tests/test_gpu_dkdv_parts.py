@@ -1,14 +1,16 @@
 """Key tiles whose steps several dK/dV workgroups share: few keys, a last round of a few tiles, and lists of steps
 under a media mask, against float64 from the same O and L.  P, dS and the results are bf16 (2^-9 each,
 relative): 2^-7.5 of the norm bounds dK and dV; the parts' float32 sums add nothing to that.  The smallest workspace
-that the library takes has no room for the parts and has to give the same up to the rounding of the results."""
+that the library takes has no room for the parts and has to give the same up to the rounding of the results, and so
+has one with room for some of them.  Whether a call has parts is seen in the workspace: nothing but their sums is written
+behind that smallest size by a call without the dQ kernel."""
 import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
 
 
-def _case(B, Hq, Hkv, D, Sq, Skv, q_chunk=0, kv_block=0, rule="causal"):
+def _case(B, Hq, Hkv, D, Sq, Skv, q_chunk=0, kv_block=0, rule="causal", parts=True):
     from paper_2502_02406_amd import binding as L
     from paper_2502_02406_amd.blockloop import BlockLoop, MediaMask
     g = torch.Generator(device="cuda").manual_seed(5)
@@ -50,9 +52,20 @@ def _case(B, Hq, Hkv, D, Sq, Skv, q_chunk=0, kv_block=0, rule="causal"):
             hi = mid
         except L.LvxError:
             lo = mid
-    assert hi * 256 < loop.ws.numel(), "this shape has no parts: the test does not test them"
-    for got, one in zip((dk, dv), backward(loop.ws[:hi * 256], L.LVX_BWD_ALL)):
-        assert float((got.float() - one.float()).norm() / one.float().norm()) <= 2.0 ** -8
+    ones = backward(loop.ws[:hi * 256], L.LVX_BWD_ALL)
+    need = L.lvx_xattn_workspace_bytes(L.make_problem(q, k), L.LVX_BF16, L.LVX_WS_BWD)
+    for size in (need, hi * 256 + 7 * (need - hi * 256) // 8):
+        ws = torch.full_like(loop.ws[:size // 256 * 256], 0xa5)
+        got = backward(ws, L.LVX_BWD_DELTA | L.LVX_BWD_DKDV)
+        assert bool((ws[hi * 256:] != 0xa5).any()) == parts, f"parts or none in {size} bytes"
+        for two, one in zip(got, ones):
+            assert float((two.float() - one.float()).norm() / one.float().norm()) <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("shape", [(1, 8, 1, 64, 31, 700), (2, 8, 8, 64, 64, 16 * 256)], ids=lambda s: "x".join(map(str, s)))
+def test_no_parts(shape):
+    """Fewer rows than a step; a full round of tiles."""
+    _case(*shape, parts=False)
 
 
 @pytest.mark.parametrize("D", [64, 96, 128])
