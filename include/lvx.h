@@ -86,8 +86,12 @@ enum { LVX_MAX_PARTS = 64 };
 /* Bytes of workspace lvx_xattn_fwd (which = LVX_WS_FWD), lvx_xattn_bwd (LVX_WS_BWD) or
  * lvx_xattn_fwd_merge (LVX_WS_FWD_MERGE) needs for this problem and dtype.  Returns 0 on invalid
  * arguments.  A workspace of this size also serves the same heads and batches with fewer query rows, fewer keys or
- * both (the key range is then split into as many parts as there is room for).  (lvx_xattn_bwd takes less as
- * well: the room for key tiles that several dK/dV workgroups share is used where it is there.) */
+ * both (the key range is then split into as many parts as there is room for).
+ * The backward's size is that of its statistics (three float32 a row) and the dQ sums of the parts that the key range is
+ * split into (B Hq Sq D float32 each; at least one, and as many again for dense bf16 calls with D = 128), and for
+ * bf16, where key tiles are few, as much again or 2048 D bytes for every compute unit more (64 MiB with D = 128), whichever is
+ * larger: sums of key tiles that several dK/dV workgroups share.  lvx_xattn_bwd takes less as well: the key
+ * tiles are shared by as many workgroups as there is room for (which the last bit of dK and dV depends on). */
 size_t lvx_xattn_workspace_bytes(const lvx_problem* p, lvx_dtype dtype, int which);
 
 /* Forward pass of one visit (Algorithm 1, the FlashAttention call; Section 2 defines the result):

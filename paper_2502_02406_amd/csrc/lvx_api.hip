@@ -168,13 +168,14 @@ size_t bwd_ws_fixed(const Dims& d) {   // delta [B,Hq,Sq] + padded statistics [B
 }
 // How the dQ kernels split the key range, and the workspace of a backward call: `list` splits under masks that
 // run over lists, else dq; partial sums [n_slices, split rows, D].  A masked bf16 call always has one
-// slice at least: the words of MaskRows go into the last slice, which the kernels that read them
+// slice at least: the words of MaskRows go into the first slice, which the kernels that read them
 // leave alone (`list` is one less at least), and which the others fill only after the words' last reader.
-struct BwdPlan { TailPlan dq; int list, n_slices; size_t part, need; };
+// The order: statistics, the fused kernel's dQ tiles, locks and error word (`part_at` bytes up to here), the slices.
+struct BwdPlan { TailPlan dq; int list, n_slices; size_t part_at, part, need; };
 size_t bwd_slice_bytes(const Dims& d) { return (size_t)d.B * d.Hq * d.Sq * d.D * sizeof(float); }
 bool can_fuse(const Dims& d, lvx_dtype dtype, bool masked) { return dtype == LVX_BF16 && bwd_fused_bf16_supported(d, masked); }
 BwdPlan bwd_plan_with(const Dims& d, lvx_dtype dtype, bool masked, bool fused, bool coarse, int most = LVX_MAX_PARTS) {
-  BwdPlan p = {{0, 1}, 1, 0, 0, 0};
+  BwdPlan p = {{0, 1}, 1, 0, 0, 0, 0};
   if (dtype == LVX_BF16) {
     const int n_cu = device_cu_count();
     if (!bwd_dq_bf16_dense(d, masked)) p.dq.parts = bwd_bf16_pick_split(d, n_cu, masked);
@@ -186,7 +187,8 @@ BwdPlan bwd_plan_with(const Dims& d, lvx_dtype dtype, bool masked, bool fused, b
     p.n_slices = !masked ? (n > 1 ? n : 0) : n > p.list || coarse ? n : p.list + 1;
     p.part = align_up(p.n_slices * split_rows(d, p.dq.whole) * d.D * sizeof(float));
   }
-  p.need = bwd_ws_fixed(d) + p.part + (fused ? align_up(bwd_fused_ws_bytes(d)) : 0);   // ... + the fused kernel's dQ tiles and locks
+  p.part_at = bwd_ws_fixed(d) + (fused ? align_up(bwd_fused_ws_bytes(d)) : 0);
+  p.need = p.part_at + p.part;
   return p;
 }
 // ... in a workspace of `room` bytes.  Fewer keys or rows may want more parts than what the workspace was made for (a block
@@ -206,9 +208,40 @@ KvPlan kv_plan(const Dims& d, lvx_dtype dtype, bool masked, size_t room) {
   const size_t counts = dkdv_bf16_counts_bytes(d), set = dkdv_bf16_set_bytes(d);
   return dkdv_bf16_plan(d, device_cu_count(), masked, room > counts ? (long)((room - counts) / set) : 0);
 }
-size_t bwd_ws_kv(const Dims& d, lvx_dtype dtype, bool masked) {
-  const KvPlan p = kv_plan(d, dtype, masked, SIZE_MAX);
-  return p.parts > 1 ? dkdv_bf16_sums_bytes(d, p) + dkdv_bf16_counts_bytes(d) : 0;
+// The sums lie where the dQ kernel's slices do: they have been added up when that kernel starts.  (Under a mask the
+// first slice holds the words, which dK/dV reads too.)
+size_t bwd_kv_at(const Dims& d, lvx_dtype dtype, bool masked) {
+  return bwd_ws_fixed(d) + (can_fuse(d, dtype, masked) ? align_up(bwd_fused_ws_bytes(d)) : 0) + (masked ? align_up(bwd_slice_bytes(d)) : 0);
+}
+// A call's workspace without room for the sums: the larger of the dense and the masked plans'.
+size_t bwd_ws_base(const Dims& d, lvx_dtype dtype) {
+  const auto larger = [](size_t x, size_t y) { return x > y ? x : y; };
+  const auto of = [&](bool masked) -> size_t {
+    const bool fused = can_fuse(d, dtype, false);
+    return larger(bwd_plan_with(d, dtype, masked, fused, false).need, bwd_plan_with(d, dtype, masked, fused, true).need);
+  };
+  return larger(of(true), of(false));
+}
+// What a backward call may fill: twice that, or a set of sums for every compute unit more.  One round of workgroups is
+// what few key tiles need (28 / 4 heads, D = 128, delta + dK/dV: 1226 rows x 1024 keys 322 -> 65 us with 64 MB of
+// sums, 74 with 32, 125 with 16; 185 x 1905 61 -> 45, 50, 61); masks, whose tiles may all be cut, want more where there are many.
+size_t bwd_ws_most(const Dims& d, lvx_dtype dtype) {
+  const size_t base = bwd_ws_base(d, dtype), round = (size_t)device_cu_count() * dkdv_bf16_set_bytes(d) + dkdv_bf16_counts_bytes(d);
+  return base + (base > round ? base : round);
+}
+KvPlan bwd_kv_plan(const Dims& d, lvx_dtype dtype, bool masked, size_t workspace_bytes) {
+  if (dtype != LVX_BF16) return {0, 1, 0};
+  const size_t at = bwd_kv_at(d, dtype, masked), most = bwd_ws_most(d, dtype), end = workspace_bytes < most ? workspace_bytes : most;
+  return kv_plan(d, dtype, masked, end > at ? end - at : 0);
+}
+size_t bwd_ws_query(const Dims& d, lvx_dtype dtype) {
+  size_t n = bwd_ws_base(d, dtype);
+  for (int masked = 0; masked < 2; ++masked) {
+    const KvPlan p = bwd_kv_plan(d, dtype, masked, SIZE_MAX);
+    const size_t kv = p.parts > 1 ? bwd_kv_at(d, dtype, masked) + dkdv_bf16_sums_bytes(d, p) + dkdv_bf16_counts_bytes(d) : 0;
+    if (kv > n) n = kv;
+  }
+  return n;
 }
 }  // namespace
 
@@ -255,13 +288,8 @@ size_t lvx_xattn_workspace_bytes(const lvx_problem* p, lvx_dtype dtype, int whic
     return dtype == LVX_BF16 && fwd_bf16_dense(d, false) ? most(fwd_plan(d, dtype, make_mask(nullptr), reserve, SIZE_MAX).need,
                                                                 fwd_ws(d, cap_parts(fwd_bf16_coarse_split(d, device_cu_count()), reserve))) : 0;
   };
-  const auto bwd = [&](bool masked) -> size_t {
-    const bool fused = can_fuse(d, dtype, false);
-    return most(bwd_plan_with(d, dtype, masked, fused, false).need, bwd_plan_with(d, dtype, masked, fused, true).need);
-  };
   if (which == LVX_WS_FWD) return most(fwd_ws(d, parts(0)) + rows_most, dense(0));
-  if (which == LVX_WS_BWD)
-    return most(bwd(true), bwd(false)) + most(bwd_ws_kv(d, dtype, true), bwd_ws_kv(d, dtype, false));
+  if (which == LVX_WS_BWD) return bwd_ws_query(d, dtype);
   if (which == LVX_WS_FWD_MERGE) return most(fwd_merge_ws(d, dtype, parts(1)) + rows_most, dense(1));
   return 0;
 }
@@ -462,17 +490,19 @@ static lvx_status bwd_visit(const lvx_problem* p, lvx_dtype dtype, const void* q
   a.stats_ovl = has_stats_ovl(a.d) ? a.stats + stats_floats(a.d) : nullptr;
   a.dq_accum = dq_accum; a.dk = dk; a.dv = dv;
   a.dq_first = first; a.dq_last = dq_last;
-  a.dq_part = n_slices > 0 ? (float*)((char*)workspace + bwd_ws_fixed(a.d)) : nullptr;
+  const auto at = [&](size_t x) -> char* { return (char*)workspace + x; };
+  a.dq_part = n_slices > 0 ? (float*)at(plan.part_at) : nullptr;
   a.rows = MaskRows{};
-  a.rows_ws = mask != nullptr && n_slices > 0 ? (char*)workspace + bwd_ws_fixed(a.d) + (n_slices - 1) * bwd_slice_bytes(a.d) : nullptr;
+  a.rows_ws = mask != nullptr && n_slices > 0 ? at(plan.part_at) : nullptr;
   a.rows_ws_bytes = bwd_slice_bytes(a.d);
-  a.dq_tiles = fused ? (float*)((char*)workspace + bwd_ws_fixed(a.d) + plan.part) : nullptr;
+  a.dq_tiles = fused ? (float*)at(bwd_ws_fixed(a.d)) : nullptr;
   a.kv = {0, 1, 0}; a.kv_sums = nullptr; a.kv_counts = nullptr;
   if (!fused) {
-    a.kv = kv_plan(a.d, dtype, mask != nullptr, workspace_bytes - need);
+    a.kv = bwd_kv_plan(a.d, dtype, mask != nullptr, workspace_bytes);
     if (a.kv.parts > 1) {
-      a.kv_sums = (float*)((char*)workspace + need);
-      a.kv_counts = (int*)((char*)workspace + need + dkdv_bf16_sums_bytes(a.d, a.kv));
+      const size_t kv_at = bwd_kv_at(a.d, dtype, mask != nullptr);
+      a.kv_sums = (float*)at(kv_at);
+      a.kv_counts = (int*)at(kv_at + dkdv_bf16_sums_bytes(a.d, a.kv));
     }
   }
   a.dq_locks = nullptr; a.dq_err = nullptr; a.dq_stagger = 0;
@@ -514,7 +544,7 @@ lvx_status lvx_xattn_bwd_error_word(const lvx_problem* p, lvx_dtype dtype, const
   const bool fused = can_fuse(d, dtype, mask != nullptr);
   const BwdPlan plan = bwd_plan(d, dtype, mask != nullptr, fused, workspace_bytes);
   if (!workspace || ((uintptr_t)workspace % ALIGN) != 0 || workspace_bytes < plan.need) return LVX_ERR_WORKSPACE;
-  *word = fused ? (const int*)((char*)workspace + bwd_ws_fixed(d) + plan.part + bwd_fused_ws_bytes(d) - 256)
+  *word = fused ? (const int*)((char*)workspace + bwd_ws_fixed(d) + bwd_fused_ws_bytes(d) - 256)
                 : nullptr;
   return LVX_OK;
 }

@@ -220,6 +220,16 @@ def test_workspace_holds_for_fewer_keys(lib, B_, Hq, Hkv, D, Sq, Skv, fewer):
                                             C.byref(word)) == 0
 
 
+@pytest.mark.parametrize("Hq,Hkv,Sq,Skv,slices", [(28, 4, 185, 1905, 2), (28, 4, 1226, 1024, 2), (28, 4, 2048, 23328, 6), (32, 8, 8192, 3072, 2)])
+def test_backward_workspace_is_bounded(lib, Hq, Hkv, Sq, Skv, slices):
+    """Statistics, dQ slices and tiles (`slices` together), and as much again or 256 sets of 256 keys' sums (256 compute
+    units are assumed without a device)."""
+    pad = (Sq + 31) // 32 * 32
+    base = Hq * (Sq + 2 * pad + 64) * 4 + slices * Hq * pad * 128 * 4 + 65536
+    n = B.lvx_xattn_workspace_bytes(problem(Hq=Hq, Hkv=Hkv, Sq=Sq, Skv=Skv), B.LVX_BF16, B.LVX_WS_BWD)
+    assert n <= base + max(base, 256 * 2 * 256 * 128 * 4 + 65536)
+
+
 def test_workspace_holds_for_fewer_keys_and_rows(lib):
     """Any smaller problem of the same heads is taken (and gets as far as the launch, which fails without a device) in the
     workspace that the query gives for the larger one: few rows, dense and masked, forward, merge and backward."""
