@@ -215,8 +215,9 @@ bwd_dq_bf16_kernel(BwdArgs a) {
 
   // KV range of this split, in tiles
   const int n_tiles = (d.Skv + TN - 1) / TN;
-  int t_begin = (int)((long)split * n_tiles / n_split);         // (with a media mask: re-cut below over the visible tiles)
-  int t_end = (int)((long)(split + 1) * n_tiles / n_split);
+  const int tps = (n_tiles + n_split - 1) / n_split;
+  int t_begin = split * tps;                        // (with a media mask: re-cut below over the visible tiles)
+  int t_end = min(n_tiles, t_begin + tps);
 
   // ---- stationary operands and statistics of this lane's query rows i_wave0 + 32 qb + ql
   // The dense variant folds the statistics into the matrix products: Q is held as

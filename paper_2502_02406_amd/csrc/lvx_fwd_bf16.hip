@@ -266,8 +266,9 @@ fwd_bf16_kernel(FwdArgs a) {
 
   // KV range of this split, in tiles
   const int n_tiles = (d.Skv + TN - 1) / TN;
-  int t_begin = (int)((long)split * n_tiles / n_split);         // (LIST: re-cut below over the list)
-  int t_end = (int)((long)(split + 1) * n_tiles / n_split);
+  const int tps = (n_tiles + n_split - 1) / n_split;
+  int t_begin = split * tps;                        // (LIST: re-cut below over the list)
+  int t_end = min(n_tiles, t_begin + tps);
 
   // ---- stationary operands: Q of this lane's rows r_wave0 + 32 qb + ql of the list
   const float c2 = d.scale * LOG2E;

@@ -47,6 +47,35 @@ def test_last_round(shape):
     _case(*shape)
 
 
+@pytest.mark.parametrize("Sq,Skv", [(100, 6407), (300, 20000), (2000, 3000)])
+def test_parts_are_runs_of_whole_tiles(Sq, Skv):
+    """Part k holds tiles k t .. k t + t - 1 of 64 keys, t the same for all but the last: what P is rounded against, and so the bits
+    of O, depends on nothing else about the split.  Seen in the parts' L, which follow the parts' O in the workspace."""
+    from paper_2502_02406_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(7)
+    D, Hq = 64, 2
+    q = torch.randn((1, Hq, Sq, D), generator=g, device="cuda").bfloat16()
+    k, v = (torch.randn((1, 1, Skv, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+    p = B.make_problem(q, k)
+    ws = torch.zeros(B.lvx_xattn_workspace_bytes(p, B.LVX_BF16, B.LVX_WS_FWD), dtype=torch.uint8, device="cuda")
+    o, lse = torch.empty_like(q), torch.empty((1, Hq, Sq), device="cuda")
+    B.lvx_xattn_fwd(p, q, k, v, None, o, lse, ws)
+    rows, f = Hq * Sq, ws.view(torch.float32)
+    for n in range(2, 65):
+        at = (rows * D * n + 63) // 64 * 64
+        if at + rows * n > f.numel():
+            break
+        part = f[at:at + rows * n].view(n, rows).double()
+        if torch.allclose(torch.logsumexp(part, 0), lse.double().flatten(), rtol=0, atol=1e-3):
+            break
+    else:
+        pytest.fail("no parts found")
+    s = (q[0].reshape(rows, D).double() @ k[0, 0].double().T) * D ** -0.5
+    t = -(-(-(-Skv // 64)) // n) * 64
+    want = torch.stack([torch.logsumexp(s[:, i * t:(i + 1) * t], 1) for i in range(n)])
+    assert float((part - want).abs().max()) <= 1e-3
+
+
 @pytest.mark.parametrize("D", [64, 96, 128])
 @pytest.mark.parametrize("mask", [(1, 4, 2, 300, 1900, 40, 729), (2, 2, 2, 80, 4096, 64, 256), (1, 8, 2, 64, 1088, 2, 64)],
                          ids=lambda m: "x".join(map(str, m)))
