@@ -82,7 +82,7 @@ MaskDev make_mask(const lvx_mask* m) {
 int fwd_split(const Dims& d, lvx_dtype dtype, bool masked) {
   return dtype == LVX_BF16 ? fwd_bf16_pick_split(d, device_cu_count(), masked) : 1;
 }
-int fwd_list_split(const Dims& d) { return list_split((long)d.B * d.Hq * ((d.Sq + 255) / 256), (d.Skv + 63) / 64); }
+int fwd_list_split(const Dims& d) { return list_split((long)d.B * d.Hq * ((d.Sq + 255) / 256), (d.Skv + 63) / 64, device_cu_count()); }
 
 // bf16 under a media mask that fits (fwd_bf16_two_pass_fits): the dense kernel over the key tiles
 // that every row of a workgroup sees, then the general kernel on the other visible tiles; each

@@ -266,14 +266,15 @@ TailPlan bwd_dq_bf16_dense_plan(const Dims& d, int n_cu);
 int bwd_dq_bf16_coarse_split(const Dims& d, int n_cu);
 // KV splits of the masked kernels that walk a list of the tiles some row sees (LIST >= 2; each split takes an even share
 // of the list, wherever it ends), for `wgs` row tiles and n_tiles key tiles of which the mask shows any
-// number.  They start longest first, so two rounds of the chip (512 workgroups) even out lists as uneven
+// number.  They start longest first, so two rounds of the chip even out lists as uneven
 // as a causal mask's while a workgroup keeps tiles enough to be worth its set-up and list (15 us); else one
 // round, down to three tiles a split.  (Four times the compute units halved, 1024 keys a split at least, before.)
 // Forward and dQ, us: 28 row tiles (D = 128) x 92 key tiles 68 -> 38 and 84 -> 46, 64 x 29 (D = 64) 53 -> 37 and 53 -> 37, 64
 // x 201 88 -> 72 and 109 -> 89; two rounds of long ones: 128 x 2048, causal 457 -> 382 and 581 -> 482 against
 // one round (each chunk one frame: 152 -> 168).  Between one round and one and a half, two splits: 160 x 160 232 -> 202 (three before).
-inline int list_split(long wgs, int n_tiles) {
-  const long two = wgs <= 256 ? 512 / wgs : wgs <= 400 ? 2 : 1, one = wgs <= 128 ? 256 / wgs : wgs <= 400 ? 2 : 1;
+inline int list_split(long wgs, int n_tiles, int n_cu) {
+  const long some = 16 * wgs <= 25L * n_cu ? 2 : 1;                // (a round and a half of them)
+  const long two = wgs <= n_cu ? 2L * n_cu / wgs : some, one = 2 * wgs <= n_cu ? n_cu / wgs : some;
   long s = n_tiles / two >= 64 ? two : one;
   if (s > n_tiles / 3) s = n_tiles / 3;
   return s < 1 ? 1 : s > 60 ? 60 : (int)s;
