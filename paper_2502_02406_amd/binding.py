@@ -198,6 +198,16 @@ def lvx_xattn_fwd_merge(p: lvx_problem, q, k, v, mask: Optional[lvx_mask], o_acc
     _check(code, "lvx_xattn_fwd_merge")
 
 
+def lvx_xattn_fwd_merge_last(p: lvx_problem, q, k, v, mask: Optional[lvx_mask], o_acc, lse_acc, o, workspace) -> None:
+    """The last visit: the merged O goes to o (dtype and strides of q, or q itself), o_acc then holds nothing of use."""
+    if not q.is_cuda or not o.is_cuda:
+        raise RuntimeError("lvx_xattn_fwd_merge_last needs device tensors")
+    assert o_acc.dtype == torch.float32 and o_acc.is_contiguous() and lse_acc.is_contiguous()
+    assert o.dtype == q.dtype and o.shape == q.shape and o.stride() == q.stride()
+    Calls(p, q.dtype, workspace).fwd_merge_last(q.data_ptr(), k.data_ptr(), v.data_ptr(), mask, o_acc.data_ptr(),
+                                                lse_acc.data_ptr(), o.data_ptr())
+
+
 def lvx_xattn_merge(o_parts: Sequence[torch.Tensor], lse_parts: Sequence[torch.Tensor],
                     o_out: torch.Tensor, lse_out: torch.Tensor) -> None:
     """Rescale of Algorithm 1 over the given parts (each contiguous [B,Hq,Sq,D] / [B,Hq,Sq])."""
@@ -233,6 +243,21 @@ def lvx_xattn_bwd(p: lvx_problem, q, k, v, o, lse, d_o, mask: Optional[lvx_mask]
         _check(load().lvx_xattn_bwd(*args), "lvx_xattn_bwd")
     else:
         _check(load().lvx_xattn_bwd_stages(*args, stages), "lvx_xattn_bwd_stages")
+
+
+def lvx_xattn_bwd_visit(p: lvx_problem, q, k, v, o, lse, d_o, mask: Optional[lvx_mask], dq_accum, dk, dv, workspace,
+                        first: bool, dq=None) -> None:
+    """One visit of a block loop's backward: dq_accum overwritten by the first; rounded into dq (dtype, shape and strides of q)
+    by the last, for which dq is given."""
+    if not q.is_cuda:
+        raise RuntimeError("lvx_xattn_bwd_visit needs device tensors")
+    assert dq_accum.dtype == torch.float32 and dq_accum.is_contiguous()
+    assert dk.stride() == k.stride() and dv.stride() == k.stride()
+    for t in (o, d_o) if dq is None else (o, d_o, dq):
+        assert t.dtype == q.dtype and t.shape == q.shape and t.stride() == q.stride()
+    Calls(p, q.dtype, workspace).bwd_visit(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), d_o.data_ptr(),
+                                           mask, dq_accum.data_ptr(), dk.data_ptr(), dv.data_ptr(), first,
+                                           dq.data_ptr() if dq is not None else None)
 
 
 def lvx_xattn_bwd_error_word(p: lvx_problem, dtype: int, mask: Optional[lvx_mask], workspace) -> int:

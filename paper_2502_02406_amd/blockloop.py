@@ -218,8 +218,7 @@ class RecomputeLayer:
             elif n < self.n_blocks - 1 or self.q.dtype == torch.float32:
                 B.lvx_xattn_fwd_merge(p, self.q, self.k, self.v, None, self.o_acc, lp.lse, lp.ws)
             else:
-                B.Calls(p, self.q.dtype, lp.ws).fwd_merge_last(self.q.data_ptr(), self.k.data_ptr(), self.v.data_ptr(), None,
-                                                               self.o_acc.data_ptr(), lp.lse.data_ptr(), lp.o.data_ptr())
+                B.lvx_xattn_fwd_merge_last(p, self.q, self.k, self.v, None, self.o_acc, lp.lse, lp.o, lp.ws)
                 return lp.o, lp.lse
         B.lvx_xattn_merge([self.o_acc], [lp.lse], lp.o, lp.lse)
         return lp.o, lp.lse
@@ -231,14 +230,11 @@ class RecomputeLayer:
         self.dwq.zero_()
         self.dwkv.zero_()
         p = B.make_problem(self.q, self.k, lp.scale)
-        assert o.stride() == self.q.stride() and d_o.stride() == self.q.stride()
-        call = B.Calls(p, self.q.dtype, lp.ws)
-        last = lp.dq.data_ptr() if lp.dq is not lp.dq_accum else None
+        last = lp.dq if lp.dq is not lp.dq_accum else None
         for n in range(self.n_blocks):
             yb = self._kv_of_block(y, wkv, n)                       # K, V of the block again
-            call.bwd_visit(self.q.data_ptr(), self.k.data_ptr(), self.v.data_ptr(), o.data_ptr(), lse.data_ptr(), d_o.data_ptr(), None,
-                           lp.dq_accum.data_ptr(), self.dk.data_ptr(), self.dv.data_ptr(), n == 0,
-                           last if n == self.n_blocks - 1 else None)
+            B.lvx_xattn_bwd_visit(p, self.q, self.k, self.v, o, lse, d_o, None, lp.dq_accum, self.dk, self.dv, lp.ws, n == 0,
+                                  last if n == self.n_blocks - 1 else None)
             B.lvx_xattn_project_bwd(yb, wkv, [self.dk, self.dv],
                                     dx=self.dy[:, n * self.blk:(n + 1) * self.blk], dw=self.dwkv)
         B.lvx_xattn_project_bwd(x, wq, [lp.dq], dx=self.dx, dw=self.dwq)

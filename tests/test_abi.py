@@ -129,6 +129,22 @@ def test_fwd_merge_errors(lib):
     assert B.lvx_xattn_workspace_bytes(p, B.LVX_BF16, B.LVX_WS_FWD_MERGE) >= 256
 
 
+def test_visit_errors(lib):
+    p = problem()
+    args = [C.byref(p), B.LVX_BF16, FAKE, FAKE, FAKE, None, FAKE, FAKE, FAKE, FAKE, 1 << 40, None]
+    call = lambda at, x: lib.lvx_xattn_fwd_merge_last(*(args[:at] + [x] + args[at + 1:]))
+    assert call(1, B.LVX_F32) == -3                              # a float32 running result is the result
+    assert call(8, None) == -1 and call(8, FAKE + 8) == -4       # o
+    assert call(6, None) == -1 and call(7, None) == -1
+    assert call(2, FAKE + 4) == -4 and call(10, 16) == -6
+    args = [C.byref(p), B.LVX_BF16] + [FAKE] * 6 + [None, FAKE, FAKE, FAKE, FAKE, 1 << 40, None, 1, FAKE]
+    call = lambda at, x: lib.lvx_xattn_bwd_visit(*(args[:at] + [x] + args[at + 1:]))
+    assert call(1, B.LVX_F32) == -3                              # float32 sums are the result
+    assert call(16, FAKE + 8) == -4                              # dq
+    assert call(9, None) == -1 and call(10, None) == -1 and call(4, None) == -1
+    assert call(13, 16) == -6 and call(9, FAKE + 4) == -4
+
+
 def test_project_errors(lib):
     p = B.lvx_projection()
     p.B, p.S, p.E, p.H, p.D = 1, 100, 256, 2, 128
@@ -268,6 +284,11 @@ def test_binding_refuses_cpu_tensors():
     p = B.make_problem(q, q)
     with pytest.raises(RuntimeError):
         B.lvx_xattn_fwd(p, q, q, q, None, q, torch.zeros(1, 2, 8), torch.zeros(256, dtype=torch.uint8))
+    f = torch.zeros(1, 2, 8, 128)
+    with pytest.raises(RuntimeError):
+        B.lvx_xattn_fwd_merge_last(p, q, q, q, None, f, f[..., 0].contiguous(), q, f)
+    with pytest.raises(RuntimeError):
+        B.lvx_xattn_bwd_visit(p, q, q, q, q, f[..., 0].contiguous(), q, None, f, q, q, f, True)
     from paper_2502_02406_amd.blockloop import BlockLoop
     with pytest.raises(RuntimeError):
         BlockLoop((1, 2, 8, 128), (1, 2, 64, 128), torch.bfloat16)

@@ -139,3 +139,19 @@ def test_results_as_inputs(dtype):
     dq = a.backward(q, k, v, o, lse, do, dk, dv)
     want = [t.clone() for t in (b.backward(q, k, v, o, lse, dq.clone(), dk, dv), dk, dv)]
     assert all(torch.equal(x, y) for x, y in zip((a.backward(q, k, v, o, lse, dq, dk, dv), dk, dv), want))
+
+
+def test_layer_refuses_gradients_that_are_not_laid_out_as_q(lib, monkeypatch):
+    # what RecomputeLayer.backward is handed reaches the library by address: its type, shape and strides are looked at first
+    from paper_2502_02406_amd import blockloop
+    monkeypatch.setattr(B, "lvx_xattn_project", lambda *a, **k: None)
+    monkeypatch.setattr(B, "lvx_xattn_project_bwd", lambda *a, **k: None)
+    layer = blockloop.RecomputeLayer(1, 64, 256, 128, 4, 2, 64, torch.bfloat16, 2, device="cpu")
+    layer.q = Dev(layer.q)
+    x, y, good, lse = torch.zeros(1, 64, 128), torch.zeros(1, 256, 128), torch.zeros((1, 4, 64, 64), dtype=torch.bfloat16), torch.zeros(1, 4, 64)
+    layer.backward(x, y, None, None, good, lse, good)
+    assert [c[0] for c in lib.calls] == ["lvx_xattn_bwd_visit"] * 2
+    for bad in (good.float(), good[:, :, :32], good.transpose(1, 2).contiguous().transpose(1, 2), good[:, :3]):
+        for o, do in ((bad, good), (good, bad)):
+            with pytest.raises(AssertionError):
+                layer.backward(x, y, None, None, o, lse, do)

@@ -82,3 +82,29 @@ def test_results_come_back_as_inputs(dtype):
         want = [t.clone() for t in (loop.backward(*(t.clone() for t in back), dk, dv), dk, dv)]
         loop.dq.copy_(x)
         assert all(torch.equal(a, b) for a, b in zip((loop.backward(*back, dk, dv), dk, dv), want))
+
+
+@pytest.mark.parametrize("D,Hq,Hkv,Sq,Skv,q_chunk,kv_block", [
+    (64, 8, 8, 33 * 256 - 5, 2000, 0, 0),                  # row tiles left whole beside split ones
+    (128, 4, 2, 700, 150, 0, 0), (96, 8, 2, 3, 100, 0, 0), (64, 8, 2, 3, 4000, 0, 0), (128, 4, 2, 100, 50, 0, 0),
+    (64, 4, 2, 500, 640, 64, 128), (64, 4, 2, 500, 320, 24, 64), (96, 4, 2, 500, 8 * 729, 48, 729), (64, 4, 2, 300, 640, 7, 20),
+])
+def test_last_visit_into_q_itself(D, Hq, Hkv, Sq, Skv, q_chunk, kv_block):
+    from paper_2502_02406_amd import binding as L
+    g = torch.Generator(device="cuda").manual_seed(8)
+    q = torch.randn((2, Hq, Sq, D), generator=g, device="cuda").bfloat16()
+    k, v = (torch.randn((2, Hkv, Skv, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+    mask = None
+    if q_chunk:
+        c, f = torch.arange(-(-Sq // q_chunk))[:, None], torch.arange(-(-Skv // kv_block))[None, :]
+        allow = ((f - c) % 3 == 0).to(torch.uint8).cuda()
+        mask = L.make_mask(allow, q_chunk, kv_block)
+    acc0, l0 = torch.randn(q.shape, generator=g, device="cuda"), torch.randn((2, Hq, Sq), generator=g, device="cuda")
+    p = L.make_problem(q, k)
+    ws = torch.empty(L.lvx_xattn_workspace_bytes(p, L.LVX_BF16, L.LVX_WS_FWD_MERGE), dtype=torch.uint8, device="cuda")
+    out = []
+    for o in (torch.full_like(q, float("nan")), q):
+        acc, lse = acc0.clone(), l0.clone()
+        L.lvx_xattn_fwd_merge_last(p, q, k, v, mask, acc, lse, o, ws)
+        out.append((o.clone(), lse))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
