@@ -29,11 +29,12 @@ def _asm(src):
         return open(out).read()
 
 
-def _kernel(asm, pattern):
+def _kernels(asm, pattern):
+    """Every instantiation that the pattern matches."""
     # (up to the end of the function: an early exit may put an s_endpgm ahead of the loops)
-    m = re.search(r"^(_ZN[^\n]*" + pattern + r"[^\n]*):.*?^\.Lfunc_end\d+:", asm, re.S | re.M)
-    assert m, f"kernel {pattern} not found"
-    return m.group(0)
+    found = [m.group(0) for m in re.finditer(r"^(_ZN[^\n]*" + pattern + r"[^\n]*):.*?^\.Lfunc_end\d+:", asm, re.S | re.M)]
+    assert found, f"kernel {pattern} not found"
+    return found
 
 
 def _blocks(body):
@@ -41,8 +42,19 @@ def _blocks(body):
     return re.split(r"^\.LBB\d+_\d+:.*$", body, flags=re.M)
 
 
+def _check_dense_loop(body, loop_mfma):
+    loops = [b for b in _blocks(body) if b.count("v_mfma_f32_32x32x16_bf16") == loop_mfma]
+    assert len(loops) == 1, "steady-state loop not found as one basic block"
+    loop = loops[0]
+    assert "v_accvgpr" not in loop, "an accumulator or operand leaves the accumulation file inside the loop"
+    assert "scratch_" not in loop, "register spill inside the loop"
+    # LDS waits must be exact (no tile copy known to the compiler forces them to zero)
+    waits = re.findall(r"lgkmcnt\((\d+)\)", loop)
+    assert sum(1 for w in waits if w != "0") > len(waits) // 2
+
+
 @pytest.mark.parametrize("src,kernel,loop_mfma", [
-    ("lvx_bwd_dkdv_bf16.hip", "bwd_dkdv_bf16_kernelILi128ELb0ELb0E", 128),   # two steps of 64 per trip
+    ("lvx_bwd_dkdv_bf16.hip", "bwd_dkdv_bf16_kernelILi128ELb0ELb0E", 128),   # two steps of 64 per trip; with and without parts
     ("lvx_bwd_dkdv_bf16.hip", "bwd_dkdv_bf16_kernelILi128ELb0ELb1E", 128),   # the same loop over a list of steps
     ("lvx_bwd_dq_bf16.hip", "bwd_dq_bf16_kernelILi128ELb0ELi0E", 96),        # one tile = two halves of 48
     ("lvx_bwd_dq_bf16.hip", "bwd_dq_bf16_kernelILi128ELb0ELi1E", 96),        # the same loop over a list of tiles
@@ -61,23 +73,16 @@ def _blocks(body):
     ("lvx_bwd_fused_bf16.hip", "bwd_fused_bf16_kernelILi128E", 80),
 ])
 def test_dense_loop_moves_no_accumulator(src, kernel, loop_mfma):
-    body = _kernel(_asm(src), kernel)
-    loops = [b for b in _blocks(body) if b.count("v_mfma_f32_32x32x16_bf16") == loop_mfma]
-    assert len(loops) == 1, "steady-state loop not found as one basic block"
-    loop = loops[0]
-    assert "v_accvgpr" not in loop, "an accumulator or operand leaves the accumulation file inside the loop"
-    assert "scratch_" not in loop, "register spill inside the loop"
-    # LDS waits must be exact (no tile copy known to the compiler forces them to zero)
-    waits = re.findall(r"lgkmcnt\((\d+)\)", loop)
-    assert sum(1 for w in waits if w != "0") > len(waits) // 2
+    for body in _kernels(_asm(src), kernel):
+        _check_dense_loop(body, loop_mfma)
 
 
 def test_general_dkdv_leaves_half_the_accumulation_file():
     asm = _asm("lvx_bwd_dkdv_bf16.hip")
-    body = _kernel(asm, "bwd_dkdv_bf16_kernelILi128ELb1ELb0E")
-    for blk in _blocks(body):
-        if "v_mfma_f32_32x32x16_bf16" in blk:
-            assert "v_accvgpr" not in blk, "accumulator moved next to matrix instructions"
+    for body in _kernels(asm, "bwd_dkdv_bf16_kernelILi128ELb1ELb0E"):
+        for blk in _blocks(body):
+            if "v_mfma_f32_32x32x16_bf16" in blk:
+                assert "v_accvgpr" not in blk, "accumulator moved next to matrix instructions"
     # kernel metadata: ".agpr_count: N" precedes the ".name:" entry of its kernel
     m = re.search(r"\.agpr_count:\s*(\d+)\n(?:(?!\.agpr_count).*\n)*?\s*\.name:\s*\S*bwd_dkdv_bf16_kernelILi128ELb1ELb0E", asm)
     assert m and int(m.group(1)) <= 128
@@ -103,14 +108,14 @@ def test_blocks_with_matrix_instructions_move_no_accumulator(src, kernel):
     their loops are several basic blocks; the rule is then per block: where matrix instructions are
     issued, no accumulator move and no spill.  The moves of the (rare) rescale of O^T sit in
     blocks of their own, behind an explicit wait."""
-    body = _kernel(_asm(src), kernel)
-    n = 0
-    for blk in _blocks(body):
-        if "v_mfma_f32_32x32x16_bf16" in blk:
-            n += 1
-            assert "v_accvgpr" not in blk, "accumulator moved next to matrix instructions"
-            assert "scratch_" not in blk, "register spill next to matrix instructions"
-    assert n > 0
+    for body in _kernels(_asm(src), kernel):
+        n = 0
+        for blk in _blocks(body):
+            if "v_mfma_f32_32x32x16_bf16" in blk:
+                n += 1
+                assert "v_accvgpr" not in blk, "accumulator moved next to matrix instructions"
+                assert "scratch_" not in blk, "register spill next to matrix instructions"
+        assert n > 0
 
 
 def test_fused_backward_accumulators_stay_put():
@@ -118,7 +123,7 @@ def test_fused_backward_accumulators_stay_put():
     S, dP and dQ are matrix instructions the compiler knows.  Wherever a hand-written one is issued,
     no accumulator may move.  (Spills of ordinary registers are the compiler's own business: it knows
     every instruction that wrote them; the steady-state block, checked above, has none.)"""
-    body = _kernel(_asm("lvx_bwd_fused_bf16.hip"), "bwd_fused_bf16_kernelILi128E")
+    (body,) = _kernels(_asm("lvx_bwd_fused_bf16.hip"), "bwd_fused_bf16_kernelILi128E")
     n = 0
     for blk in _blocks(body):
         if re.search(r"v_mfma_f32_32x32x16_bf16 a\[", blk):

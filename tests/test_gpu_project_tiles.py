@@ -38,6 +38,16 @@ def test_parts_of_dw(S, E, H, D):
     check_bwd(x, w, gs, dx, dw, H, "bf16", "parts", cols=cols, rows=rows)
 
 
+@pytest.mark.parametrize("B,S,n_out", [(2, 832, 1), (3, 768, 2), (5, 640, 1), (4, 448, 2)],
+                         ids=["three_parts", "four_parts", "six_parts", "three_parts_of_a_pair_of_outputs"])
+def test_parts_of_dw_that_start_in_a_later_batch(B, S, n_out):
+    # batches of whole pairs of 64 tokens, whose addresses run on from pair to pair
+    rows, cols = _sample(S, n_out * 256)
+    rows[:, 0] = np.arange(len(rows)) % B
+    x, w, gs, dx, dw = run_bwd(B, S, 256, 4, 64, n_out, "bf16", seed=9)
+    check_bwd(x, w, gs, dx, dw, 4, "bf16", "batches", cols=cols, rows=rows)
+
+
 def test_infinity_in_the_last_part_of_dw():
     # An infinite gradient of the last token, which the last of five parts sums: the row of dW it reaches is
     # infinite with x's signs, not NaN, and every other row is finite.

@@ -42,6 +42,10 @@ def _case(B, Hq, Hkv, D, Sq, Skv, n_blocks=1, q_chunk=0, kv_block=0, made_for=0)
     (1, 12, 4, 128, 5600, 2100, 1),                # heads of a group in one list, four K/V heads: two XCDs each
     (1, 3, 3, 96, 90 * 256 + 1, 2048, 1),          # an odd number of heads
     (2, 8, 4, 128, 130, 700, 1),                   # fewer tiles than compute units, three key tiles a part
+    (1, 4, 4, 64, 1024, 4096, 1),                  # 4096 rows of more than four parts, combined a workgroup a row,
+    (1, 4, 4, 128, 1024, 4096, 2),
+    (1, 4, 4, 64, 1025, 4096, 1),                  # ... and four rows more: a thread per 16 bytes
+    (1, 4, 4, 128, 1025, 4096, 2),
 ], ids=lambda s: "x".join(map(str, s)))
 def test_last_round(shape):
     _case(*shape)
