@@ -116,10 +116,10 @@ size_t fwd_merge_ws(const Dims& d, lvx_dtype dtype, int n_split, int whole = 0) 
   return fwd_ws(d, dtype == LVX_F32 ? 2 : n_split, whole);      // (fwd_ws(d, 2) holds more than one partial result)
 }
 int cap_parts(int n, int reserve) { return n < LVX_MAX_PARTS - reserve ? n : LVX_MAX_PARTS - reserve; }
-// How a forward call runs: the KV splits of each launch, whether a media mask makes it two launches,
-// the partial results the combine then reads, the bytes of MaskRows' words the kernel reads, and the
-// workspace it all takes.  The dense kernel leaves the first `whole` row tiles of a K/V head unsplit.  `reserve` parts of the combine are taken already (lvx_xattn_fwd_merge: the
-// running state).
+// How a forward call runs: the KV splits of each launch, whether a media mask makes it two launches, the partial
+// results the combine then reads, the bytes of MaskRows' words the kernel reads, and the workspace it all takes. The
+// dense kernel leaves the first `whole` row tiles of a K/V head unsplit. `reserve` parts of the combine are taken
+// already (lvx_xattn_fwd_merge: the running state).
 struct FwdPlan { int n_split, whole; bool two; int n_parts; size_t rows_bytes, need; };
 FwdPlan fwd_plan_with(const Dims& d, lvx_dtype dtype, const MaskDev& m, int reserve, bool rows, size_t room) {
   const bool masked = m.allow != nullptr, bf16 = dtype == LVX_BF16;
@@ -285,8 +285,9 @@ size_t lvx_xattn_workspace_bytes(const lvx_problem* p, lvx_dtype dtype, int whic
   };
   const auto most = [](size_t x, size_t y) { return x > y ? x : y; };
   const auto dense = [&](int reserve) -> size_t {
-    return dtype == LVX_BF16 && fwd_bf16_dense(d, false) ? most(fwd_plan(d, dtype, make_mask(nullptr), reserve, SIZE_MAX).need,
-                                                                fwd_ws(d, cap_parts(fwd_bf16_coarse_split(d, device_cu_count()), reserve))) : 0;
+    if (dtype != LVX_BF16 || !fwd_bf16_dense(d, false)) return 0;
+    return most(fwd_plan(d, dtype, make_mask(nullptr), reserve, SIZE_MAX).need,
+                fwd_ws(d, cap_parts(fwd_bf16_coarse_split(d, device_cu_count()), reserve)));
   };
   if (which == LVX_WS_FWD) return most(fwd_ws(d, parts(0)) + rows_most, dense(0));
   if (which == LVX_WS_BWD) return bwd_ws_query(d, dtype);

@@ -825,7 +825,8 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   }
   if (PARTS && np > 1) {
     // A part's sums stay float32 and in the order of the registers: a kilobyte per store, nothing to turn around.
-    float* const out = a.kv_sums + ((((long)hw.head * (n_kt - n_whole) + tile - n_whole) * n_part + part) * 2 * NWV + wave) * (32 * KVB * D);
+    float* const out = a.kv_sums + ((((long)hw.head * (n_kt - n_whole) + tile - n_whole) * n_part + part) * 2 * NWV + wave) *
+                                       (32 * KVB * D);
 #pragma unroll
     for (int kb = 0; kb < KVB; ++kb)
 #pragma unroll
@@ -983,8 +984,15 @@ KvPlan dkdv_bf16_plan(const Dims& d, int n_cu, bool masked, long most_sets) {
   const double t_step = d.D == 128 ? 2750. : d.D == 96 ? 2150. : 1550., t_fix = 25e3, t_list = 10e3;
   const double t_sums = 4e3, t_sum = 200. * d.D / 128, t_launch = 9e3;
   if (masked) {
-    // (what the mask shows is not known here: every number of steps from none to all as often as any other, as
-    // under a causal mask; other masks leave more of the chip idle, so a tie goes to the parts)
+    // What the mask shows is not known here: every number of steps from none to all as often as any other, as
+    // under a causal mask, so a tile has half of the steps and half of the parts on average, and the last round is
+    // half full of workgroups that are half done (a quarter of a part).  Other masks leave more of the chip idle, so a
+    // tie goes to the parts: without the tenth in their favour 34 masks of 512 to 131072 keys take 0.6 % more on average (one
+    // frame of 64 keys a chunk, 64 rows x 640 keys, 13.2 -> 15.0 us; nothing is faster by more than 1.3 %).
+    // `len` is shorter than p parts of a full list need, down to 14 steps (about a set-up and a half): lists are
+    // mostly shorter than that, and the tiles that see most then end last by less.  With the length for a full list 0.5 % more on
+    // average, causal 2 x 28 / 4 heads x 1583 rows x 4288 keys 310 -> 338 us and 32 / 8 heads (D = 64) x 2559 x 9088 293 -> 304; no
+    // mask of the 34 is faster by more than 2 % with it.
     const double ts = 1.15 * t_step, tf = t_fix + t_list + t_sums;
     const double whole_t = steps * ts + tf, even_t = (double)tiles / n_cu * (0.5 * steps * ts + tf);
     double best_t = 1.1 * (whole_t > even_t ? whole_t : even_t);

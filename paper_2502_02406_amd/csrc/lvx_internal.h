@@ -51,8 +51,9 @@ struct FwdArgs {
   const void *q, *k, *v;
   void* o;              // final output (Q's strides) when n_split == 1
   int o_is_f32;         // 1: o is float32, 0: o has the input dtype
-  int merge_into;       // 1 (n_split == 1 only): o (float32, CONTIGUOUS [B,Hq,Sq,D]) and lse hold a running
-                        // result; the kernel leaves in them the Rescale of it with this visit's result
+  int merge_into;       // 1: o (float32, CONTIGUOUS [B,Hq,Sq,D]) and lse hold a running result; for rows that are
+                        // not split the kernel leaves in them the Rescale of it with this visit's result (for
+                        // the others the combine does)
   void* o_last;         // with merge_into, or nullptr: the last visit's O goes here (input dtype, Q's strides) instead
   float* lse;           // [B,Hq,Sq]
   int n_split;          // number of KV splits handled by separate workgroups
@@ -227,14 +228,21 @@ inline int pick_split_balanced(long base, int n_cu, long cap, double t_full, dou
   }
   return best;
 }
-// The same for workgroups that take a tile of rows each, n_qt tiles in each of `heads` groups: whole rounds of
-// row tiles are left unsplit, and the tiles of the last round (or of the last two) are split `parts` ways, down to three
-// key tiles a part.  t_tile: one workgroup's time for one of the n_tiles key tiles, t_fix: its set-up and
-// epilogue, t_part: what a set of partial results of one row tile costs, t_join: the launch that combines them.  Splitting every row tile (to 16 key tiles a
-// part at least) sent all rows through memory for the sake of the last round: 32 / 8 heads x 2650 rows x 9447 keys, 336
-// row tiles, forward with its combine 439 -> 428 us, dQ 550 -> 511; and few rows against few keys waited for long
-// parts: 8 heads (D = 64) x 427 rows x 2576 keys forward 36 -> 28, 16 heads x 134 rows x 1024 keys 33 -> 27.
-// Of 31 shapes with 64 to 8192 rows and 1024 to 131072 keys the choice is within 8 % of the best of up to 28 on all but two.
+// The same for workgroups that take a tile of rows each, n_qt tiles in each of `heads` groups: whole rounds of row
+// tiles are left unsplit, and the tiles of the last round (or of the last two) are split `parts` ways, down to three
+// key tiles a part. t_tile: one workgroup's time for one of the n_tiles key tiles, t_fix: its set-up and epilogue,
+// t_part: what a set of partial results of one row tile costs, t_join: the launch that combines them. Splitting every
+// row tile (to 16 key tiles a part at least) sent all rows through memory for the sake of the last round: 32 / 8
+// heads x 2650 rows x 9447 keys, 336 row tiles, forward with its combine 439 -> 428 us, dQ 550 -> 511; and few rows
+// against few keys waited for long parts: 8 heads (D = 64) x 427 rows x 2576 keys forward 36 -> 28, 16 heads x 134
+// rows x 1024 keys 33 -> 27. Of 31 shapes with 64 to 8192 rows and 1024 to 131072 keys the choice is within 8 % of
+// the best of up to 28 on all but two.
+// The model errs by more than its margins (3 % to split at all, 0.5 % for each step to more parts), which were
+// measured all the same: of 12 calls that it splits for a predicted 3 to 8 %, 10 are faster than unsplit ones (by up
+// to 8.9 %, 3.8 % on average over the 12), two slower (by 0.7 %: 28 / 4 heads x 3846 rows x 6912 keys 361 -> 363 and
+// 454 -> 457 us). Steps of 2 % and more only would change 59 calls of over 100 us and make them slower by 0.5 % on
+// average (from 3.8 % slower, 16 heads x 4443 rows x 2048 keys dQ 112 -> 116, to 2.7 % faster, 28 / 4 heads x 960
+// rows x 32768 keys 423 -> 412), and most short ones, by 1 to 5 %.
 struct TailPlan { int whole, parts; };
 inline TailPlan pick_tail(long heads, int n_qt, int n_tiles, int n_cu, long most, double t_tile, double t_fix,
                           double t_part, double t_join) {
@@ -264,14 +272,14 @@ int fwd_bf16_coarse_split(const Dims& d, int n_cu);             // every row til
 bool bwd_dq_bf16_dense(const Dims& d, bool masked);
 TailPlan bwd_dq_bf16_dense_plan(const Dims& d, int n_cu);
 int bwd_dq_bf16_coarse_split(const Dims& d, int n_cu);
-// KV splits of the masked kernels that walk a list of the tiles some row sees (LIST >= 2; each split takes an even share
-// of the list, wherever it ends), for `wgs` row tiles and n_tiles key tiles of which the mask shows any
-// number.  They start longest first, so two rounds of the chip even out lists as uneven
-// as a causal mask's while a workgroup keeps tiles enough to be worth its set-up and list (15 us); else one
-// round, down to three tiles a split.  (Four times the compute units halved, 1024 keys a split at least, before.)
-// Forward and dQ, us: 28 row tiles (D = 128) x 92 key tiles 68 -> 38 and 84 -> 46, 64 x 29 (D = 64) 53 -> 37 and 53 -> 37, 64
-// x 201 88 -> 72 and 109 -> 89; two rounds of long ones: 128 x 2048, causal 457 -> 382 and 581 -> 482 against
-// one round (each chunk one frame: 152 -> 168).  Between one round and one and a half, two splits: 160 x 160 232 -> 202 (three before).
+// KV splits of the masked kernels that walk a list of the tiles some row sees (LIST >= 2; each split takes an even
+// share of the list, wherever it ends), for `wgs` row tiles and n_tiles key tiles of which the mask shows any number.
+// They start longest first, so two rounds of the chip even out lists as uneven as a causal mask's while a workgroup
+// keeps tiles enough to be worth its set-up and list (15 us); else one round, down to three tiles a split. (Four
+// times the compute units halved, 1024 keys a split at least, before.) Forward and dQ, us: 28 row tiles (D = 128) x
+// 92 key tiles 68 -> 38 and 84 -> 46, 64 x 29 (D = 64) 53 -> 37 and 53 -> 37, 64 x 201 88 -> 72 and 109 -> 89; two
+// rounds of long ones: 128 x 2048, causal 457 -> 382 and 581 -> 482 against one round (each chunk one frame: 152 ->
+// 168). Between one round and one and a half, two splits: 160 x 160 232 -> 202 (three before).
 inline int list_split(long wgs, int n_tiles, int n_cu) {
   const long some = 16 * wgs <= 25L * n_cu ? 2 : 1;                // (a round and a half of them)
   const long two = wgs <= n_cu ? 2L * n_cu / wgs : some, one = 2 * wgs <= n_cu ? n_cu / wgs : some;

@@ -1,16 +1,16 @@
 // Masks by words (LIST = 3 of the forward and dQ kernels), row tiles whose blocks of 32 rows see little of what the
-// tile's 256 rows see together: chunks of a few rows that see a frame each.  The dense loop forms 256 x 64
-// scores for every key tile that any row sees; here each wave takes two of the tile's row blocks, one
-// after the other, and streams units of 32 keys of the key blocks that the block sees through LDS stages of its
-// own (lvx_key_units.h), without barriers and without the other waves.  A unit lies in one key block, so the word
-// of (row block, key block) says which rows see it, the same for all of its keys.
+// tile's 256 rows see together: chunks of a few rows that see a frame each. The dense loop forms 256 x 64 scores for
+// every key tile that any row sees; here each wave takes two of the tile's row blocks, one after the other, and
+// streams units of 32 keys of the key blocks that the block sees through LDS stages of its own (lvx_key_units.h),
+// without barriers and without the other waves. A unit lies in one key block, so the word of (row block, key block)
+// says which rows see it, the same for all of its keys.
 //
-// Bound by memory and by the latency of a unit's chain (LDS, 8 or 16 matrix instructions, exponentials), one wave
-// per SIMD with two to four units in flight.  4096 rows x 8 heads (D = 64) in chunks of 2, each seeing one of 2048
-// frames of 64 keys: forward 153 -> 74 us, dQ 165 -> 80 (268 MB of K and V, 52 us at a large copy's rate); 4096
-// x 16 heads in chunks of 32 on frames of 729, 3680 rows x 60507 keys, the step 835 -> 660.  A unit takes about a third of what the dense loop's quarter
-// of a tile (a wave's 64 x 64 scores) does, so a tile is streamed when no wave's two blocks see more (row block, key
-// block) pairs than 0.9 times the key blocks of the tile (mask_streams).
+// Bound by memory and by the latency of a unit's chain (LDS, 8 or 16 matrix instructions, exponentials), one wave per
+// SIMD with two to four units in flight. 4096 rows x 8 heads (D = 64) in chunks of 2, each seeing one of 2048 frames
+// of 64 keys: forward 153 -> 74 us, dQ 165 -> 80 (268 MB of K and V, 52 us at a large copy's rate); 4096 x 16 heads
+// in chunks of 32 on frames of 729, 3680 rows x 60507 keys, the step 835 -> 660. A unit takes about a third of what
+// the dense loop's quarter of a tile (a wave's 64 x 64 scores) does, so a tile is streamed when no wave's two blocks
+// see more (row block, key block) pairs than 0.9 times the key blocks of the tile (mask_streams).
 #pragma once
 #include "lvx_kv_ring.h"
 #include "lvx_key_units.h"
