@@ -103,7 +103,8 @@ __device__ __forceinline__ void div_tokens(int m, int S, float inv_S, int* b, in
 // tile pair lie in one batch (dw_one_batch), so that their rows of G are one stretch and a copy's address is
 // an addition and a minimum per lane.  The general form divides every lane's token by S: about 200 vector instructions, 40 of them
 // multiplications at a quarter of the rate, on top of the 64 matrix instructions of a pair: dW of 32768 tokens x 4096 features x
-// 2048 columns 463 us, 431 without them; 2048 tokens x 4096 x 4096 84 and 77; 131072 x 512 x 1024 142 and 134.
+// 2048 columns 465 us, 434 without them; 2048 tokens x 4096 x 4096 83 and 76; 65536 x 512 x 1536 108 and 104; 131072 x 512 x
+// 1024, bound by what its 32 parts fetch and sum, 130 to 145 and 134 to 138 in four sessions: no difference that shows.
 template <int MODE, int RB, bool GA = true>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 project_bwd_bf16_kernel(ProjBwdArgs a) {
