@@ -173,6 +173,12 @@ size_t bwd_ws_fixed(const Dims& d) {   // delta [B,Hq,Sq] + padded statistics [B
 // The order: statistics, the fused kernel's dQ tiles, locks and error word (`part_at` bytes up to here), the slices.
 struct BwdPlan { TailPlan dq; int list, n_slices; size_t part_at, part, need; };
 size_t bwd_slice_bytes(const Dims& d) { return (size_t)d.B * d.Hq * d.Sq * d.D * sizeof(float); }
+// The first slice of a masked call, which the words may fill: a slice, and where a slice is less than the words may be (one
+// or two heads) the four bytes more that they take for 64 key blocks since they hold counts.
+size_t bwd_words_room(const Dims& d) {
+  const size_t slice = bwd_slice_bytes(d), most = fwd_bf16_rows_bytes_most(d);
+  return slice + (most > slice ? align_up(fwd_bf16_rows_counts_most(d)) : 0);
+}
 bool can_fuse(const Dims& d, lvx_dtype dtype, bool masked) { return dtype == LVX_BF16 && bwd_fused_bf16_supported(d, masked); }
 BwdPlan bwd_plan_with(const Dims& d, lvx_dtype dtype, bool masked, bool fused, bool coarse, int most = LVX_MAX_PARTS) {
   BwdPlan p = {{0, 1}, 1, 0, 0, 0, 0};
@@ -186,6 +192,7 @@ BwdPlan bwd_plan_with(const Dims& d, lvx_dtype dtype, bool masked, bool fused, b
     if (masked) p.list = !coarse ? fwd_list_split(d) : n > 1 ? n / 2 : 1;
     p.n_slices = !masked ? (n > 1 ? n : 0) : n > p.list || coarse ? n : p.list + 1;
     p.part = align_up(p.n_slices * split_rows(d, p.dq.whole) * d.D * sizeof(float));
+    if (masked) p.part += bwd_words_room(d) - bwd_slice_bytes(d);
   }
   p.part_at = bwd_ws_fixed(d) + (fused ? align_up(bwd_fused_ws_bytes(d)) : 0);
   p.need = p.part_at + p.part;
@@ -211,7 +218,7 @@ KvPlan kv_plan(const Dims& d, lvx_dtype dtype, bool masked, size_t room) {
 // The sums lie where the dQ kernel's slices do: they have been added up when that kernel starts.  (Under a mask the
 // first slice holds the words, which dK/dV reads too.)
 size_t bwd_kv_at(const Dims& d, lvx_dtype dtype, bool masked) {
-  return bwd_ws_fixed(d) + (can_fuse(d, dtype, masked) ? align_up(bwd_fused_ws_bytes(d)) : 0) + (masked ? align_up(bwd_slice_bytes(d)) : 0);
+  return bwd_ws_fixed(d) + (can_fuse(d, dtype, masked) ? align_up(bwd_fused_ws_bytes(d)) : 0) + (masked ? bwd_words_room(d) : 0);
 }
 // A call's workspace without room for the sums: the larger of the dense and the masked plans'.
 size_t bwd_ws_base(const Dims& d, lvx_dtype dtype) {
@@ -495,7 +502,7 @@ static lvx_status bwd_visit(const lvx_problem* p, lvx_dtype dtype, const void* q
   a.dq_part = n_slices > 0 ? (float*)at(plan.part_at) : nullptr;
   a.rows = MaskRows{};
   a.rows_ws = mask != nullptr && n_slices > 0 ? at(plan.part_at) : nullptr;
-  a.rows_ws_bytes = bwd_slice_bytes(a.d);
+  a.rows_ws_bytes = bwd_words_room(a.d);
   a.dq_tiles = fused ? (float*)at(bwd_ws_fixed(a.d)) : nullptr;
   a.kv = {0, 1, 0}; a.kv_sums = nullptr; a.kv_counts = nullptr;
   if (!fused) {

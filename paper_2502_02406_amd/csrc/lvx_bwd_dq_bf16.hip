@@ -1049,7 +1049,7 @@ hipError_t launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s) {
     if (a.rows.words != nullptr && bwd_dq_bf16_takes_rows(d, a.mask)) {
       BwdArgs p4 = a;
       p4.dq_pass = 4;
-      p4.dq_part = a.dq_part + (long)d.B * d.Hq * d.Sq * d.D;       // (the first slice holds the words)
+      p4.dq_part = a.dq_part + a.rows_ws_bytes / sizeof(float);       // (the words come first)
       p4.frame_magic = frame_magic_of(a.mask.kv_block);
       p4.n_split_dq = a.dq_list;
       return launch_one(p4, false, s);

@@ -436,7 +436,8 @@ __device__ void bwd_dkdv_f32(const BwdArgs& a, int tile, int hk, int b, char* sm
         gp.x[it] = *(const f32x4*)(gt + r * P + c);
       }
     }
-    const int l31 = lane & 31, rr = min(r0 + l31, rows - 1);   // (32 streamed rows: -L from the first half of the lanes, delta from the other)
+    // (32 streamed rows: -L from the first half of the lanes, delta from the other)
+    const int l31 = lane & 31, rr = min(r0 + l31, rows - 1);
     const float x = lane < 32 ? a.lse[row_b + rr] : a.delta[row_b + rr];
     const bool past = r0 + l31 >= rows;
     sp = lane < 32 ? (x == -INFINITY || past ? -INFINITY : -x) : past ? 0.f : x;

@@ -1011,12 +1011,20 @@ bool fwd_bf16_takes_rows(const Dims& d, const MaskDev& m) {
   return m.allow != nullptr && d.Skv >= TN && (d.Skv + TN - 1) / TN <= KvSmem<128>::WIN_BYTES / 4 - 1 && m.kv_block >= TN &&
          !fwd_bf16_one_pass_fits(d, m);
 }
+static bool rows_most(const Dims& d, MaskDev* m) {
+  if (d.Skv < TN || (d.Skv + TN - 1) / TN > KvSmem<128>::WIN_BYTES / 4 - 1) return false;
+  *m = {};
+  m->kv_block = TN;                                // (the smallest key block it takes, a bitmap per batch)
+  m->stride_b = 1;
+  return true;
+}
 size_t fwd_bf16_rows_bytes_most(const Dims& d) {
-  if (d.Skv < TN || (d.Skv + TN - 1) / TN > KvSmem<128>::WIN_BYTES / 4 - 1) return 0;
-  MaskDev m = {};
-  m.kv_block = TN;                                 // (the smallest key block it takes, a bitmap per batch)
-  m.stride_b = 1;
-  return mask_rows_bytes(d, mask_rows_of(d, m));
+  MaskDev m;
+  return rows_most(d, &m) ? mask_rows_bytes(d, mask_rows_of(d, m)) : 0;
+}
+size_t fwd_bf16_rows_counts_most(const Dims& d) {
+  MaskDev m;
+  return rows_most(d, &m) ? mask_rows_counts_bytes(d, mask_rows_of(d, m)) : 0;
 }
 
 hipError_t launch_fwd_bf16(const FwdArgs& a, hipStream_t s) {

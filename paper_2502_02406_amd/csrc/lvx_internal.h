@@ -292,6 +292,7 @@ bool fwd_bf16_two_pass_fits(const Dims& d, const MaskDev& m);   // a masked forw
 bool fwd_bf16_one_pass_fits(const Dims& d, const MaskDev& m);   // ... or as one launch of the dense kernel over tile lists
 bool fwd_bf16_takes_rows(const Dims& d, const MaskDev& m);      // ... or as one launch of it that masks by MaskRows
 size_t fwd_bf16_rows_bytes_most(const Dims& d);                 // the most those words can take for any mask on this problem
+size_t fwd_bf16_rows_counts_most(const Dims& d);                // ... and their counts of these
 bool fwd_rows_bf16_takes(const Dims& d, bool masked);           // few query rows: a stream from memory
 int fwd_rows_bf16_pick_split(const Dims& d, int n_cu);
 hipError_t launch_fwd_rows_bf16(const FwdArgs& a, hipStream_t s);
@@ -299,6 +300,7 @@ hipError_t launch_fwd_general_bf16(const FwdArgs& a, hipStream_t s);   // masked
 int bwd_bf16_pick_split(const Dims& d, int n_cu, bool masked);
 MaskRows mask_rows_of(const Dims& d, const MaskDev& m);                 // the geometry (no words yet)
 size_t mask_rows_bytes(const Dims& d, const MaskRows& r);
+size_t mask_rows_counts_bytes(const Dims& d, const MaskRows& r);   // ... of which `counts`
 hipError_t launch_mask_rows(const Dims& d, const MaskDev& m, MaskRows* r, void* words, hipStream_t s);
 bool bwd_dq_bf16_takes_rows(const Dims& d, const MaskDev& m);           // the dQ kernel masks by MaskRows
 bool bwd_dkdv_bf16_takes_rows(const Dims& d, const MaskDev& m);         // the dK/dV kernel masks by MaskRows

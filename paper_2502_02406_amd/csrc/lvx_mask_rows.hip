@@ -80,6 +80,10 @@ size_t mask_rows_bytes(const Dims& d, const MaskRows& r) {
   return (size_t)(r.stride_b != 0 ? d.B : 1) * r.n_qt * ((size_t)r.w1 * 32 + (size_t)(r.w1 + FB - 1) / FB * 12);
 }
 
+size_t mask_rows_counts_bytes(const Dims& d, const MaskRows& r) {
+  return (size_t)(r.stride_b != 0 ? d.B : 1) * r.n_qt * ((size_t)(r.w1 + FB - 1) / FB * 4);
+}
+
 hipError_t launch_mask_rows(const Dims& d, const MaskDev& m, MaskRows* r, void* words, hipStream_t s) {
   const dim3 grid((r->w1 + FB - 1) / FB, r->n_qt, r->stride_b != 0 ? d.B : 1);
   r->words = (const unsigned*)words;

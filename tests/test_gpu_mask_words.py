@@ -6,6 +6,7 @@ before (Sq % 32), a last key block of a few keys, rows and keys that pair with n
 batch entry, several heads per K/V head.  Tolerances: those of test_gpu_parity (bf16)."""
 import numpy as np
 import pytest
+import torch
 
 from test_gpu_parity import run_case, small
 
@@ -142,3 +143,39 @@ def test_words_that_do_not_fit_the_workspace(merge):
     assert (o - o2).abs().max() <= 1e-2 and (lse - lse2)[seen].abs().max() <= 1e-3
     with pytest.raises(B.LvxError):
         run(torch.empty(128, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("Hq,Sq,w", [(1, 256, 2036), (1, 256, 2000), (1, 512, 2038), (2, 100, 1000)])
+def test_backward_of_one_head_has_room_for_the_words(Hq, Sq, w):
+    """Key blocks of 64 whose words fill the place of a slice of dQ sums almost, or to the last byte: they are used (the place is
+    written to by a call without the dQ kernel, as the general kernels would not), and the results are right."""
+    from paper_2502_02406_amd import binding as L
+    from paper_2502_02406_amd.blockloop import BlockLoop, MediaMask
+    g = torch.Generator(device="cuda").manual_seed(15)
+    D, Skv = 64, 64 * w
+    q, do = (torch.randn((1, Hq, Sq, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+    k, v = (torch.randn((1, 1, Skv, D), generator=g, device="cuda").bfloat16() for _ in range(2))
+    c, f = torch.arange(-(-Sq // 20))[:, None], torch.arange(w)[None, :]
+    allow = ((f * 7 + c * 3) % 40 == 0).to(torch.uint8).cuda()
+    loop = BlockLoop(tuple(q.shape), tuple(k.shape), torch.bfloat16, 1, MediaMask(allow, 20, 64))
+    o, lse = (t.clone() for t in loop.forward(q, k, v))
+    dk, dv = torch.empty_like(k), torch.empty_like(v)
+    dq = loop.backward(q, k, v, o, lse, do, dk, dv)
+    seen = allow.bool().repeat_interleave(20, 0)[:Sq].repeat_interleave(64, 1)
+    kd, vd = k[0, 0].double(), v[0, 0].double()
+    rk, rv = torch.zeros_like(kd), torch.zeros_like(vd)
+    for h in range(Hq):
+        qd, gd, od = q[0, h].double(), do[0, h].double(), o[0, h].double()
+        p = torch.where(seen, torch.exp(qd @ kd.T * D ** -0.5 - lse[0, h].double()[:, None]), 0.0)
+        ds = p * (gd @ vd.T - (gd * od).sum(-1, keepdim=True))
+        rq = ds @ kd * D ** -0.5
+        rk, rv = rk + ds.T @ qd * D ** -0.5, rv + p.T @ gd
+        assert float((dq[0, h].double() - rq).norm() / rq.norm()) <= 2.0 ** -7.5
+    assert float((dk[0, 0].double() - rk).norm() / rk.norm()) <= 2.0 ** -7.5
+    assert float((dv[0, 0].double() - rv).norm() / rv.norm()) <= 2.0 ** -7.5
+    loop.ws.fill_(0xa5)
+    acc = torch.zeros(q.shape, device="cuda")
+    L.lvx_xattn_bwd(L.make_problem(q, k), q, k, v, o, lse, do, loop._mask_for(0), acc, dk, dv, loop.ws, L.LVX_BWD_DELTA | L.LVX_BWD_DKDV)
+    rows = (Sq + 31) // 32 * 32 * Hq
+    at = -(-Hq * Sq * 4 // 256) * 256 + -(-(rows * 2 + (Hq * 64 if Sq % 32 else 0)) * 4 // 256) * 256
+    assert bool((loop.ws[at:at + 32 * w] != 0xa5).any()), "no words"
