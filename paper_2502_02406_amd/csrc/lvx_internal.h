@@ -13,6 +13,7 @@ struct MaskDev {
   const uint8_t* allow;
   int q_chunk, kv_block, n_q_chunks, n_kv_blocks;
   long stride_b, stride_q;
+  int c0, f0;           // chunk and key block that allow[0] is of: 0, or the first of a window's copy in LDS
 };
 
 // The bitmap regrouped by launch_mask_rows: word ((b, qt, f), rb) holds, for the 32 query rows
@@ -105,7 +106,7 @@ struct BwdArgs {
   int dq_first;         // 1: ... overwritten instead (the first visit)
   void* dq_last;        // or nullptr: the last visit's sum goes here (input dtype, Q's strides) instead
   void *dk, *dv;        // K's strides, input dtype, overwritten
-  float* kv_sums;
+  float* kv_sums;       // workspace, where dq_part is written later (a call's dQ kernel follows)
   int* kv_counts;       // media mask: parts that a tile was cut into, [B Hkv, tiles] (its number of steps is the mask's)
   int n_split_dq;       // KV splits of the dQ kernel
   int dq_whole;         // as FwdArgs::whole

@@ -177,7 +177,7 @@ __device__ inline int list_row_tiles(const MaskRows& rows, int b, int qt, int kv
 // Returns false, having done nothing, when the shapes do not fit (more than 32 chunks per
 // workgroup, window and words beyond win_cap bytes, planes beyond bits_cap bytes: the test is
 // plan_fits below, which the host can evaluate too); on success *mk
-// addresses the LDS copy of the window and *seen_out the per-block words, which is what the loop
+// is the LDS copy of the window and *seen_out the per-block words, which is what the loop
 // probes for mixed tiles: (seen[j / kv_block] >> (i / q_chunk - c0)) & 1 says whether row i sees key j.
 // (h: chunks the rows of a workgroup can touch, w: key blocks, n_tiles: key tiles)
 __host__ __device__ inline bool plan_fits(int h, int w, int n_tiles, int bits_cap, int win_cap) {
@@ -246,7 +246,9 @@ __device__ inline bool plan_masked_tiles(const MaskDev& m, int b, int i_wg0, int
   __syncthreads();
   *seen_out = seen;
   *mk = m;
-  mk->allow = win - ((long)c0 * w);
+  mk->allow = win;
+  mk->c0 = c0;
+  mk->f0 = 0;
   mk->stride_b = 0;
   mk->stride_q = w;
   return true;

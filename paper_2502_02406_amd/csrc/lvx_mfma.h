@@ -181,7 +181,7 @@ __device__ __forceinline__ int mask_rect(const MaskDev& m, int b, int i0, int i1
   bool any = false, all = true;
   for (int c = i0 / m.q_chunk; c <= i1 / m.q_chunk; ++c)
     for (int f = j0 / m.kv_block; f <= j1 / m.kv_block; ++f) {
-      const bool on = base[(long)c * m.stride_q + f] != 0;
+      const bool on = base[(long)(c - m.c0) * m.stride_q + (f - m.f0)] != 0;
       any |= on;
       all &= on;
     }
@@ -203,7 +203,7 @@ __device__ inline int mask_rect_tall(const MaskDev& m, int b, int i0, int i1, in
     for (int c = ca; c <= cb; c += 8) {
       uint8_t v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = base[(long)min(c + u, cb) * m.stride_q + f];
+      for (int u = 0; u < 8; ++u) v[u] = base[(long)(min(c + u, cb) - m.c0) * m.stride_q + (f - m.f0)];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         any |= v[u];
@@ -214,7 +214,7 @@ __device__ inline int mask_rect_tall(const MaskDev& m, int b, int i0, int i1, in
 }
 
 __device__ __forceinline__ bool mask_elem(const MaskDev& m, int b, int i, int j) {
-  return m.allow[b * m.stride_b + (long)(i / m.q_chunk) * m.stride_q + (j / m.kv_block)] != 0;
+  return m.allow[b * m.stride_b + (long)(i / m.q_chunk - m.c0) * m.stride_q + (j / m.kv_block - m.f0)] != 0;
 }
 
 // ---- media mask, staged for a workgroup -----------------------------------------------------
@@ -222,7 +222,7 @@ __device__ __forceinline__ bool mask_elem(const MaskDev& m, int b, int i, int j)
 // once per tile or step.  Two helpers take that off the critical path (every thread of the
 // workgroup, nthreads of them, must call them; both end with a barrier):
 //  * mask_to_lds copies the window [c0, c1] x [f0, f1] of batch b's bitmap into LDS when it fits
-//    in `cap` bytes and returns a MaskDev that addresses the copy (mask_rect / mask_elem work
+//    in `cap` bytes and returns a MaskDev of the copy (mask_rect / mask_elem work
 //    unchanged: the pointer is generic); otherwise it returns the mask as it is.
 //  * build_bits evaluates pred(i), i in [0, n), with all threads at once and leaves bit i in the
 //    word array bits[2 ..] (bits[0] = number of set bits); next_bit then finds the next set bit.
@@ -238,7 +238,12 @@ __device__ inline MaskDev mask_to_lds(const MaskDev& m, int b, int c0, int c1, i
     lds[i] = m.allow[b * m.stride_b + (long)(c0 + i / w) * m.stride_q + f0 + i % w];
   __syncthreads();
   MaskDev r = m;
-  r.allow = lds - ((long)c0 * w + f0);
+  // (the copy itself, and where it starts: a pointer that many bytes before it would be formed in LDS's 32-bit
+  // addresses, wrap there once the window starts further on than the copy lies, and be no address of LDS as
+  // a generic one: a memory fault for 1102 rows in chunks of one against 2640 keys in blocks of 16)
+  r.allow = lds;
+  r.c0 = c0;
+  r.f0 = f0;
   r.stride_b = 0;
   r.stride_q = w;
   return r;
