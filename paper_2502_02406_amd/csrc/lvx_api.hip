@@ -72,11 +72,10 @@ Dims make_dims(const lvx_problem* p) {
 
 MaskDev make_mask(const lvx_mask* m) {
   MaskDev r;
-  if (!m) { r.allow = nullptr; r.q_chunk = r.kv_block = 1; r.n_q_chunks = r.n_kv_blocks = 0; r.stride_b = r.stride_q = 0; r.c0 = r.f0 = 0; return r; }
+  if (!m) { r.allow = nullptr; r.q_chunk = r.kv_block = 1; r.n_q_chunks = r.n_kv_blocks = 0; r.stride_b = r.stride_q = 0; return r; }
   r.allow = m->allow; r.q_chunk = m->q_chunk; r.kv_block = m->kv_block;
   r.n_q_chunks = m->n_q_chunks; r.n_kv_blocks = m->n_kv_blocks;
   r.stride_b = (long)m->stride_b; r.stride_q = (long)m->stride_q;
-  r.c0 = r.f0 = 0;
   return r;
 }
 

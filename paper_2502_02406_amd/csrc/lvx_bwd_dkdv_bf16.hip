@@ -155,7 +155,7 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   const int spH = (d.Sq + KM - 1) / KM;
   const int n_all = G * spH;
   const int j_wg1 = min(d.Skv, j_wg0 + KN) - 1;
-  MaskDev mk = a.mask;
+  MaskWin mk = {a.mask, 0};
   unsigned* const bits = (unsigned*)(smem + SM::RING);
   bool have_bits = false;
   int per_head = spH;

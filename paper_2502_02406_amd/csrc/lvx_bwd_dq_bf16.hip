@@ -320,7 +320,7 @@ bwd_dq_bf16_kernel(BwdArgs a) {
   // visibility of every tile is worked out by all threads at once into a bit array, so that the
   // loop never waits on the bitmap.
   const int i_wg0 = qt * QM, i_wg1 = min(d.Sq, i_wg0 + QM) - 1;
-  MaskDev mk = a.mask;
+  MaskWin mk = {a.mask, 0};
   unsigned* const bits = (unsigned*)(smem + SM::RING);
   bool have_bits = false, have_cls = false;
   const unsigned *cls_any = bits, *cls_all = bits; // this wave's class planes (valid with have_cls)

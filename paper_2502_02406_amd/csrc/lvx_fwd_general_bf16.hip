@@ -148,7 +148,7 @@ fwd_general_bf16_kernel(FwdArgs a) {
   // rows and key range can touch is copied to LDS, and the visibility of every tile is worked out
   // by all threads at once into a bit array, so that the loop never waits on the bitmap.
   const int i_wg0 = qt * BM, i_wg1 = min(d.Sq, i_wg0 + BM) - 1;
-  MaskDev mk = a.mask;
+  MaskWin mk = {a.mask, 0};
   unsigned* const bits = (unsigned*)(smem + SM::RING);
   bool have_bits = false;
   if (mk.allow) {

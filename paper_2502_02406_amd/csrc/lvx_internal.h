@@ -13,7 +13,11 @@ struct MaskDev {
   const uint8_t* allow;
   int q_chunk, kv_block, n_q_chunks, n_kv_blocks;
   long stride_b, stride_q;
-  int c0, f0;           // chunk and key block that allow[0] is of: 0, or the first of a window's copy in LDS
+};
+// A bitmap of which allow[0] is byte `first`: all of it (0), or a window's copy in LDS.  (A type of its own: kernels
+// make it, and with eight bytes more among the arguments a call of 12.24 us took 12.37.)
+struct MaskWin : MaskDev {
+  long first;
 };
 
 // The bitmap regrouped by launch_mask_rows: word ((b, qt, f), rb) holds, for the 32 query rows

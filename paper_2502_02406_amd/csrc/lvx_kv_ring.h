@@ -186,7 +186,7 @@ __host__ __device__ inline bool plan_fits(int h, int w, int n_tiles, int bits_ca
 template <int D>
 __device__ inline bool plan_masked_tiles(const MaskDev& m, int b, int i_wg0, int i_wg1, int Sq, int Skv,
                                          int n_tiles, unsigned* bits, int bits_cap, uint8_t* win,
-                                         int win_cap, int tid, MaskDev* mk, const unsigned** seen_out,
+                                         int win_cap, int tid, MaskWin* mk, const unsigned** seen_out,
                                          bool skip_full = false) {
   const int c0 = i_wg0 / m.q_chunk, h = i_wg1 / m.q_chunk - c0 + 1;
   const int w = (Skv - 1) / m.kv_block + 1;
@@ -245,10 +245,8 @@ __device__ inline bool plan_masked_tiles(const MaskDev& m, int b, int i_wg0, int
   }
   __syncthreads();
   *seen_out = seen;
-  *mk = m;
+  *mk = {m, (long)c0 * w};
   mk->allow = win;
-  mk->c0 = c0;
-  mk->f0 = 0;
   mk->stride_b = 0;
   mk->stride_q = w;
   return true;

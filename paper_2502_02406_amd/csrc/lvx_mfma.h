@@ -175,13 +175,13 @@ __device__ __forceinline__ float xhalf_sum(float x) {
 
 // Media-mask classification of the rectangle query rows [i0, i1] x key rows [j0, j1]:
 // 0 = nothing visible, 1 = everything visible, 2 = mixed.  Wave-uniform arguments.
-__device__ __forceinline__ int mask_rect(const MaskDev& m, int b, int i0, int i1, int j0, int j1) {
+__device__ __forceinline__ int mask_rect(const MaskWin& m, int b, int i0, int i1, int j0, int j1) {
   if (!m.allow) return 1;
-  const uint8_t* base = m.allow + b * m.stride_b;
+  const long at = b * m.stride_b - m.first;
   bool any = false, all = true;
   for (int c = i0 / m.q_chunk; c <= i1 / m.q_chunk; ++c)
     for (int f = j0 / m.kv_block; f <= j1 / m.kv_block; ++f) {
-      const bool on = base[(long)(c - m.c0) * m.stride_q + (f - m.f0)] != 0;
+      const bool on = m.allow[at + (long)c * m.stride_q + f] != 0;
       any |= on;
       all &= on;
     }
@@ -193,9 +193,9 @@ __device__ __forceinline__ int mask_rect(const MaskDev& m, int b, int i0, int i1
 // same probes and the same answer, the bitmap's rows taken eight at a time so that their round
 // trips overlap when the bitmap is in global memory (the rows past the last chunk repeat the last
 // one).
-__device__ inline int mask_rect_tall(const MaskDev& m, int b, int i0, int i1, int j0, int j1) {
+__device__ inline int mask_rect_tall(const MaskWin& m, int b, int i0, int i1, int j0, int j1) {
   if (!m.allow) return 1;
-  const uint8_t* base = m.allow + b * m.stride_b;
+  const long at = b * m.stride_b - m.first;
   const int ca = i0 / m.q_chunk, cb = i1 / m.q_chunk;
   if (cb - ca < 4) return mask_rect(m, b, i0, i1, j0, j1);
   unsigned any = 0, all = 1;
@@ -203,7 +203,7 @@ __device__ inline int mask_rect_tall(const MaskDev& m, int b, int i0, int i1, in
     for (int c = ca; c <= cb; c += 8) {
       uint8_t v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = base[(long)(min(c + u, cb) - m.c0) * m.stride_q + (f - m.f0)];
+      for (int u = 0; u < 8; ++u) v[u] = m.allow[at + (long)min(c + u, cb) * m.stride_q + f];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         any |= v[u];
@@ -213,8 +213,8 @@ __device__ inline int mask_rect_tall(const MaskDev& m, int b, int i0, int i1, in
   return all ? 1 : (any ? 2 : 0);
 }
 
-__device__ __forceinline__ bool mask_elem(const MaskDev& m, int b, int i, int j) {
-  return m.allow[b * m.stride_b + (long)(i / m.q_chunk - m.c0) * m.stride_q + (j / m.kv_block - m.f0)] != 0;
+__device__ __forceinline__ bool mask_elem(const MaskWin& m, int b, int i, int j) {
+  return m.allow[b * m.stride_b - m.first + (long)(i / m.q_chunk) * m.stride_q + j / m.kv_block] != 0;
 }
 
 // ---- media mask, staged for a workgroup -----------------------------------------------------
@@ -222,28 +222,27 @@ __device__ __forceinline__ bool mask_elem(const MaskDev& m, int b, int i, int j)
 // once per tile or step.  Two helpers take that off the critical path (every thread of the
 // workgroup, nthreads of them, must call them; both end with a barrier):
 //  * mask_to_lds copies the window [c0, c1] x [f0, f1] of batch b's bitmap into LDS when it fits
-//    in `cap` bytes and returns a MaskDev of the copy (mask_rect / mask_elem work
+//    in `cap` bytes and returns the copy (mask_rect / mask_elem work
 //    unchanged: the pointer is generic); otherwise it returns the mask as it is.
 //  * build_bits evaluates pred(i), i in [0, n), with all threads at once and leaves bit i in the
 //    word array bits[2 ..] (bits[0] = number of set bits); next_bit then finds the next set bit.
 //  * class_of reads a three-way classification back from two such planes: the query-stationary
 //    kernels keep one pair per wave, so that inside the loop the class of a (wave, tile) pair is
 //    two LDS words away and only mixed tiles ever touch the bitmap.
-__device__ inline MaskDev mask_to_lds(const MaskDev& m, int b, int c0, int c1, int f0, int f1,
+__device__ inline MaskWin mask_to_lds(const MaskDev& m, int b, int c0, int c1, int f0, int f1,
                                       uint8_t* lds, int cap, int tid, int nthreads) {
-  if (!m.allow) return m;
+  MaskWin r = {m, 0};
+  if (!m.allow) return r;
   const int w = f1 - f0 + 1, h = c1 - c0 + 1;
-  if (w <= 0 || h <= 0 || (long)w * h > cap) return m;               // workgroup-uniform
+  if (w <= 0 || h <= 0 || (long)w * h > cap) return r;               // workgroup-uniform
   for (int i = tid; i < w * h; i += nthreads)
     lds[i] = m.allow[b * m.stride_b + (long)(c0 + i / w) * m.stride_q + f0 + i % w];
   __syncthreads();
-  MaskDev r = m;
   // (the copy itself, and where it starts: a pointer that many bytes before it would be formed in LDS's 32-bit
   // addresses, wrap there once the window starts further on than the copy lies, and be no address of LDS as
   // a generic one: a memory fault for 1102 rows in chunks of one against 2640 keys in blocks of 16)
   r.allow = lds;
-  r.c0 = c0;
-  r.f0 = f0;
+  r.first = (long)c0 * w + f0;
   r.stride_b = 0;
   r.stride_q = w;
   return r;
