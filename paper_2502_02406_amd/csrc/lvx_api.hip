@@ -146,8 +146,11 @@ FwdPlan fwd_plan_with(const Dims& d, lvx_dtype dtype, const MaskDev& m, int rese
 FwdPlan fwd_plan(const Dims& d, lvx_dtype dtype, const MaskDev& m, int reserve, size_t room) {
   if (dtype == LVX_BF16 && fwd_bf16_dense(d, m.allow != nullptr)) {
     const auto plan = [&](TailPlan t) -> FwdPlan { return {t.parts, t.whole, false, t.parts, 0, fwd_ws(d, t.parts, t.whole)}; };
-    const FwdPlan f = plan(fwd_bf16_dense_plan(d, device_cu_count(), LVX_MAX_PARTS - reserve));
-    if (f.need <= room) return f;
+    // (parts for every place on the chip, or, where that many do not fit the workspace, for every compute unit)
+    for (int per_cu = fwd_bf16_dense_per_cu(d); per_cu >= 1; --per_cu) {
+      const FwdPlan f = plan(fwd_bf16_dense_plan(d, device_cu_count(), LVX_MAX_PARTS - reserve, per_cu));
+      if (f.need <= room) return f;
+    }
     // (coarse parts, or down to half of them: those of fewer keys or rows may be a few more than a larger problem's)
     const int coarse = cap_parts(fwd_bf16_coarse_split(d, device_cu_count()), reserve);
     int n = coarse;

@@ -31,6 +31,8 @@
 
 #include <type_traits>
 
+#include "lvx_fwd_narrow.h"
+
 namespace lvx {
 
 namespace {
@@ -205,8 +207,13 @@ __device__ __forceinline__ void fwd_mask_stream(const FwdArgs& a, char* smem, in
 // visible pairs); 4096 rows x 8 heads in chunks of 2, each seeing one of 2048 frames of 64 keys, D = 64:
 // 0.80 -> 0.16 ms for 268 MB of K and V, 0.02 of them for the references: every tile is some row's first
 // (such tiles are streamed since: fwd_mask_stream).
+// 64-wide heads, dense: the loop of lvx_fwd_narrow.h, two workgroups on a compute unit (wider heads do not fit half of the
+// registers, and beside the lists of the masked forms two rings do not fit LDS).
+template <int D, int LIST> constexpr bool narrow() { return D == 64 && LIST == 0; }
+constexpr int wg_per_cu(int D) { return D == 64 ? 2 : 1; }
+template <int D, int LIST> constexpr int waves_per_simd() { return narrow<D, LIST>() ? wg_per_cu(D) : 1; }
 template <int D, int LIST = 0>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, LIST>(), waves_per_simd<D, LIST>())))
 fwd_bf16_kernel(FwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   using SM = KvSmem<D>;
@@ -465,6 +472,23 @@ fwd_bf16_kernel(FwdArgs a) {
     l_half[qb] = 0.f;
   }
 
+  // Waits until every matrix instruction issued so far has written its result.  The accumulators
+  // are operands of the statement, so that the compiler cannot read them before it.
+  auto drain_oacc = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      if constexpr (DB == 4)
+        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(oacc[qb][0]), "+a"(oacc[qb][1]), "+a"(oacc[qb][2]), "+a"(oacc[qb][3]));
+      else if constexpr (DB == 3)
+        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(oacc[qb][0]), "+a"(oacc[qb][1]), "+a"(oacc[qb][2]));
+      else
+        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(oacc[qb][0]), "+a"(oacc[qb][1]));
+    }
+  };
+  if constexpr (narrow<D, LIST>()) {
+    fwdnarrow::fwd_narrow_loop<D>(smem, qf, oacc, r, l_run, c2, t_begin, nt, d.Skv % TN != 0 ? n_tiles - 1 : -1,
+                                  n_tiles * TN - d.Skv, LAZY_SUM, lane, tid, issue_part);
+  } else {
   // ---- building blocks, all on one 32-key half hb of the tile at st ---------------------------
   struct FirstK { bf16x8 k; };
   auto first_k = [&](const char* __restrict__ st, int hb) __attribute__((always_inline)) -> bf16x8 {
@@ -504,19 +528,6 @@ fwd_bf16_kernel(FwdArgs a) {
   // matrix instructions into the next phase; everywhere else this wait comes first.
   auto settle_scores = [&](f32x16 (&s)[QB]) __attribute__((always_inline)) {
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" : "+v"(s[0]), "+v"(s[1]));
-  };
-  // Waits until every matrix instruction issued so far has written its result.  The accumulators
-  // are operands of the statement, so that the compiler cannot read them before it.
-  auto drain_oacc = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      if constexpr (DB == 4)
-        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(oacc[qb][0]), "+a"(oacc[qb][1]), "+a"(oacc[qb][2]), "+a"(oacc[qb][3]));
-      else if constexpr (DB == 3)
-        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(oacc[qb][0]), "+a"(oacc[qb][1]), "+a"(oacc[qb][2]));
-      else
-        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(oacc[qb][0]), "+a"(oacc[qb][1]));
-    }
   };
   // Conversion of scores into the P^T operands, element x of a half (x = 0..31: query block
   // qb = x / 16, register v = x % 16): p = exp2(s c2 - r), added to the half's sum and packed in pairs as
@@ -866,6 +877,7 @@ fwd_bf16_kernel(FwdArgs a) {
     shift_e();
   }
 
+  }
   // ---- epilogue: O = acc / l, L = r ln 2 + ln l (the reference is in units of log2).  The last
   // matrix instructions must have retired before their registers are read.
   drain_oacc();
@@ -949,7 +961,7 @@ fwd_bf16_kernel(FwdArgs a) {
 template <int D, int LIST = 0>
 hipError_t launch(const FwdArgs& a, long grid, hipStream_t s) {
   static SmemOnce once;
-  constexpr int lds = LIST == 3 ? mask_words_lds<D>() : KvSmem<D>::TOTAL;
+  constexpr int lds = LIST == 3 ? mask_words_lds<D>() : narrow<D, LIST>() ? KvSmem<D>::RING : KvSmem<D>::TOTAL;
   static_assert(lds <= 160 * 1024, "the layout fits a compute unit");
   const hipError_t e = ensure_dynamic_lds((const void*)fwd_bf16_kernel<D, LIST>, lds, &once);
   if (e != hipSuccess) return e;
@@ -960,11 +972,13 @@ hipError_t launch(const FwdArgs& a, long grid, hipStream_t s) {
 }  // namespace
 
 bool fwd_bf16_dense(const Dims& d, bool masked) { return !masked && d.Skv >= TN && !fwd_rows_bf16_takes(d, masked); }
-TailPlan fwd_bf16_dense_plan(const Dims& d, int n_cu, int most) {
+TailPlan fwd_bf16_dense_plan(const Dims& d, int n_cu, int most, int per_cu) {
   const long n_qt = ((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM;
   const double t_tile = d.D == 128 ? 1.75e-6 : d.D == 96 ? 1.45e-6 : 1.2e-6;
-  return pick_tail((long)d.B * d.Hkv, (int)n_qt, (d.Skv + TN - 1) / TN, n_cu, most, t_tile, 10e-6, 2.0 * QM * d.D * 4.0 / 4.5e12, 5e-6);
+  return pick_tail((long)d.B * d.Hkv, (int)n_qt, (d.Skv + TN - 1) / TN, n_cu, most, t_tile, 10e-6, 2.0 * QM * d.D * 4.0 / 4.5e12, 5e-6,
+                   per_cu == 2 ? 2.0e-6 : 0.);
 }
+int fwd_bf16_dense_per_cu(const Dims& d) { return wg_per_cu(d.D); }
 // Parts of 1024 keys at least, fewer as a rule than the plan's: lvx_xattn_fwd_static's fixed scratch may have room for these only.
 int fwd_bf16_coarse_split(const Dims& d, int n_cu) {
   const long base = (long)d.B * d.Hkv * (((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM), cap = (d.Skv + TN - 1) / TN / 16;

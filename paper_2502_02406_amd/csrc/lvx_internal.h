@@ -248,20 +248,27 @@ inline int pick_split_balanced(long base, int n_cu, long cap, double t_full, dou
 // 454 -> 457 us). Steps of 2 % and more only would change 59 calls of over 100 us and make them slower by 0.5 % on
 // average (from 3.8 % slower, 16 heads x 4443 rows x 2048 keys dQ 112 -> 116, to 2.7 % faster, 28 / 4 heads x 960
 // rows x 32768 keys 423 -> 412), and most short ones, by 1 to 5 %.
+// t_two: a key tile's time where two workgroups share a compute unit, which a last round of up to n_cu workgroups does not
+// (0: one workgroup has it to itself).  Parts beside one whole tile on every compute unit cost it what they slow it by.
 struct TailPlan { int whole, parts; };
 inline TailPlan pick_tail(long heads, int n_qt, int n_tiles, int n_cu, long most, double t_tile, double t_fix,
-                          double t_part, double t_join) {
-  const long tiles = heads * n_qt;
+                          double t_part, double t_join, double t_two = 0.) {
+  const long tiles = heads * n_qt, places = t_two > 0. ? 2L * n_cu : n_cu;
   const auto time = [&](long n, int kt) {          // n workgroups of kt key tiles each
-    return (double)((n + n_cu - 1) / n_cu) * (kt * t_tile + t_fix);
+    const long full = n / places, rest = n % places;
+    const double t_full = kt * (t_two > 0. ? t_two : t_tile) + t_fix;
+    return full * t_full + (rest == 0 ? 0. : t_two > 0. && rest <= n_cu ? kt * t_tile + t_fix : t_full);
   };
   TailPlan best = {0, 1};
   double best_t = time(tiles, n_tiles);
   const long full = tiles / n_cu;
-  for (long k = full; k >= 0 && k >= full - 1; --k) {
+  for (long k = full; k >= 0 && k >= full - (t_two > 0. ? 2 : 1); --k) {
     const long whole = k * n_cu / heads, cut = tiles - heads * whole;
+    const bool beside = t_two > 0. && k % 2 == 1;
     for (long p = 2; p <= most && p <= 64 && 3 * p <= n_tiles; ++p) {
-      const double t = time(heads * whole, n_tiles) + time(cut * p, (int)((n_tiles + p - 1) / p)) + (double)(cut * p) * t_part + t_join;
+      const int kt = (int)((n_tiles + p - 1) / p);
+      const double t_cut = beside ? (double)((cut * p + n_cu - 1) / n_cu) * kt * (t_two - t_tile) : time(cut * p, kt);
+      const double t = time(heads * whole, n_tiles) + t_cut + (double)(cut * p) * t_part + t_join;
       if (t < best_t * (best.parts == 1 ? 0.97 : 0.995)) {
         best_t = t;
         best = {(int)whole, (int)p};
@@ -272,7 +279,8 @@ inline TailPlan pick_tail(long heads, int n_qt, int n_tiles, int n_cu, long most
 }
 // the dense forward and dQ kernels (bf16, no mask): whether they take the problem, and how
 bool fwd_bf16_dense(const Dims& d, bool masked);
-TailPlan fwd_bf16_dense_plan(const Dims& d, int n_cu, int most);
+int fwd_bf16_dense_per_cu(const Dims& d);                         // workgroups of the forward that a compute unit holds
+TailPlan fwd_bf16_dense_plan(const Dims& d, int n_cu, int most, int per_cu);
 int fwd_bf16_coarse_split(const Dims& d, int n_cu);             // every row tile, in a workspace too small for that plan
 bool bwd_dq_bf16_dense(const Dims& d, bool masked);
 TailPlan bwd_dq_bf16_dense_plan(const Dims& d, int n_cu);
