@@ -34,6 +34,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # accumulation registers, including the scores that the vector ALU consumes next.  Its own
 # accumulators are pinned to that file in the source, everything else stays in ordinary registers.
 FILE_FLAGS = {"lvx_bwd_dkdv_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+              # (two or three waves per SIMD: one file of 256 or 168 registers instead of two halves)
+              "lvx_bwd_dkdv_short_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
               # (its contraction phase is one unrolled run of 48 matrix instructions with the vector work
               # of a step between them: larger than what the unroll pragma accepts by default)
               "lvx_bwd_fused_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1",

@@ -1050,13 +1050,17 @@ bool bwd_dkdv_bf16_takes_rows(const Dims& d, const MaskDev& m) {
 hipError_t launch_bwd_dkdv_bf16(const BwdArgs& a, hipStream_t s) {
   const Dims& d = a.d;
   // a mask that only selects whole steps for whole workgroups runs on the dense kernel
-  const bool rows_ok = dkdv_rows_ok(d), steps = dkdv_steps(d, a.mask);
+  const bool rows_ok = dkdv_rows_ok(d), steps = dkdv_steps(d, a.mask), words = a.rows.words != nullptr && bwd_dkdv_bf16_takes_rows(d, a.mask);
+  // tiles of few steps, none of them cut into parts: smaller workgroups that share a compute unit
+  if (rows_ok && a.kv_sums == nullptr && (a.mask.allow == nullptr || steps || words)) {
+    const int mode = a.mask.allow == nullptr ? 0 : steps ? 1 : 2;
+    if (bwd_dkdv_short_takes(d, a.mask, mode)) return launch_bwd_dkdv_short(a, mode, s);
+  }
   static_assert(DkvSmem<64, 2>::KN == DkvSmem<128, 2>::KN && dkdv_step_list_cap<64>() == dkdv_step_list_cap<128>() &&
                 DkvSmem<96, 2>::KN == DkvSmem<128, 2>::KN && dkdv_step_list_cap<96>() == dkdv_step_list_cap<128>(),
                 "the test above is the same for both head dims");
   if (steps) return d.D == 64 ? launch<64, false, true>(a, s) : d.D == 96 ? launch<96, false, true>(a, s) : launch<128, false, true>(a, s);
-  if (a.rows.words != nullptr && bwd_dkdv_bf16_takes_rows(d, a.mask))
-    return d.D == 64 ? launch<64, false, true, true>(a, s) : d.D == 96 ? launch<96, false, true, true>(a, s) : launch<128, false, true, true>(a, s);
+  if (words) return d.D == 64 ? launch<64, false, true, true>(a, s) : d.D == 96 ? launch<96, false, true, true>(a, s) : launch<128, false, true, true>(a, s);
   const bool general = a.mask.allow != nullptr || !rows_ok;
   if (d.D == 64) return general ? launch<64, true>(a, s) : launch<64, false>(a, s);
   if (d.D == 96) return general ? launch<96, true>(a, s) : launch<96, false>(a, s);

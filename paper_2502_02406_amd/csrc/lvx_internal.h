@@ -188,6 +188,9 @@ hipError_t launch_bwd_f32(const BwdArgs& a, unsigned stages, hipStream_t s);   /
 hipError_t launch_fwd_bf16(const FwdArgs& a, hipStream_t s);
 hipError_t launch_bwd_bf16(const BwdArgs& a, unsigned stages, hipStream_t s);
 hipError_t launch_bwd_dkdv_bf16(const BwdArgs& a, hipStream_t s);
+// ... of key tiles of few steps: mode 0 dense, 1 a mask that selects steps, 2 any other, by a.rows
+bool bwd_dkdv_short_takes(const Dims& d, const MaskDev& m, int mode);
+hipError_t launch_bwd_dkdv_short(const BwdArgs& a, int mode, hipStream_t s);
 KvPlan dkdv_bf16_plan(const Dims& d, int n_cu, bool masked, long most_sets);   // with room for that many sets of a tile's sums
 size_t dkdv_bf16_set_bytes(const Dims& d);
 size_t dkdv_bf16_sums_bytes(const Dims& d, const KvPlan& p);     // of BwdArgs::kv_sums (a multiple of 256 bytes),
