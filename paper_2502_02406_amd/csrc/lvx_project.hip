@@ -24,6 +24,7 @@
 // workgroups): 2048 tokens x 4096 features x 4096 columns, 128 tiles of 256 x 256, 87 -> 67 us; 2048
 // tokens x 512 x 1024 19 -> 12.6 us.
 // The epilogue turns the tile around in LDS (rounded to bf16) and writes whole 256-byte rows.
+// More tiles than compute units, of at least 512 features: project_run_bf16_kernel, whose workgroups stay.
 #include "lvx_internal.h"
 #include "lvx_mfma.h"
 #include "lvx_kv_ring.h"
@@ -219,6 +220,256 @@ project_bf16_kernel(ProjArgs a) {
   }
 }
 
+// More 256 x 256 tiles than compute units: a workgroup stays and takes one after the other, as one sequence of tile pairs, and
+// what is left of a tile when its last pair has been multiplied moves into the pairs of the next one.  The accumulators
+// are rounded and packed into 128 ordinary registers between the first matrix instructions of the next tile, and each of
+// its first eight pairs turns 32 tokens x 64 columns around in LDS and writes them, whole lines.  Set-up (7 thousand clocks),
+// epilogue (11 thousand, at the chip's write rate, since all workgroups reach it together) and the change of
+// workgroups were 45 % of a tile with 512 features: 131072 tokens x 512 x 1024 columns 200 -> 162 us by itself, in its place between the
+// gradients 169 -> 161 (133 with nothing written: a write retires in order with the copies of the pair after it, which wait for
+// it); 20000 x 512 x 4096 108 -> 82; x 1024 features 265 -> 225; 32768 x 2048 x 2048 226 -> 216; 32768 x 4096 x 2048, whose
+// tiles are long, 437 -> 442, x 8192 1900 -> 1850.  A tile that ends past the last token, and a workgroup's last one, are written
+// at once; behind its last tile a workgroup copies its last pairs again, so that no pair asks whether there is another.
+constexpr int FB_PITCH = 64 * 2 + 16;                // 32 tokens x 64 columns on their way out, padded rows
+constexpr int FB_WAVE = 32 * FB_PITCH;
+constexpr int RUN_SMEM_B = RING_B + 4 * FB_WAVE;
+constexpr int NFLUSH = 8;                            // pairs that write a part of the tile before
+static_assert(RUN_SMEM_B <= 160 * 1024, "the layout fits a compute unit");
+
+template <int B = 0, class F> __device__ __forceinline__ void each_block(F&& f) {
+  f(std::integral_constant<int, B>{});
+  if constexpr (B < 15) each_block<B + 1>(f);
+}
+
+// PAST: the results are written past the caches.  Outputs that the last-level cache (256 MB) cannot hold beside the tokens push these out
+// of it otherwise (131072 tokens x 512 x 1024, 256 MB of output: 189 -> 162 us; 65536 x 512 x 1536, 192 MB: 109 -> 97; 80000 x
+// 1024 x 1024, 156 MB: 163 -> 145, but 20000 x 512 x 4096 82.5 -> 84.3); smaller ones stay, for whoever reads them next
+// (32768 x 4096 x 2048, 128 MB: no difference).
+template <bool PAST>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+project_run_bf16_kernel(ProjArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  constexpr int TM = 256;
+  const int n_mt = (int)((a.M + TM - 1) / TM), n_nt = a.N / TN, nk = a.E / BK;
+  const long n_pid = tile_grid(n_mt, n_nt);
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, l31 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;           // this wave's 128 tokens / 128 columns of a tile
+  struct Tile { long m0; int n0; bool on; };
+  long pid = blockIdx.x;
+  auto take = [&]() -> Tile {
+    for (; pid < n_pid; pid += gridDim.x) {
+      HeadWork hw;
+      if (!tile_decode(pid, n_mt, n_nt, &hw)) continue;
+      pid += gridDim.x;
+      return {(long)hw.head * TM, hw.item * TN, true};
+    }
+    return {0, 0, false};
+  };
+  Tile cur = take();
+  if (!cur.on) return;
+  Tile nxt = take();
+
+  // ---- copies (see project_bf16_kernel); xp, wp: the next pair of x and of w to copy, of which xk, wk of their tile have gone out
+  const unsigned xrow_b = (unsigned)(a.ldx * 2), wrow_b = (unsigned)(a.E * 2);
+  const unsigned smem_u = lds_base(smem);
+  unsigned xo[8], wo[2];
+  const char *xp, *wp;
+  auto x_tile = [&](const Tile& t) __attribute__((always_inline)) {
+    const long m_last = a.M - 1 - t.m0;
+    int ln = lane;
+    asm volatile("" : "+v"(ln));                     // (worked out again for every tile: its terms, kept, fill the registers)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int r = 64 * wave + 8 * j + (ln >> 3);
+      xo[j] = (unsigned)(r < m_last ? r : (int)m_last) * xrow_b + 16u * (unsigned)((ln & 7) ^ perm_of(8 * j + (ln >> 3)));
+    }
+    xp = (const char*)a.x + t.m0 * (long)xrow_b;
+  };
+  auto w_tile = [&](const Tile& t) __attribute__((always_inline)) { wp = (const char*)a.w + ((long)t.n0 + 64 * wave) * wrow_b; };
+#pragma unroll
+  for (int j = 0; j < 2; ++j) wo[j] = (unsigned)(lane >> 3) * wrow_b + 16u * (unsigned)((lane & 7) ^ perm_of(8 * j + (lane >> 3)));
+  auto issue_x = [&](unsigned slot, int j) __attribute__((always_inline)) { dma16u(xp, xo[j], slot + (unsigned)((64 * wave + 8 * j) * ROWB)); };
+  auto issue_w = [&](unsigned slot, int j) __attribute__((always_inline)) {
+    dma16u(wp + (long)(8 * j) * wrow_b, wo[j & 1], slot + (unsigned)(TILE_B + (64 * wave + 8 * j) * ROWB));
+  };
+
+  int rd[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) rd[q] = l31 * ROWB + 16 * ((2 * q + g) ^ perm_of(l31));
+  const int xbase = wm * 128 * ROWB, wbase = TILE_B + wn * 128 * ROWB;
+  // The accumulators: block (column block j, token block i) is a[16 (4 j + i) ...], by name.  Nothing else may use that file (as
+  // values, the compiler moved some of them through ordinary registers between two tiles, and spilled others for it).
+  asm volatile("" ::: "a0", "a255");
+  unsigned pk[4][4][4][2];                           // the tile before: [token block][column block][four columns]
+  bf16x8 xa[4], wa[4], xb[4], wb[4];                 // operands of even / odd k-steps
+  auto fetch = [&](const char* st, int q, int u, bf16x8 (&xv)[4], bf16x8 (&wv)[4]) __attribute__((always_inline)) {
+    if (u < 4) xv[u] = *(const bf16x8*)(st + xbase + 32 * u * ROWB + rd[q]);
+    else if (u < 8) wv[u - 4] = *(const bf16x8*)(st + wbase + 32 * (u - 4) * ROWB + rd[q]);
+  };
+  auto pack = [&](auto block) __attribute__((always_inline)) {         // rounds a block into pk
+    constexpr int B = decltype(block)::value, j = B / 4, i = B % 4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float y[4];
+      asm volatile("v_accvgpr_read_b32 %0, a[%4]\n\tv_accvgpr_read_b32 %1, a[%5]\n\tv_accvgpr_read_b32 %2, a[%6]\n\tv_accvgpr_read_b32 %3, a[%7]"
+                   : "=v"(y[0]), "=v"(y[1]), "=v"(y[2]), "=v"(y[3])
+                   : "n"(16 * B + 4 * q), "n"(16 * B + 4 * q + 1), "n"(16 * B + 4 * q + 2), "n"(16 * B + 4 * q + 3));
+      pk[i][j][q][0] = pack2_bf16(y[0], y[1]);
+      pk[i][j][q][1] = pack2_bf16(y[2], y[3]);
+      asm volatile("" : "+v"(pk[i][j][q][0]), "+v"(pk[i][j][q][1]));     // (packed here, not where it is written)
+    }
+  };
+  // ---- the way out.  Part e of a tile: token block e / 2, columns 64 (e % 2) .. of the wave's 128.  A lane writes 16 bytes of
+  // rows lane / 8 + 8 it of the block; a tile lies in two batches at most (S >= 256), the second from row `edge` on.
+  char* const fb = smem + RING_B + wave * FB_WAVE;
+  const int row_l = wm * 128 + (lane >> 3);          // this lane's first row of a tile
+  uint16_t* out_p[2];
+  int edge;
+  const long batch2 = (long)(a.H - 1) * a.S * a.D;
+  auto out_tile = [&](const Tile& t) __attribute__((always_inline)) {
+    const int HD = a.H * a.D, nw = t.n0 + wn * 128;
+    const long b0 = t.m0 / a.S, next = (b0 + 1) * a.S - t.m0;
+    edge = next < TM ? (int)next : TM;
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int col = nw % HD + 64 * h + 8 * (ln & 7);
+      out_p[h] = (uint16_t*)a.out[nw / HD] + (long)(col / a.D) * a.S * a.D + col % a.D + (t.m0 + wm * 128 + (ln >> 3)) * a.D + b0 * batch2;
+    }
+  };
+  auto turn = [&](int e, int x) __attribute__((always_inline)) {       // x = 0 .. 7: four columns of one of the two column blocks
+    const int i = e / 2, j = 2 * (e % 2) + x / 4, q = x % 4;
+    *(u32x2*)(fb + l31 * FB_PITCH + (32 * (x / 4) + 8 * q + 4 * g) * 2) = u32x2{pk[i][j][q][0], pk[i][j][q][1]};
+  };
+  auto turned = [&](int it) __attribute__((always_inline)) -> u32x4 { return *(const u32x4*)(fb + (8 * it + (lane >> 3)) * FB_PITCH + (lane & 7) * 16); };
+  auto out_at = [&](int e, int it) __attribute__((always_inline)) -> u32x4* {
+    int r = row_l;
+    asm volatile("" : "+v"(r));                      // (worked out here: kept for all parts, the addresses fill the registers)
+    const int d = 32 * (e / 2) + 8 * it;
+    return (u32x4*)(out_p[e % 2] + d * a.D + (r + d >= edge ? batch2 : 0));
+  };
+
+  auto write = [&](u32x4* to, u32x4 y) __attribute__((always_inline)) {
+    if constexpr (PAST) __builtin_nontemporal_store(y, to);
+    else *to = y;
+  };
+  // the 16 matrix instructions of one k-step; hook(u) is other work issued after instruction u.  FIRST: of a tile (1), behind
+  // another one (2), whose sums are packed on the way: a block's last matrix instruction lies 16 back
+  auto mma16 = [&](auto first, const bf16x8 (&xv)[4], const bf16x8 (&wv)[4], auto&& hook) __attribute__((always_inline)) {
+    constexpr int FIRST = decltype(first)::value;
+    each_block([&](auto block) __attribute__((always_inline)) {
+      constexpr int B = decltype(block)::value;
+      if constexpr (FIRST == 2) pack(block);
+      if constexpr (FIRST != 0)
+        asm volatile("v_mfma_f32_32x32x16_bf16 a[%2:%3], %0, %1, 0" ::"v"(wv[B / 4]), "v"(xv[B % 4]), "n"(16 * B), "n"(16 * B + 15));
+      else
+        asm volatile("v_mfma_f32_32x32x16_bf16 a[%2:%3], %0, %1, a[%2:%3]" ::"v"(wv[B / 4]), "v"(xv[B % 4]), "n"(16 * B), "n"(16 * B + 15));
+      hook(B);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  using I0 = std::integral_constant<int, 0>;
+  int par = 0;                                       // slot of the pair being multiplied
+  bool behind = false;                               // the tile before is still to be written
+  // One pair.  E: the part of the tile before that it writes, or -1.
+  auto pair = [&](auto first, auto part) __attribute__((always_inline)) {
+    constexpr int E = decltype(part)::value;
+    const char* const st = smem + par * SLOT_B;
+    const char* const sn = smem + (par ^ 1) * SLOT_B;
+    const unsigned su = smem_u + (unsigned)(par * SLOT_B), sv = smem_u + (unsigned)((par ^ 1) * SLOT_B);
+    u32x4 y[2];
+    mma16(first, xa, wa, [&](int u) __attribute__((always_inline)) {
+      fetch(st, 1, u, xb, wb);
+      if (u % 2 == 1) issue_w(sv, u / 2);
+    });
+    wp += ROWB;
+    mma16(I0{}, xb, wb, [&](int u) __attribute__((always_inline)) {
+      fetch(st, 2, u, xa, wa);
+      if (E >= 0 && u >= 8) turn(E, u - 8);
+    });
+    mma16(I0{}, xa, wa, [&](int u) __attribute__((always_inline)) {
+      fetch(st, 3, u, xb, wb);
+      if (E >= 0 && u >= 4 && u < 12 && u % 2 == 0) y[u / 2 % 2] = turned((u - 4) / 2);
+      if (E >= 0 && u >= 7 && u < 15 && u % 2 == 1) write(out_at(E, (u - 7) / 2), y[(u - 3) / 2 % 2]);
+    });
+    // The next pair has landed when nothing but what this pair has just written is outstanding, and this wave's last reads of
+    // the pair have returned; behind the barrier that holds for every wave.
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(E >= 0 ? 0x0074 : 0x0070);        // vmcnt(4) or (0), lgkmcnt(0)
+    wg_barrier();
+    mma16(I0{}, xb, wb, [&](int u) __attribute__((always_inline)) {
+      fetch(sn, 0, u, xa, wa);
+      if (u % 2 == 1) issue_x(su, u / 2);
+    });
+    xp += ROWB;
+    par ^= 1;
+  };
+
+  using None = std::integral_constant<int, -1>;
+
+  // ---- pair 0 and the x of pair 1 go out; from then on every pair sends the w of the next one and the x of the one after, the
+  // last two of a tile the next tile's, or this one's again
+  x_tile(cur);
+  w_tile(cur);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) issue_x(smem_u, j);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) issue_w(smem_u, j);
+  xp += ROWB;
+  wp += ROWB;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) issue_x(smem_u + SLOT_B, j);
+  xp += ROWB;
+  wait_vmcnt<8>();
+  wg_barrier();
+#pragma unroll
+  for (int u = 0; u < 8; ++u) fetch(smem, 0, u, xa, wa);
+  for (;;) {
+    if (behind) {
+      pair(std::integral_constant<int, 2>{}, I0{});
+      pair(I0{}, std::integral_constant<int, 1>{});
+      pair(I0{}, std::integral_constant<int, 2>{});
+      pair(I0{}, std::integral_constant<int, 3>{});
+      pair(I0{}, std::integral_constant<int, 4>{});
+      pair(I0{}, std::integral_constant<int, 5>{});
+      for (int P = 6; P < nk - 2; ++P) pair(I0{}, None{});
+      x_tile(nxt.on ? nxt : cur);
+      pair(I0{}, std::integral_constant<int, 6>{});
+      w_tile(nxt.on ? nxt : cur);
+      pair(I0{}, std::integral_constant<int, 7>{});
+    } else {
+      pair(std::integral_constant<int, 1>{}, None{});
+      for (int P = 1; P < nk - 2; ++P) pair(I0{}, None{});
+      x_tile(nxt.on ? nxt : cur);
+      pair(I0{}, None{});
+      w_tile(nxt.on ? nxt : cur);
+      pair(I0{}, None{});
+    }
+    out_tile(cur);
+    behind = nxt.on && cur.m0 + TM <= a.M;
+    if (!behind) {
+      asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");      // (the last matrix instruction has retired)
+      each_block([&](auto block) __attribute__((always_inline)) { pack(block); });
+#pragma unroll
+      for (int e = 0; e < NFLUSH; ++e) {
+#pragma unroll
+        for (int x = 0; x < 8; ++x) turn(e, x);
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+          const u32x4 y = turned(it);
+          if (cur.m0 + row_l + 32 * (e / 2) + 8 * it < a.M) write(out_at(e, it), y);
+        }
+      }
+      if (!nxt.on) break;
+    }
+    cur = nxt;
+    nxt = take();
+  }
+  wait_vmcnt<0>();                                   // (the copies that nobody reads have landed before the LDS is another's)
+}
+
 // float32 tensors: one thread per output element, plain FMA in the order of the definition
 __global__ void __launch_bounds__(256) project_f32_kernel(ProjArgs a) {
   const long idx = (long)blockIdx.x * 256 + threadIdx.x;
@@ -249,6 +500,13 @@ template <int IB> hipError_t launch_tiles(const ProjArgs& a, hipStream_t s) {
   project_bf16_kernel<IB><<<(unsigned)grid, 256, SMEM_B, s>>>(a);
   return hipGetLastError();
 }
+template <bool PAST> hipError_t launch_run(const ProjArgs& a, hipStream_t s) {
+  static SmemOnce once;
+  const hipError_t e = ensure_dynamic_lds((const void*)project_run_bf16_kernel<PAST>, RUN_SMEM_B, &once);
+  if (e != hipSuccess) return e;
+  project_run_bf16_kernel<PAST><<<(unsigned)(a.n_cu / 8 * 8), 256, RUN_SMEM_B, s>>>(a);
+  return hipGetLastError();
+}
 }  // namespace
 
 hipError_t launch_project(const ProjArgs& a, int is_f32, hipStream_t s) {
@@ -258,6 +516,8 @@ hipError_t launch_project(const ProjArgs& a, int is_f32, hipStream_t s) {
     return hipGetLastError();
   }
   const long tiles = (a.M + 255) / 256 * (a.N / TN);
+  const bool past = a.M * a.N * 2 > 144l << 20;
+  if (a.n_cu >= 8 && tiles > a.n_cu / 8 * 8 && a.E >= NFLUSH * BK && a.S >= 256) return past ? launch_run<true>(a, s) : launch_run<false>(a, s);
   return tiles * 4 <= 3L * a.n_cu ? launch_tiles<2>(a, s) : launch_tiles<4>(a, s);
 }
 
