@@ -28,6 +28,7 @@
 #include "lvx_internal.h"
 #include "lvx_mfma.h"
 #include "lvx_kv_ring.h"
+#include "lvx_tile_run.h"
 
 #include <type_traits>
 
@@ -230,16 +231,8 @@ project_bf16_kernel(ProjArgs a) {
 // it); 20000 x 512 x 4096 108 -> 82; x 1024 features 265 -> 225; 32768 x 2048 x 2048 226 -> 216; 32768 x 4096 x 2048, whose
 // tiles are long, 437 -> 442, x 8192 1900 -> 1850.  A tile that ends past the last token, and a workgroup's last one, are written
 // at once; behind its last tile a workgroup copies its last pairs again, so that no pair asks whether there is another.
-constexpr int FB_PITCH = 64 * 2 + 16;                // 32 tokens x 64 columns on their way out, padded rows
-constexpr int FB_WAVE = 32 * FB_PITCH;
-constexpr int RUN_SMEM_B = RING_B + 4 * FB_WAVE;
-constexpr int NFLUSH = 8;                            // pairs that write a part of the tile before
+constexpr int RUN_SMEM_B = RING_B + 4 * tilerun::FB_WAVE;
 static_assert(RUN_SMEM_B <= 160 * 1024, "the layout fits a compute unit");
-
-template <int B = 0, class F> __device__ __forceinline__ void each_block(F&& f) {
-  f(std::integral_constant<int, B>{});
-  if constexpr (B < 15) each_block<B + 1>(f);
-}
 
 // PAST: the results are written past the caches.  Outputs that the last-level cache (256 MB) cannot hold beside the tokens push these out
 // of it otherwise (131072 tokens x 512 x 1024, 256 MB of output: 189 -> 162 us; 65536 x 512 x 1536, 192 MB: 109 -> 97; 80000 x
@@ -249,6 +242,7 @@ template <bool PAST>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 project_run_bf16_kernel(ProjArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
+  using namespace tilerun;
   constexpr int TM = 256;
   const int n_mt = (int)((a.M + TM - 1) / TM), n_nt = a.N / TN, nk = a.E / BK;
   const long n_pid = tile_grid(n_mt, n_nt);
@@ -298,30 +292,14 @@ project_run_bf16_kernel(ProjArgs a) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) rd[q] = l31 * ROWB + 16 * ((2 * q + g) ^ perm_of(l31));
   const int xbase = wm * 128 * ROWB, wbase = TILE_B + wn * 128 * ROWB;
-  // The accumulators: block (column block j, token block i) is a[16 (4 j + i) ...], by name.  Nothing else may use that file (as
-  // values, the compiler moved some of them through ordinary registers between two tiles, and spilled others for it).
-  asm volatile("" ::: "a0", "a255");
-  unsigned pk[4][4][4][2];                           // the tile before: [token block][column block][four columns]
+  claim_accumulators();
+  Packed pk;                                         // the tile before
   bf16x8 xa[4], wa[4], xb[4], wb[4];                 // operands of even / odd k-steps
   auto fetch = [&](const char* st, int q, int u, bf16x8 (&xv)[4], bf16x8 (&wv)[4]) __attribute__((always_inline)) {
     if (u < 4) xv[u] = *(const bf16x8*)(st + xbase + 32 * u * ROWB + rd[q]);
     else if (u < 8) wv[u - 4] = *(const bf16x8*)(st + wbase + 32 * (u - 4) * ROWB + rd[q]);
   };
-  auto pack = [&](auto block) __attribute__((always_inline)) {         // rounds a block into pk
-    constexpr int B = decltype(block)::value, j = B / 4, i = B % 4;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      float y[4];
-      asm volatile("v_accvgpr_read_b32 %0, a[%4]\n\tv_accvgpr_read_b32 %1, a[%5]\n\tv_accvgpr_read_b32 %2, a[%6]\n\tv_accvgpr_read_b32 %3, a[%7]"
-                   : "=v"(y[0]), "=v"(y[1]), "=v"(y[2]), "=v"(y[3])
-                   : "n"(16 * B + 4 * q), "n"(16 * B + 4 * q + 1), "n"(16 * B + 4 * q + 2), "n"(16 * B + 4 * q + 3));
-      pk[i][j][q][0] = pack2_bf16(y[0], y[1]);
-      pk[i][j][q][1] = pack2_bf16(y[2], y[3]);
-      asm volatile("" : "+v"(pk[i][j][q][0]), "+v"(pk[i][j][q][1]));     // (packed here, not where it is written)
-    }
-  };
-  // ---- the way out.  Part e of a tile: token block e / 2, columns 64 (e % 2) .. of the wave's 128.  A lane writes 16 bytes of
-  // rows lane / 8 + 8 it of the block; a tile lies in two batches at most (S >= 256), the second from row `edge` on.
+  // ---- the way out: a tile lies in two batches at most (S >= 256), the second from row `edge` on
   char* const fb = smem + RING_B + wave * FB_WAVE;
   const int row_l = wm * 128 + (lane >> 3);          // this lane's first row of a tile
   uint16_t* out_p[2];
@@ -339,11 +317,6 @@ project_run_bf16_kernel(ProjArgs a) {
       out_p[h] = (uint16_t*)a.out[nw / HD] + (long)(col / a.D) * a.S * a.D + col % a.D + (t.m0 + wm * 128 + (ln >> 3)) * a.D + b0 * batch2;
     }
   };
-  auto turn = [&](int e, int x) __attribute__((always_inline)) {       // x = 0 .. 7: four columns of one of the two column blocks
-    const int i = e / 2, j = 2 * (e % 2) + x / 4, q = x % 4;
-    *(u32x2*)(fb + l31 * FB_PITCH + (32 * (x / 4) + 8 * q + 4 * g) * 2) = u32x2{pk[i][j][q][0], pk[i][j][q][1]};
-  };
-  auto turned = [&](int it) __attribute__((always_inline)) -> u32x4 { return *(const u32x4*)(fb + (8 * it + (lane >> 3)) * FB_PITCH + (lane & 7) * 16); };
   auto out_at = [&](int e, int it) __attribute__((always_inline)) -> u32x4* {
     int r = row_l;
     asm volatile("" : "+v"(r));                      // (worked out here: kept for all parts, the addresses fill the registers)
@@ -361,11 +334,9 @@ project_run_bf16_kernel(ProjArgs a) {
     constexpr int FIRST = decltype(first)::value;
     each_block([&](auto block) __attribute__((always_inline)) {
       constexpr int B = decltype(block)::value;
-      if constexpr (FIRST == 2) pack(block);
-      if constexpr (FIRST != 0)
-        asm volatile("v_mfma_f32_32x32x16_bf16 a[%2:%3], %0, %1, 0" ::"v"(wv[B / 4]), "v"(xv[B % 4]), "n"(16 * B), "n"(16 * B + 15));
-      else
-        asm volatile("v_mfma_f32_32x32x16_bf16 a[%2:%3], %0, %1, a[%2:%3]" ::"v"(wv[B / 4]), "v"(xv[B % 4]), "n"(16 * B), "n"(16 * B + 15));
+      if constexpr (FIRST == 2) pack<B>(pk);
+      if constexpr (FIRST != 0) mfma_start<B>(wv[B / 4], xv[B % 4]);
+      else mfma_add<B>(wv[B / 4], xv[B % 4]);
       hook(B);
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -387,11 +358,11 @@ project_run_bf16_kernel(ProjArgs a) {
     wp += ROWB;
     mma16(I0{}, xb, wb, [&](int u) __attribute__((always_inline)) {
       fetch(st, 2, u, xa, wa);
-      if (E >= 0 && u >= 8) turn(E, u - 8);
+      if (E >= 0 && u >= 8) turn(fb, pk, E, u - 8, lane);
     });
     mma16(I0{}, xa, wa, [&](int u) __attribute__((always_inline)) {
       fetch(st, 3, u, xb, wb);
-      if (E >= 0 && u >= 4 && u < 12 && u % 2 == 0) y[u / 2 % 2] = turned((u - 4) / 2);
+      if (E >= 0 && u >= 4 && u < 12 && u % 2 == 0) y[u / 2 % 2] = turned(fb, (u - 4) / 2, lane);
       if (E >= 0 && u >= 7 && u < 15 && u % 2 == 1) write(out_at(E, (u - 7) / 2), y[(u - 3) / 2 % 2]);
     });
     // The next pair has landed when nothing but what this pair has just written is outstanding, and this wave's last reads of
@@ -451,14 +422,14 @@ project_run_bf16_kernel(ProjArgs a) {
     behind = nxt.on && cur.m0 + TM <= a.M;
     if (!behind) {
       asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");      // (the last matrix instruction has retired)
-      each_block([&](auto block) __attribute__((always_inline)) { pack(block); });
+      each_block([&](auto block) __attribute__((always_inline)) { pack<decltype(block)::value>(pk); });
 #pragma unroll
       for (int e = 0; e < NFLUSH; ++e) {
 #pragma unroll
-        for (int x = 0; x < 8; ++x) turn(e, x);
+        for (int x = 0; x < 8; ++x) turn(fb, pk, e, x, lane);
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
-          const u32x4 y = turned(it);
+          const u32x4 y = turned(fb, it, lane);
           if (cur.m0 + row_l + 32 * (e / 2) + 8 * it < a.M) write(out_at(e, it), y);
         }
       }
@@ -517,7 +488,7 @@ hipError_t launch_project(const ProjArgs& a, int is_f32, hipStream_t s) {
   }
   const long tiles = (a.M + 255) / 256 * (a.N / TN);
   const bool past = a.M * a.N * 2 > 144l << 20;
-  if (a.n_cu >= 8 && tiles > a.n_cu / 8 * 8 && a.E >= NFLUSH * BK && a.S >= 256) return past ? launch_run<true>(a, s) : launch_run<false>(a, s);
+  if (a.n_cu >= 8 && tiles > a.n_cu / 8 * 8 && a.E >= tilerun::NFLUSH * BK && a.S >= 256) return past ? launch_run<true>(a, s) : launch_run<false>(a, s);
   return tiles * 4 <= 3L * a.n_cu ? launch_tiles<2>(a, s) : launch_tiles<4>(a, s);
 }
 

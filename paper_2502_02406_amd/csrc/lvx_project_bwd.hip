@@ -44,6 +44,7 @@
 #include "lvx_internal.h"
 #include "lvx_mfma.h"
 #include "lvx_kv_ring.h"
+#include "lvx_tile_run.h"
 
 #include <type_traits>
 
@@ -597,6 +598,222 @@ __global__ void __launch_bounds__(256) project_bwd_w_plain_kernel(ProjBwdArgs a)
 }  // namespace
 
 namespace {
+// dx with more tiles than compute units: workgroups that stay and write a finished tile during the next one, as
+// project_run_bf16_kernel of lvx_project.hip (the scheme is there), over the tile pairs and operands of MODE 0 above.  Heads are
+// multiples of 64 wide.  PAST: results of more than 96 MB are written past the caches.  Before, staying, and past the caches, us: 131072
+// tokens x 512 features x 1024 columns 172, 156, 141; 131072 x 1024 x 1024 266, 251, 224; 80000 x 1024 x 1024 167, 163, 142; 32768 x 4096
+// x 2048 473, 452, 418; smaller ones 60001 x 1024 x 1024 (117 MB) 125, 108, 107; 18000 x 2048 x 1024 (70 MB) 91, 83, 84.
+constexpr int RUN_SMEM_B = RING_B + 4 * tilerun::FB_WAVE;
+template <bool PAST>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+project_bwd_x_run_bf16_kernel(ProjBwdArgs a) {
+  using namespace tilerun;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int n_rt = (int)((a.M + T - 1) / T), n_ct = a.E / T, nk = a.N / BK;
+  const long n_pid = tile_grid(n_rt, n_ct);
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, l31 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;           // this wave's 128 tokens / 128 columns of a tile
+  struct Tile { long r0; int e0; bool on; };
+  long pid = blockIdx.x;
+  auto take = [&]() -> Tile {
+    for (; pid < n_pid; pid += gridDim.x) {
+      HeadWork hw;
+      if (!tile_decode(pid, n_rt, n_ct, &hw)) continue;
+      pid += gridDim.x;
+      return {(long)hw.head * T, hw.item * T, true};
+    }
+    return {0, 0, false};
+  };
+  Tile cur = take();
+  if (!cur.on) return;
+  Tile nxt = take();
+
+  // ---- copies.  wp: the next pair of w to copy (its rows 64 kt .., columns e0 ..); gp: the next pair of G, which starts at head g_h,
+  // column g_c of output g_o
+  const unsigned wrow_b = (unsigned)(a.E * 2), smem_u = lds_base(smem);
+  const long head_b = (long)a.S * a.D * 2;           // bytes of one head of one batch in g
+  const float inv_S = 1.0f / (float)a.S;
+  unsigned wo[2], g_row[8];
+#pragma unroll
+  for (int par = 0; par < 2; ++par)
+    wo[par] = (unsigned)(lane >> 5) * wrow_b + 16u * (unsigned)((lane & 31) ^ (4 * ((2 * par + (lane >> 5)) & 3)));
+  const char* wp;
+  int g_o, g_h, g_c;
+  auto w_tile = [&](const Tile& t) __attribute__((always_inline)) { wp = (const char*)a.w + ((long)(16 * wave) * a.E + t.e0) * 2; };
+  auto g_tile = [&](const Tile& t) __attribute__((always_inline)) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));                     // (worked out again for every tile: its terms, kept, fill the registers)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const long r = t.r0 + 64 * wave + 8 * j + (ln >> 3);
+      int b, s;
+      div_tokens((int)(r < a.M ? r : a.M - 1), a.S, inv_S, &b, &s);
+      g_row[j] = (unsigned)(((long)b * a.H * a.S + s) * a.D * 2) + 16u * (unsigned)((ln & 7) ^ perm_of(8 * j + (ln >> 3)));
+    }
+    g_o = g_h = g_c = 0;
+  };
+  const char* gp = nullptr;
+  auto g_pair = [&]() __attribute__((always_inline)) {
+    gp = (const char*)a.g[g_o] + (long)g_h * head_b + (long)g_c * 2;
+    g_c += BK;
+    if (g_c == a.D) { g_c = 0; if (++g_h == a.H) { g_h = 0; ++g_o; } }
+  };
+  auto issue_w = [&](unsigned slot, int j) __attribute__((always_inline)) {
+    dma16u(wp + (long)(2 * j) * wrow_b, wo[j & 1], slot + (unsigned)((16 * wave + 2 * j) * KR_ROWB));
+  };
+  auto issue_g = [&](unsigned slot, int j) __attribute__((always_inline)) {
+    dma16u(gp, g_row[j], slot + (unsigned)(TILE_B + (64 * wave + 8 * j) * RK_ROWB));
+  };
+
+  const int j16 = lane & 15, jr = j16 >> 2, tr_col = 32 * ((lane >> 4) & 1) + 8 * (j16 & 3);
+  int ka[4], rk[4];
+#pragma unroll
+  for (int jj = 0; jj < 4; ++jj) ka[jj] = (8 * g + jr) * KR_ROWB + tr_col + 64 * ((4 * wn + jj) ^ jr);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) rk[q] = TILE_B + (wm * 128 + l31) * RK_ROWB + 16 * ((2 * q + g) ^ perm_of(l31));
+  claim_accumulators();
+  Packed pk;                                         // the tile before
+  bf16x8 ga[4], wa[4], gb[4], wb[4];                 // operands of even / odd k-steps
+  auto fetch = [&](const char* st, int q, int u, bf16x8 (&gv)[4], bf16x8 (&wv)[4]) __attribute__((always_inline)) {
+    if (u < 4) {
+      gv[u] = __builtin_bit_cast(bf16x8, *(const u32x4*)(st + rk[q] + 32 * u * RK_ROWB));
+    } else if (u < 8) {
+      // (as an LDS address: from a generic one the compiler forms every row's address by itself, 28 registers of them)
+      typedef __attribute__((address_space(3))) char* LdsBytes;
+      typedef __attribute__((address_space(3))) s16x4* LdsQuad;
+      const LdsBytes p = (LdsBytes)(uintptr_t)(smem_u + (unsigned)(st - smem) + (unsigned)ka[u - 4]);
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsQuad)(p + 16 * q * KR_ROWB));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsQuad)(p + (16 * q + 4) * KR_ROWB));
+      typedef __attribute__((ext_vector_type(8))) short s16x8;
+      const s16x8 r = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      wv[u - 4] = __builtin_bit_cast(bf16x8, r);
+    }
+  };
+  char* const fb = smem + RING_B + wave * FB_WAVE;
+  const int row_l = wm * 128 + (lane >> 3);          // this lane's first row of a tile
+  uint16_t* out_p = nullptr;
+  auto out_tile = [&](const Tile& t) __attribute__((always_inline)) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    out_p = (uint16_t*)a.dx + (t.r0 + wm * 128 + (ln >> 3)) * a.ldx + t.e0 + wn * 128 + 8 * (ln & 7);
+  };
+  auto out_at = [&](int e, int it) __attribute__((always_inline)) -> u32x4* {
+    return (u32x4*)(out_p + (long)(32 * (e / 2) + 8 * it) * a.ldx + 64 * (e % 2));
+  };
+
+  auto write = [&](u32x4* to, u32x4 y) __attribute__((always_inline)) {
+    if constexpr (PAST) __builtin_nontemporal_store(y, to);
+    else *to = y;
+  };
+
+  auto mma16 = [&](auto first, const bf16x8 (&gv)[4], const bf16x8 (&wv)[4], auto&& hook) __attribute__((always_inline)) {
+    constexpr int FIRST = decltype(first)::value;
+    each_block([&](auto block) __attribute__((always_inline)) {
+      constexpr int B = decltype(block)::value;
+      if constexpr (FIRST == 2) pack<B>(pk);
+      if constexpr (FIRST != 0) mfma_start<B>(wv[B / 4], gv[B % 4]);
+      else mfma_add<B>(wv[B / 4], gv[B % 4]);
+      hook(B);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using None = std::integral_constant<int, -1>;
+  int par = 0;                                       // slot of the pair being multiplied
+  // One pair: sends the G of the next one and the w of the one after.  E: the part of the tile before that it writes, or -1.
+  auto pair = [&](auto first, auto part) __attribute__((always_inline)) {
+    constexpr int E = decltype(part)::value;
+    const char* const st = smem + par * SLOT_B;
+    const char* const sn = smem + (par ^ 1) * SLOT_B;
+    const unsigned su = smem_u + (unsigned)(par * SLOT_B), sv = smem_u + (unsigned)((par ^ 1) * SLOT_B);
+    u32x4 y = {};
+    g_pair();
+    mma16(first, ga, wa, [&](int u) __attribute__((always_inline)) {
+      fetch(st, 1, u, gb, wb);
+      if (u % 2 == 1) issue_g(sv, u / 2);
+    });
+    mma16(I0{}, gb, wb, [&](int u) __attribute__((always_inline)) {
+      fetch(st, 2, u, ga, wa);
+      if (E >= 0 && u >= 8) turn(fb, pk, E, u - 8, lane);
+    });
+    mma16(I0{}, ga, wa, [&](int u) __attribute__((always_inline)) {
+      fetch(st, 3, u, gb, wb);
+      if (E >= 0 && u % 4 == 0) y = turned(fb, u / 4, lane);
+      if (E >= 0 && u % 4 == 3) write(out_at(E, u / 4), y);
+    });
+    // The next pair has landed when nothing but what this pair has just written is outstanding, and this wave's last reads of
+    // the pair have returned; behind the barrier that holds for every wave.
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(E >= 0 ? 0x0074 : 0x0070);        // vmcnt(4) or (0), lgkmcnt(0)
+    wg_barrier();
+    mma16(I0{}, gb, wb, [&](int u) __attribute__((always_inline)) {
+      fetch(sn, 0, u, ga, wa);
+      if (u % 2 == 1) issue_w(su, u / 2);
+    });
+    wp += (long)BK * wrow_b;
+    par ^= 1;
+  };
+
+  // ---- pair 0 and the w of pair 1 go out; the last two pairs of a tile send the next tile's, or this one's again
+  g_tile(cur);
+  w_tile(cur);
+  g_pair();
+#pragma unroll
+  for (int j = 0; j < 8; ++j) { issue_w(smem_u, j); issue_g(smem_u, j); }
+  wp += (long)BK * wrow_b;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) issue_w(smem_u + SLOT_B, j);
+  wp += (long)BK * wrow_b;
+  wait_vmcnt<8>();
+  wg_barrier();
+#pragma unroll
+  for (int u = 0; u < 8; ++u) fetch(smem, 0, u, ga, wa);
+  bool behind = false;                               // the tile before is still to be written
+  for (;;) {
+    if (behind) {
+      pair(std::integral_constant<int, 2>{}, I0{});
+      pair(I0{}, std::integral_constant<int, 1>{});
+      pair(I0{}, std::integral_constant<int, 2>{});
+      pair(I0{}, std::integral_constant<int, 3>{});
+      pair(I0{}, std::integral_constant<int, 4>{});
+      pair(I0{}, std::integral_constant<int, 5>{});
+      for (int P = 6; P < nk - 2; ++P) pair(I0{}, None{});
+      w_tile(nxt.on ? nxt : cur);
+      pair(I0{}, std::integral_constant<int, 6>{});
+      g_tile(nxt.on ? nxt : cur);
+      pair(I0{}, std::integral_constant<int, 7>{});
+    } else {
+      pair(std::integral_constant<int, 1>{}, None{});
+      for (int P = 1; P < nk - 2; ++P) pair(I0{}, None{});
+      w_tile(nxt.on ? nxt : cur);
+      pair(I0{}, None{});
+      g_tile(nxt.on ? nxt : cur);
+      pair(I0{}, None{});
+    }
+    out_tile(cur);
+    behind = nxt.on && cur.r0 + T <= a.M;
+    if (!behind) {
+      asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");      // (the last matrix instruction has retired)
+      each_block([&](auto block) __attribute__((always_inline)) { pack<decltype(block)::value>(pk); });
+#pragma unroll
+      for (int e = 0; e < NFLUSH; ++e) {
+#pragma unroll
+        for (int x = 0; x < 8; ++x) turn(fb, pk, e, x, lane);
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+          const u32x4 y = turned(fb, it, lane);
+          if (cur.r0 + row_l + 32 * (e / 2) + 8 * it < a.M) write(out_at(e, it), y);
+        }
+      }
+      if (!nxt.on) break;
+    }
+    cur = nxt;
+    nxt = take();
+  }
+  wait_vmcnt<0>();                                   // (the copies that nobody reads have landed before the LDS is another's)
+}
+
 // what both matrix-core kernels need: 16-byte chunks inside one head, a tile of 256 columns inside
 // one output, tokens countable in a float, and every G offset inside 32 bits
 bool mfma_common(const ProjBwdArgs& a) {
@@ -608,6 +825,13 @@ bool mfma_common(const ProjBwdArgs& a) {
 bool project_bwd_bf16_supported(const ProjBwdArgs& a) { return mfma_common(a); }
 
 namespace {
+template <bool PAST> hipError_t launch_dx_run(const ProjBwdArgs& a, hipStream_t s) {
+  static SmemOnce once;
+  const hipError_t e = ensure_dynamic_lds((const void*)project_bwd_x_run_bf16_kernel<PAST>, RUN_SMEM_B, &once);
+  if (e != hipSuccess) return e;
+  project_bwd_x_run_bf16_kernel<PAST><<<(unsigned)(a.n_cu / 8 * 8), 256, RUN_SMEM_B, s>>>(a);
+  return hipGetLastError();
+}
 template <int RB, bool GA> hipError_t launch_dx(const ProjBwdArgs& a, hipStream_t s) {
   static SmemOnce once;
   const hipError_t e = ensure_dynamic_lds((const void*)project_bwd_bf16_kernel<0, RB, GA>, SMEM_B, &once);
@@ -644,7 +868,9 @@ hipError_t launch_project_bwd(const ProjBwdArgs& a, int is_f32, hipStream_t s) {
   if (mfma_w) {
     if (a.dx && mfma_x) {
       const bool low = (a.M + T - 1) / T * (a.E / T) * 4 <= (long)a.n_cu * 3;      // (as in the forward projection)
-      const hipError_t e = low ? (a.D % BK == 0 ? launch_dx<2, true>(a, s) : launch_dx<2, false>(a, s))
+      const bool run = a.n_cu >= 8 && (a.M + T - 1) / T * (a.E / T) > a.n_cu / 8 * 8 && a.D % BK == 0 && a.N >= tilerun::NFLUSH * BK;
+      const hipError_t e = run ? (a.M * a.E * 2 > 96l << 20 ? launch_dx_run<true>(a, s) : launch_dx_run<false>(a, s))
+                         : low ? (a.D % BK == 0 ? launch_dx<2, true>(a, s) : launch_dx<2, false>(a, s))
                                : (a.D % BK == 0 ? launch_dx<4, true>(a, s) : launch_dx<4, false>(a, s));
       if (e != hipSuccess) return e;
     }

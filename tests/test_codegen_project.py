@@ -1,12 +1,16 @@
-"""The projection kernel whose accumulators are named registers (no GPU needed): nothing but its own statements may touch that
+"""The projection kernels whose accumulators are named registers (no GPU needed): nothing but its own statements may touch that
 file, so the generated code must hold no other move into it and no spill."""
 import re
+
+import pytest
 
 from test_codegen import _asm, _kernels
 
 
-def test_named_accumulators_are_nobody_elses():
-    for body in _kernels(_asm("lvx_project.hip"), "project_run_bf16_kernel"):
+@pytest.mark.parametrize("src,kernel", [("lvx_project.hip", "project_run_bf16_kernel"),
+                                        ("lvx_project_bwd.hip", "project_bwd_x_run_bf16_kernel")])
+def test_named_accumulators_are_nobody_elses(src, kernel):
+    for body in _kernels(_asm(src), kernel):
         assert "v_accvgpr_write" not in body and "v_accvgpr_mov" not in body and "scratch_" not in body
         # every read is one of the 256 of a tile's packing, which stands in the code twice
         assert len(re.findall(r"v_accvgpr_read", body)) == 512

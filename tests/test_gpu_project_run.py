@@ -1,4 +1,4 @@
-"""The projection kernel whose workgroups take several tiles, against float64: more tiles than compute units by a few, twice as
+"""The projection kernels whose workgroups take several tiles, outputs and gradients of the tokens, against float64: more tiles than compute units by a few, twice as
 many and some, a last tile of few tokens (which a workgroup may have to write before it goes on), an odd number of tile
 pairs, eight pairs and nine, tokens in several batches, every head width, results large enough to be written past the
 caches; nothing is written beside the results.  bf16 products are exact in float32, their sum over E terms is off by at most
@@ -40,3 +40,30 @@ def test_runs_of_tiles(B, S, E, H, D, n_out):
                 got = torch.cat([outs[(first + i) // H][b, (first + i) % H, s0:s0 + 20000] for i in range(min(8, n_out * H - first))], 1)
                 over = (got.double() - ref).abs() - (2.0 ** -8 * ref.abs() + 2.0 ** -20 * most)
                 assert float(over.max()) <= 0, f"head {first} batch {b} token {s0}"
+
+
+@pytest.mark.parametrize("B,S,E,H,D,n_out", [
+    (1, 65 * 256, 1024, 4, 64, 2),           # 260 tiles of eight pairs
+    (1, 65 * 256 + 1, 1024, 4, 64, 2),
+    (1, 33 * 256 - 3, 2048, 12, 64, 1),      # twelve pairs, the last tiles short
+    (1, 17 * 256 + 40, 12288, 8, 64, 1),     # 48 column tiles: a workgroup goes on after a short tile
+    (3, 11001, 512, 4, 128, 2),              # batches that end inside tiles
+    (130, 100, 2048, 8, 64, 1),              # several batches a tile
+    (1, 40000, 768, 16, 96, 1),              # (96-wide heads: not by these kernels)
+], ids=lambda x: str(x))
+def test_runs_of_token_gradients(B, S, E, H, D, n_out):
+    from paper_2502_02406_amd import binding as L
+    g = torch.Generator(device="cuda").manual_seed(12)
+    w = (torch.randn((n_out * H * D, E), generator=g, device="cuda") * (H * D) ** -0.5).bfloat16()
+    gr = [torch.randn((B, H, S, D), generator=g, device="cuda").bfloat16() for _ in range(n_out)]
+    guard, n = 4096, B * S * E
+    buf = torch.full((n + 2 * guard,), -7.0, dtype=torch.bfloat16, device="cuda")
+    dx = buf[guard:guard + n].view(B, S, E)
+    L.lvx_xattn_project_bwd(torch.zeros((B, S, E), dtype=torch.bfloat16, device="cuda"), w, gr, dx=dx)
+    assert bool((buf[:guard] == -7.0).all()) and bool((buf[guard + n:] == -7.0).all()), "written beside the result"
+    wd = w.double()
+    for b in range(B):
+        for s0 in range(0, S, 10000):
+            gd = torch.cat([t[b, :, s0:s0 + 10000].permute(1, 0, 2).reshape(-1, H * D) for t in gr], 1).double()
+            over = (dx[b, s0:s0 + 10000].double() - gd @ wd).abs() - (2.0 ** -8 * (gd @ wd).abs() + 2.0 ** -20 * (gd.abs() @ wd.abs()))
+            assert float(over.max()) <= 0, f"batch {b} token {s0}"
