@@ -24,6 +24,8 @@
 // into probabilities; two sets of score registers alternate.
 // The grid is cut along the KV axis (split-KV) when the query block alone cannot fill the chip;
 // partial (O, L) pairs are combined by the merge kernel.
+// Dense problems with 64-wide heads run the loop of lvx_fwd_narrow.h instead: two workgroups on a compute unit, two waves
+// per SIMD.
 #include "lvx_internal.h"
 #include "lvx_mfma.h"
 #include "lvx_kv_ring.h"
