@@ -519,9 +519,11 @@ static lvx_status bwd_visit(const lvx_problem* p, lvx_dtype dtype, const void* q
   a.dq_locks = nullptr; a.dq_err = nullptr; a.dq_stagger = 0;
   hipStream_t s = (hipStream_t)hip_stream;
   hipError_t e = hipSuccess;
-  if (stages & LVX_BWD_DELTA) e = launch_delta(a.d, o, d_o, dtype == LVX_F32, lse, a.delta, a.stats, a.sq_pad, a.stats_ovl, s);
+  const bool kernels = (stages & (LVX_BWD_DKDV | LVX_BWD_DQ)) != 0;
+  // (bf16: launch_bwd_bf16 makes the row statistics, with a mask's words in one launch)
+  if ((stages & LVX_BWD_DELTA) && (dtype == LVX_F32 || !kernels)) e = launch_delta(a.d, o, d_o, dtype == LVX_F32, lse, a.delta, a.stats, a.sq_pad, a.stats_ovl, s);
   if (e != hipSuccess) return LVX_ERR_HIP;
-  if (stages & (LVX_BWD_DKDV | LVX_BWD_DQ))
+  if (kernels)
     e = dtype == LVX_BF16 ? launch_bwd_bf16(a, stages & LVX_BWD_ALL, s) : launch_bwd_f32(a, stages & LVX_BWD_ALL, s);
   return e == hipSuccess ? LVX_OK : LVX_ERR_HIP;
 }

@@ -1073,7 +1073,10 @@ bool bwd_dq_bf16_takes_rows(const Dims& d, const MaskDev& m) { return fwd_bf16_t
 
 hipError_t launch_bwd_bf16(const BwdArgs& a, unsigned stages, hipStream_t s) {
   hipError_t e = hipSuccess;
+  const auto row_stats = [&] { return launch_delta(a.d, a.o, a.d_o, 0, a.lse, a.delta, a.stats, a.sq_pad, a.stats_ovl, s); };
   if ((stages & 6) == 6 && a.dq_tiles != nullptr) {
+    if (stages & 1) e = row_stats();
+    if (e != hipSuccess) return e;
     // One pass over the whole tiles of 256 keys with the fused kernel; the keys that are left go
     // through the two kernels below (dQ is a sum over keys, dK and dV rows are independent).
     e = launch_bwd_fused_bf16(a, s);
@@ -1089,14 +1092,18 @@ hipError_t launch_bwd_bf16(const BwdArgs& a, unsigned stages, hipStream_t s) {
     rest.dq_whole = 0;
     rest.dq_part = nullptr;
     rest.dq_tiles = nullptr;
-    return launch_bwd_bf16(rest, stages, s);
+    return launch_bwd_bf16(rest, stages & ~1u, s);
   }
   BwdArgs m = a;
   if (a.mask.allow != nullptr && (((stages & 2) && bwd_dkdv_bf16_takes_rows(a.d, a.mask)) ||
                                   ((stages & 4) && bwd_dq_bf16_takes_rows(a.d, a.mask)))) {
     m.rows = mask_rows_of(a.d, a.mask);
-    if (a.rows_ws != nullptr && mask_rows_bytes(a.d, m.rows) <= a.rows_ws_bytes) e = launch_mask_rows(a.d, a.mask, &m.rows, a.rows_ws, s);
+    if (a.rows_ws != nullptr && mask_rows_bytes(a.d, m.rows) <= a.rows_ws_bytes) {
+      e = stages & 1 ? launch_mask_rows_delta(a, &m.rows, s) : launch_mask_rows(a.d, a.mask, &m.rows, a.rows_ws, s);
+      stages &= ~1u;
+    }
   }
+  if (e == hipSuccess && (stages & 1)) e = row_stats();
   if (e == hipSuccess && (stages & 2)) e = launch_bwd_dkdv_bf16(m, s);
   if (e == hipSuccess && (stages & 4)) e = launch_bwd_dq_bf16(m, s);
   return e;

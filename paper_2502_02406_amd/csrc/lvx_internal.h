@@ -318,6 +318,7 @@ MaskRows mask_rows_of(const Dims& d, const MaskDev& m);                 // the g
 size_t mask_rows_bytes(const Dims& d, const MaskRows& r);
 size_t mask_rows_counts_bytes(const Dims& d, const MaskRows& r);   // ... of which `counts`
 hipError_t launch_mask_rows(const Dims& d, const MaskDev& m, MaskRows* r, void* words, hipStream_t s);
+hipError_t launch_mask_rows_delta(const BwdArgs& a, MaskRows* r, hipStream_t s);     // ... in a.rows_ws, and launch_delta's work (bf16)
 bool bwd_dq_bf16_takes_rows(const Dims& d, const MaskDev& m);           // the dQ kernel masks by MaskRows
 bool bwd_dkdv_bf16_takes_rows(const Dims& d, const MaskDev& m);         // the dK/dV kernel masks by MaskRows
 // memory-bound helpers
