@@ -28,7 +28,9 @@ template <int D> struct ShortSmem {
   static constexpr int STAT_OFF = ILV_ROWS * P;     // 32 x -L log2(e), then 32 x -delta
   static constexpr int STAGE = STAT_OFF + 256;      // [Q; dO] as one 64-row interleaved tile + statistics
   static constexpr int RING = NSTG * STAGE;
-  static constexpr int TOTAL = 160 * 1024 / wg_per_cu(D) / 256 * 256;
+  // (a few hundred bytes more and 64-wide heads have two workgroups on a compute unit: 16 heads x 65536 keys, 1024 rows, causal 360 -> 336 us with
+  // three, 256 rows of which every key block of 128 in four is seen 196 -> 154)
+  static constexpr int TOTAL = lds_share(wg_per_cu(D));
   static constexpr int LIST_CAP = (TOTAL - RING) / 4 - 1;      // list of steps and words behind it; the length in the last word
   static_assert(NWV * 32 * (D * 2 + 16) <= RING, "the turn-around buffers fit the ring");
   static_assert(RUN >= 64, "a run must hold at least one full copy");
@@ -259,6 +261,7 @@ template <int D, int MODE>
 hipError_t launch(const BwdArgs& a, hipStream_t s) {
   static SmemOnce once;
   constexpr int lds = MODE == 0 ? ShortSmem<D>::RING : ShortSmem<D>::TOTAL;
+  static_assert(lds_holds(wg_per_cu(D), lds), "the workgroups of a compute unit share its LDS");
   const hipError_t e = ensure_dynamic_lds((const void*)bwd_dkdv_short_kernel<D, MODE>, lds, &once);
   if (e != hipSuccess) return e;
   const long grid = xcd_grid(a.d.B * a.d.Hkv, (a.d.Skv + KN - 1) / KN);
@@ -276,7 +279,8 @@ template <int D> hipError_t launch(const BwdArgs& a, int mode, hipStream_t s) {
 // workgroups -> these, us: D = 64, 1 step 124 -> 82, 4 steps 164 -> 123, 16 steps 314 -> 290, 32 steps 521 -> 517, 64 (32 / 8 heads x
 // 512 rows x 65536 keys) 470 -> 494; D = 96, 4 steps 260 -> 193, 16 steps 455 -> 443, 32 steps 730 -> 767; D = 128, 4 steps 321 -> 257,
 // 8 steps 401 -> 366, 12 steps 492 -> 482, 16 steps 575 -> 591.  Under a mask a tile has fewer steps than there are, how many only the
-// device knows: about half under a causal one (16 heads x 65536 keys, 32 steps: D = 64 382 -> 374, D = 96 515 -> 491; D = 128 637 -> 630).
+// device knows: about half under a causal one (16 heads x 65536 keys, 32 steps: D = 64 398 -> 336, D = 96 515 -> 491; D = 128 637 -> 630;
+// 48 steps, D = 64 396 -> 347).
 // And the list of steps, and the words that mode 2 needs, have to fit beside the ring.
 bool bwd_dkdv_short_takes(const Dims& d, const MaskDev& m, int mode) {
   const int spH = (d.Sq + KM - 1) / KM;

@@ -964,7 +964,7 @@ template <int D, int LIST = 0>
 hipError_t launch(const FwdArgs& a, long grid, hipStream_t s) {
   static SmemOnce once;
   constexpr int lds = LIST == 3 ? mask_words_lds<D>() : narrow<D, LIST>() ? KvSmem<D>::RING : KvSmem<D>::TOTAL;
-  static_assert(lds <= 160 * 1024, "the layout fits a compute unit");
+  static_assert(lds_holds(waves_per_simd<D, LIST>(), lds), "the workgroups of a compute unit share its LDS");
   const hipError_t e = ensure_dynamic_lds((const void*)fwd_bf16_kernel<D, LIST>, lds, &once);
   if (e != hipSuccess) return e;
   fwd_bf16_kernel<D, LIST><<<(unsigned)grid, 256, lds, s>>>(a);

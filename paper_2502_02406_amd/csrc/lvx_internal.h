@@ -201,6 +201,11 @@ hipError_t launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s);
 bool bwd_fused_bf16_supported(const Dims& d, bool masked);
 size_t bwd_fused_ws_bytes(const Dims& d);
 hipError_t launch_bwd_fused_bf16(const BwdArgs& a, hipStream_t s);
+// LDS is handed out in pieces of 1280 bytes of a compute unit's 160 KB: 768 workgroups of 53760 bytes run all at once on 256 compute
+// units, of 54272 in two rounds.  What n workgroups may have each, and whether that many fit.
+constexpr int LDS_CU = 160 * 1024, LDS_PIECE = 1280;
+constexpr int lds_share(int n) { return LDS_CU / n / LDS_PIECE * LDS_PIECE; }
+constexpr bool lds_holds(int n, int bytes) { return bytes <= lds_share(n); }
 // Raises a kernel's dynamic LDS limit once per device (the attribute belongs to the device's copy
 // of the kernel).  `done` is the caller's per-kernel table; a race between host threads only
 // repeats a harmless call.
