@@ -307,13 +307,15 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   }
   if ((GENERAL || STEPS) && n == 0) {              // keys that no query sees: dK = dV = 0, nothing to read
     const u32x4 z = {0, 0, 0, 0};
-    for (int c = tid; c < KN * CPR; c += 256) {
-      const int j = j_wg0 + c / CPR, col = (c % CPR) * 8;
-      if (j >= d.Skv) continue;
-      const long off = b * d.kv_sb + hk * d.kv_sh + (long)j * d.kv_ss + col;
-      __builtin_nontemporal_store(z, (u32x4*)((uint16_t*)a.dk + off));
-      __builtin_nontemporal_store(z, (u32x4*)((uint16_t*)a.dv + off));
-    }
+    dkdv_rows(dkdv_past(d.B * d.Hkv, d.Skv, D), [&](auto past) __attribute__((always_inline)) {
+      for (int c = tid; c < KN * CPR; c += 256) {
+        const int j = j_wg0 + c / CPR, col = (c % CPR) * 8;
+        if (j >= d.Skv) continue;
+        const long off = b * d.kv_sb + hk * d.kv_sh + (long)j * d.kv_ss + col;
+        store_dkdv<past.value>((uint16_t*)a.dk + off, z);
+        store_dkdv<past.value>((uint16_t*)a.dv + off, z);
+      }
+    });
     return;
   }
 
@@ -870,19 +872,19 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   constexpr int RPI = 64 / LPR;                    // rows per instruction
   constexpr bool EVEN = 64 % LPR == 0 && (32 * KVB) % RPI == 0;   // else: idle lanes, and a last instruction with fewer rows
   const int rsub = lane / LPR, cb = (lane % LPR) * 16;
+  dkdv_rows(dkdv_past(d.B * d.Hkv, d.Skv, D), [&](auto past) __attribute__((always_inline)) {
 #pragma unroll 4
-  for (int r0 = 0; r0 < 32 * KVB; r0 += RPI) {
-    const int r = r0 + rsub, j = j_wave0 + r;
-    if (!EVEN && (rsub >= RPI || r >= 32 * KVB)) continue;
-    const u32x4 yk = *(const u32x4*)(tk + r * RP + cb);
-    const u32x4 yv = *(const u32x4*)(tv + r * RP + cb);
-    if (j >= d.Skv) continue;
-    const long off = (b * d.kv_sb + hk * d.kv_sh + (long)j * d.kv_ss) * 2 + cb;
-    // (past the caches: K and V, which the dQ kernel reads next, stay in them instead.  8 heads x 131072 keys, D = 64, of which
-    // every row sees 64: the step 353 -> 322 us; 32 heads x 131072 keys, D = 128, three quarters seen by nobody, 1 % of it)
-    __builtin_nontemporal_store(yk, (u32x4*)((char*)a.dk + off));
-    __builtin_nontemporal_store(yv, (u32x4*)((char*)a.dv + off));
-  }
+    for (int r0 = 0; r0 < 32 * KVB; r0 += RPI) {
+      const int r = r0 + rsub, j = j_wave0 + r;
+      if (!EVEN && (rsub >= RPI || r >= 32 * KVB)) continue;
+      const u32x4 yk = *(const u32x4*)(tk + r * RP + cb);
+      const u32x4 yv = *(const u32x4*)(tv + r * RP + cb);
+      if (j >= d.Skv) continue;
+      const long off = (b * d.kv_sb + hk * d.kv_sh + (long)j * d.kv_ss) * 2 + cb;
+      store_dkdv<past.value>((char*)a.dk + off, yk);
+      store_dkdv<past.value>((char*)a.dv + off, yv);
+    }
+  });
 #ifdef LVX_DKDV_PROBE
   wait_vmcnt<0>();
   const unsigned long long stamp3 = __builtin_readcyclecounter();

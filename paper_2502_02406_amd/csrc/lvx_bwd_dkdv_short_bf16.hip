@@ -99,13 +99,15 @@ bwd_dkdv_short_kernel(BwdArgs a) {
   const long kv_head = b * d.kv_sb + hk * d.kv_sh;
   if (MODE != 0 && n == 0) {                       // keys that no query sees: dK = dV = 0, nothing to read
     const u32x4 z = {0, 0, 0, 0};
-    for (int c = tid; c < KN * CPR; c += 256) {
-      const int j = j_wg0 + c / CPR, col = (c % CPR) * 8;
-      if (j >= d.Skv) continue;
-      const long off = kv_head + (long)j * d.kv_ss + col;
-      __builtin_nontemporal_store(z, (u32x4*)((uint16_t*)a.dk + off));
-      __builtin_nontemporal_store(z, (u32x4*)((uint16_t*)a.dv + off));
-    }
+    dkdv_rows(dkdv_past(d.B * d.Hkv, d.Skv, D), [&](auto past) __attribute__((always_inline)) {
+      for (int c = tid; c < KN * CPR; c += 256) {
+        const int j = j_wg0 + c / CPR, col = (c % CPR) * 8;
+        if (j >= d.Skv) continue;
+        const long off = kv_head + (long)j * d.kv_ss + col;
+        store_dkdv<past.value>((uint16_t*)a.dk + off, z);
+        store_dkdv<past.value>((uint16_t*)a.dv + off, z);
+      }
+    });
     return;
   }
 
@@ -247,13 +249,15 @@ bwd_dkdv_short_kernel(BwdArgs a) {
       }
     // (each wave reads back only what it wrote itself: no barrier, the LDS queue keeps the order)
     char* const out = (char*)(which == 0 ? a.dk : a.dv);
+    dkdv_rows(dkdv_past(d.B * d.Hkv, d.Skv, D), [&](auto past) __attribute__((always_inline)) {
 #pragma unroll
-    for (int r0 = 0; r0 < 32; r0 += RPI) {
-      const int r = r0 + rsub, j = j_wave0 + r;
-      if ((64 % LPR != 0 && rsub >= RPI) || r >= 32) continue;
-      const u32x4 y = *(const u32x4*)(buf + r * RP + cb);
-      if (j < d.Skv) __builtin_nontemporal_store(y, (u32x4*)(out + (kv_head + (long)j * d.kv_ss) * 2 + cb));
-    }
+      for (int r0 = 0; r0 < 32; r0 += RPI) {
+        const int r = r0 + rsub, j = j_wave0 + r;
+        if ((64 % LPR != 0 && rsub >= RPI) || r >= 32) continue;
+        const u32x4 y = *(const u32x4*)(buf + r * RP + cb);
+        if (j < d.Skv) store_dkdv<past.value>(out + (kv_head + (long)j * d.kv_ss) * 2 + cb, y);
+      }
+    });
   }
 }
 
