@@ -252,7 +252,8 @@ fwd_bf16_kernel(FwdArgs a) {
     // that share it take them in turn)
     const int whole = PACK ? a.whole : 0, n_cut = per_split - whole;
     HeadWork hw;
-    if (!xcd_decode(blockIdx.x, d.B * d.Hkv, whole + a.n_split * n_cut, &hw, whole > 0)) return;
+    if (narrow<D, LIST>() ? !tail_decode(blockIdx.x, d.B * d.Hkv, whole, a.n_split * n_cut, &hw)
+                          : !xcd_decode(blockIdx.x, d.B * d.Hkv, whole + a.n_split * n_cut, &hw, whole > 0)) return;
     b = hw.head / d.Hkv;
     hk = hw.head % d.Hkv;
     const int cut = max(hw.item - whole, 0);
@@ -1065,7 +1066,8 @@ hipError_t launch_fwd_bf16(const FwdArgs& a, hipStream_t s) {
   if (fwd_rows_bf16_takes(d, a.mask.allow != nullptr)) return launch_fwd_rows_bf16(a, s);
   if (a.mask.allow != nullptr || d.Skv < TN) return launch_fwd_general_bf16(a, s);
   const int n_qt = (int)(((long)(d.Hq / d.Hkv) * d.Sq + QM - 1) / QM);
-  const long grid = xcd_grid(d.B * d.Hkv, a.whole + a.n_split * (n_qt - a.whole));
+  const int heads = d.B * d.Hkv, n_parts = a.n_split * (n_qt - a.whole);
+  const long grid = wg_per_cu(d.D) > 1 ? tail_grid(heads, a.whole, n_parts) : xcd_grid(heads, a.whole + n_parts);
   return d.D == 64 ? launch<64>(a, grid, s) : d.D == 96 ? launch<96>(a, grid, s) : launch<128>(a, grid, s);
 }
 
