@@ -355,7 +355,7 @@ __host__ __device__ __forceinline__ bool xcd_decode(long pid, int n_heads, int i
 // which a compute unit holds two.  Head by head, an XCD with two heads starts parts of the first where whole row tiles of the
 // second belong, and these then share compute units two by two.  64-wide forward, one workgroup a compute unit, two head by head, two in
 // this order, us: 2 x 16 heads x 2805 rows x 7318 keys 262, 240, 177; 2 x 8 x 5404 x 11643 306, 338, 263; 2 x 32 / 8 x 1153 x 5543 137, 157, 122;
-// 44 others the same to 1.5 % or better.  (One workgroup a compute unit, 96- and 128-wide: from 26 % less to 6 % more.)
+// 44 others the same to 2 % or better.  (One workgroup a compute unit, 96- and 128-wide: from 26 % less to 6 % more.)
 __host__ __device__ inline long tail_grid(int n_heads, int n_whole, int n_parts) {
   return xcd_grid(n_heads, n_whole) + xcd_grid(n_heads, n_parts);
 }

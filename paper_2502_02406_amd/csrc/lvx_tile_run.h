@@ -19,7 +19,8 @@ template <int B = 0, class F> __device__ __forceinline__ void each_block(F&& f) 
 }
 
 // The accumulators of a wave's 128 x 128: block B = 4 j + i (column block j, row block i, transposed) is a[16 B ...], by name.
-// Nothing else may use that file (as values, the compiler moved some of them through ordinary registers between two
+// Nothing else may use that file, and the compiler does not know it: the build looks at the code that it made and fails if
+// something does (check_named_accumulators in build.py; as values, the compiler moved some of them through ordinary registers between two
 // tiles, and spilled others for it).
 __device__ __forceinline__ void claim_accumulators() { asm volatile("" ::: "a0", "a255"); }
 template <int B> __device__ __forceinline__ void mfma_start(bf16x8 a, bf16x8 b) {        // block B = a b
