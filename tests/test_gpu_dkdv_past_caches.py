@@ -4,6 +4,8 @@ kernels, dense and under masks, zeros of unseen keys among them; nothing is writ
 import pytest
 import torch
 
+import plans
+
 pytestmark = pytest.mark.gpu
 
 _HEADS = 5
@@ -11,12 +13,15 @@ _AT_MOST = {64: 39321, 96: 26214, 128: 19660}        # keys of five heads in 48 
 
 
 @pytest.mark.parametrize("D", [64, 96, 128])
-@pytest.mark.parametrize("Sq", [40, 1000])           # few steps, and more than the kernel for few takes
+@pytest.mark.parametrize("Sq", [40, 1700])           # few steps, and more than the kernel for few takes
 @pytest.mark.parametrize("q_chunk,kv_block", [(0, 0), (32, 256), (5, 100)], ids=lambda x: str(x))
 def test_same_bits_on_both_sides(D, Sq, q_chunk, kv_block):
     from paper_2502_02406_amd import binding as B
     n = _AT_MOST[D]
     assert _HEADS * n * D * 4 <= 48 << 20 < _HEADS * (n + 1) * D * 4
+    shapes = [(1, _HEADS, _HEADS, Sq, keys, D) for keys in (n, n + 1)]
+    assert len({plans.dkdv_parts(*s, masked=q_chunk > 0) for s in shapes}) == 1
+    assert all(plans.dkdv_is_short(*s, q_chunk=q_chunk, kv_block=kv_block) == (Sq == 40) for s in shapes)
     g = torch.Generator(device="cuda").manual_seed(D + Sq + q_chunk)
     q, o, do = (torch.randn((1, _HEADS, Sq, D), generator=g, device="cuda").mul(0.5).bfloat16() for _ in range(3))
     k, v = (torch.randn((1, _HEADS, n + 2, D), generator=g, device="cuda").mul(0.5).bfloat16() for _ in range(2))

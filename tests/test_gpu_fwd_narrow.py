@@ -5,6 +5,7 @@ tiles.  Tolerances: those of test_gpu_parity (bf16)."""
 import pytest
 import torch
 
+import plans
 from test_gpu_parity import run_case, small
 from test_gpu_tail_split import _case
 
@@ -42,10 +43,20 @@ def test_one_large_score_raises_the_reference(key, row):
     assert float((o[0, 0, row].double() - v[0, 0, key].double()).abs().max()) <= 2.0 ** -7 * float(v[0, 0, key].abs().max())
 
 
-@pytest.mark.parametrize("shape", [
-    (1, 8, 8, 64, 34 * 256 + 3, 700, 1),           # 272 row tiles: a whole one for every compute unit, parts beside them
-    (1, 8, 8, 64, 50 * 256, 2000, 2),              # 400: parts of all
-    (1, 8, 8, 64, 70 * 256 - 1, 1100, 1),          # 560: two for every compute unit, then parts
+@pytest.mark.parametrize("shape,plan", [
+    ((1, 8, 8, 64, 32 * 256 + 3, 900, 1), (32, 5)),             # a whole row tile for every compute unit, parts beside them
+    ((1, 16, 16, 64, 17 * 256 + 3, 1100, 1), (16, 3)),          # ... of two heads on an XCD
+    ((1, 8, 8, 64, 8 * 256, 2000, 2), (0, 4)),                  # parts of all, the second time merged with the running result
+    ((1, 8, 8, 64, 70 * 256 - 1, 1100, 1), (64, 3)),            # two for every compute unit, then parts
+    ((1, 2, 1, 64, 100, 6407, 1), (0, 26)),                     # a last part of one tile, which the tile before overlaps
 ], ids=lambda s: "x".join(map(str, s)))
-def test_parts_beside_whole_row_tiles(shape):
+def test_parts_beside_whole_row_tiles(shape, plan):
+    B, Hq, Hkv, D, Sq, Skv, n_blocks = shape
+    for n in range(n_blocks):                                   # (what the shape is here for)
+        assert plans.fwd_plan(B, Hq, Hkv, Sq, Skv // n_blocks, D, running=n > 0) == plan
     _case(*shape)
+
+
+def test_the_last_part_is_one_ragged_tile():
+    tiles, parts = -(-6407 // 64), 26
+    assert tiles - (parts - 1) * -(-tiles // parts) == 1 and 6407 % 64 != 0
