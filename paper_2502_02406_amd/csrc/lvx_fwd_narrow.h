@@ -28,8 +28,9 @@ __device__ __forceinline__ void mfma_next_aa(f32x16& c, bf16x8 a_acc, bf16x8 b_a
 // fetched into the registers it has just been used from, eight matrix instructions ahead of its next use: 209 registers
 // in all, so that a second workgroup's waves issue while these wait.  8 heads x 4096 rows x 131072 keys: 2.51 -> 1.88
 // million clocks, matrix pipes busy for 42 -> 56 % of them, at a clock that the power limit takes from 2.15 to 1.84
-// GHz: 1158 -> 1040 us (1060 TFLOP/s).  Power is what bounds it now; 64 shapes of 64 to 8192 rows and 1024
-// to 131072 keys take 9 % less on average (24 % less to 5 % more).
+// GHz: 1158 -> 1040 us (1060 TFLOP/s).  Power is what bounds it now; 300 shapes of 64 to 16384 rows and 1024 to 131072 keys, half of
+// them where the plans differ most, take 10 % less on average (33 % less to 9 % more; 11 more than 1 % more: calls of 48 to 82 us, most of them of 20 to
+// 28 row tiles cut into about 500 parts where half as many would do, 4 heads x 1033 rows x 29869 keys 59 -> 65).
 template <int D, class Issue>
 __device__ __forceinline__ void fwd_narrow_loop(char* smem, const bf16x8 (&qf)[QB][D / 16], f32x16 (&o)[QB][D / 32], float (&r)[QB],
                                                 float (&l)[QB], float c2, int t_begin, int nt, int cut_tile, int low,

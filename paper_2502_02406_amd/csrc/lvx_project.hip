@@ -226,10 +226,12 @@ project_bf16_kernel(ProjArgs a) {
 // are rounded and packed into 128 ordinary registers between the first matrix instructions of the next tile, and each of
 // its first eight pairs turns 32 tokens x 64 columns around in LDS and writes them, whole lines.  Set-up (7 thousand clocks),
 // epilogue (11 thousand, at the chip's write rate, since all workgroups reach it together) and the change of
-// workgroups were 45 % of a tile with 512 features: 131072 tokens x 512 x 1024 columns 200 -> 162 us by itself, in its place between the
-// gradients 169 -> 161 (133 with nothing written: a write retires in order with the copies of the pair after it, which wait for
-// it); 20000 x 512 x 4096 108 -> 82; x 1024 features 265 -> 225; 32768 x 2048 x 2048 226 -> 216; 32768 x 4096 x 2048, whose
-// tiles are long, 437 -> 442, x 8192 1900 -> 1850.  A tile that ends past the last token, and a workgroup's last one, are written
+// workgroups were 45 % of a tile with 512 features.  In its place between a pass's other kernels, the two forms switched from pass to pass,
+// events around the call, us: 131072 tokens x 512 x 1024 columns 170 -> 155 (the whole pass with its gradients 458 -> 437; a kernel trace, where no two
+// kernels overlap, has 172 and 173; 133 with nothing written: a write retires in order with the copies of the pair after
+// it, which wait for it); 20000 x 512 x 4096 106 -> 94; 131072 x 1024 x 1024 272 -> 253; 65536 x 512 x 1024 86 -> 87; 32768 x 3072 x 2048 331 ->
+// 325.  Long tiles gain and lose 1 to 2 %, so there is no upper end to the rule: 32768 x 2048 x 2048 226 and 224, x 4096 427 and 424 (back to back
+// 511 and 525), x 8192 815 and 822; 32768 x 4096 x 1024 214 -> 217.  A tile that ends past the last token, and a workgroup's last one, are written
 // at once; behind its last tile a workgroup copies its last pairs again, so that no pair asks whether there is another.
 constexpr int RUN_SMEM_B = RING_B + 4 * tilerun::FB_WAVE;
 static_assert(RUN_SMEM_B <= 160 * 1024, "the layout fits a compute unit");

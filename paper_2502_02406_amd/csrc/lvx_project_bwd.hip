@@ -600,9 +600,11 @@ __global__ void __launch_bounds__(256) project_bwd_w_plain_kernel(ProjBwdArgs a)
 namespace {
 // dx with more tiles than compute units: workgroups that stay and write a finished tile during the next one, as
 // project_run_bf16_kernel of lvx_project.hip (the scheme is there), over the tile pairs and operands of MODE 0 above.  Heads are
-// multiples of 64 wide.  PAST: results of more than 96 MB are written past the caches.  Before, staying, and past the caches, us: 131072
-// tokens x 512 features x 1024 columns 172, 156, 141; 131072 x 1024 x 1024 266, 251, 224; 80000 x 1024 x 1024 167, 163, 142; 32768 x 4096
-// x 2048 473, 452, 418; smaller ones 60001 x 1024 x 1024 (117 MB) 125, 108, 107; 18000 x 2048 x 1024 (70 MB) 91, 83, 84.
+// multiples of 64 wide.  PAST: results of more than 96 MB are written past the caches.  Before, staying, and past the caches, one call after the
+// other, us: 131072 tokens x 512 features x 1024 columns 172, 156, 141; 131072 x 1024 x 1024 266, 251, 224; 80000 x 1024 x 1024 167, 163, 142; 32768 x
+// 4096 x 2048 473, 452, 418; smaller ones 60001 x 1024 x 1024 (117 MB) 125, 108, 107; 18000 x 2048 x 1024 (70 MB) 91, 83, 84.  In its place before dW, the
+// two together, events around the call: 131072 x 512 x 1024 275 -> 265 (kernel trace: dx 144 -> 133), 131072 x 1024 x 1024 521 -> 491, 32768 x 4096 x 2048 886
+// -> 865, x 8192 1874 -> 1802.
 constexpr int RUN_SMEM_B = RING_B + 4 * tilerun::FB_WAVE;
 template <bool PAST>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
