@@ -113,7 +113,8 @@ __device__ unsigned long long dkdv_probe[8];
 // PARTS: key tiles that several workgroups share (see dkdv_bf16_plan).  A variant of its own, since the workgroups that
 // only write zeros are over in a microsecond and notice what it adds to the set-up (16384 workgroups of which 12288
 // write zeros: 927 -> 938 us).
-template <int D, bool GENERAL, bool STEPS = false, bool WORDS = false, bool PARTS = false>
+// PAST: dK and dV are written past the caches (dkdv_past).
+template <int D, bool GENERAL, bool STEPS, bool WORDS, bool PARTS, bool PAST>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 bwd_dkdv_bf16_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -307,15 +308,13 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   }
   if ((GENERAL || STEPS) && n == 0) {              // keys that no query sees: dK = dV = 0, nothing to read
     const u32x4 z = {0, 0, 0, 0};
-    dkdv_rows(dkdv_past(d.B * d.Hkv, d.Skv, D), [&](auto past) __attribute__((always_inline)) {
-      for (int c = tid; c < KN * CPR; c += 256) {
-        const int j = j_wg0 + c / CPR, col = (c % CPR) * 8;
-        if (j >= d.Skv) continue;
-        const long off = b * d.kv_sb + hk * d.kv_sh + (long)j * d.kv_ss + col;
-        store_dkdv<past.value>((uint16_t*)a.dk + off, z);
-        store_dkdv<past.value>((uint16_t*)a.dv + off, z);
-      }
-    });
+    for (int c = tid; c < KN * CPR; c += 256) {
+      const int j = j_wg0 + c / CPR, col = (c % CPR) * 8;
+      if (j >= d.Skv) continue;
+      const long off = b * d.kv_sb + hk * d.kv_sh + (long)j * d.kv_ss + col;
+      store_dkdv<PAST>((uint16_t*)a.dk + off, z);
+      store_dkdv<PAST>((uint16_t*)a.dv + off, z);
+    }
     return;
   }
 
@@ -872,19 +871,17 @@ bwd_dkdv_bf16_kernel(BwdArgs a) {
   constexpr int RPI = 64 / LPR;                    // rows per instruction
   constexpr bool EVEN = 64 % LPR == 0 && (32 * KVB) % RPI == 0;   // else: idle lanes, and a last instruction with fewer rows
   const int rsub = lane / LPR, cb = (lane % LPR) * 16;
-  dkdv_rows(dkdv_past(d.B * d.Hkv, d.Skv, D), [&](auto past) __attribute__((always_inline)) {
 #pragma unroll 4
-    for (int r0 = 0; r0 < 32 * KVB; r0 += RPI) {
-      const int r = r0 + rsub, j = j_wave0 + r;
-      if (!EVEN && (rsub >= RPI || r >= 32 * KVB)) continue;
-      const u32x4 yk = *(const u32x4*)(tk + r * RP + cb);
-      const u32x4 yv = *(const u32x4*)(tv + r * RP + cb);
-      if (j >= d.Skv) continue;
-      const long off = (b * d.kv_sb + hk * d.kv_sh + (long)j * d.kv_ss) * 2 + cb;
-      store_dkdv<past.value>((char*)a.dk + off, yk);
-      store_dkdv<past.value>((char*)a.dv + off, yv);
-    }
-  });
+  for (int r0 = 0; r0 < 32 * KVB; r0 += RPI) {
+    const int r = r0 + rsub, j = j_wave0 + r;
+    if (!EVEN && (rsub >= RPI || r >= 32 * KVB)) continue;
+    const u32x4 yk = *(const u32x4*)(tk + r * RP + cb);
+    const u32x4 yv = *(const u32x4*)(tv + r * RP + cb);
+    if (j >= d.Skv) continue;
+    const long off = (b * d.kv_sb + hk * d.kv_sh + (long)j * d.kv_ss) * 2 + cb;
+    store_dkdv<PAST>((char*)a.dk + off, yk);
+    store_dkdv<PAST>((char*)a.dv + off, yv);
+  }
 #ifdef LVX_DKDV_PROBE
   wait_vmcnt<0>();
   const unsigned long long stamp3 = __builtin_readcyclecounter();
@@ -931,24 +928,25 @@ __global__ void __launch_bounds__(256) dkdv_sum_kernel(BwdArgs a) {
                                                             pack2_bf16(hi[0], hi[1]), pack2_bf16(hi[2], hi[3])};
 }
 
-template <int D, bool GENERAL, bool STEPS, bool WORDS, bool PARTS>
+template <int D, bool GENERAL, bool STEPS, bool WORDS, bool PARTS, bool PAST>
 hipError_t launch_as(const BwdArgs& a, hipStream_t s) {
   using SM = DkvSmem<D, kvb_of(GENERAL)>;
   const int n_kt = (a.d.Skv + SM::KN - 1) / SM::KN, n_cut = PARTS ? n_kt - a.kv.whole : 0;
   const long grid = xcd_grid(a.d.B * a.d.Hkv, n_kt - n_cut + n_cut * a.kv.parts);
   static SmemOnce once;
   constexpr int lds = WORDS ? SM::TOTAL_WORDS : SM::TOTAL;
-  hipError_t e = ensure_dynamic_lds((const void*)bwd_dkdv_bf16_kernel<D, GENERAL, STEPS, WORDS, PARTS>, lds, &once);
+  hipError_t e = ensure_dynamic_lds((const void*)bwd_dkdv_bf16_kernel<D, GENERAL, STEPS, WORDS, PARTS, PAST>, lds, &once);
   if (e != hipSuccess) return e;
-  bwd_dkdv_bf16_kernel<D, GENERAL, STEPS, WORDS, PARTS><<<(unsigned)grid, 256, lds, s>>>(a);
+  bwd_dkdv_bf16_kernel<D, GENERAL, STEPS, WORDS, PARTS, PAST><<<(unsigned)grid, 256, lds, s>>>(a);
   if constexpr (PARTS) dkdv_sum_kernel<D, STEPS><<<(unsigned)(a.d.B * a.d.Hkv * n_cut * 2 * (D / 8)), 256, 0, s>>>(a);
   return hipGetLastError();
 }
 template <int D, bool GENERAL, bool STEPS = false, bool WORDS = false>
 hipError_t launch(const BwdArgs& a, hipStream_t s) {
+  const bool past = dkdv_past(a.d.B * a.d.Hkv, a.d.Skv, D);
   if constexpr (!GENERAL)
-    if (a.kv_sums != nullptr) return launch_as<D, false, STEPS, WORDS, true>(a, s);
-  return launch_as<D, GENERAL, STEPS, WORDS, false>(a, s);
+    if (a.kv_sums != nullptr) return past ? launch_as<D, false, STEPS, WORDS, true, true>(a, s) : launch_as<D, false, STEPS, WORDS, true, false>(a, s);
+  return past ? launch_as<D, GENERAL, STEPS, WORDS, false, true>(a, s) : launch_as<D, GENERAL, STEPS, WORDS, false, false>(a, s);
 }
 
 bool dkdv_rows_ok(const Dims& d) { return d.Sq % KM == 0 || d.Sq >= KM; }   // (a ragged Sq needs 32 rows to overlap)

@@ -38,8 +38,8 @@ template <int D> struct ShortSmem {
 
 // MODE 0: dense.  1: a media mask whose chunks are multiples of 32 rows and whose key blocks are multiples of 128
 // keys: it selects which steps a workgroup performs.  2: any other, by the words of MaskRows.  (The variants of
-// bwd_dkdv_bf16_kernel, which explains them.)
-template <int D, int MODE>
+// bwd_dkdv_bf16_kernel, which explains them.)  PAST: dK and dV are written past the caches (dkdv_past).
+template <int D, int MODE, bool PAST>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(wg_per_cu(D), wg_per_cu(D))))
 bwd_dkdv_short_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -99,15 +99,13 @@ bwd_dkdv_short_kernel(BwdArgs a) {
   const long kv_head = b * d.kv_sb + hk * d.kv_sh;
   if (MODE != 0 && n == 0) {                       // keys that no query sees: dK = dV = 0, nothing to read
     const u32x4 z = {0, 0, 0, 0};
-    dkdv_rows(dkdv_past(d.B * d.Hkv, d.Skv, D), [&](auto past) __attribute__((always_inline)) {
-      for (int c = tid; c < KN * CPR; c += 256) {
-        const int j = j_wg0 + c / CPR, col = (c % CPR) * 8;
-        if (j >= d.Skv) continue;
-        const long off = kv_head + (long)j * d.kv_ss + col;
-        store_dkdv<past.value>((uint16_t*)a.dk + off, z);
-        store_dkdv<past.value>((uint16_t*)a.dv + off, z);
-      }
-    });
+    for (int c = tid; c < KN * CPR; c += 256) {
+      const int j = j_wg0 + c / CPR, col = (c % CPR) * 8;
+      if (j >= d.Skv) continue;
+      const long off = kv_head + (long)j * d.kv_ss + col;
+      store_dkdv<PAST>((uint16_t*)a.dk + off, z);
+      store_dkdv<PAST>((uint16_t*)a.dv + off, z);
+    }
     return;
   }
 
@@ -249,31 +247,32 @@ bwd_dkdv_short_kernel(BwdArgs a) {
       }
     // (each wave reads back only what it wrote itself: no barrier, the LDS queue keeps the order)
     char* const out = (char*)(which == 0 ? a.dk : a.dv);
-    dkdv_rows(dkdv_past(d.B * d.Hkv, d.Skv, D), [&](auto past) __attribute__((always_inline)) {
 #pragma unroll
-      for (int r0 = 0; r0 < 32; r0 += RPI) {
-        const int r = r0 + rsub, j = j_wave0 + r;
-        if ((64 % LPR != 0 && rsub >= RPI) || r >= 32) continue;
-        const u32x4 y = *(const u32x4*)(buf + r * RP + cb);
-        if (j < d.Skv) store_dkdv<past.value>(out + (kv_head + (long)j * d.kv_ss) * 2 + cb, y);
-      }
-    });
+    for (int r0 = 0; r0 < 32; r0 += RPI) {
+      const int r = r0 + rsub, j = j_wave0 + r;
+      if ((64 % LPR != 0 && rsub >= RPI) || r >= 32) continue;
+      const u32x4 y = *(const u32x4*)(buf + r * RP + cb);
+      if (j < d.Skv) store_dkdv<PAST>(out + (kv_head + (long)j * d.kv_ss) * 2 + cb, y);
+    }
   }
 }
 
-template <int D, int MODE>
+template <int D, int MODE, bool PAST>
 hipError_t launch(const BwdArgs& a, hipStream_t s) {
   static SmemOnce once;
   constexpr int lds = MODE == 0 ? ShortSmem<D>::RING : ShortSmem<D>::TOTAL;
   static_assert(lds_holds(wg_per_cu(D), lds), "the workgroups of a compute unit share its LDS");
-  const hipError_t e = ensure_dynamic_lds((const void*)bwd_dkdv_short_kernel<D, MODE>, lds, &once);
+  const hipError_t e = ensure_dynamic_lds((const void*)bwd_dkdv_short_kernel<D, MODE, PAST>, lds, &once);
   if (e != hipSuccess) return e;
   const long grid = xcd_grid(a.d.B * a.d.Hkv, (a.d.Skv + KN - 1) / KN);
-  bwd_dkdv_short_kernel<D, MODE><<<(unsigned)grid, 256, lds, s>>>(a);
+  bwd_dkdv_short_kernel<D, MODE, PAST><<<(unsigned)grid, 256, lds, s>>>(a);
   return hipGetLastError();
 }
+template <int D, bool PAST> hipError_t launch(const BwdArgs& a, int mode, hipStream_t s) {
+  return mode == 0 ? launch<D, 0, PAST>(a, s) : mode == 1 ? launch<D, 1, PAST>(a, s) : launch<D, 2, PAST>(a, s);
+}
 template <int D> hipError_t launch(const BwdArgs& a, int mode, hipStream_t s) {
-  return mode == 0 ? launch<D, 0>(a, s) : mode == 1 ? launch<D, 1>(a, s) : launch<D, 2>(a, s);
+  return dkdv_past(a.d.B * a.d.Hkv, a.d.Skv, D) ? launch<D, true>(a, mode, s) : launch<D, false>(a, mode, s);
 }
 
 }  // namespace

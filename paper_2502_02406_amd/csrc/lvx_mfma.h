@@ -13,8 +13,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <type_traits>
-
 namespace lvx {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -303,21 +301,12 @@ __device__ inline int nth_bit(const unsigned* bits, int k, int n) {     // index
 // 6983 -> 6969.  Without projections, 16 heads of 128: 17, 67, 134, 268 MB 58.1 -> 56.5, 101 -> 95, 157 -> 152, 295 -> 275; 8 heads x 131072 keys, D =
 // 64, of which every row sees 64 (134 MB): the step 353 -> 322.
 constexpr long DKDV_PAST = 48l << 20;
-__device__ __forceinline__ bool dkdv_past(int heads, int keys, int width) { return (long)heads * keys * width * 4 > DKDV_PAST; }
+inline bool dkdv_past(int heads, int keys, int width) { return (long)heads * keys * width * 4 > DKDV_PAST; }
+// (a kernel is compiled for either, since with both forms in its code the compiler arranged other parts differently: 8 heads x 4096 rows x 131072
+// keys, D = 64, chunks of two rows that see a frame of 64 each, the step 328 -> 331 us)
 template <bool PAST> __device__ __forceinline__ void store_dkdv(void* to, u32x4 y) {
   if constexpr (PAST) __builtin_nontemporal_store(y, (u32x4*)to);
   else *(u32x4*)to = y;
-}
-// rows(true_type or false_type): a loop of its own for either (with the test at every store 8 heads x 256 rows x 8192 keys, D = 64, took 49.3 us
-// for 47.4)
-template <class F> __device__ __forceinline__ void dkdv_rows(bool past, F&& rows) {
-  if (past) {
-    asm volatile("");                              // (a bracket: stores that both loops begin or end with became one, an ordinary one)
-    rows(std::true_type{});
-    asm volatile("");
-  } else {
-    rows(std::false_type{});
-  }
 }
 
 // XCD-aware decode of a 1-D grid.  Workgroup ids are dealt round-robin to the 8 XCDs, each with

@@ -134,11 +134,13 @@ def test_fused_backward_accumulators_stay_put():
 
 @pytest.mark.parametrize("D,registers", [(64, 168), (96, 256), (128, 256)])
 def test_short_dkdv_keeps_to_its_registers(D, registers):
-    """Three workgroups (64-wide heads) or two share a compute unit: dense, with a list of steps, with words."""
+    """Three workgroups (64-wide heads) or two share a compute unit: dense, with a list of steps, with words; both kinds of stores."""
     asm = _asm("lvx_bwd_dkdv_short_bf16.hip")
     for mode in range(3):
-        kernel = f"bwd_dkdv_short_kernelILi{D}ELi{mode}EE"
-        (body,) = _kernels(asm, kernel)
-        assert body.count("v_mfma_f32_32x32x16_bf16") == 2 * D // 16 + 2 * 2 * D // 32 and "scratch_" not in body
-        (count,) = re.findall(r"\.name:\s+\S*" + kernel + r"\S*\n(?:(?!\s+\.name:).*\n)*?\s+\.vgpr_count:\s+(\d+)", asm)
-        assert int(count) <= registers
+        kernel = f"bwd_dkdv_short_kernelILi{D}ELi{mode}E"
+        bodies = _kernels(asm, kernel)
+        assert len(bodies) == 2
+        for body in bodies:
+            assert body.count("v_mfma_f32_32x32x16_bf16") == 2 * D // 16 + 2 * 2 * D // 32 and "scratch_" not in body
+        counts = re.findall(r"\.name:\s+\S*" + kernel + r"\S*\n(?:(?!\s+\.name:).*\n)*?\s+\.vgpr_count:\s+(\d+)", asm)
+        assert len(counts) == 2 and all(int(n) <= registers for n in counts)
