@@ -297,9 +297,9 @@ __device__ inline int nth_bit(const unsigned* bits, int k, int n) {     // index
 // dK and dV of more than 48 MB go past the caches: what these hold of K and V, which the dQ kernel reads next, stays in them.  Smaller ones
 // stay there themselves, for the gradients of the projections (RecomputeLayer), which read both twice.  Backward of a layer of 256 rows, two
 // blocks, through the caches -> past them, by the size of dK and dV of a block, us: 4, 8, 17 MB (8 heads of 64) 208 -> 215, 217 -> 224, 246 -> 249;
-// 17, 34, 67, 134 MB (16 of 128) 486 -> 517, 620 -> 635, 999 -> 991, 1756 -> 1749; 67 and 268 MB (32 / 8 of 128, 4096 features) 1923 -> 1949 and
-// 6983 -> 6969.  Without projections, 16 heads of 128: 17, 67, 134, 268 MB 58.1 -> 56.5, 101 -> 95, 157 -> 152, 295 -> 275; 8 heads x 131072 keys, D =
-// 64, of which every row sees 64 (134 MB): the step 353 -> 322.
+// 17, 36, 50, 56, 67, 134 MB (16 of 128) 486 -> 517, 826 -> 875, 929 -> 983, 919 -> 923, 999 -> 991, 1756 -> 1749; 67 and 268 MB (32 / 8 of 128, 4096
+// features) 1923 -> 1949 and 6983 -> 6969.  Without projections, 16 heads of 128: 17, 50, 67, 134, 268 MB 58.1 -> 56.5, 85.1 -> 81.7, 101 -> 95, 157 -> 152,
+// 295 -> 275; 8 heads x 131072 keys, D = 64, of which every row sees 64 (134 MB): the step 353 -> 322.
 constexpr long DKDV_PAST = 48l << 20;
 inline bool dkdv_past(int heads, int keys, int width) { return (long)heads * keys * width * 4 > DKDV_PAST; }
 // (a kernel is compiled for either, since with both forms in its code the compiler arranged other parts differently: 8 heads x 4096 rows x 131072
